@@ -133,8 +133,7 @@ BwdWs carve_bwd(const Dims& d, void* ws) {
     w.wrowB_lo = gw == 2 ? c.take<float>(d.BHT) : nullptr;
     w.bsum = c.take<double>(d.BH * ((d.T + 1023) / 1024));
     w.wrowB = c.take<float>(d.BHT); w.sQ = c.take<float>(d.BHT);
-    w.nbQ = d.dqk / tile_bd2(d.dhv, d.dqk, d.dtype, MODE_DQ, d.L);
-    w.nbK = d.dqk / tile_bd2(d.dhv, d.dqk, d.dtype, MODE_DK, d.L);
+    w.nbQ = w.nbK = d.dqk / tile_bd2(d.dhv, d.dqk, d.dtype, d.L, d.BHT);
     w.partQ = c.take<float>((size_t)w.nbQ * d.BHT); w.partK = c.take<float>((size_t)w.nbK * d.BHT);
     w.cdot = c.take<float>(d.BH);
     w.Cfinal = c.take<float>((size_t)d.BH * d.dqk * d.dhv);
@@ -836,7 +835,7 @@ int tfla_mlstm_layer_fwd(const void* q, const void* k, const void* v, const floa
     // y = sigma(o~) (.) NORM(h~) itself, next to h~: one read of h~ and one launch less.  Wider heads span several
     // workgroups per row and take the separate kernel below.
     const bool fuse = check_dims(TFLA_FWD, B, NH, T, dqk, dhv, chunk, variant, dtype) == TFLA_OK &&
-                      layer_fusion_applies(dqk, dhv, dtype, chunk) && !needs_pad(T, dqk, dhv, chunk) && !misaligned16(o_pre) &&
+                      layer_fusion_applies(dqk, dhv, dtype, chunk, (long)B * NH * T) && !needs_pad(T, dqk, dhv, chunk) && !misaligned16(o_pre) &&
                       !misaligned16(gamma) && !misaligned16(beta) && !misaligned16(Y);
     const LayerFuse fz{o_pre, gamma, beta, Y, norm_kind, NH, norm_eps};
     const int rc = fwd_impl(q, k, v, i_pre, f_pre, C0, n0, m0, B, NH, T, dqk, dhv, chunk, variant, dtype, eps,

@@ -218,10 +218,14 @@ struct LayerFuse {
     int kind, NH; float eps;
 };
 template <int MODE> hipError_t launch_tile_mode(const TileArgs& a, int BH, int dtype, hipStream_t s);
-// d2 block of a tiled kernel (mode MODE_*) with contraction width d1.  128 columns keep a bf16
-// wavefront within 256 registers, so that two workgroups share a CU when d1 <= 256.  The bf16 dQ and
-// dK kernels take a 256-wide block when d1 = 512 (one workgroup per CU anyway): half as many
-// workgroups fetch the same X rows and column tiles, and dQ computes S once per 256 columns.
+// d2 block of a tiled kernel (mode MODE_*) with contraction width d1; rows = batch*head x steps.
+// 128 columns keep a bf16 wavefront within 256 registers, so that two workgroups share a CU when d1 <= 256.  From
+// d1 = 512 on (also as the halves of a contraction over 1024) a workgroup's own X rows fill half of the register file
+// and one workgroup takes the CU in any case: a 256-wide block then halves how often the X rows and the column tiles
+// are fetched and the score tile is computed (forward + backward, 4096 steps, 4 heads of 1024: 3.18 -> 2.78 ms; 8
+// heads of 512, batch 4: 1.418 -> 1.335 ms).  It pays only while its workgroups still cover the 256 CUs: at 64
+// workgroups (8 heads of 512, 512 steps, forward) it measured 40.5 us against 36.0 us for 128 columns, at 128
+// workgroups (1024 steps, forward + backward) 155 against 144 us.
 // (The 256-wide instantiations exist for the four-wavefront workgroups only, i.e. for chunk sizes that are
 // multiples of 128.)
 // tile_width_override (set through tfla_tile_width, a measurement aid for tile-size sweeps): 0 = the choice
@@ -229,17 +233,16 @@ template <int MODE> hipError_t launch_tile_mode(const TileArgs& a, int BH, int d
 // wherever it is built).  The workspace layout depends on the width, so it must not change between the
 // workspace query, the forward call and the backward call of one step.
 extern int tile_width_override;
-inline int tile_bd2(int d1, int d2, int dtype, int mode, int L) {
+inline int tile_bd2(int d1, int d2, int dtype, int L, long rows) {
     const int ov = tile_width_override;
     if (dtype == 1 && (ov == 64 || ov == 128) && d2 % ov == 0) return ov;
-    if (dtype == 1 && (mode == MODE_DK || mode == MODE_DQ) && d1 == 512 && d2 % 256 == 0 && L % 128 == 0) return 256;
-    // (contractions over 1024 columns run as 512-wide halves with 128- or 64-wide blocks)
+    if (dtype == 1 && d1 >= 512 && d2 % 256 == 0 && L % 128 == 0 && (rows / 128) * (d2 / 256) >= 256) return 256;
     if (d2 % 128 == 0) return 128;
     return 64;
 }
 // the fused layer output needs whole rows of h~ in one workgroup of the H kernel
-inline bool layer_fusion_applies(int dqk, int dhv, int dtype, int L) {
-    return dtype == 1 && (dhv == 64 || dhv == 128) && tile_bd2(dqk, dhv, dtype, MODE_H, L) == dhv;
+inline bool layer_fusion_applies(int dqk, int dhv, int dtype, int L, long rows) {
+    return dtype == 1 && (dhv == 64 || dhv == 128) && tile_bd2(dqk, dhv, dtype, L, rows) == dhv;
 }
 
 }  // namespace tfla

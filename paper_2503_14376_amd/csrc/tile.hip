@@ -332,8 +332,8 @@ static hipError_t launch_tile_t(const TileArgs& a0, int BH, hipStream_t s) {
 template <typename DT, int D1, int MODE, int SPLIT = 0>
 static hipError_t launch_tile_d1(const TileArgs& a, int BH, int bd2, hipStream_t s) {
     if (a.L % 128 == 0) {
-        if constexpr (sizeof(DT) == 2 && D1 > 256 && SPLIT == 0 && (MODE == MODE_DQ || MODE == MODE_DK)) {   // see tile_bd2()
-            if (bd2 == 256) return launch_tile_t<DT, D1, 256, 4, MODE>(a, BH, s);
+        if constexpr (sizeof(DT) == 2 && D1 > 256) {   // see tile_bd2()
+            if (bd2 == 256) return launch_tile_t<DT, D1, 256, 4, MODE, SPLIT>(a, BH, s);
         }
         if (bd2 == 128) return launch_tile_t<DT, D1, 128, 4, MODE, SPLIT>(a, BH, s);
         if (bd2 == 64) return launch_tile_t<DT, D1, 64, 4, MODE, SPLIT>(a, BH, s);
@@ -377,7 +377,7 @@ hipError_t launch_tile_mode(const TileArgs& a0, int BH, int dtype, hipStream_t s
 #define TFLA_KC_ORDER 0x8   // bit m = 1: mode m walks the chunks last to first.  H, dV, dQ first to last, dK last to first
 #endif
     a.kc_desc = ((TFLA_KC_ORDER) >> MODE) & 1;
-    const int bd2 = tile_bd2(a.d1, a.d2, dtype, MODE, a.L);
+    const int bd2 = tile_bd2(a.d1, a.d2, dtype, a.L, (long)BH * a.T);
     const bool nrm = MODE == MODE_H && a.variant == 0;
     if (dtype != 1) {
         if (a.d1 <= 256) return launch_tile_m<float, MODE>(a, BH, bd2, s);

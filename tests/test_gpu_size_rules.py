@@ -1,0 +1,52 @@
+"""GPU parity on both sides of the rules that pick a kernel variant by size: the whole problem runs on the GPU in the
+variant that its size selects, the fp64 oracle is evaluated on two (batch, head) slices of it (the first and the last).
+The tolerance is the suite's own per-tensor bar (gpu_util.TOL): the variants round the same operands at the same places."""
+import pytest
+import torch
+
+import workloads as wl
+from oracle import mlstm_oracle as orc
+
+pytestmark = pytest.mark.gpu
+
+
+def _check_slices(w, dCn=False):
+    import paper_2503_14376_amd as tfla
+    from tests import gpu_util as gu
+    d = wl.make_inputs(w)
+    dev = gu.dev_inputs(w, d)
+    print("rule", w.variant, w.dtype, (w.B, w.NH, w.T, w.dqk, w.dhv, w.chunk), flush=True)
+    st = [dev.get(x) for x in ("C0", "n0", "m0")]
+    dC = torch.randn((w.B, w.NH, w.dqk, w.dhv), device="cuda", generator=torch.Generator("cuda").manual_seed(5)) if dCn else None
+    f = tfla.mlstm_fwd(dev["q"], dev["k"], dev["v"], dev["i_pre"], dev["f_pre"], *st, chunk=w.chunk, variant=w.variant, eps=1e-6)
+    b = tfla.mlstm_bwd(dev["q"], dev["k"], dev["v"], dev["i_pre"], dev["f_pre"], dev["dH"], f["n_out"], f["m_out"], *st, dC,
+                       chunk=w.chunk, variant=w.variant, eps=1e-6, fwd_workspace=f["workspace"])
+    torch.cuda.synchronize()
+    idx = sorted({0, w.B * w.NH - 1})
+    sub = lambda t: t.reshape((-1,) + tuple(t.shape[2:]))[idx]
+    oi = gu.oracle_inputs(wl.make_inputs(w, slices=idx))
+    tol = gu.TOL[w.dtype]
+    ref = orc.recurrent_fwd(**oi, variant=w.variant, eps=1e-6)
+    rb = orc.chunkwise_bwd(**oi, dH=gu.flat(wl.make_inputs(w, slices=idx)["dH"]), variant=w.variant, eps=1e-6, chunk=128,
+                           **({"dCn": sub(dC).double().cpu().numpy()} if dCn else {}))
+    errs = {k: gu.rel_err(sub(f[k]), ref[k]) for k in ("H", "Cn") + (("nn", "n_out") if w.variant == wl.EXP else ())}
+    names = dict(dq="dq", dk="dk", dv="dv", d_i_pre="di", d_f_pre="df")
+    if w.init_state:
+        names["dC0"] = "dC0"
+    errs.update({k: gu.rel_err(sub(b[k]), rb[r]) for k, r in names.items()})
+    print("   ", errs, flush=True)
+    for k, e in errs.items():
+        assert e <= tol, (k, e, errs)
+
+
+# 256-wide output blocks of the tiled kernels: rows / 128 * (columns / 256) >= 256 workgroups, chunk a multiple of 128
+@pytest.mark.parametrize("variant,B,NH,T,dqk,dhv,chunk", [
+    (wl.EXP, 1, 4, 2048, 1024, 1024, 256),      # exactly 256 workgroups in every mode (split contraction)
+    (wl.SIG, 1, 4, 1920, 1024, 1024, 128),      # 240: below the line
+    (wl.EXP, 1, 8, 2048, 512, 512, 256),        # exactly 256, one launch per mode
+    (wl.EXP, 3, 5, 2304, 512, 512, 384),        # an odd number of heads, three row blocks per chunk
+    (wl.SIG, 1, 16, 2048, 512, 256, 128),       # dQ / dK contract over 256 columns, H / dV over 512
+])
+def test_wide_output_blocks(variant, B, NH, T, dqk, dhv, chunk):
+    w = wl.small(variant, wl.BF16, B=B, NH=NH, T=T, dqk=dqk, dhv=dhv, chunk=chunk, seed=700 + T + dqk)
+    _check_slices(w)
