@@ -31,11 +31,11 @@
  *    B * NH <= 65535.
  *  - T need not be a multiple of chunk (N_c = ceil(T / chunk), Sec. 2.2), and the head dimensions need
  *    not be among the kernels' own widths 64, 128, 256, 512, 1024.  The kernels work on whole chunks and on
- *    those widths: otherwise the library copies the inputs into zero-padded buffers inside the workspace
- *    (which is correspondingly larger, see tfla_mlstm_workspace_bytes), gives the padding steps a forget
- *    gate of one and an input gate of zero, scales q by 1/sqrt of the true dqk, and copies the true part
- *    of the results back, so the result is that of the problem as given; tensor and state pointers must
- *    then be 16-byte aligned (TFLA_ERR_SHAPE).
+ *    those widths: otherwise they read and write the caller's tensors in place, taking the steps past T and
+ *    the columns past the head dimension as zeros, give the steps past T a forget gate of one and an input
+ *    gate of zero, and scale q by 1/sqrt of the true dqk, so the result is that of the problem as given;
+ *    tensor and state pointers must then be 16-byte aligned (TFLA_ERR_SHAPE), and the workspace that
+ *    tfla_mlstm_workspace_bytes asks for is larger.
  *  - Global state: the compute entry points keep none (their only shared data is the read-only table of
  *    kernel instantiations).  The two measurement aids at the end of this file, per-kernel timing
  *    (tfla_profile_*) and the tile-width override (tfla_tile_width), are process-wide, mutable and not
@@ -90,8 +90,7 @@ enum {
  *   workspace: device scratch of at least tfla_mlstm_workspace_bytes(TFLA_FWD, ...) bytes,
  *        256-byte aligned.  Afterwards it holds, in a layout private to the library, what the
  *        backward pass can reuse (the gate vectors, the chunk states C_{k-1} of Sec. 2.2,
- *        C_T and, where the library padded them, its padded copies of q, k, v and the gate
- *        pre-activations): a caller that keeps it untouched until the matching tfla_mlstm_bwd call may pass
+ *        C_T): a caller that keeps it untouched until the matching tfla_mlstm_bwd call may pass
  *        it there as fwd_workspace; a caller that does not may overwrite or free it.
  */
 TFLA_API int tfla_mlstm_fwd(const void* q, const void* k, const void* v,

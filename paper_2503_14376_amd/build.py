@@ -17,7 +17,7 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fvisibility=hi
 # (source, object name, extra defines)
 # recurrent.hip: MFMA accumulators in ordinary VGPRs (the kernel also scales and stores them with
 # vector ALU instructions, which cannot read accumulation registers)
-UNITS = [("api.hip", "api.o", []), ("gates.hip", "gates.o", []), ("step.hip", "step.o", []), ("norm.hip", "norm.o", []), ("pad.hip", "pad.o", []),
+UNITS = [("api.hip", "api.o", []), ("gates.hip", "gates.o", []), ("step.hip", "step.o", []), ("norm.hip", "norm.o", []),
          ("recurrent.hip", "recurrent.o", ["-mllvm", "-amdgpu-mfma-vgpr-form"])] + [
     # tile kernels: the start-up loop over X and state slices must unroll completely (its items differ in kind and
     # index registers by compile-time constants); with the widest shapes its body exceeds the default size limit

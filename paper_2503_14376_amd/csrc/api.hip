@@ -16,29 +16,26 @@ namespace {
 inline size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
 
 struct Dims {
-    int B, NH, T, dqk, dhv, L, variant, dtype;   // T: whole chunks (the padded length when the caller's is ragged)
+    int B, NH, L, variant, dtype;
+    int T, dqk, dhv;             // what the kernels work on: whole chunks, head dimensions among their own widths
+    int T_in, dqk_in, dhv_in;    // the caller's: T_in <= T, ...; the steps and columns in between count as zeros
     long BH, BHT;
     int Nc;
     size_t esz;
 };
 
-// the head dimension the kernels run a caller's head dimension at (zero-padded columns in between)
 // a contraction wider than the tiled kernels hold in registers runs as two launches that meet in fp32
 inline bool contraction_split(int d1, int dtype) { return dtype == TFLA_BF16 ? d1 > 512 : d1 > 256; }
+// the head dimension the kernels run a caller's head dimension at (the columns in between count as zeros)
 inline int kernel_dim(int d) { return d <= 64 ? 64 : (d <= 128 ? 128 : (d <= 256 ? 256 : (d <= 512 ? 512 : 1024))); }
 
-// core = true: the kernels' own widths only (what the kernel sequences are called with)
-int check_dims(int direction, int B, int NH, int T, int dqk, int dhv, int chunk, int variant, int dtype, bool core = false) {
+int check_dims(int direction, int B, int NH, int T, int dqk, int dhv, int chunk, int variant, int dtype) {
     if (direction != TFLA_FWD && direction != TFLA_BWD) return TFLA_ERR_ENUM;
     if (variant != TFLA_EXP && variant != TFLA_SIG) return TFLA_ERR_ENUM;
     if (dtype != TFLA_F32 && dtype != TFLA_BF16) return TFLA_ERR_ENUM;
     if (B <= 0 || NH <= 0 || T <= 0 || dqk <= 0 || dhv <= 0) return TFLA_ERR_SHAPE;
     const int dmax = dtype == TFLA_BF16 ? 1024 : 512;
-    auto ok_d = [&](int d) {
-        if (d > dmax || d % 8 != 0) return false;
-        return !core || d == 64 || d == 128 || d == 256 || d == 512 || d == 1024;
-    };
-    if (!ok_d(dqk) || !ok_d(dhv)) return TFLA_ERR_SHAPE;
+    if (dqk > dmax || dqk % 8 != 0 || dhv > dmax || dhv % 8 != 0) return TFLA_ERR_SHAPE;
     if ((long)B * NH > 65535) return TFLA_ERR_SHAPE;
     if (chunk < 64 || chunk > 2048 || chunk % 64 != 0) return TFLA_ERR_CHUNK;
     const int nc = (T + chunk - 1) / chunk;
@@ -52,7 +49,8 @@ int check_dims(int direction, int B, int NH, int T, int dqk, int dhv, int chunk,
 Dims make_dims(int B, int NH, int T, int dqk, int dhv, int chunk, int variant, int dtype) {
     Dims d;
     d.Nc = (T + chunk - 1) / chunk;
-    d.B = B; d.NH = NH; d.T = d.Nc * chunk; d.dqk = dqk; d.dhv = dhv; d.L = chunk; d.variant = variant; d.dtype = dtype;
+    d.T_in = T; d.dqk_in = dqk; d.dhv_in = dhv;
+    d.B = B; d.NH = NH; d.T = d.Nc * chunk; d.dqk = kernel_dim(dqk); d.dhv = kernel_dim(dhv); d.L = chunk; d.variant = variant; d.dtype = dtype;
     d.BH = (long)B * NH; d.BHT = d.BH * d.T;
     d.esz = dtype == TFLA_BF16 ? 2 : 4;
     return d;
@@ -164,10 +162,10 @@ BwdWs carve_bwd(const Dims& d, void* ws) {
 
 // ---- optional per-kernel timing with HIP events on the caller's stream -------------------
 enum { K_GATES = 0, K_BWD_PREP, K_REC_FWD, K_REC_BWD, K_TILE_H, K_TILE_DV, K_TILE_DQ, K_TILE_DK, K_GATE_GRADS,
-       K_STATE_DOT, K_FILL, K_STEP, K_NORM_FWD, K_NORM_BWD, K_GAIN, K_PAD, K_COUNT };
+       K_STATE_DOT, K_FILL, K_STEP, K_NORM_FWD, K_NORM_BWD, K_GAIN, K_COUNT };
 const char* const kKernelNames[K_COUNT] = {"gates", "gate_bwd_prep", "recurrent_fwd", "recurrent_bwd", "tile_H",
                                            "tile_dV", "tile_dQ", "tile_dK", "gate_grads", "state_dot", "fill_zero",
-                                           "recurrent_step", "norm_gate_fwd", "norm_gate_bwd", "transfer_gain", "pad_copy"};
+                                           "recurrent_step", "norm_gate_fwd", "norm_gate_bwd", "transfer_gain"};
 struct Profiler {
     bool on = false;
     int cap = 0, used = 0;
@@ -212,41 +210,70 @@ void prof_collect() {
 }
 
 int run_gates(const Dims& d, const float* i_pre, const float* f_pre, const float* m0, float* wrow, float* ucol,
-              float* sH, float* aK, float* gbar, float* mout, float* mfinal, float* tmp, float* csum, float* wrow_lo,
-              float* ucol_lo, float softcap, int Tvalid, int dqk_true, hipStream_t s) {
+              float* sH, float* aK, float* gbar, float* mout, float* mout_user, float* mfinal, float* tmp, float* csum, float* wrow_lo,
+              float* ucol_lo, float softcap, hipStream_t s) {
     GateArgs g;
-    g.softcap = softcap; g.Tvalid = Tvalid;
+    g.softcap = softcap; g.Tvalid = d.T_in;
     g.i_pre = i_pre; g.f_pre = f_pre; g.m0 = d.variant == TFLA_EXP ? m0 : nullptr;
     g.T = d.T; g.L = d.L; g.Nc = d.Nc; g.variant = d.variant;
-    g.qscale = 1.0f / sqrtf((float)dqk_true);   // of the caller's head dimension, not of the padded one
-    g.wrow = wrow; g.ucol = ucol; g.sH = sH; g.aK = aK; g.gbar = gbar; g.mout = mout; g.mfinal = mfinal; g.tmp = tmp; g.csum = csum;
+    g.qscale = 1.0f / sqrtf((float)d.dqk_in);
+    g.wrow = wrow; g.ucol = ucol; g.sH = sH; g.aK = aK; g.gbar = gbar; g.mout = mout; g.mout_user = mout_user; g.mfinal = mfinal; g.tmp = tmp; g.csum = csum;
     g.wrow_lo = wrow_lo; g.ucol_lo = ucol_lo; g.precise = d.dtype == TFLA_BF16 ? 0 : 1;
     TFLA_LAUNCH(K_GATES, launch_gates(g, (int)d.BH, s));
     return TFLA_OK;
 }
 
-// Forward pass over whole chunks: T is a multiple of chunk, steps >= Tvalid are padding.
-int fwd_core(const void* q, const void* k, const void* v, const float* i_pre, const float* f_pre, const float* C0,
-             const float* n0, const float* m0, int B, int NH, int T, int Tvalid, int dqk_true, int dhv_true, int dqk, int dhv,
-             int chunk, int variant, int dtype, float eps, float softcap, void* H, float* Cn, float* nn, float* mn, float* n_out, float* m_out,
+inline bool misaligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) != 0; }
+// whether the caller's tensors end before the kernels' blocks do.  The kernels then read and write them in place, with
+// everything past their end taken as zero: a zero k, v (and upstream gradient) row or column adds nothing to any state,
+// output or gradient, and the gate kernels give the steps past the end a forget gate of one and an input gate of zero,
+// so the result is exactly that of the problem as given.  (For T = 1000, 8 heads of 256 / 512, forward with its layer,
+// copies into padded buffers instead cost five launches before and two after the kernels; for 16 heads of 96 / 192,
+// 3000 steps, forward + backward, 115 of 367 us.)
+inline bool needs_pad(int T, int dqk, int dhv, int chunk) {
+    return T % chunk != 0 || dqk != kernel_dim(dqk) || dhv != kernel_dim(dhv);
+}
+// Workspace bytes of the two directions.  For a problem whose tensors end before the blocks do they are what they were
+// when its inputs were copied (the copies' bytes included), so that sizes that callers have planned with, and what
+// tfla_mlstm_fwd_static accepts, stay the same; the space behind the carved pieces is not touched.
+size_t copies_bytes(const Dims& d, int direction) {
+    if (!needs_pad(d.T_in, d.dqk_in, d.dhv_in, d.L)) return 0;
+    const size_t sq = align_up((size_t)d.BHT * d.dqk * d.esz), sv = align_up((size_t)d.BHT * d.dhv * d.esz);
+    const size_t row = align_up((size_t)d.BHT * sizeof(float)), n = align_up((size_t)d.BH * d.dqk * sizeof(float));
+    const size_t st = align_up((size_t)d.BH * d.dqk * d.dhv * sizeof(float));
+    return direction == TFLA_FWD ? 2 * sq + sv + 4 * row + 2 * st + 2 * n : 2 * sq + 2 * sv + 6 * row + 3 * st + n;
+}
+size_t fwd_total_bytes(const Dims& d) { return carve_fwd(d, nullptr).bytes + copies_bytes(d, TFLA_FWD); }
+size_t bwd_total_bytes(const Dims& d) { return carve_bwd(d, nullptr).bytes + copies_bytes(d, TFLA_BWD); }
+
+int fwd_impl(const void* q, const void* k, const void* v, const float* i_pre, const float* f_pre, const float* C0,
+             const float* n0, const float* m0, int B, int NH, int T, int dqk, int dhv, int chunk, int variant, int dtype,
+             float eps, float softcap, void* H, float* Cn, float* nn, float* mn, float* n_out, float* m_out,
              void* workspace, size_t workspace_bytes, void* stream, const LayerFuse* fz = nullptr) {
-    const int rc = check_dims(TFLA_FWD, B, NH, T, dqk, dhv, chunk, variant, dtype, true);
+    const int rc = check_dims(TFLA_FWD, B, NH, T, dqk, dhv, chunk, variant, dtype);
     if (rc != TFLA_OK) return rc;
+    const bool padded = needs_pad(T, dqk, dhv, chunk);
+    if (fz && padded) return TFLA_ERR_SHAPE;      // (the fused layer output is for whole blocks)
     if (!q || !k || !v || !i_pre || !f_pre || !H) return TFLA_ERR_NULL;
     if (variant == TFLA_EXP) {
         const int given = (C0 != nullptr) + (n0 != nullptr) + (m0 != nullptr);
         if (given != 0 && given != 3) return TFLA_ERR_STATE;
     }
+    if (padded && (misaligned16(q) || misaligned16(k) || misaligned16(v) || misaligned16(H) || misaligned16(C0) || misaligned16(Cn)))
+        return TFLA_ERR_SHAPE;
     const Dims d = make_dims(B, NH, T, dqk, dhv, chunk, variant, dtype);
     if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255) != 0) return TFLA_ERR_WORKSPACE;
     const FwdWs w = carve_fwd(d, workspace);
-    if (workspace_bytes < w.bytes) return TFLA_ERR_WORKSPACE;
+    if (workspace_bytes < fwd_total_bytes(d)) return TFLA_ERR_WORKSPACE;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     const bool is_exp = variant == TFLA_EXP;
 
     // 1. gates, max states
-    float* mout = (is_exp && m_out) ? m_out : w.mout;
-    int st = run_gates(d, i_pre, f_pre, m0, w.wrow, w.ucol, w.sH, w.aK, w.gbar, mout, is_exp ? mn : nullptr, w.tmp, w.csum, w.wrow_lo, w.ucol_lo, softcap, Tvalid, dqk_true, s);
+    // (m_out goes to the caller's tensor; the kernels that read it back count in whole chunks)
+    const bool own_mout = is_exp && m_out && d.T == d.T_in;
+    float* mout = own_mout ? m_out : w.mout;
+    int st = run_gates(d, i_pre, f_pre, m0, w.wrow, w.ucol, w.sH, w.aK, w.gbar, mout, (is_exp && !own_mout) ? m_out : nullptr, is_exp ? mn : nullptr,
+                       w.tmp, w.csum, w.wrow_lo, w.ucol_lo, softcap, s);
     if (st != TFLA_OK) return st;
 
     // 2. recurrent kernel: C_{k-1} (transposed, element type of q/k/v) and n_{k-1} for every chunk
@@ -254,16 +281,17 @@ int fwd_core(const void* q, const void* k, const void* v, const float* i_pre, co
     r.X = k; r.Y = v; r.rs = w.aK; r.gbar = w.gbar; r.S0 = C0;
     r.stT = w.stT; r.stN = nullptr; r.Sfinal = Cn; r.Sfinal2 = w.Cfin;
     r.n0 = is_exp ? n0 : nullptr; r.nst = is_exp ? w.nst : nullptr; r.nfinal = is_exp ? nn : nullptr;
-    r.T = T; r.L = chunk; r.Nc = d.Nc; r.d1 = dqk; r.d2 = dhv; r.reverse = 0;
+    r.T = d.T; r.L = chunk; r.Nc = d.Nc; r.d1 = d.dqk; r.d2 = d.dhv; r.reverse = 0;
+    r.T_in = T; r.d1_in = dqk; r.d2_in = dhv;
     r.anc = w.anc; r.anc_in = nullptr; r.anc_part = nullptr; r.anc_G = anchor_G(d);
     TFLA_LAUNCH(K_REC_FWD, launch_recurrent(r, (int)d.BH, dtype, s));
 
     // 3. parallel kernel
     TileArgs t{};
-    t.X = q; t.Y = k; t.Z = v; t.Out = H; t.out_T = Tvalid; t.out_ld = dhv_true; t.out_cols = dhv_true;
+    t.X = q; t.Y = k; t.Z = v; t.Out = H; t.out_T = T; t.out_ld = dhv; t.in_ld1 = t.in_cols1 = dqk;
     t.part_acc = w.pacc; t.part_nrm = w.pnrm;
     t.wrow = w.wrow; t.wcol = w.ucol; t.srow = w.sH; t.St = w.stT;
-    t.T = T; t.L = chunk; t.Nc = d.Nc; t.d1 = dqk; t.d2 = dhv;
+    t.T = d.T; t.L = chunk; t.Nc = d.Nc; t.d1 = d.dqk; t.d2 = d.dhv;
     t.variant = variant; t.eps = eps; t.nstate = w.nst; t.mout = mout; t.nout = is_exp ? n_out : nullptr;
     t.wrowB_out = is_exp ? w.wrowB : nullptr; t.sQ_out = is_exp ? w.sQ : nullptr;
     t.wrow_lo = w.wrow_lo; t.wcol_lo = w.ucol_lo; t.wrowB_lo_out = is_exp ? w.wrowB_lo : nullptr;
@@ -280,21 +308,20 @@ int fwd_core(const void* q, const void* k, const void* v, const float* i_pre, co
         FillList fl{};
         if (nn) { fl.p[0] = nn; fl.n[0] = d.BH * dqk; }
         if (mn) { fl.p[1] = mn; fl.n[1] = d.BH; }
-        if (n_out) { fl.p[2] = n_out; fl.n[2] = d.BHT; }
-        if (m_out) { fl.p[3] = m_out; fl.n[3] = d.BHT; }
+        if (n_out) { fl.p[2] = n_out; fl.n[2] = d.BH * T; }
+        if (m_out) { fl.p[3] = m_out; fl.n[3] = d.BH * T; }
         if (nn || mn || n_out || m_out) TFLA_LAUNCH(K_FILL, launch_fill_zero4(fl, s));
     }
     return TFLA_OK;
 }
 
 
-int bwd_core(const void* q, const void* k, const void* v, const float* i_pre, const float* f_pre, const float* C0,
+int bwd_impl(const void* q, const void* k, const void* v, const float* i_pre, const float* f_pre, const float* C0,
              const float* n0, const float* m0, const float* n_out, const float* m_out, const void* dH, const float* dCn,
-             int B, int NH, int T, int Tvalid, int dqk_true, int dhv_true, int dqk, int dhv, int chunk, int variant, int dtype,
-             float eps, float softcap, void* dq,
+             int B, int NH, int T, int dqk, int dhv, int chunk, int variant, int dtype, float eps, float softcap, void* dq,
              void* dk, void* dv, float* d_i_pre, float* d_f_pre, float* dC0, const void* fwd_workspace,
              size_t fwd_workspace_bytes, void* workspace, size_t workspace_bytes, void* stream) {
-    const int rc = check_dims(TFLA_BWD, B, NH, T, dqk, dhv, chunk, variant, dtype, true);
+    const int rc = check_dims(TFLA_BWD, B, NH, T, dqk, dhv, chunk, variant, dtype);
     if (rc != TFLA_OK) return rc;
     if (!q || !k || !v || !i_pre || !f_pre || !dH || !dq || !dk || !dv || !d_i_pre || !d_f_pre) return TFLA_ERR_NULL;
     const bool is_exp = variant == TFLA_EXP;
@@ -303,10 +330,14 @@ int bwd_core(const void* q, const void* k, const void* v, const float* i_pre, co
         const int given = (C0 != nullptr) + (n0 != nullptr) + (m0 != nullptr);
         if (given != 0 && given != 3) return TFLA_ERR_STATE;
     }
+    if (needs_pad(T, dqk, dhv, chunk) &&
+        (misaligned16(q) || misaligned16(k) || misaligned16(v) || misaligned16(dH) || misaligned16(dq) || misaligned16(dk) ||
+         misaligned16(dv) || misaligned16(C0) || misaligned16(dCn) || misaligned16(dC0)))
+        return TFLA_ERR_SHAPE;
     const Dims d = make_dims(B, NH, T, dqk, dhv, chunk, variant, dtype);
     if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255) != 0) return TFLA_ERR_WORKSPACE;
     const BwdWs w = carve_bwd(d, workspace);
-    if (workspace_bytes < w.bytes) return TFLA_ERR_WORKSPACE;
+    if (workspace_bytes < bwd_total_bytes(d)) return TFLA_ERR_WORKSPACE;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
 
     // What the matching forward call left in its workspace (gate vectors, C_{k-1} for every chunk,
@@ -332,7 +363,7 @@ int bwd_core(const void* q, const void* k, const void* v, const float* i_pre, co
 
     // 1. gates as in the forward pass, then fold 1/h_denom into the backward weights
     if (!reuse) {
-        int st = run_gates(d, i_pre, f_pre, m0, w.wrow, w.ucol, w.sH, w.aK, w.gbar, w.mout, nullptr, w.tmp, w.csum, w.wrow_lo, w.ucol_lo, softcap, Tvalid, dqk_true, s);
+        int st = run_gates(d, i_pre, f_pre, m0, w.wrow, w.ucol, w.sH, w.aK, w.gbar, w.mout, nullptr, nullptr, w.tmp, w.csum, w.wrow_lo, w.ucol_lo, softcap, s);
         if (st != TFLA_OK) return st;
     }
     // mLSTMsig has no denominator (the weights are the forward pass's own); for mLSTMexp the forward call has left
@@ -346,7 +377,7 @@ int bwd_core(const void* q, const void* k, const void* v, const float* i_pre, co
         } else {
             GateBwdPrepArgs p;
             p.wrow = wrow; p.sH = sH; p.n_out = n_out; p.m_out = m_out; p.wrowB = w.wrowB; p.sQ = w.sQ;
-            p.n = d.BHT; p.variant = variant; p.eps = eps;
+            p.n = d.BHT; p.variant = variant; p.eps = eps; p.T = d.T; p.Tvalid = T;
             p.wrow_lo = wrow_lo; p.wrowB_lo = wrow_lo ? w.wrowB_lo : nullptr;
             TFLA_LAUNCH(K_BWD_PREP, launch_gate_bwd_prep(p, s));
             wrowB = w.wrowB; sQ = w.sQ; wrowB_lo = p.wrowB_lo;
@@ -360,9 +391,10 @@ int bwd_core(const void* q, const void* k, const void* v, const float* i_pre, co
         RecArgs r;
         r.X = k; r.Y = v; r.rs = aK; r.gbar = gbar; r.S0 = C0;
         r.stT = tonly ? w.cN : nullptr; r.stN = tonly ? nullptr : w.cN;
-        r.Sfinal = dCn ? w.Cfinal : nullptr; r.Sfinal2 = nullptr;
+        r.Sfinal = nullptr; r.Sfinal2 = dCn ? w.Cfinal : nullptr;
         r.n0 = nullptr; r.nst = nullptr; r.nfinal = nullptr;
-        r.T = T; r.L = chunk; r.Nc = d.Nc; r.d1 = dqk; r.d2 = dhv; r.reverse = 0;
+        r.T = d.T; r.L = chunk; r.Nc = d.Nc; r.d1 = d.dqk; r.d2 = d.dhv; r.reverse = 0;
+        r.T_in = T; r.d1_in = dqk; r.d2_in = dhv;
         r.anc = w.ancC; r.anc_in = nullptr; r.anc_part = nullptr; r.anc_G = anchor_G(d);
         TFLA_LAUNCH(K_REC_FWD, launch_recurrent(r, (int)d.BH, dtype, s));
     }
@@ -372,7 +404,8 @@ int bwd_core(const void* q, const void* k, const void* v, const float* i_pre, co
     rb.X = q; rb.Y = dH; rb.rs = sQ; rb.gbar = gbar; rb.S0 = dCn;
     rb.stT = w.dcT; rb.stN = tonly ? nullptr : w.dcN; rb.Sfinal = dC0; rb.Sfinal2 = nullptr;
     rb.n0 = nullptr; rb.nst = nullptr; rb.nfinal = nullptr;
-    rb.T = T; rb.L = chunk; rb.Nc = d.Nc; rb.d1 = dqk; rb.d2 = dhv; rb.reverse = 1;
+    rb.T = d.T; rb.L = chunk; rb.Nc = d.Nc; rb.d1 = d.dqk; rb.d2 = d.dhv; rb.reverse = 1;
+    rb.T_in = T; rb.d1_in = dqk; rb.d2_in = dhv;
     // bf16: the reversed launch also forms <C, dC> at the block boundaries of the forget-gate gradient scan, from the
     // fp32 copies of C that the forward launch left there and its own fp32 accumulators
     rb.anc = nullptr; rb.anc_in = tonly ? (reuse_states ? fw.anc : w.ancC) : nullptr; rb.anc_part = tonly ? w.anchor : nullptr;
@@ -381,26 +414,26 @@ int bwd_core(const void* q, const void* k, const void* v, const float* i_pre, co
 
     // 4. the three gradient kernels
     TileArgs t{};
-    t.T = T; t.L = chunk; t.Nc = d.Nc; t.variant = variant; t.eps = eps;
+    t.T = d.T; t.L = chunk; t.Nc = d.Nc; t.variant = variant; t.eps = eps;
     t.nstate = nullptr; t.mout = nullptr; t.nout = nullptr; t.E = w.E; t.E2 = w.E2; t.part_acc = w.pacc;
     // dV: rows = kv index j
-    t.X = k; t.Y = q; t.Z = dH; t.Out = dv; t.out_T = Tvalid; t.out_ld = dhv_true; t.out_cols = dhv_true; t.wrow_lo = ucol_lo; t.wcol_lo = wrowB_lo; t.wrowB_lo_out = nullptr; t.wrow = ucol; t.wcol = wrowB; t.srow = aK; t.St = w.dcT;
-    t.d1 = dqk; t.d2 = dhv; t.dotwith = nullptr; t.dotpart = nullptr;
+    t.X = k; t.Y = q; t.Z = dH; t.Out = dv; t.out_T = T; t.out_ld = dhv; t.in_ld1 = t.in_cols1 = dqk; t.wrow_lo = ucol_lo; t.wcol_lo = wrowB_lo; t.wrowB_lo_out = nullptr; t.wrow = ucol; t.wcol = wrowB; t.srow = aK; t.St = w.dcT;
+    t.d1 = d.dqk; t.d2 = d.dhv; t.dotwith = nullptr; t.dotpart = nullptr;
     TFLA_LAUNCH(K_TILE_DV, launch_tile_mode<MODE_DV>(t, (int)d.BH, dtype, s));
     // dQ: rows = query index i
-    t.X = dH; t.Y = v; t.Z = k; t.Out = dq; t.out_ld = dqk_true; t.out_cols = dqk_true; t.wrow_lo = wrowB_lo; t.wcol_lo = ucol_lo; t.wrow = wrowB; t.wcol = ucol; t.srow = sQ; t.St = cstates;
-    t.d1 = dhv; t.d2 = dqk; t.dotwith = q; t.dotpart = w.partQ;
+    t.X = dH; t.Y = v; t.Z = k; t.Out = dq; t.out_ld = dqk; t.in_ld1 = t.in_cols1 = dhv; t.wrow_lo = wrowB_lo; t.wcol_lo = ucol_lo; t.wrow = wrowB; t.wcol = ucol; t.srow = sQ; t.St = cstates;
+    t.d1 = d.dhv; t.d2 = d.dqk; t.dotwith = q; t.dotpart = w.partQ;
     TFLA_LAUNCH(K_TILE_DQ, launch_tile_mode<MODE_DQ>(t, (int)d.BH, dtype, s));
     // dK: rows = kv index j
     t.X = v; t.Y = dH; t.Z = q; t.Out = dk; t.wrow_lo = ucol_lo; t.wcol_lo = wrowB_lo; t.wrow = ucol; t.wcol = wrowB; t.srow = aK; t.St = tonly ? w.dcT : w.dcN;
-    t.d1 = dhv; t.d2 = dqk; t.dotwith = k; t.dotpart = w.partK;
+    t.d1 = d.dhv; t.d2 = d.dqk; t.dotwith = k; t.dotpart = w.partK;
     TFLA_LAUNCH(K_TILE_DK, launch_tile_mode<MODE_DK>(t, (int)d.BH, dtype, s));
 
     // 5. gate gradients
-    if (dCn) TFLA_LAUNCH(K_STATE_DOT, launch_state_dot(Cfinal, dCn, w.cdot, (long)dqk * dhv, (int)d.BH, s));
+    if (dCn) TFLA_LAUNCH(K_STATE_DOT, launch_state_dot(Cfinal, (long)d.dqk * d.dhv, d.dhv, dCn, dqk, dhv, w.cdot, (int)d.BH, s));
     GateGradArgs gg;
     gg.partQ = w.partQ; gg.nbQ = w.nbQ; gg.partK = w.partK; gg.nbK = w.nbK; gg.cdot = dCn ? w.cdot : nullptr;
-    gg.i_pre = i_pre; gg.f_pre = f_pre; gg.d_i = d_i_pre; gg.d_f = d_f_pre; gg.T = T; gg.variant = variant;
+    gg.i_pre = i_pre; gg.f_pre = f_pre; gg.d_i = d_i_pre; gg.d_f = d_f_pre; gg.T = d.T; gg.Tvalid = T; gg.variant = variant;
     gg.BHT = d.BHT; gg.bsum = w.bsum; gg.softcap = softcap;
     gg.anchor = nullptr; gg.L = chunk; gg.Nc = d.Nc; gg.G = 1; gg.npart = 0;
     // bf16: the forget-gate scan is anchored with <C_k, dC_k> at the end of every block of anchor_chunks() chunks
@@ -410,203 +443,12 @@ int bwd_core(const void* q, const void* k, const void* v, const float* i_pre, co
     // boundaries and the reversed launch multiplies them with its fp32 accumulators (see RecArgs).
     if (tonly) {
         gg.G = anchor_G(d);
-        gg.anchor = w.anchor; gg.npart = rec_anchor_parts(dqk, dhv);
+        gg.anchor = w.anchor; gg.npart = rec_anchor_parts(d.dqk, d.dhv);
     }
     TFLA_LAUNCH(K_GATE_GRADS, launch_gate_grads(gg, (int)d.BH, s));
     return TFLA_OK;
 }
 
-
-// ---- sequence lengths that do not fill the last chunk, head dimensions between the kernels' own -------
-// The cores work on whole chunks and on head dimensions 64, 128, 256, 512 (bf16 also 1024).  For any other T or head
-// dimension the entry points copy q, k, v (and dH) into zero-padded buffers behind the core's own workspace and
-// run the core there (Tvalid = T, the 1/sqrt(dqk) of the true dqk).  The tiled kernels store the true steps and
-// columns of H, dq, dk, dv straight into the caller's tensors; per-step scalars go through padded copies only when
-// the sequence itself is padded, states only when a head dimension is.  `d` below always describes the padded problem.
-struct PadFwd {
-    void *q, *k, *v;
-    float *ip, *fp, *nout, *mout, *C0, *n0, *Cn, *nn;
-    size_t bytes;
-};
-PadFwd carve_pad_fwd(const Dims& d, void* base) {
-    Carver c(base);
-    PadFwd p;
-    p.q = c.take_bytes((size_t)d.BHT * d.dqk * d.esz); p.k = c.take_bytes((size_t)d.BHT * d.dqk * d.esz);
-    p.v = c.take_bytes((size_t)d.BHT * d.dhv * d.esz);
-    p.ip = c.take<float>(d.BHT); p.fp = c.take<float>(d.BHT); p.nout = c.take<float>(d.BHT); p.mout = c.take<float>(d.BHT);
-    p.C0 = c.take<float>((size_t)d.BH * d.dqk * d.dhv); p.n0 = c.take<float>((size_t)d.BH * d.dqk);
-    p.Cn = c.take<float>((size_t)d.BH * d.dqk * d.dhv); p.nn = c.take<float>((size_t)d.BH * d.dqk);
-    p.bytes = c.off;
-    return p;
-}
-struct PadBwd {
-    void *q, *k, *v, *dH;
-    float *ip, *fp, *nout, *mout, *di, *df, *C0, *n0, *dCn, *dC0;
-    size_t bytes;
-};
-PadBwd carve_pad_bwd(const Dims& d, void* base) {
-    Carver c(base);
-    PadBwd p;
-    const size_t sq = (size_t)d.BHT * d.dqk * d.esz, sv = (size_t)d.BHT * d.dhv * d.esz;
-    p.q = c.take_bytes(sq); p.k = c.take_bytes(sq); p.v = c.take_bytes(sv); p.dH = c.take_bytes(sv);
-    p.ip = c.take<float>(d.BHT); p.fp = c.take<float>(d.BHT); p.nout = c.take<float>(d.BHT); p.mout = c.take<float>(d.BHT);
-    p.di = c.take<float>(d.BHT); p.df = c.take<float>(d.BHT);
-    const size_t ss = (size_t)d.BH * d.dqk * d.dhv;
-    p.C0 = c.take<float>(ss); p.n0 = c.take<float>((size_t)d.BH * d.dqk); p.dCn = c.take<float>(ss); p.dC0 = c.take<float>(ss);
-    p.bytes = c.off;
-    return p;
-}
-// dp: the padded problem; padded = whether the caller's problem differs from it
-size_t fwd_total_bytes(const Dims& dp, bool padded) {
-    return carve_fwd(dp, nullptr).bytes + (padded ? carve_pad_fwd(dp, nullptr).bytes : 0);
-}
-size_t bwd_total_bytes(const Dims& dp, bool padded) {
-    return carve_bwd(dp, nullptr).bytes + (padded ? carve_pad_bwd(dp, nullptr).bytes : 0);
-}
-inline bool misaligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) != 0; }
-inline bool needs_pad(int T, int dqk, int dhv, int chunk) {
-    return T % chunk != 0 || dqk != kernel_dim(dqk) || dhv != kernel_dim(dhv);
-}
-
-int fwd_impl(const void* q, const void* k, const void* v, const float* i_pre, const float* f_pre, const float* C0,
-             const float* n0, const float* m0, int B, int NH, int T, int dqk, int dhv, int chunk, int variant, int dtype,
-             float eps, float softcap, void* H, float* Cn, float* nn, float* mn, float* n_out, float* m_out,
-             void* workspace, size_t workspace_bytes, void* stream, const LayerFuse* fz = nullptr) {
-    const int rc = check_dims(TFLA_FWD, B, NH, T, dqk, dhv, chunk, variant, dtype);
-    if (rc != TFLA_OK) return rc;
-    if (!needs_pad(T, dqk, dhv, chunk))
-        return fwd_core(q, k, v, i_pre, f_pre, C0, n0, m0, B, NH, T, T, dqk, dhv, dqk, dhv, chunk, variant, dtype, eps, softcap, H,
-                        Cn, nn, mn, n_out, m_out, workspace, workspace_bytes, stream, fz);
-    if (fz) return TFLA_ERR_SHAPE;      // (the fused layer output is for problems that need no padding)
-    if (!q || !k || !v || !i_pre || !f_pre || !H) return TFLA_ERR_NULL;
-    const bool is_exp = variant == TFLA_EXP;
-    if (is_exp) {
-        const int given = (C0 != nullptr) + (n0 != nullptr) + (m0 != nullptr);
-        if (given != 0 && given != 3) return TFLA_ERR_STATE;
-    }
-    if (misaligned16(q) || misaligned16(k) || misaligned16(v) || misaligned16(H) || misaligned16(C0) || misaligned16(Cn))
-        return TFLA_ERR_SHAPE;
-    const int dq_p = kernel_dim(dqk), dv_p = kernel_dim(dhv);
-    const Dims d = make_dims(B, NH, T, dq_p, dv_p, chunk, variant, dtype);
-    if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255) != 0) return TFLA_ERR_WORKSPACE;
-    const size_t core_bytes = carve_fwd(d, nullptr).bytes;
-    const PadFwd p = carve_pad_fwd(d, reinterpret_cast<char*>(workspace) + core_bytes);
-    if (workspace_bytes < core_bytes + p.bytes) return TFLA_ERR_WORKSPACE;
-    hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    const int Tp = d.T, es = (int)d.esz;
-    const bool dpad = dq_p != dqk || dv_p != dhv;       // states need padding too
-    TFLA_LAUNCH(K_PAD, launch_pad_rows(q, p.q, d.BH, T, Tp, dqk * es, dq_p * es, s));
-    TFLA_LAUNCH(K_PAD, launch_pad_rows(k, p.k, d.BH, T, Tp, dqk * es, dq_p * es, s));
-    TFLA_LAUNCH(K_PAD, launch_pad_rows(v, p.v, d.BH, T, Tp, dhv * es, dv_p * es, s));
-    // per-step scalars need copies only when the sequence itself is padded
-    const bool tpad = Tp != T;
-    if (tpad) {
-        TFLA_LAUNCH(K_PAD, launch_pad_scalar(i_pre, p.ip, d.BH, T, Tp, 0.0f, s));
-        TFLA_LAUNCH(K_PAD, launch_pad_scalar(f_pre, p.fp, d.BH, T, Tp, 0.0f, s));
-    }
-    const float* C0c = C0; const float* n0c = n0;
-    if (dpad && C0) {
-        TFLA_LAUNCH(K_PAD, launch_pad_rows(C0, p.C0, d.BH, dqk, dq_p, dhv * 4, dv_p * 4, s));
-        C0c = p.C0;
-        if (is_exp) { TFLA_LAUNCH(K_PAD, launch_pad_scalar(n0, p.n0, d.BH, dqk, dq_p, 0.0f, s)); n0c = p.n0; }
-    }
-    float* Cnc = (dpad && Cn) ? p.Cn : Cn;
-    float* nnc = (dpad && nn) ? p.nn : nn;
-    // (the H kernel stores the true steps and columns straight into the caller's H)
-    const int st = fwd_core(p.q, p.k, p.v, tpad ? p.ip : i_pre, tpad ? p.fp : f_pre, C0c, n0c, m0, B, NH, Tp, T, dqk, dhv, dq_p,
-                            dv_p, chunk, variant, dtype, eps, softcap, H, Cnc, nnc, mn, (n_out && tpad) ? p.nout : n_out,
-                            (m_out && tpad) ? p.mout : m_out, workspace, core_bytes, stream);
-    if (st != TFLA_OK) return st;
-    if (n_out && tpad) TFLA_LAUNCH(K_PAD, launch_unpad_scalar(p.nout, n_out, d.BH, T, Tp, s));
-    if (m_out && tpad) TFLA_LAUNCH(K_PAD, launch_unpad_scalar(p.mout, m_out, d.BH, T, Tp, s));
-    if (dpad && Cn) TFLA_LAUNCH(K_PAD, launch_unpad_rows(p.Cn, Cn, d.BH, dqk, dq_p, dhv * 4, dv_p * 4, s));
-    if (dpad && nn) TFLA_LAUNCH(K_PAD, launch_unpad_scalar(p.nn, nn, d.BH, dqk, dq_p, s));
-    return TFLA_OK;
-}
-
-int bwd_impl(const void* q, const void* k, const void* v, const float* i_pre, const float* f_pre, const float* C0,
-             const float* n0, const float* m0, const float* n_out, const float* m_out, const void* dH, const float* dCn,
-             int B, int NH, int T, int dqk, int dhv, int chunk, int variant, int dtype, float eps, float softcap, void* dq,
-             void* dk, void* dv, float* d_i_pre, float* d_f_pre, float* dC0, const void* fwd_workspace,
-             size_t fwd_workspace_bytes, void* workspace, size_t workspace_bytes, void* stream) {
-    const int rc = check_dims(TFLA_BWD, B, NH, T, dqk, dhv, chunk, variant, dtype);
-    if (rc != TFLA_OK) return rc;
-    if (!needs_pad(T, dqk, dhv, chunk))
-        return bwd_core(q, k, v, i_pre, f_pre, C0, n0, m0, n_out, m_out, dH, dCn, B, NH, T, T, dqk, dhv, dqk, dhv, chunk, variant,
-                        dtype, eps, softcap, dq, dk, dv, d_i_pre, d_f_pre, dC0, fwd_workspace, fwd_workspace_bytes,
-                        workspace, workspace_bytes, stream);
-    if (!q || !k || !v || !i_pre || !f_pre || !dH || !dq || !dk || !dv || !d_i_pre || !d_f_pre) return TFLA_ERR_NULL;
-    const bool is_exp = variant == TFLA_EXP;
-    if (is_exp) {
-        if (!n_out || !m_out) return TFLA_ERR_NULL;
-        const int given = (C0 != nullptr) + (n0 != nullptr) + (m0 != nullptr);
-        if (given != 0 && given != 3) return TFLA_ERR_STATE;
-    }
-    if (misaligned16(q) || misaligned16(k) || misaligned16(v) || misaligned16(dH) || misaligned16(dq) || misaligned16(dk) ||
-        misaligned16(dv) || misaligned16(C0) || misaligned16(dCn) || misaligned16(dC0))
-        return TFLA_ERR_SHAPE;
-    const int dq_p = kernel_dim(dqk), dv_p = kernel_dim(dhv);
-    const Dims d = make_dims(B, NH, T, dq_p, dv_p, chunk, variant, dtype);
-    if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255) != 0) return TFLA_ERR_WORKSPACE;
-    if (fwd_workspace && ((reinterpret_cast<uintptr_t>(fwd_workspace) & 255) != 0 ||
-                          fwd_workspace_bytes < carve_fwd(d, nullptr).bytes))
-        return TFLA_ERR_WORKSPACE;
-    const size_t core_bytes = carve_bwd(d, nullptr).bytes;
-    const PadBwd p = carve_pad_bwd(d, reinterpret_cast<char*>(workspace) + core_bytes);
-    if (workspace_bytes < core_bytes + p.bytes) return TFLA_ERR_WORKSPACE;
-    hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    const int Tp = d.T, es = (int)d.esz, eq = dqk * es, ev = dhv * es, eqp = dq_p * es, evp = dv_p * es;
-    const bool dpad = dq_p != dqk || dv_p != dhv;
-    const bool tpad = Tp != T;      // per-step scalars need copies only when the sequence itself is padded
-    // The forward call left its padded copies of q, k, v and the gate pre-activations behind its core workspace:
-    // a backward call that is handed that workspace (whole) reads them there instead of copying again.
-    const void *pq = p.q, *pk = p.k, *pv = p.v;
-    const float *pip = p.ip, *pfp = p.fp;
-    const size_t fwd_core_bytes = carve_fwd(d, nullptr).bytes;
-    if (fwd_workspace && fwd_workspace_bytes >= fwd_core_bytes + carve_pad_fwd(d, nullptr).bytes) {
-        const PadFwd pf = carve_pad_fwd(d, const_cast<char*>(reinterpret_cast<const char*>(fwd_workspace)) + fwd_core_bytes);
-        pq = pf.q; pk = pf.k; pv = pf.v; pip = pf.ip; pfp = pf.fp;
-    } else {
-        TFLA_LAUNCH(K_PAD, launch_pad_rows(q, p.q, d.BH, T, Tp, eq, eqp, s));
-        TFLA_LAUNCH(K_PAD, launch_pad_rows(k, p.k, d.BH, T, Tp, eq, eqp, s));
-        TFLA_LAUNCH(K_PAD, launch_pad_rows(v, p.v, d.BH, T, Tp, ev, evp, s));
-        if (tpad) {
-            TFLA_LAUNCH(K_PAD, launch_pad_scalar(i_pre, p.ip, d.BH, T, Tp, 0.0f, s));
-            TFLA_LAUNCH(K_PAD, launch_pad_scalar(f_pre, p.fp, d.BH, T, Tp, 0.0f, s));
-        }
-    }
-    if (!tpad) { pip = i_pre; pfp = f_pre; }
-    TFLA_LAUNCH(K_PAD, launch_pad_rows(dH, p.dH, d.BH, T, Tp, ev, evp, s));
-    if (is_exp && tpad) {
-        // denominators of the padding steps: max{|1|, exp(0)} -- any finite non-zero value would do
-        TFLA_LAUNCH(K_PAD, launch_pad_scalar(n_out, p.nout, d.BH, T, Tp, 1.0f, s));
-        TFLA_LAUNCH(K_PAD, launch_pad_scalar(m_out, p.mout, d.BH, T, Tp, 0.0f, s));
-    }
-    const float* C0c = C0; const float* n0c = n0; const float* dCnc = dCn;
-    if (dpad && C0) {
-        TFLA_LAUNCH(K_PAD, launch_pad_rows(C0, p.C0, d.BH, dqk, dq_p, dhv * 4, dv_p * 4, s));
-        C0c = p.C0;
-        if (is_exp) { TFLA_LAUNCH(K_PAD, launch_pad_scalar(n0, p.n0, d.BH, dqk, dq_p, 0.0f, s)); n0c = p.n0; }
-    }
-    if (dpad && dCn) {
-        TFLA_LAUNCH(K_PAD, launch_pad_rows(dCn, p.dCn, d.BH, dqk, dq_p, dhv * 4, dv_p * 4, s));
-        dCnc = p.dCn;
-    }
-    float* dC0c = (dpad && dC0) ? p.dC0 : dC0;
-    const float* noc = !is_exp ? nullptr : (tpad ? p.nout : n_out);
-    const float* moc = !is_exp ? nullptr : (tpad ? p.mout : m_out);
-    const int st = bwd_core(pq, pk, pv, pip, pfp, C0c, n0c, m0, noc, moc, p.dH, dCnc, B, NH, Tp, T, dqk, dhv, dq_p, dv_p,
-                            chunk, variant, dtype, eps, softcap, dq, dk, dv, tpad ? p.di : d_i_pre, tpad ? p.df : d_f_pre,
-                            dC0c, fwd_workspace, fwd_workspace_bytes, workspace, core_bytes, stream);
-    if (st != TFLA_OK) return st;
-    // (the gradient kernels stored the true steps and columns straight into the caller's dq, dk, dv)
-    if (tpad) {
-        TFLA_LAUNCH(K_PAD, launch_unpad_scalar(p.di, d_i_pre, d.BH, T, Tp, s));
-        TFLA_LAUNCH(K_PAD, launch_unpad_scalar(p.df, d_f_pre, d.BH, T, Tp, s));
-    }
-    if (dpad && dC0) TFLA_LAUNCH(K_PAD, launch_unpad_rows(p.dC0, dC0, d.BH, dqk, dq_p, dhv * 4, dv_p * 4, s));
-    return TFLA_OK;
-}
 
 }  // namespace
 
@@ -712,9 +554,8 @@ int tfla_mlstm_check(int direction, int B, int NH, int T, int dqk, int dhv, int 
 size_t tfla_mlstm_workspace_bytes(int direction, int B, int NH, int T, int dqk, int dhv, int chunk, int variant,
                                   int dtype) {
     if (check_dims(direction, B, NH, T, dqk, dhv, chunk, variant, dtype) != TFLA_OK) return 0;
-    const Dims d = make_dims(B, NH, T, kernel_dim(dqk), kernel_dim(dhv), chunk, variant, dtype);
-    const bool padded = needs_pad(T, dqk, dhv, chunk);
-    return direction == TFLA_FWD ? fwd_total_bytes(d, padded) : bwd_total_bytes(d, padded);
+    const Dims d = make_dims(B, NH, T, dqk, dhv, chunk, variant, dtype);
+    return direction == TFLA_FWD ? fwd_total_bytes(d) : bwd_total_bytes(d);
 }
 
 int tfla_mlstm_fwd(const void* q, const void* k, const void* v, const float* i_pre, const float* f_pre,
@@ -868,13 +709,12 @@ int tfla_mlstm_layer_bwd(const void* q, const void* k, const void* v, const floa
         const int given = (C0 != nullptr) + (n0 != nullptr) + (m0 != nullptr);
         if (given != 0 && given != 3) return TFLA_ERR_STATE;
     }
-    // d: the problem the cell's kernels run (whole chunks, their own head dimensions)
-    const Dims d = make_dims(B, NH, T, kernel_dim(dqk), kernel_dim(dhv), chunk, variant, dtype);
+    const Dims d = make_dims(B, NH, T, dqk, dhv, chunk, variant, dtype);
     if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255) != 0) return TFLA_ERR_WORKSPACE;
     if (fwd_workspace && ((reinterpret_cast<uintptr_t>(fwd_workspace) & 255) != 0 ||
                           fwd_workspace_bytes < carve_fwd(d, nullptr).bytes))
         return TFLA_ERR_WORKSPACE;
-    const size_t base = bwd_total_bytes(d, needs_pad(T, dqk, dhv, chunk));
+    const size_t base = bwd_total_bytes(d);
     const int nblk = norm_row_blocks(T);
     Carver c(reinterpret_cast<char*>(workspace) + base);
     void* dHt = c.take_bytes((size_t)d.BH * T * dhv * d.esz);

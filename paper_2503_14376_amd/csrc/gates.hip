@@ -106,10 +106,11 @@ __global__ void __launch_bounds__(GATE_WAVES * 64) gates_chunk_kernel(GateArgs a
     const long t0 = (long)kc * a.L + (long)lane * E;
     // log gates of step t; the padding steps of a sequence that does not fill its last chunk keep the
     // state as it is (log forget gate 0) and add nothing (log input gate far below every other)
-    auto fbar_at = [&](long t) { return t < a.Tvalid ? log_sigmoid_t<AT>(soft_cap_t<AT>((AT)a.f_pre[row + t], a.softcap)) : (AT)0; };
+    const long urow = (long)bh * a.Tvalid;          // the caller's tensors
+    auto fbar_at = [&](long t) { return t < a.Tvalid ? log_sigmoid_t<AT>(soft_cap_t<AT>((AT)a.f_pre[urow + t], a.softcap)) : (AT)0; };
     auto ibar_at = [&](long t) {
         if (t >= a.Tvalid) return (AT)-1.0e30f;
-        const AT ip = soft_cap_t<AT>((AT)a.i_pre[row + t], a.softcap);
+        const AT ip = soft_cap_t<AT>((AT)a.i_pre[urow + t], a.softcap);
         return is_exp ? ip : log_sigmoid_t<AT>(ip);
     };
     constexpr int NC = EC > 0 ? EC : 1;
@@ -240,6 +241,7 @@ __global__ void __launch_bounds__(GATE_WAVES * 64) gates_step_kernel(GateArgs a)
         a.sH[row + t0 + e] = (float)sh;
         a.aK[row + t0 + e] = (float)exp_t<AT>(av - mk);
         a.mout[row + t0 + e] = (float)mo;
+        if (a.mout_user && t0 + e < a.Tvalid) a.mout_user[(long)bh * a.Tvalid + t0 + e] = (float)mo;
     }
 }
 
@@ -266,7 +268,16 @@ __global__ void gate_bwd_prep_kernel(GateBwdPrepArgs a) {
     const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= a.n) return;
     float den = 1.0f;
-    if (a.variant == 0) den = fmaxf(fabsf(a.n_out[i]), expf(-a.m_out[i])) + a.eps;
+    if (a.variant == 0) {
+        long u = i;
+        bool there = true;
+        if (a.Tvalid != a.T) {          // (steps past the end of the sequence: any finite non-zero value would do)
+            const long bh = i / a.T, t = i - bh * a.T;
+            there = t < a.Tvalid;
+            u = bh * a.Tvalid + t;
+        }
+        if (there) den = fmaxf(fabsf(a.n_out[u]), expf(-a.m_out[u])) + a.eps;
+    }
     if (a.wrowB_lo) {
         // fp32 kernels: the difference to double accuracy, as a (rounded, remainder) pair
         const double w = (double)a.wrow[i] + (double)a.wrow_lo[i] - log2((double)den);
@@ -360,9 +371,12 @@ __global__ void __launch_bounds__(256) gate_grads_kernel(GateGradArgs a) {
         const int t = t0 + e;
         if (t < a.T) {
             run += (double)r[e] - (double)c[e];
-            const float fp = a.f_pre[row + t], ip = a.i_pre[row + t];
-            a.d_f[row + t] = (float)run * sigmoid_neg(soft_cap(fp, a.softcap)) * soft_cap_grad(fp, a.softcap);
-            a.d_i[row + t] = (a.variant == 0 ? c[e] : c[e] * sigmoid_neg(soft_cap(ip, a.softcap))) * soft_cap_grad(ip, a.softcap);
+            if (t < a.Tvalid) {
+                const long u = (long)bh * a.Tvalid + t;
+                const float fp = a.f_pre[u], ip = a.i_pre[u];
+                a.d_f[u] = (float)run * sigmoid_neg(soft_cap(fp, a.softcap)) * soft_cap_grad(fp, a.softcap);
+                a.d_i[u] = (a.variant == 0 ? c[e] : c[e] * sigmoid_neg(soft_cap(ip, a.softcap))) * soft_cap_grad(ip, a.softcap);
+            }
         }
     }
 }
@@ -420,9 +434,12 @@ __global__ void __launch_bounds__(256) gate_grads_anchored_kernel(GateGradArgs a
         if (e < SEG && l0 + e < len) {
             const long t = tb + l0 + e;
             run += (double)r[e] - (double)c[e];
-            const float fp = a.f_pre[row + t], ip = a.i_pre[row + t];
-            a.d_f[row + t] = (float)run * sigmoid_neg(soft_cap(fp, a.softcap)) * soft_cap_grad(fp, a.softcap);
-            a.d_i[row + t] = (a.variant == 0 ? c[e] : c[e] * sigmoid_neg(soft_cap(ip, a.softcap))) * soft_cap_grad(ip, a.softcap);
+            if (t < a.Tvalid) {
+                const long u = (long)bh * a.Tvalid + t;
+                const float fp = a.f_pre[u], ip = a.i_pre[u];
+                a.d_f[u] = (float)run * sigmoid_neg(soft_cap(fp, a.softcap)) * soft_cap_grad(fp, a.softcap);
+                a.d_i[u] = (a.variant == 0 ? c[e] : c[e] * sigmoid_neg(soft_cap(ip, a.softcap))) * soft_cap_grad(ip, a.softcap);
+            }
         }
     }
 }
@@ -471,12 +488,16 @@ hipError_t launch_fill_zero4(const FillList& f, hipStream_t s) {
     return hipGetLastError();
 }
 
-// out[bh] = <A[bh], B[bh]> over `per` floats
-__global__ void __launch_bounds__(1024) state_dot_kernel(const float* A, const float* Bm, float* out, long per) {
+// out[bh] = <A[bh], Bm[bh]> over the d1 x d2 values of Bm; A's rows are lda apart
+__global__ void __launch_bounds__(1024) state_dot_kernel(const float* A, long perA, int lda, const float* Bm, int d1, int d2, float* out) {
     __shared__ double wt[16];
     const int bh = blockIdx.x, tid = threadIdx.x;
+    const long per = (long)d1 * d2;
     double acc = 0.0;
-    for (long i = tid; i < per; i += 1024) acc += (double)A[bh * per + i] * (double)Bm[bh * per + i];
+    for (long i = tid; i < per; i += 1024) {
+        const long r = i / d2;
+        acc += (double)A[bh * perA + r * lda + (i - r * d2)] * (double)Bm[bh * per + i];
+    }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o, 64);
     if ((tid & 63) == 0) wt[tid >> 6] = acc;
@@ -487,8 +508,8 @@ __global__ void __launch_bounds__(1024) state_dot_kernel(const float* A, const f
         out[bh] = (float)t;
     }
 }
-hipError_t launch_state_dot(const float* A, const float* Bm, float* out, long per, int BH, hipStream_t s) {
-    hipLaunchKernelGGL(state_dot_kernel, dim3(BH), dim3(1024), 0, s, A, Bm, out, per);
+hipError_t launch_state_dot(const float* A, long perA, int lda, const float* Bm, int d1, int d2, float* out, int BH, hipStream_t s) {
+    hipLaunchKernelGGL(state_dot_kernel, dim3(BH), dim3(1024), 0, s, A, perA, lda, Bm, d1, d2, out);
     return hipGetLastError();
 }
 

@@ -90,6 +90,43 @@ __device__ __forceinline__ void dma16_free_nt(const void* gbase_uniform, uint32_
                  :: "s"(la), "v"(voff), "s"(gu) : "m0");
 }
 
+// The same load through a buffer descriptor: lanes whose offset lies at or beyond `bytes` (measured from gbase) read
+// nothing and leave zeros in LDS.  For operands that end before the tile does: the steps past the end of a sequence and
+// the columns past a head dimension are filled with zeros on the way instead of being copied into padded buffers first.
+// CLOBBER: ordered with the surrounding memory accesses like dma16, else free like dma16_free.
+template <bool ONCE, bool CLOBBER>
+__device__ __forceinline__ void dma16_bounded(const void* gbase_uniform, uint32_t bytes, uint32_t voff, uint32_t lds_uniform) {
+    const uint32_t la = __builtin_amdgcn_readfirstlane(lds_uniform);
+    const uint64_t gb = (uint64_t)(uintptr_t)gbase_uniform;
+    u32x4 rsrc;
+    rsrc[0] = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)gb);
+    rsrc[1] = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(gb >> 32)) & 0xffffu;   // stride 0: a raw buffer
+    rsrc[2] = (uint32_t)__builtin_amdgcn_readfirstlane((int)bytes);
+    rsrc[3] = 0x00020000u;                                                                    // 32-bit data format
+    if constexpr (CLOBBER) {
+        if constexpr (ONCE)
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tbuffer_load_dwordx4 %1, %2, 0 offen nt lds"
+                         :: "s"(la), "v"(voff), "s"(rsrc) : "memory", "m0");
+        else
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
+                         :: "s"(la), "v"(voff), "s"(rsrc) : "memory", "m0");
+    } else {
+        if constexpr (ONCE)
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tbuffer_load_dwordx4 %1, %2, 0 offen nt lds"
+                         :: "s"(la), "v"(voff), "s"(rsrc) : "m0");
+        else
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
+                         :: "s"(la), "v"(voff), "s"(rsrc) : "m0");
+    }
+}
+// Bytes from the first element of a tile to the end of what may be read: rows_left rows of the tensor (from the tile's
+// first row on) of which cols_left columns lie at or behind the tile's first column; 0 when there is nothing.
+__device__ __forceinline__ uint32_t bounded_bytes(int rows_left, int cols_left, int row_bytes) {
+    const int r = rows_left < 8192 ? rows_left : 8192;      // (more than any tile has; keeps the product in 32 bits)
+    return (r > 0 && cols_left > 0) ? (uint32_t)(r - 1) * (uint32_t)row_bytes + 2u * (uint32_t)cols_left : 0u;
+}
+static constexpr uint32_t DMA_NOTHING = 0x7ffffff0u;        // an offset beyond every bounded_bytes()
+
 // Same for 64 x 4 bytes: lane l copies one dword to LDS address lds_uniform + 4 * l.
 __device__ __forceinline__ void dma4(const void* gbase_uniform, uint32_t voff, uint32_t lds_uniform) {
     const uint32_t la = __builtin_amdgcn_readfirstlane(lds_uniform);
@@ -149,6 +186,25 @@ template <int ROWS, int COLS, int NT, int KIND> struct DmaTile {
             if constexpr (ONCE) dma16_nt(gtile, goff[j], lds + (wave + j * NWV) * 1024);
             else dma16(gtile, goff[j], lds + (wave + j * NWV) * 1024);
         }
+    }
+    // The loads j = part, part + nparts, ... of a tile that reaches past the end of its tensor: `bytes` as
+    // bounded_bytes() gives it (rows past the end lie beyond it), cols_left the columns that exist from the tile's first
+    // on (the lanes behind them are sent out of range).
+    template <bool ONCE, bool CLOBBER>
+    __device__ __forceinline__ void issue_bounded(const bf16_t* gtile, uint32_t bytes, int cols_left, uint32_t lds, int tid,
+                                                  int part = 0, int nparts = 1) const {
+        const int lane = tid & 63, wave = tid >> 6;
+#pragma unroll
+        for (int j = 0; j < N; ++j)
+            if (j % nparts == part) {
+                uint32_t vo = goff[j];
+                if (cols_left < COLS) {
+                    const int q = (wave + j * NWV) * 64 + lane;
+                    const int c = (q % CPR) ^ swz_mask<KIND, CPR>(q / CPR);
+                    vo = c * 8 < cols_left ? vo : DMA_NOTHING;
+                }
+                dma16_bounded<ONCE, CLOBBER>(gtile, bytes, vo, lds + (wave + j * NWV) * 1024);
+            }
     }
     // the loads j = part, part + nparts, ... only (part, nparts compile-time in the callers)
     template <bool ONCE = false>

@@ -17,7 +17,7 @@ namespace tfla {
 // Generic kernel (any element type, operands staged transposed through registers); bf16 uses
 // recurrent_kernel_bf16 (recurrent_fast.h), this one serves fp32.
 
-template <typename DT, int MI, int NI, int BK>
+template <typename DT, int MI, int NI, int BK, bool PAD>
 __global__ void __launch_bounds__(256) recurrent_kernel(RecArgs a) {
     using E = Elem<DT>;
     constexpr int BM = 64 * MI, BN = 64 * NI, NT = 256;
@@ -34,8 +34,11 @@ __global__ void __launch_bounds__(256) recurrent_kernel(RecArgs a) {
     const int bx = wg % gridDim.x; wg /= gridDim.x;
     const int by = wg % gridDim.y; const int bh = wg / gridDim.y;
     const int n0 = bx * BN, m0 = by * BM;
-    const DT* X = reinterpret_cast<const DT*>(a.X) + (long)bh * a.T * a.d1 + m0;
-    const DT* Y = reinterpret_cast<const DT*>(a.Y) + (long)bh * a.T * a.d2 + n0;
+    // the caller's tensors: row strides, and (PAD) what exists of them from this tile's first column on
+    const int xld = PAD ? a.d1_in : a.d1, yld = PAD ? a.d2_in : a.d2, tld = PAD ? a.T_in : a.T;
+    const int xcols = PAD ? a.d1_in - m0 : 0, ycols = PAD ? a.d2_in - n0 : 0;
+    const DT* X = reinterpret_cast<const DT*>(a.X) + (long)bh * tld * xld + m0;
+    const DT* Y = reinterpret_cast<const DT*>(a.Y) + (long)bh * tld * yld + n0;
     const float* rs = a.rs + (long)bh * a.T;
     const bool with_n = (a.nst != nullptr) && bx == 0;
 
@@ -48,11 +51,12 @@ __global__ void __launch_bounds__(256) recurrent_kernel(RecArgs a) {
             for (int v = 0; v < 16; ++v) {
                 const int m = m0 + wm * 32 * MI + 32 * mi + acc_row(v, g);
                 const int n = n0 + wn * 32 * NI + 32 * ni + l32;
-                acc[mi][ni][v] = a.S0 ? a.S0[((long)bh * a.d1 + m) * a.d2 + n] : 0.0f;
+                const bool there = !PAD || (m < a.d1_in && n < a.d2_in);
+                acc[mi][ni][v] = (a.S0 && there) ? a.S0[((long)bh * xld + m) * yld + n] : 0.0f;
             }
         }
     float nacc = 0.0f;
-    if (with_n && tid < BM && a.n0) nacc = a.n0[(long)bh * a.d1 + m0 + tid];
+    if (with_n && tid < BM && a.n0 && (!PAD || tid < xcols)) nacc = a.n0[(long)bh * xld + m0 + tid];
 
     // The sequence is consumed as P pieces of BK rows; piece i belongs to chunk step i / PPC.
     const int PPC = a.L / BK, P = a.Nc * PPC;
@@ -70,16 +74,16 @@ __global__ void __launch_bounds__(256) recurrent_kernel(RecArgs a) {
     for (int d = 0; d < D; ++d)
         if (d < P) {
             const long tr = piece_row(d);
-            px[d].load(X + tr * a.d1, a.d1, tid);
-            py[d].load(Y + tr * a.d2, a.d2, tid);
+            px[d].template load<PAD>(X + tr * xld, xld, tid, tld - (int)tr, xcols);
+            py[d].template load<PAD>(Y + tr * yld, yld, tid, tld - (int)tr, ycols);
             px[d].load_scales(prs[d], rs + tr, tid);
         }
     px[0].store_scaled(ldsX[0], LS, prs[0], tid);
     py[0].template store<false>(ldsY[0], LS, nullptr, tid);
     if (D < P) {
         const long tr = piece_row(D);
-        px[0].load(X + tr * a.d1, a.d1, tid);
-        py[0].load(Y + tr * a.d2, a.d2, tid);
+        px[0].template load<PAD>(X + tr * xld, xld, tid, tld - (int)tr, xcols);
+        py[0].template load<PAD>(Y + tr * yld, yld, tid, tld - (int)tr, ycols);
         px[0].load_scales(prs[0], rs + tr, tid);
     }
     __syncthreads();
@@ -96,8 +100,8 @@ __global__ void __launch_bounds__(256) recurrent_kernel(RecArgs a) {
                     py[r].template store<false>(ldsY[(i + 1) & 1], LS, nullptr, tid);
                     if (i + 1 + D < P) {
                         const long tr = piece_row(i + 1 + D);
-                        px[r].load(X + tr * a.d1, a.d1, tid);
-                        py[r].load(Y + tr * a.d2, a.d2, tid);
+                        px[r].template load<PAD>(X + tr * xld, xld, tid, tld - (int)tr, xcols);
+                        py[r].template load<PAD>(Y + tr * yld, yld, tid, tld - (int)tr, ycols);
                         px[r].load_scales(prs[r], rs + tr, tid);
                     }
                 }
@@ -182,21 +186,20 @@ __global__ void __launch_bounds__(256) recurrent_kernel(RecArgs a) {
                 for (int v = 0; v < 16; ++v) {
                     const int m = m0 + wm * 32 * MI + 32 * mi + acc_row(v, g);
                     const int n = n0 + wn * 32 * NI + 32 * ni + l32;
-                    {
-                    const long o = ((long)bh * a.d1 + m) * a.d2 + n;
-                    if (a.Sfinal) a.Sfinal[o] = acc[mi][ni][v];
-                    if (a.Sfinal2) a.Sfinal2[o] = acc[mi][ni][v];
-                }
+                    const bool there = !PAD || (m < a.d1_in && n < a.d2_in);
+                    if (a.Sfinal && there) a.Sfinal[((long)bh * xld + m) * yld + n] = acc[mi][ni][v];
+                    if (a.Sfinal2) a.Sfinal2[((long)bh * a.d1 + m) * a.d2 + n] = acc[mi][ni][v];
                 }
     }
-    if (with_n && tid < BM && a.nfinal) a.nfinal[(long)bh * a.d1 + m0 + tid] = nacc;
+    if (with_n && tid < BM && a.nfinal && (!PAD || tid < xcols)) a.nfinal[(long)bh * xld + m0 + tid] = nacc;
 }
 
 template <typename DT, int MI, int NI>
 static hipError_t launch_rec_t(const RecArgs& a, int BH, hipStream_t s) {
     constexpr int BK = sizeof(DT) == 2 ? 64 : 32;
     dim3 grid(a.d2 / (64 * NI), a.d1 / (64 * MI), BH);
-    hipLaunchKernelGGL((recurrent_kernel<DT, MI, NI, BK>), grid, dim3(256), 0, s, a);
+    if (a.padded()) hipLaunchKernelGGL((recurrent_kernel<DT, MI, NI, BK, true>), grid, dim3(256), 0, s, a);
+    else hipLaunchKernelGGL((recurrent_kernel<DT, MI, NI, BK, false>), grid, dim3(256), 0, s, a);
     return hipGetLastError();
 }
 
@@ -204,8 +207,14 @@ template <int WN>
 static hipError_t launch_rec_bf16(const RecArgs& a, int BH, hipStream_t s) {
     dim3 grid(a.d2 / (WN * 32), a.d1 / 64, BH);
     // pieces of 128 rows (half as many workgroup barriers) whenever the chunk size allows
-    if (a.L % 128 == 0) hipLaunchKernelGGL((recurrent_kernel_bf16<WN, 128>), grid, dim3(WN * 128), 0, s, a);
-    else hipLaunchKernelGGL((recurrent_kernel_bf16<WN, 64>), grid, dim3(WN * 128), 0, s, a);
+    const bool wide = a.L % 128 == 0;
+    if (a.padded()) {
+        if (wide) hipLaunchKernelGGL((recurrent_kernel_bf16<WN, 128, true>), grid, dim3(WN * 128), 0, s, a);
+        else hipLaunchKernelGGL((recurrent_kernel_bf16<WN, 64, true>), grid, dim3(WN * 128), 0, s, a);
+    } else {
+        if (wide) hipLaunchKernelGGL((recurrent_kernel_bf16<WN, 128>), grid, dim3(WN * 128), 0, s, a);
+        else hipLaunchKernelGGL((recurrent_kernel_bf16<WN, 64>), grid, dim3(WN * 128), 0, s, a);
+    }
     return hipGetLastError();
 }
 

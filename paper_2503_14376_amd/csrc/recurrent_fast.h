@@ -47,7 +47,9 @@ static __device__ unsigned long long tfla_rec_timeline[8192];
 #define TFLA_RTL_FLUSH
 #endif
 
-template <int WN, int BK>
+// PAD: the caller's tensors end before the kernel's pieces and tiles do (RecArgs::T_in, d1_in, d2_in): loads past their
+// end leave zeros in LDS, and only what exists of the caller's states is read and written.
+template <int WN, int BK, bool PAD = false>
 __global__ void __launch_bounds__(WN * 128) recurrent_kernel_bf16(RecArgs a) {
     using E = Elem<bf16_t>;
     using frag = E::frag;
@@ -89,6 +91,9 @@ __global__ void __launch_bounds__(WN * 128) recurrent_kernel_bf16(RecArgs a) {
     // the normaliser vector n (one value per state row) is kept by the workgroups bx == 0:
     // lane l of the first producer owns row m0 + l
     const bool with_n = (a.nst != nullptr) && bx == 0;
+    // the caller's tensors: row strides, steps per (batch, head), and (PAD) columns from this tile's first on
+    const int xld = PAD ? a.d1_in : a.d1, yld = PAD ? a.d2_in : a.d2, tld = PAD ? a.T_in : a.T;
+    const int xcols = PAD ? a.d1_in - m0 : 0, ycols = PAD ? a.d2_in - n0 : 0;
 
     if (producer) {
         // =============================== producers ===========================================
@@ -96,20 +101,21 @@ __global__ void __launch_bounds__(WN * 128) recurrent_kernel_bf16(RecArgs a) {
         __builtin_amdgcn_s_setprio(3);
         const int ptid = tid - NTP;
         const bool n_owner = with_n && wc == 0;
-        float nacc = (n_owner && a.n0) ? a.n0[(long)bh * a.d1 + m0 + lane] : 0.0f;
+        float nacc = (n_owner && a.n0 && (!PAD || lane < xcols)) ? a.n0[(long)bh * xld + m0 + lane] : 0.0f;
         // make the compiler wait for this plain load here: a wait that it places later, inside the
         // loop, would also wait for every global->LDS load in flight
         asm volatile("" : "+v"(nacc));
         float nsum[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) nsum[e] = 0.0f;
-        DX dx; dx.init(a.d1, ptid);
+        DX dx; dx.init(xld, ptid);
         // Pieces are requested in order.  The addresses of the next piece to request advance
         // incrementally (no multiplication or division in the loop): 64 rows per piece; when the
         // recurrence runs backwards the chunks are visited last to first, rows inside a chunk still
         // ascending, so the step at a chunk's end is 64 - 2 L rows.
         const long row0 = a.reverse ? (long)(a.Nc - 1) * a.L : 0;
-        const bf16_t* xreq = reinterpret_cast<const bf16_t*>(a.X) + ((long)bh * a.T + row0) * a.d1 + m0;
+        const bf16_t* xreq = reinterpret_cast<const bf16_t*>(a.X) + ((long)bh * tld + row0) * xld + m0;
+        int xleft = PAD ? a.T_in - (int)row0 : 0;      // steps of the sequence from the next piece's first on
         const float* rsreq = a.rs + (long)bh * a.T + row0;
         const float* greq = a.gbar + (long)bh * a.Nc + (a.reverse ? a.Nc - 1 : 0);
         const long step_rows = BK, wrap_rows = a.reverse ? (long)BK - 2L * a.L : (long)BK;
@@ -117,8 +123,8 @@ __global__ void __launch_bounds__(WN * 128) recurrent_kernel_bf16(RecArgs a) {
         int lsub = 0, lslot = 0;
         uint32_t lst = smem_a;
         auto request = [&]() {
-#pragma unroll
-            for (int q = 0; q < DX::N; ++q) dma16(xreq, dx.goff[q], lst + (wc + q * WN) * 1024);
+            if constexpr (PAD) dx.template issue_bounded<false, true>(xreq, bounded_bytes(xleft, xcols, 2 * xld), xcols, lst, ptid);
+            else dx.issue(xreq, lst, ptid);
             // every producer fetches the same 64 row scales and gbar to the same place: identical
             // data, and each wavefront's own counter then covers what it reads
 #pragma unroll
@@ -127,7 +133,7 @@ __global__ void __launch_bounds__(WN * 128) recurrent_kernel_bf16(RecArgs a) {
             dma4(greq, 0u, g_a + (uint32_t)(lslot * 64 * 4));
             const bool wrap = ++lsub == PPC;
             const long dr = wrap ? wrap_rows : step_rows;
-            xreq += dr * a.d1; rsreq += dr;
+            xreq += dr * xld; rsreq += dr; xleft -= (int)dr;
             if (wrap) { lsub = 0; greq += gstep; }
             if (++lslot == NS) { lslot = 0; lst = smem_a; } else lst += STAGE;
         };
@@ -228,7 +234,7 @@ __global__ void __launch_bounds__(WN * 128) recurrent_kernel_bf16(RecArgs a) {
             for (int h = NH; h > 0; --h) sth[h] = sth[h - 1];
             sth[0] = st0;
         }
-        if (n_owner && a.nfinal) a.nfinal[(long)bh * a.d1 + m0 + lane] = nacc;
+        if (n_owner && a.nfinal && (!PAD || lane < xcols)) a.nfinal[(long)bh * xld + m0 + lane] = nacc;
     } else {
         // =============================== consumers ===========================================
         f32x16 acc[MI];
@@ -238,7 +244,8 @@ __global__ void __launch_bounds__(WN * 128) recurrent_kernel_bf16(RecArgs a) {
             for (int v = 0; v < 16; ++v) {
                 const int m = m0 + mi * 32 + acc_row(v, g);
                 const int n = n0 + wc * 32 + l32;
-                acc[mi][v] = a.S0 ? a.S0[((long)bh * a.d1 + m) * a.d2 + n] : 0.0f;
+                const bool there = !PAD || (m < a.d1_in && n < a.d2_in);
+                acc[mi][v] = (a.S0 && there) ? a.S0[((long)bh * xld + m) * yld + n] : 0.0f;
             }
         // make the compiler wait for these plain loads here rather than inside the loop, where its
         // wait would also cover the state stores in flight
@@ -253,16 +260,21 @@ __global__ void __launch_bounds__(WN * 128) recurrent_kernel_bf16(RecArgs a) {
         // that it places inside the loop would also wait for every global->LDS load in flight)
         asm volatile("" : "+v"(boff));
         // the consumers fetch the Y pieces (same order and address stepping as the producers' X)
-        DY dy; dy.init(a.d2, tid);
+        DY dy; dy.init(yld, tid);
         const long row0 = a.reverse ? (long)(a.Nc - 1) * a.L : 0;
-        const bf16_t* yreq = reinterpret_cast<const bf16_t*>(a.Y) + ((long)bh * a.T + row0) * a.d2 + n0;
+        const bf16_t* yreq = reinterpret_cast<const bf16_t*>(a.Y) + ((long)bh * tld + row0) * yld + n0;
+        int yleft = PAD ? a.T_in - (int)row0 : 0;
         const long step_rows = BK, wrap_rows = a.reverse ? (long)BK - 2L * a.L : (long)BK;
         int lsub = 0, lslot = 0;
         uint32_t lst = smem_a + XB;
-        auto request_part = [&](int q) { dma16(yreq, dy.goff[q], lst + (wc + q * WN) * 1024); };
+        auto request_part = [&](int q) {
+            if constexpr (PAD) dy.template issue_bounded<false, true>(yreq, bounded_bytes(yleft, ycols, 2 * yld), ycols, lst, tid, q, CPC);
+            else dma16(yreq, dy.goff[q], lst + (wc + q * WN) * 1024);
+        };
         auto request_end = [&]() {
             const bool wrap = ++lsub == PPC;
-            yreq += (wrap ? wrap_rows : step_rows) * a.d2;
+            const long dr = wrap ? wrap_rows : step_rows;
+            yreq += dr * yld; yleft -= (int)dr;
             if (wrap) lsub = 0;
             if (++lslot == NS) { lslot = 0; lst = smem_a + XB; } else lst += STAGE;
         };
@@ -418,9 +430,9 @@ __global__ void __launch_bounds__(WN * 128) recurrent_kernel_bf16(RecArgs a) {
                 for (int v = 0; v < 16; ++v) {
                     const int m = m0 + mi * 32 + acc_row(v, g);
                     const int n = n0 + wc * 32 + l32;
-                    const long o = ((long)bh * a.d1 + m) * a.d2 + n;
-                    if (a.Sfinal) a.Sfinal[o] = acc[mi][v];
-                    if (a.Sfinal2) a.Sfinal2[o] = acc[mi][v];
+                    const bool there = !PAD || (m < a.d1_in && n < a.d2_in);
+                    if (a.Sfinal && there) a.Sfinal[((long)bh * xld + m) * yld + n] = acc[mi][v];
+                    if (a.Sfinal2) a.Sfinal2[((long)bh * a.d1 + m) * a.d2 + n] = acc[mi][v];
                 }
         }
     }

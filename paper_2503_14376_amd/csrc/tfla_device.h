@@ -73,6 +73,12 @@ template <> struct Elem<float> {
         for (int e = 0; e < 4; ++e) { f.v[e] = a[e]; f.v[4 + e] = b[e]; }
         return f;
     }
+    static __device__ __forceinline__ frag zero() {
+        frag f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) f.v[e] = 0.0f;
+        return f;
+    }
     static __device__ __forceinline__ f32x16 mma(const frag& a, const frag& b, f32x16 c) {
 #pragma unroll
         for (int e = 0; e < 8; ++e) c = __builtin_amdgcn_mfma_f32_32x32x2f32(a.v[e], b.v[e], c, 0, 0, 0);
@@ -179,12 +185,16 @@ template <typename DT, int ROWS, int COLS, int NT> struct RowsPrefetch {
     static constexpr int EPC = 16 / (int)sizeof(DT), CPR = COLS / EPC, TOTAL = ROWS * CPR;
     static constexpr int N = (TOTAL + NT - 1) / NT;
     u32x4 r[N];
-    __device__ __forceinline__ void load(const DT* g, long gstride, int tid) {
+    // PAD: only rows_left rows and cols_left columns exist from the tile's first on, the rest reads as zero
+    template <bool PAD = false>
+    __device__ __forceinline__ void load(const DT* g, long gstride, int tid, int rows_left = 0, int cols_left = 0) {
 #pragma unroll
         for (int i = 0; i < N; ++i) {
             const int c = tid + i * NT;
-            if (TOTAL % NT == 0 || c < TOTAL)
-                r[i] = *reinterpret_cast<const u32x4*>(g + (long)(c / CPR) * gstride + (c % CPR) * EPC);
+            if (TOTAL % NT == 0 || c < TOTAL) {
+                if (PAD && (c / CPR >= rows_left || (c % CPR) * EPC >= cols_left)) r[i] = u32x4{0u, 0u, 0u, 0u};
+                else r[i] = *reinterpret_cast<const u32x4*>(g + (long)(c / CPR) * gstride + (c % CPR) * EPC);
+            }
         }
     }
     __device__ __forceinline__ void store(DT* lds, int lstride, int tid) const {
@@ -281,14 +291,18 @@ template <int ROWS, int COLS, int NT, bool PERM> struct TrPrefetch<bf16_t, ROWS,
 template <int ROWS, int COLS, int NT, bool PERM> struct TrPrefetch<float, ROWS, COLS, NT, PERM> {
     static constexpr int UNITS = (ROWS / 8) * COLS, N = (UNITS + NT - 1) / NT;
     float w[N][8];
-    __device__ __forceinline__ void load(const float* g, long gstride, int tid) {
+    template <bool PAD = false>
+    __device__ __forceinline__ void load(const float* g, long gstride, int tid, int rows_left = 0, int cols_left = 0) {
 #pragma unroll
         for (int i = 0; i < N; ++i) {
             const int idx = tid + i * NT;
             if (UNITS % NT == 0 || idx < UNITS) {
                 const int col = idx % COLS, u = idx / COLS;
 #pragma unroll
-                for (int e = 0; e < 8; ++e) w[i][e] = g[(long)tr_src_row<PERM>(u, e) * gstride + col];
+                for (int e = 0; e < 8; ++e) {
+                    const int row = tr_src_row<PERM>(u, e);
+                    w[i][e] = (PAD && (row >= rows_left || col >= cols_left)) ? 0.0f : g[(long)row * gstride + col];
+                }
             }
         }
     }

@@ -8,11 +8,11 @@ namespace tfla {
 
 // ---- chunkwise gates (App. B.2 "Chunkwise Gates", App. B.2 inter-chunk max state) ----------
 struct GateArgs {
-    const float* i_pre;   // (BH, T)
-    const float* f_pre;   // (BH, T)
+    const float* i_pre;   // (BH, Tvalid)
+    const float* f_pre;   // (BH, Tvalid)
     const float* m0;      // (BH) or NULL
     int T, L, Nc, variant;
-    int Tvalid;           // steps t >= Tvalid of every (batch, head) are padding: forget gate 1, input gate 0
+    int Tvalid;           // the caller's sequence length; steps Tvalid .. T - 1 get forget gate 1, input gate 0
     float qscale;         // 1/sqrt(dqk)
     float softcap;        // c of the gate soft-cap c tanh(x / c) on both pre-activations; 0 = none
     // outputs, all (BH, T) unless noted
@@ -22,6 +22,7 @@ struct GateArgs {
     float* aK;            // a-bar_j = exp(a_j - m_k)
     float* gbar;          // (BH, Nc) g-bar_k
     float* mout;          // combined max state m_t of every step
+    float* mout_user;     // (BH, Tvalid) a second copy in the caller's layout, or NULL
     float* mfinal;        // (BH) m after the last chunk, or NULL
     float* tmp;           // (BH, 3, T) scratch (values of the pre-pass's arithmetic type: doubles when `precise`)
     // fp32 kernels: pre-pass in double, and the rounding remainders of the two exponents (wrow + wrow_lo and
@@ -36,6 +37,7 @@ struct GateBwdPrepArgs {
     float* wrowB; float* sQ;
     long n; int variant; float eps;
     const float* wrow_lo; float* wrowB_lo;   // fp32 kernels: remainders of wrow / wrowB, or NULL
+    int T, Tvalid;        // n_out, m_out are (BH, Tvalid), everything else (BH, T); the steps in between get den = 1
 };
 hipError_t launch_gate_bwd_prep(const GateBwdPrepArgs& a, hipStream_t s);
 
@@ -47,6 +49,7 @@ struct GateGradArgs {
     float* d_i; float* d_f;
     double* bsum;                  // (BH, ceil(T / 1024)) scratch: block sums
     int T, variant; long BHT;
+    int Tvalid;                    // i_pre, f_pre, d_i, d_f are (BH, Tvalid)
     float softcap;                 // as in GateArgs: the gradients are taken through the cap
     // optional anchors of the reverse cumulative sum, one per block of G chunks (G * L <= 2048): its exact value
     // just after the last step of the block, <C, dC> at that boundary, as npart partial sums per boundary
@@ -58,13 +61,8 @@ hipError_t launch_gate_grads(const GateGradArgs& a, int BH, hipStream_t s);
 hipError_t launch_fill_zero(float* p, long n, hipStream_t s);
 struct FillList { float* p[4]; long n[4]; };     // n[q] = 0: slot unused
 hipError_t launch_fill_zero4(const FillList& f, hipStream_t s);
-// (BH, T, row) <-> (BH, Tp, row_p) copies for sequence lengths that are not a multiple of the chunk and head
-// dimensions between the supported ones (pad.hip); row bytes multiples of 16, pointers 16-byte aligned
-hipError_t launch_pad_rows(const void* in, void* out, long BH, int T, int Tp, int row_bytes, int row_bytes_p, hipStream_t s);
-hipError_t launch_unpad_rows(const void* in, void* out, long BH, int T, int Tp, int row_bytes, int row_bytes_p, hipStream_t s);
-hipError_t launch_pad_scalar(const float* in, float* out, long BH, int T, int Tp, float fill, hipStream_t s);
-hipError_t launch_unpad_scalar(const float* in, float* out, long BH, int T, int Tp, hipStream_t s);
-hipError_t launch_state_dot(const float* A, const float* Bm, float* out, long per, int BH, hipStream_t s);
+// out[bh] = <A[bh], Bm[bh]>; A (BH, *, lda), Bm (BH, d1, d2): the first d2 columns of the first d1 rows of A's `perA` values
+hipError_t launch_state_dot(const float* A, long perA, int lda, const float* Bm, int d1, int d2, float* out, int BH, hipStream_t s);
 // Chunks per block of the anchored forget-gate gradient scan: four (a block has at most 2048 steps); two for heads
 // wider than 512, where a row's dot products run over so many terms that the noise of a few chunks already shows
 // (behind a norm layer the forget-gate gradient is what survives of an almost complete cancellation).
@@ -126,20 +124,24 @@ hipError_t launch_transfer_gain(const GainArgs& a, int BH, hipStream_t s);
 // state <- gbar[k] * state + (rs (.) X_k)^T Y_k, chunk by chunk; the state *before* each
 // update is written to slot k.
 struct RecArgs {
-    const void* X;        // (BH, T, d1)
-    const void* Y;        // (BH, T, d2)
+    const void* X;        // (BH, T_in, d1_in)
+    const void* Y;        // (BH, T_in, d2_in)
     const float* rs;      // (BH, T)
     const float* gbar;    // (BH, Nc)
-    const float* S0;      // (BH, d1, d2) fp32 or NULL (zero)
+    const float* S0;      // (BH, d1_in, d2_in) fp32 or NULL (zero)
     void* stT;            // (BH, Nc, d2, d1) element type DT, or NULL
     void* stN;            // (BH, Nc, d1, d2) element type DT, or NULL
-    float* Sfinal;        // (BH, d1, d2) fp32 or NULL
-    float* Sfinal2;       // second copy of the final state, or NULL
-    const float* n0;      // (BH, d1) or NULL; normaliser vector, forward mLSTMexp only
+    float* Sfinal;        // (BH, d1_in, d2_in) fp32 or NULL
+    float* Sfinal2;       // second copy of the final state, (BH, d1, d2), or NULL
+    const float* n0;      // (BH, d1_in) or NULL; normaliser vector, forward mLSTMexp only
     float* nst;           // (BH, Nc, d1) or NULL (NULL = no normaliser vector); the bf16 kernel stores the same
                           // bytes as (BH, Nc, 2, d1) bf16: n rounded to bf16, and the rounding remainder
-    float* nfinal;        // (BH, d1) or NULL
+    float* nfinal;        // (BH, d1_in) or NULL
     int T, L, Nc, d1, d2, reverse;
+    // the caller's sequence length and head dimensions: the kernels work on whole chunks and on their own widths
+    // (T >= T_in, d1 >= d1_in, d2 >= d2_in) and take the steps and columns in between as zeros
+    int T_in, d1_in, d2_in;
+    bool padded() const { return T_in != T || d1_in != d1 || d2_in != d2; }
     // bf16 kernel only, for the anchors of the forget-gate gradient scan (the boundaries between its blocks of anc_G
     // chunks; slot s = the boundary between chunks s * anc_G - 1 and s * anc_G, slot 0 unused):
     //   anc      (forward launch) receives fp32 copies of the state at those boundaries, (BH, nslot, d1 * d2) in the
@@ -167,8 +169,8 @@ inline int rec_anchor_parts(int d1, int d2) { return (d1 / 64) * (d2 / 32); }
 //            + srow[r] * (X_r St)
 enum { MODE_H = 0, MODE_DV = 1, MODE_DQ = 2, MODE_DK = 3 };
 struct TileArgs {
-    const void* X; const void* Y;   // (BH, T, d1)
-    const void* Z; void* Out;       // Z: (BH, T, d2); Out: (BH, out_T, out_ld), see below
+    const void* X; const void* Y;   // (BH, out_T, in_ld1)
+    const void* Z; void* Out;       // (BH, out_T, out_ld), see below
     const float* wrow; const float* wcol; const float* srow;   // (BH, T)
     const void* St;                 // (BH, Nc, d2, d1)
     int T, L, Nc, d1, d2;
@@ -177,12 +179,12 @@ struct TileArgs {
     int variant; float eps;
     const float* nstate;            // (BH, Nc, d1); bf16 kernels: (BH, Nc, 2, d1) bf16 as RecArgs::nst
     const float* mout;              // (BH, T)
-    float* nout;                    // (BH, T) or NULL
+    float* nout;                    // (BH, out_T) or NULL
     // MODE_H, mLSTMexp: the backward pass's row weights with 1 / h_denom folded in (what gate_bwd_prep_kernel
     // computes from n_out and m_out), written here while the denominator is at hand; (BH, T) each, or NULL
     float* wrowB_out; float* sQ_out;
     // MODE_DQ / MODE_DK: partial row dots  sum_n out[r,n] * dotwith[r,n]
-    const void* dotwith;            // (BH, T, d2)
+    const void* dotwith;            // (BH, out_T, out_ld)
     float* dotpart;                 // (d2/BD2, BH*T)
     // bf16 MODE_DQ writes, bf16 MODE_DK reads: the weighted matrix E of every chunk, (BH, Nc, L, L)
     void* E;
@@ -194,10 +196,12 @@ struct TileArgs {
     void* E2;                       // the second half's E (MODE_DQ writes, MODE_DK reads)
     const float* acc_in; const float* nrm_in;   // add these to the accumulators / normaliser before the epilogue
     float* acc_out; float* nrm_out;             // store the raw accumulators / normaliser instead of the output
-    // The output goes straight into the caller's tensor also when the kernels run on a zero-padded copy of the
-    // problem: only steps t < out_T and columns < out_cols are stored, rows are out_ld elements apart
-    // (out_T = T, out_ld = out_cols = d2 when nothing is padded).  out_cols is a multiple of 8.
-    int out_T, out_ld, out_cols;
+    // The caller's tensors are read and written where they are also when the sequence ends inside its last chunk or a
+    // head dimension lies between the kernels' widths: their first d1-wide operands have in_ld1 columns (in_cols1 of
+    // them behind the pointer: less than in_ld1 in the second half of a split contraction), their d2-wide ones out_ld,
+    // and all of them out_T steps; everything past that is taken as zero and not stored.  Nothing is padded:
+    // out_T = T, in_ld1 = in_cols1 = the contraction's whole width, out_ld = d2.  All are multiples of 8 (out_T is not).
+    int out_T, out_ld, in_ld1, in_cols1;
     // fp32 kernels: rounding remainders of the row and column exponents (the weight is exp2 of the sum of all four),
     // and where MODE_H leaves the remainder that belongs to wrowB_out; NULL = none
     const float* wrow_lo; const float* wcol_lo; float* wrowB_lo_out;

@@ -30,7 +30,8 @@ namespace tfla {
 // tile_kernel_bf16 (tile_fast.h); this one serves fp32.
 // SPLIT as in tile_kernel_bf16: 1 / 2 = the first / second D1-wide half of a contraction over 2 D1 columns (rows of
 // X, Y and the state are 2 D1 apart); the first half stores its raw accumulators, the second adds them to its own.
-template <typename DT, int D1, int BD2, int BC, int NW, int MODE, int SPLIT = 0>
+// PAD: the caller's tensors end before the kernel's blocks do (TileArgs::out_T, out_ld, in_ld1); what lies past is zero.
+template <typename DT, int D1, int BD2, int BC, int NW, int MODE, int SPLIT = 0, bool PAD = false>
 __global__ void __launch_bounds__(NW * 64) tile_kernel(TileArgs a) {
     using E = Elem<DT>;
     using frag = typename E::frag;
@@ -38,7 +39,7 @@ __global__ void __launch_bounds__(NW * 64) tile_kernel(TileArgs a) {
     constexpr int NT = NW * 64, BR = NW * 32;
     constexpr int KS1 = D1 / 16, NB = BD2 / 32, NK = D1 / BC;
     constexpr int YS = D1 + E::PAD, ZS = BC + E::PAD;
-    constexpr int ld1 = SPLIT ? 2 * D1 : D1;    // row stride of the operands with D1 columns
+    constexpr int ld1 = SPLIT ? 2 * D1 : D1;    // row stride of the state's rows over the contraction index
     // two stages of (Y tile, Z tile, column weights): one is multiplied while the other is filled
     __shared__ __attribute__((aligned(16))) DT ldsY[2][BC * YS];
     __shared__ __attribute__((aligned(16))) DT ldsZ[2][BD2 * ZS];
@@ -66,8 +67,12 @@ __global__ void __launch_bounds__(NW * 64) tile_kernel(TileArgs a) {
     const int d2 = a.d2;
 
     const DT* X = reinterpret_cast<const DT*>(a.X);
-    const DT* Y = reinterpret_cast<const DT*>(a.Y) + tbase * ld1;
-    const DT* Z = reinterpret_cast<const DT*>(a.Z) + tbase * d2 + (long)nb2 * BD2;
+    // the caller's tensors: row strides, first step of the chunk, and (PAD) what is left of them from there on
+    const int xld = PAD ? a.in_ld1 : ld1, zld = PAD ? a.out_ld : d2;
+    const long tin = PAD ? (long)bh * a.out_T + (long)kc * a.L : tbase;
+    const int steps_left = PAD ? a.out_T - kc * a.L : 0, cols1 = PAD ? a.in_cols1 : 0, cols2 = PAD ? a.out_ld - nb2 * BD2 : 0;
+    const DT* Y = reinterpret_cast<const DT*>(a.Y) + tin * xld;
+    const DT* Z = reinterpret_cast<const DT*>(a.Z) + tin * zld + (long)nb2 * BD2;
     const DT* St = reinterpret_cast<const DT*>(a.St) + (((long)bh * a.Nc + kc) * d2 + (long)nb2 * BD2) * ld1;
     const float* wcol = a.wcol + tbase;
     const float* wcol_lo = a.wcol_lo ? a.wcol_lo + tbase : nullptr;
@@ -75,9 +80,12 @@ __global__ void __launch_bounds__(NW * 64) tile_kernel(TileArgs a) {
     // X fragments of the wavefront's 32 rows (lane: row l32, k-group g)
     frag xf[KS1];
     {
-        const DT* xr = X + (tbase + wr0 + l32) * ld1 + 8 * g;
+        const DT* xr = X + (tin + wr0 + l32) * xld + 8 * g;
 #pragma unroll
-        for (int ks = 0; ks < KS1; ++ks) xf[ks] = E::load(xr + 16 * ks);
+        for (int ks = 0; ks < KS1; ++ks) {
+            if (!PAD || (wr0 + l32 < steps_left && 16 * ks + 8 * g < cols1)) xf[ks] = E::load(xr + 16 * ks);
+            else xf[ks] = E::zero();
+        }
     }
     if (MODE == MODE_H) {
         if (a.variant == 0)
@@ -108,8 +116,8 @@ __global__ void __launch_bounds__(NW * 64) tile_kernel(TileArgs a) {
         if (j + 1 < NK) {
             ps.load(St + (j + 1) * BC, ld1, tid);
         } else {
-            py.load(Y + (long)ct_lo * BC * ld1, ld1, tid);
-            pz.load(Z + (long)ct_lo * BC * d2, d2, tid);
+            py.template load<PAD>(Y + (long)ct_lo * BC * xld, xld, tid, steps_left - ct_lo * BC, cols1);
+            pz.template load<PAD>(Z + (long)ct_lo * BC * zld, zld, tid, steps_left - ct_lo * BC, cols2);
             if (tid < BC) { pw = wcol[ct_lo * BC + tid]; pwl = wcol_lo ? wcol_lo[ct_lo * BC + tid] : 0.0f; }
         }
         const DT* zb = ldsZ[buf];
@@ -160,8 +168,8 @@ __global__ void __launch_bounds__(NW * 64) tile_kernel(TileArgs a) {
         const int c0 = ct * BC;
         const bool more = ct + 1 < ct_hi;
         if (more) {
-            py.load(Y + (long)(c0 + BC) * ld1, ld1, tid);
-            pz.load(Z + (long)(c0 + BC) * d2, d2, tid);
+            py.template load<PAD>(Y + (long)(c0 + BC) * xld, xld, tid, steps_left - (c0 + BC), cols1);
+            pz.template load<PAD>(Z + (long)(c0 + BC) * zld, zld, tid, steps_left - (c0 + BC), cols2);
             if (tid < BC) { pw = wcol[c0 + BC + tid]; pwl = wcol_lo ? wcol_lo[c0 + BC + tid] : 0.0f; }
         }
         const DT* yb = ldsY[buf];
@@ -247,7 +255,7 @@ __global__ void __launch_bounds__(NW * 64) tile_kernel(TileArgs a) {
             const float den = fmaxf(fabsf(nrm), expf(-a.mout[t])) + a.eps;
             if (g == 0) {
                 ldsR[wave * 32 + l32] = 1.0f / den;
-                if (a.nout && nb2 == 0) a.nout[t] = nrm;
+                if (a.nout && nb2 == 0 && (!PAD || wr0 + l32 < steps_left)) a.nout[tin + wr0 + l32] = nrm;
                 if (a.wrowB_out && nb2 == 0) {
                     if (a.wrowB_lo_out) {
                         const double w = (double)wr + (double)wrl - log2((double)den);
@@ -271,19 +279,21 @@ __global__ void __launch_bounds__(NW * 64) tile_kernel(TileArgs a) {
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
             // straight into the caller's tensor: its own row count and row length, true steps and columns only
-            const int ts = kc * a.L + wr0 + acc_row(v, g), col = nb2 * BD2 + nb * 32 + l32;
-            if (ts < a.out_T && col < a.out_cols)
-                Out[((long)bh * a.out_T + ts) * a.out_ld + col] = E::from_f32(acc[nb][v] * inv[v]);
+            const int ts = wr0 + acc_row(v, g), col = nb * 32 + l32;
+            if (!PAD || (ts < steps_left && col < cols2))
+                Out[(tin + ts) * zld + nb2 * BD2 + col] = E::from_f32(acc[nb][v] * inv[v]);
         }
     if (MODE == MODE_DQ || MODE == MODE_DK) {
         const DT* W = reinterpret_cast<const DT*>(a.dotwith);
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
-            const long t = tbase + wr0 + acc_row(v, g);
+            const int ts = wr0 + acc_row(v, g);
+            const long t = tbase + ts;
             float d = 0.0f;
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb)
-                d += acc[nb][v] * E::to_f32(W[t * d2 + (long)nb2 * BD2 + nb * 32 + l32]);
+                if (!PAD || (ts < steps_left && nb * 32 + l32 < cols2))
+                    d += acc[nb][v] * E::to_f32(W[(tin + ts) * zld + nb2 * BD2 + nb * 32 + l32]);
             d = half_sum(d);
             if (l32 == 0) a.dotpart[(long)nb2 * (long)(nwg / (gx * gy * (unsigned)a.Nc)) * a.T + t] = d;
         }
@@ -295,6 +305,8 @@ template <typename DT, int D1, int BD2, int NW, int MODE, int SPLIT = 0>
 static hipError_t launch_tile_t(const TileArgs& a0, int BH, hipStream_t s) {
     TileArgs a = a0;
     dim3 grid((unsigned)((long)(a.d2 / BD2) * (a.L / (32 * NW)) * BH * a.Nc));
+    // the caller's tensors may end before the kernels' blocks do
+    const bool padded = a.out_T != a.T || a.out_ld != a.d2 || a.in_ld1 != (SPLIT ? 2 * D1 : D1);
     if constexpr (sizeof(DT) == 2) {
         // what the kernel's decomposition of the linear workgroup id divides by
         auto log2_or_neg = [](int v) { return (v > 0 && (v & (v - 1)) == 0) ? __builtin_ctz((unsigned)v) : -1; };
@@ -306,9 +318,6 @@ static hipError_t launch_tile_t(const TileArgs& a0, int BH, hipStream_t s) {
         constexpr int OCC = (BD2 <= 128 && D1 <= 256) ? 2 : 1;
         // dQ / dK share the weighted matrix E through memory only where the contraction that forms it is wide
         constexpr int NOE = ((MODE == MODE_DQ || MODE == MODE_DK) && D1 <= TFLA_NOE_MAX_D1) ? 1 : 0;
-        // a padded problem stores its true part straight into the caller's tensor (the first half of a split
-        // contraction stores no output at all)
-        const bool padded = a.out_T != a.T || a.out_ld != a.d2;
         if constexpr (MODE == MODE_H && SPLIT == 0 && BD2 <= 128) {
             // the layer output next to h~: whole rows in one workgroup, nothing padded (the entry point has checked)
             if (a.fz_y) {
@@ -318,13 +327,14 @@ static hipError_t launch_tile_t(const TileArgs& a0, int BH, hipStream_t s) {
             }
         }
         if (a.fz_y) return hipErrorInvalidValue;
-        if (SPLIT != 1 && padded)
-            hipLaunchKernelGGL((tile_kernel_bf16<D1, BD2, NW, MODE, OCC, SPLIT, NOE, SPLIT != 1>), grid, dim3(64 * NW), 0, s, a);
+        if (padded)
+            hipLaunchKernelGGL((tile_kernel_bf16<D1, BD2, NW, MODE, OCC, SPLIT, NOE, 1>), grid, dim3(64 * NW), 0, s, a);
         else
             hipLaunchKernelGGL((tile_kernel_bf16<D1, BD2, NW, MODE, OCC, SPLIT, NOE, 0>), grid, dim3(64 * NW), 0, s, a);
     } else {
         constexpr int BC = 32;   // two LDS stages must fit in 160 KB
-        hipLaunchKernelGGL((tile_kernel<DT, D1, BD2, BC, NW, MODE, SPLIT>), grid, dim3(64 * NW), 0, s, a);
+        if (padded) hipLaunchKernelGGL((tile_kernel<DT, D1, BD2, BC, NW, MODE, SPLIT, true>), grid, dim3(64 * NW), 0, s, a);
+        else hipLaunchKernelGGL((tile_kernel<DT, D1, BD2, BC, NW, MODE, SPLIT, false>), grid, dim3(64 * NW), 0, s, a);
     }
     return hipGetLastError();
 }
@@ -392,6 +402,7 @@ hipError_t launch_tile_mode(const TileArgs& a0, int BH, int dtype, hipStream_t s
         h.acc_out = nullptr; h.nrm_out = nullptr;
         h.acc_in = a.part_acc; h.nrm_in = a.part_nrm;
         h.X = reinterpret_cast<const float*>(a.X) + 256;
+        h.in_cols1 = a.in_cols1 - 256;
         h.Y = reinterpret_cast<const float*>(a.Y) + 256;
         h.St = reinterpret_cast<const float*>(a.St) + 256;
         if (a.nstate) h.nstate = a.nstate + 256;
@@ -413,6 +424,7 @@ hipError_t launch_tile_mode(const TileArgs& a0, int BH, int dtype, hipStream_t s
     h.acc_out = nullptr; h.nrm_out = nullptr;
     h.acc_in = a.part_acc; h.nrm_in = a.part_nrm;
     h.X = reinterpret_cast<const bf16_t*>(a.X) + 512;
+    h.in_cols1 = a.in_cols1 - 512;
     if (MODE != MODE_DK) h.Y = reinterpret_cast<const bf16_t*>(a.Y) + 512;
     h.St = reinterpret_cast<const bf16_t*>(a.St) + (STT ? (long)512 * a.d2 : 512);
     // (n_{k-1} is stored as bf16 rows: 512 columns are 1024 bytes)

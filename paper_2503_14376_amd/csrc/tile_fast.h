@@ -47,13 +47,13 @@ __host__ __device__ constexpr int pre_item(int item, int BXS, int BCS) {
 // accumulators, the second adds them to its own before the epilogue.
 // NOE: 1 = the dQ kernel does not store the weighted matrix E and the dK kernel recomputes it from dH and V
 // like every other mode (narrow contractions: E, L x L per chunk, is then more bytes than the operands it replaces).
-// PADOUT: 1 = the kernel runs on a zero-padded copy of the problem and stores only the true steps and columns,
-// straight into the caller's tensor (TileArgs::out_T, out_ld, out_cols); 0 = whole blocks, nothing padded.
+// PAD: 1 = the caller's tensors end before the kernel's blocks do (TileArgs::out_T, out_ld, in_ld1): loads past their
+// end leave zeros in LDS (dma16_bounded) and only the true steps and columns are stored; 0 = whole blocks.
 // FUSE: 1 = MODE_H also stores the layer output y = sigma(o~) (.) NORM(h~) (Sec. 2.1, hidden-state output equation) of
 // its rows; the column block covers all of d2 (the launcher checks), nothing is padded.
-template <int D1, int BD2, int NW, int MODE, int OCC, int SPLIT = 0, int NOE = 0, int PADOUT = 0, int FUSE = 0>
+template <int D1, int BD2, int NW, int MODE, int OCC, int SPLIT = 0, int NOE = 0, int PAD = 0, int FUSE = 0>
 __global__ void __launch_bounds__(NW * 64, OCC) tile_kernel_bf16(TileArgs a) {
-    static_assert(!FUSE || (MODE == MODE_H && SPLIT == 0 && !PADOUT), "the fused layer output belongs to the plain H kernel");
+    static_assert(!FUSE || (MODE == MODE_H && SPLIT == 0 && !PAD), "the fused layer output belongs to the plain H kernel");
     using E = Elem<bf16_t>;
     using frag = E::frag;
     constexpr bool UPPER = (MODE & 1) != 0;
@@ -133,11 +133,16 @@ __global__ void __launch_bounds__(NW * 64, OCC) tile_kernel_bf16(TileArgs a) {
     const long tbase = (long)bh * a.T + (long)kc * a.L;
     const int r0 = rb * BR, wr0 = r0 + wave * 32;
     const int d2 = a.d2;
-    constexpr int ld1 = SPLIT ? 2 * D1 : D1;    // row stride of the operands with D1 columns
+    constexpr int ld1 = SPLIT ? 2 * D1 : D1;    // row stride of the state's rows over the contraction index
+    // the caller's tensors: row strides, and the first step of the chunk
+    const int xld = PAD ? a.in_ld1 : ld1, zld = PAD ? a.out_ld : d2;
+    const long tin = PAD ? (long)bh * a.out_T + (long)kc * a.L : tbase;
+    const int steps_left = PAD ? a.out_T - kc * a.L : 0;       // of the sequence, from the first step of the chunk on
+    const int cols2 = PAD ? a.out_ld - nb2 * BD2 : 0;          // columns of the d2-wide tensors from this block's first on
 
     const bf16_t* X = reinterpret_cast<const bf16_t*>(a.X);
-    const bf16_t* Y = reinterpret_cast<const bf16_t*>(a.Y) + tbase * ld1;
-    const bf16_t* Z = reinterpret_cast<const bf16_t*>(a.Z) + tbase * d2 + (long)nb2 * BD2;
+    const bf16_t* Y = reinterpret_cast<const bf16_t*>(a.Y) + tin * xld;
+    const bf16_t* Z = reinterpret_cast<const bf16_t*>(a.Z) + tin * zld + (long)nb2 * BD2;
     const bf16_t* St = reinterpret_cast<const bf16_t*>(a.St) +
                        (STT ? ((long)bh * a.Nc + kc) * ld1 * d2 + (long)nb2 * BD2
                             : (((long)bh * a.Nc + kc) * d2 + (long)nb2 * BD2) * ld1);
@@ -149,14 +154,14 @@ __global__ void __launch_bounds__(NW * 64, OCC) tile_kernel_bf16(TileArgs a) {
     using DS = typename std::conditional<STT, DmaTile<BCS, BD2, NT, SWZ_T>, DmaTile<BD2, BCS, NT, SWZ_K>>::type;
     DS ds;  ds.init(STT ? d2 : ld1, tid);
     using DYT = typename std::conditional<ELITE, DmaTile<BC, BR, NT, SWZ_T>, DmaTile<BC, D1, NT, SWZ_K>>::type;
-    DYT dy;    dy.init(ELITE ? a.L : ld1, tid);
-    DmaTile<BC, BD2, NT, SWZ_T> dz;   dz.init(d2, tid);
+    DYT dy;    dy.init(ELITE ? a.L : xld, tid);
+    DmaTile<BC, BD2, NT, SWZ_T> dz;   dz.init(zld, tid);
     // E of this chunk: (L, L), rows = query index; the dK kernel reads the columns of its own rows
     const bf16_t* Eb = reinterpret_cast<const bf16_t*>(a.E) + ((long)bh * a.Nc + kc) * a.L * a.L + (ELITE ? r0 : 0);
     constexpr int CS = DS::N;
-    DmaTile<BR, BXS, NT, SWZ_K> dxs;  dxs.init(ld1, tid);
+    DmaTile<BR, BXS, NT, SWZ_K> dxs;  dxs.init(xld, tid);
     constexpr int CX = DmaTile<BR, BXS, NT, SWZ_K>::N;
-    const bf16_t* Xb = X + (tbase + r0) * ld1;
+    const bf16_t* Xb = X + (tin + r0) * xld;
     constexpr int CT = DYT::N + DmaTile<BC, BD2, NT, SWZ_T>::N + (ELITE ? 0 : 1);
     const uint32_t smem_a = lds_addr(smem), w_a = lds_addr(ldsW);
     const float* wcol = a.wcol + tbase;
@@ -167,7 +172,10 @@ __global__ void __launch_bounds__(NW * 64, OCC) tile_kernel_bf16(TileArgs a) {
             const int pi = pre_item(item, BXS, BCS), sl = pi >> 1;
             if (pi & 1) {
                 // the workgroup's own rows: no other workgroup reads them when its block covers all output columns
-                if (gx == 1) dxs.template issue<true>(Xb + sl * BXS, st, tid);
+                if constexpr (PAD) {
+                    const int cl = a.in_cols1 - sl * BXS;
+                    dxs.template issue_bounded<false, true>(Xb + sl * BXS, bounded_bytes(steps_left - r0, cl, 2 * xld), cl, st, tid);
+                } else if (gx == 1) dxs.template issue<true>(Xb + sl * BXS, st, tid);
                 else dxs.issue(Xb + sl * BXS, st, tid);
             } else {
                 // (state slices of the dQ / dK kernels carry the hint too: measured, -3 us on dQ)
@@ -178,10 +186,17 @@ __global__ void __launch_bounds__(NW * 64, OCC) tile_kernel_bf16(TileArgs a) {
             if (ELITE) {
                 // (E of this workgroup's rows: read by this workgroup only)
                 dy.template issue<true>(Eb + (long)ct * BC * a.L, st, tid);
-                dz.issue(Z + (long)ct * BC * d2, st + YB, tid);
+            } else if constexpr (PAD) {
+                dy.template issue_bounded<false, true>(Y + (long)ct * BC * xld, bounded_bytes(steps_left - ct * BC, a.in_cols1, 2 * xld),
+                                                       a.in_cols1, st, tid);
             } else {
-                dy.issue(Y + (long)ct * BC * ld1, st, tid);
-                dz.issue(Z + (long)ct * BC * d2, st + YB, tid);
+                dy.issue(Y + (long)ct * BC * xld, st, tid);
+            }
+            if constexpr (PAD)
+                dz.template issue_bounded<false, true>(Z + (long)ct * BC * zld, bounded_bytes(steps_left - ct * BC, cols2, 2 * zld), cols2,
+                                                       st + YB, tid);
+            else dz.issue(Z + (long)ct * BC * zld, st + YB, tid);
+            if (!ELITE) {
                 // the tile's 32 column weights (both half-waves fetch the same 32 floats)
                 dma4(wcol + ct * BC, (uint32_t)(lane & 31) * 4u, w_a + (uint32_t)(((item % NS) * NW + wave) * 256));
             }
@@ -193,7 +208,10 @@ __global__ void __launch_bounds__(NW * 64, OCC) tile_kernel_bf16(TileArgs a) {
         if (item < NPRE) {
             const int pi = pre_item(item, BXS, BCS), sl = pi >> 1;
             if (pi & 1) {
-                if (gx == 1) dxs.template issue_part<true>(Xb + sl * BXS, st, tid, part, nparts);
+                if constexpr (PAD) {
+                    const int cl = a.in_cols1 - sl * BXS;
+                    dxs.template issue_bounded<false, false>(Xb + sl * BXS, bounded_bytes(steps_left - r0, cl, 2 * xld), cl, st, tid, part, nparts);
+                } else if (gx == 1) dxs.template issue_part<true>(Xb + sl * BXS, st, tid, part, nparts);
                 else dxs.issue_part(Xb + sl * BXS, st, tid, part, nparts);
             } else {
                 ds.template issue_part<STT>(St + (STT ? (long)sl * BCS * d2 : (long)sl * BCS), st, tid, part, nparts);
@@ -202,10 +220,17 @@ __global__ void __launch_bounds__(NW * 64, OCC) tile_kernel_bf16(TileArgs a) {
             const int ct = ct_lo + item - NPRE;
             if (ELITE) {
                 dy.template issue_part<true>(Eb + (long)ct * BC * a.L, st, tid, part, nparts);
-                dz.issue_part(Z + (long)ct * BC * d2, st + YB, tid, part, nparts);
+            } else if constexpr (PAD) {
+                dy.template issue_bounded<false, false>(Y + (long)ct * BC * xld, bounded_bytes(steps_left - ct * BC, a.in_cols1, 2 * xld),
+                                                        a.in_cols1, st, tid, part, nparts);
             } else {
-                dy.issue_part(Y + (long)ct * BC * ld1, st, tid, part, nparts);
-                dz.issue_part(Z + (long)ct * BC * d2, st + YB, tid, part, nparts);
+                dy.issue_part(Y + (long)ct * BC * xld, st, tid, part, nparts);
+            }
+            if constexpr (PAD)
+                dz.template issue_bounded<false, false>(Z + (long)ct * BC * zld, bounded_bytes(steps_left - ct * BC, cols2, 2 * zld), cols2,
+                                                        st + YB, tid, part, nparts);
+            else dz.issue_part(Z + (long)ct * BC * zld, st + YB, tid, part, nparts);
+            if (!ELITE) {
                 if (part == 0)
                     dma4(wcol + ct * BC, (uint32_t)(lane & 31) * 4u, w_a + (uint32_t)(((item % NS) * NW + wave) * 256));
             }
@@ -398,10 +423,12 @@ __global__ void __launch_bounds__(NW * 64, OCC) tile_kernel_bf16(TileArgs a) {
             if (i == NI - 1) {
                 const int sl = wave, stg = (i + 1 + sl / SPS) % NS;
                 DmaTile<32, BD2, 64, SWZ_K> dw;
-                dw.init(d2, lane);
-                const bf16_t* wsrc = reinterpret_cast<const bf16_t*>(FUSE ? a.fz_o : a.dotwith) + (tbase + wr0) * d2 + (long)nb2 * BD2;
+                dw.init(zld, lane);
+                const bf16_t* wsrc = reinterpret_cast<const bf16_t*>(FUSE ? a.fz_o : a.dotwith) + (tin + wr0) * zld + (long)nb2 * BD2;
                 const uint32_t wdst = smem_a + (uint32_t)(stg * STAGE + (sl % SPS) * SLOT);
                 if (FUSE && !a.fz_o) {}                  // no output gate: nothing to fetch
+                else if constexpr (PAD)
+                    dw.template issue_bounded<false, true>(wsrc, bounded_bytes(steps_left - wr0, cols2, 2 * zld), cols2, wdst, lane);
                 else if (gx == 1) dw.template issue<true>(wsrc, wdst, lane);
                 else dw.issue(wsrc, wdst, lane);
             }
@@ -577,7 +604,10 @@ __global__ void __launch_bounds__(NW * 64, OCC) tile_kernel_bf16(TileArgs a) {
         if (a.variant == 0) {
             const float den = fmaxf(fabsf(nrm), expf(-ldsM[wave][l32])) + a.eps;
             inv = 1.0f / den;
-            if (g == 0 && a.nout && nb2 == 0) a.nout[t] = nrm;
+            if constexpr (PAD) {
+                const int ts = wr0 + l32;
+                if (g == 0 && a.nout && nb2 == 0 && ts < steps_left) a.nout[tin + ts] = nrm;
+            } else if (g == 0 && a.nout && nb2 == 0) a.nout[t] = nrm;
             if (g == 0 && a.wrowB_out && nb2 == 0) {
                 a.wrowB_out[t] = wr - log2f(den);
                 a.sQ_out[t] = srl / den;
@@ -594,9 +624,11 @@ __global__ void __launch_bounds__(NW * 64, OCC) tile_kernel_bf16(TileArgs a) {
     char* wtile = WPRE ? slot_at(wave) : smem + NW * (32 * ORB) + wave * (32 * ORB);
     if (WTILE && !WPRE) {
         DmaTile<32, BD2, 64, SWZ_K> dw;                  // this wave's rows of the dot operand (of the gate pre-activations)
-        dw.init(d2, lane);
-        const bf16_t* wsrc = reinterpret_cast<const bf16_t*>(FUSE ? a.fz_o : a.dotwith) + (tbase + wr0) * d2 + (long)nb2 * BD2;
+        dw.init(zld, lane);
+        const bf16_t* wsrc = reinterpret_cast<const bf16_t*>(FUSE ? a.fz_o : a.dotwith) + (tin + wr0) * zld + (long)nb2 * BD2;
         if (FUSE && !a.fz_o) {}                          // no output gate: nothing to fetch
+        else if constexpr (PAD)
+            dw.template issue_bounded<false, true>(wsrc, bounded_bytes(steps_left - wr0, cols2, 2 * zld), cols2, lds_addr(wtile), lane);
         else if (gx == 1) dw.template issue<true>(wsrc, lds_addr(wtile), lane);
         else dw.issue(wsrc, lds_addr(wtile), lane);
     }
@@ -631,7 +663,7 @@ __global__ void __launch_bounds__(NW * 64, OCC) tile_kernel_bf16(TileArgs a) {
         }
     {
         constexpr int RPI = 64 / OCPR;                   // tile rows covered by one 64-lane store
-        if constexpr (!PADOUT) {
+        if constexpr (!PAD) {
             char* obase = reinterpret_cast<char*>(a.Out) + ((tbase + wr0) * d2 + (long)nb2 * BD2) * 2;
 #pragma unroll
             for (int q = 0; q < 32 / RPI; ++q) {
@@ -643,14 +675,13 @@ __global__ void __launch_bounds__(NW * 64, OCC) tile_kernel_bf16(TileArgs a) {
             }
         } else {
             // straight into the caller's tensor: its own row count and row length, true steps and columns only
-            const int ts0 = kc * a.L + wr0;              // first step of this wave's rows within the sequence
-            char* obase = reinterpret_cast<char*>(a.Out) + (((long)bh * a.out_T + ts0) * a.out_ld + (long)nb2 * BD2) * 2;
+            char* obase = reinterpret_cast<char*>(a.Out) + ((tin + wr0) * zld + (long)nb2 * BD2) * 2;
 #pragma unroll
             for (int q = 0; q < 32 / RPI; ++q) {
                 const int r = q * RPI + lane / OCPR, c = lane % OCPR;
                 const u32x4 w = *reinterpret_cast<const u32x4*>(otile + r * ORB + ((c ^ swz_mask<SWZ_K, OCPR>(r)) * 16));
-                if (ts0 + r < a.out_T && nb2 * BD2 + c * 8 < a.out_cols)
-                    __builtin_nontemporal_store(w, reinterpret_cast<u32x4*>(obase + (long)r * a.out_ld * 2 + c * 16));
+                if (wr0 + r < steps_left && c * 8 < cols2)
+                    __builtin_nontemporal_store(w, reinterpret_cast<u32x4*>(obase + (long)r * zld * 2 + c * 16));
             }
         }
     }
@@ -710,7 +741,7 @@ __global__ void __launch_bounds__(NW * 64, OCC) tile_kernel_bf16(TileArgs a) {
         // the dot operand has landed: its loads are older than the output stores above (and than the E stores of the
         // last tile), which may still be on their way.  (A padded problem issues a store only where a lane has
         // something to store, so their number is not known here.)
-        if constexpr (PADOUT) wait_vmcnt<0>();
+        if constexpr (PAD) wait_vmcnt<0>();
         else wait_vmcnt<32 / (64 / OCPR)>();
         float d = 0.0f;
 #pragma unroll

@@ -10,7 +10,7 @@ from oracle import mlstm_oracle as orc
 pytestmark = pytest.mark.gpu
 
 
-def _check_slices(w, dCn=False):
+def _check_slices(w, dCn=False, keep=True):
     import paper_2503_14376_amd as tfla
     from tests import gpu_util as gu
     d = wl.make_inputs(w)
@@ -20,7 +20,7 @@ def _check_slices(w, dCn=False):
     dC = torch.randn((w.B, w.NH, w.dqk, w.dhv), device="cuda", generator=torch.Generator("cuda").manual_seed(5)) if dCn else None
     f = tfla.mlstm_fwd(dev["q"], dev["k"], dev["v"], dev["i_pre"], dev["f_pre"], *st, chunk=w.chunk, variant=w.variant, eps=1e-6)
     b = tfla.mlstm_bwd(dev["q"], dev["k"], dev["v"], dev["i_pre"], dev["f_pre"], dev["dH"], f["n_out"], f["m_out"], *st, dC,
-                       chunk=w.chunk, variant=w.variant, eps=1e-6, fwd_workspace=f["workspace"])
+                       chunk=w.chunk, variant=w.variant, eps=1e-6, fwd_workspace=f["workspace"] if keep else None)
     torch.cuda.synchronize()
     idx = sorted({0, w.B * w.NH - 1})
     sub = lambda t: t.reshape((-1,) + tuple(t.shape[2:]))[idx]
@@ -50,3 +50,19 @@ def _check_slices(w, dCn=False):
 def test_wide_output_blocks(variant, B, NH, T, dqk, dhv, chunk):
     w = wl.small(variant, wl.BF16, B=B, NH=NH, T=T, dqk=dqk, dhv=dhv, chunk=chunk, seed=700 + T + dqk)
     _check_slices(w)
+
+
+# tensors that end before the kernels' blocks do: whole row blocks, pieces and column blocks past the end, odd remainders,
+# initial state and upstream state gradient, both ways of the backward pass (kept and recomputed states)
+@pytest.mark.parametrize("keep", [True, False])
+@pytest.mark.parametrize("variant,dtype,T,dqk,dhv,chunk", [
+    (wl.EXP, wl.BF16, 130, 256, 512, 512),      # two of four row blocks empty
+    (wl.SIG, wl.BF16, 257, 40, 520, 256),       # one step in the last chunk; a contraction split behind 512 of 520 columns
+    (wl.EXP, wl.BF16, 3, 64, 64, 2048),         # almost everything past the end
+    (wl.EXP, wl.BF16, 700, 1000, 72, 192),      # two-wavefront workgroups, 64-row pieces
+    (wl.EXP, wl.F32, 70, 72, 136, 192),
+    (wl.SIG, wl.F32, 333, 264, 328, 64),        # fp32 contraction split behind 256 of 264 / 328 columns
+])
+def test_tensors_that_end_inside_a_block(keep, variant, dtype, T, dqk, dhv, chunk):
+    w = wl.small(variant, dtype, B=1, NH=3, T=T, dqk=dqk, dhv=dhv, chunk=chunk, seed=800 + T + dqk)
+    _check_slices(w, dCn=True, keep=keep)
