@@ -729,13 +729,13 @@ int tfla_mlstm_layer_bwd(const void* q, const void* k, const void* v, const floa
     a.part = want_params ? part : nullptr;
     a.NH = NH; a.T = T; a.d = dhv; a.kind = norm_kind; a.dtype = dtype; a.eps = norm_eps;
     TFLA_LAUNCH(K_NORM_BWD, launch_norm_gate_bwd(a, (int)d.BH, s));
-    if (want_params) {
+    if (dgamma || dbeta) {
+        // (the RMS norm has no shift: its dbeta comes back as zeros)
         NormParamGradArgs pg;
-        pg.part = part; pg.dgamma = dgamma; pg.dbeta = norm_kind == TFLA_NORM_LAYER ? dbeta : nullptr;
-        pg.B = B; pg.NH = NH; pg.nblk = nblk; pg.d = dhv;
+        pg.part = part; pg.dgamma = dgamma; pg.dbeta = dbeta; pg.kind = norm_kind;
+        pg.B = B; pg.NH = NH; pg.nblk = want_params ? nblk : 0; pg.d = dhv;
         TFLA_LAUNCH(K_NORM_BWD, launch_norm_param_grad(pg, s));
     }
-    if (dbeta && norm_kind != TFLA_NORM_LAYER) TFLA_LAUNCH(K_FILL, launch_fill_zero(dbeta, (long)NH * dhv, s));
     return bwd_impl(q, k, v, i_pre, f_pre, C0, n0, m0, n_out, m_out, dHt, dCn, B, NH, T, dqk, dhv, chunk, variant, dtype,
                     eps, gate_softcap, dq, dk, dv, d_i_pre, d_f_pre, dC0, fwd_workspace, fwd_workspace_bytes, workspace,
                     base, stream);

@@ -458,16 +458,6 @@ hipError_t launch_gate_grads(const GateGradArgs& a, int BH, hipStream_t s) {
     return hipGetLastError();
 }
 
-__global__ void fill_zero_kernel(float* p, long n) {
-    const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = 0.0f;
-}
-hipError_t launch_fill_zero(float* p, long n, hipStream_t s) {
-    if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(fill_zero_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, p, n);
-    return hipGetLastError();
-}
-
 // up to four arrays in one launch: element i of the concatenation belongs to the first array whose end lies beyond i
 __global__ void __launch_bounds__(256) fill_zero4_kernel(FillList f) {
     long i = (long)blockIdx.x * 256 + threadIdx.x;

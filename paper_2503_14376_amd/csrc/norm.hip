@@ -10,7 +10,10 @@ namespace tfla {
 
 namespace {
 
-constexpr int NORM_RPB = 128;   // rows per workgroup of the backward kernel (32 per wavefront)
+// Rows per workgroup of the backward kernels, and the wavefronts that share them for rows of 257 to 512 values.  With
+// four wavefronts of 32 rows each the launch has too few in flight to stream (16 heads, 4000 steps of 512: 126 us at
+// 2.6 TB/s); sixteen take 70 us, 4.7 TB/s (a large copy moves 5.0).
+constexpr int NORM_RPB = 128, NORM_BW1 = 16;
 
 // eight consecutive elements of a row as floats
 template <typename DT> struct Row8;
@@ -54,9 +57,14 @@ __device__ __forceinline__ void load8f(const float* p, float (&x)[8]) {
     x[0] = a.x; x[1] = a.y; x[2] = a.z; x[3] = a.w; x[4] = b.x; x[5] = b.y; x[6] = b.z; x[7] = b.w;
 }
 
-__device__ __forceinline__ float sigmoidf_(float x) {
+// sigma(x) as accurate as the rows' element type asks for.  bf16 rows: the hardware's exp2 and reciprocal (about 1e-7
+// relative, 5e-6 at x = -80, against the 4e-3 of a bf16 value); with the library's exponential and an IEEE division the
+// row kernels are bound by their vector instructions and not by memory.
+template <typename DT> __device__ __forceinline__ float sigmoid_row(float x);
+template <> __device__ __forceinline__ float sigmoid_row<bf16_t>(float x) { return fast_sigmoid(x); }
+template <> __device__ __forceinline__ float sigmoid_row<float>(float x) {
     const float e = expf(-fabsf(x));
-    return x >= 0.0f ? 1.0f / (1.0f + e) : e / (1.0f + e);
+    return (x >= 0.0f ? 1.0f : e) / (1.0f + e);
 }
 
 // A row of d values spread over a wavefront: lane l holds the 8-element groups l, l + 64, ...
@@ -82,7 +90,7 @@ template <typename DT, int J> struct RowRegs {
             for (int j = 0; j < J; ++j)
 #pragma unroll
                 for (int e = 0; e < 8; ++e) s += x[j][e];
-            const float mu = wave_sum(s) / (float)d;
+            const float mu = lanes_sum<64>(s) / (float)d;
 #pragma unroll
             for (int j = 0; j < J; ++j)
                 if ((lane + 64 * j) * 8 < d) {
@@ -95,36 +103,48 @@ template <typename DT, int J> struct RowRegs {
         for (int j = 0; j < J; ++j)
 #pragma unroll
             for (int e = 0; e < 8; ++e) ss += x[j][e] * x[j][e];
-        return 1.0f / sqrtf(wave_sum(ss) / (float)d + eps);
+        return 1.0f / sqrtf(lanes_sum<64>(ss) / (float)d + eps);
     }
 };
 
+// grid (row blocks, batch*head): a workgroup takes rpb consecutive steps of one (batch, head), its wavefronts one row at
+// a time, so that the head's scale and shift are loaded once and no row number is divided.
 template <typename DT, int J>
-__global__ void __launch_bounds__(256) norm_gate_fwd_kernel(NormArgs a) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const long row = (long)blockIdx.x * 4 + wave;
-    if (row >= a.rows) return;
-    const int d = a.d;
-    const int head = (int)((row / a.T) % a.NH);
-    RowRegs<DT, J> r;
-    r.load(a.h, row, d, lane);
-    const float rstd = r.center(d, lane, a.kind, a.eps);
+__global__ void __launch_bounds__(256) norm_gate_fwd_kernel(NormArgs a, int rpb) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
+    const int d = a.d, bh = blockIdx.y, head = bh % a.NH;
+    const int t_end = min(a.T, ((int)blockIdx.x + 1) * rpb);
+    int t = blockIdx.x * rpb + wave;
+    if (t >= t_end) return;
+    float g[J][8], be[J][8];
 #pragma unroll
     for (int j = 0; j < J; ++j) {
         const int c = (lane + 64 * j) * 8;
-        if (c >= d) continue;
-        float g[8], be[8], o[8], y[8];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) { g[e] = 1.0f; be[e] = 0.0f; o[e] = 0.0f; }
-        if (a.gamma) load8f(a.gamma + (long)head * d + c, g);
-        if (a.beta && a.kind == 1) load8f(a.beta + (long)head * d + c, be);
-        if (a.o_pre) Row8<DT>::load(a.o_pre, row * d + c, o);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const float n = r.x[j][e] * rstd * g[e] + be[e];
-            y[e] = a.o_pre ? n * sigmoidf_(o[e]) : n;
+        for (int e = 0; e < 8; ++e) { g[j][e] = 1.0f; be[j][e] = 0.0f; }
+        if (c < d) {
+            if (a.gamma) load8f(a.gamma + (long)head * d + c, g[j]);
+            if (a.beta && a.kind == 1) load8f(a.beta + (long)head * d + c, be[j]);
         }
-        Row8<DT>::store_stream(a.y, row * d + c, y);
+    }
+    for (; t < t_end; t += nw) {
+        const long row = (long)bh * a.T + t;
+        RowRegs<DT, J> r, o;
+        r.load(a.h, row, d, lane);
+        if (a.o_pre) o.load(a.o_pre, row, d, lane);
+        const float rstd = r.center(d, lane, a.kind, a.eps);
+#pragma unroll
+        for (int j = 0; j < J; ++j) {
+            const int c = (lane + 64 * j) * 8;
+            if (c >= d) continue;
+            float y[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const float n = r.x[j][e] * rstd * g[j][e] + be[j][e];
+                y[e] = a.o_pre ? n * sigmoid_row<DT>(o.x[j][e]) : n;
+            }
+            Row8<DT>::store_stream(a.y, row * d + c, y);
+        }
     }
 }
 
@@ -134,9 +154,9 @@ __global__ void __launch_bounds__(256) norm_gate_fwd_kernel(NormArgs a) {
 //   d gamma = sum over rows of dn (.) x^,  d beta = sum over rows of dn.
 // A workgroup takes NORM_RPB consecutive steps of one (batch, head) and leaves its partial
 // parameter sums in `part` (reduced in a fixed order by norm_param_grad_kernel).
-template <typename DT, int J>
-__global__ void __launch_bounds__(256) norm_gate_bwd_kernel(NormBwdArgs a) {
-    __shared__ float red[4][2][J * 512];
+template <typename DT, int J, int NW>
+__global__ void __launch_bounds__(NW * 64) norm_gate_bwd_kernel(NormBwdArgs a) {
+    __shared__ float red[NW][2][J * 512];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int bh = blockIdx.y, blk = blockIdx.x, d = a.d;
     const int head = bh % a.NH;
@@ -152,10 +172,12 @@ __global__ void __launch_bounds__(256) norm_gate_bwd_kernel(NormBwdArgs a) {
         }
     }
     const int t_end = min(a.T, (blk + 1) * NORM_RPB);
-    for (int t = blk * NORM_RPB + wave; t < t_end; t += 4) {
+    for (int t = blk * NORM_RPB + wave; t < t_end; t += NW) {
         const long row = (long)bh * a.T + t;
-        RowRegs<DT, J> r;
+        RowRegs<DT, J> r, dyr, o;
         r.load(a.h, row, d, lane);
+        dyr.load(a.dy, row, d, lane);
+        if (a.o_pre) o.load(a.o_pre, row, d, lane);
         const float rstd = r.center(d, lane, a.kind, a.eps);
         float dx[J][8];
         float s1 = 0.0f, s2 = 0.0f;
@@ -165,18 +187,16 @@ __global__ void __launch_bounds__(256) norm_gate_bwd_kernel(NormBwdArgs a) {
 #pragma unroll
             for (int e = 0; e < 8; ++e) dx[j][e] = 0.0f;
             if (c >= d) continue;
-            float dy[8], o[8], dop[8];
-            Row8<DT>::load(a.dy, row * d + c, dy);
-            if (a.o_pre) Row8<DT>::load(a.o_pre, row * d + c, o);
+            float dop[8];
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-                const float xh = r.x[j][e] * rstd;
+                const float xh = r.x[j][e] * rstd, dy = dyr.x[j][e];
                 r.x[j][e] = xh;
-                float dn = dy[e];
+                float dn = dy;
                 if (a.o_pre) {
-                    const float og = sigmoidf_(o[e]);
-                    dop[e] = dy[e] * (xh * g[j][e] + be[j][e]) * og * (1.0f - og);
-                    dn = dy[e] * og;
+                    const float og = sigmoid_row<DT>(o.x[j][e]);
+                    dop[e] = dy * (xh * g[j][e] + be[j][e]) * og * (1.0f - og);
+                    dn = dy * og;
                 }
                 ag[j][e] += dn * xh;
                 ab[j][e] += dn;
@@ -186,8 +206,8 @@ __global__ void __launch_bounds__(256) norm_gate_bwd_kernel(NormBwdArgs a) {
             }
             if (a.o_pre && a.do_pre) Row8<DT>::store_stream(a.do_pre, row * d + c, dop);
         }
-        s1 = a.kind == 1 ? wave_sum(s1) / (float)d : 0.0f;
-        s2 = wave_sum(s2) / (float)d;
+        s1 = a.kind == 1 ? lanes_sum<64>(s1) / (float)d : 0.0f;
+        s2 = lanes_sum<64>(s2) / (float)d;
 #pragma unroll
         for (int j = 0; j < J; ++j) {
             const int c = (lane + 64 * j) * 8;
@@ -208,20 +228,18 @@ __global__ void __launch_bounds__(256) norm_gate_bwd_kernel(NormBwdArgs a) {
     }
     __syncthreads();
     float* out = a.part + ((long)bh * gridDim.x + blk) * 2 * d;
-    for (int i = threadIdx.x; i < 2 * d; i += 256) {
-        const int w = i / d, c = i - w * d;
-        out[i] = (red[0][w][c] + red[1][w][c]) + (red[2][w][c] + red[3][w][c]);
+    for (int i = threadIdx.x; i < 2 * d; i += NW * 64) {
+        const int w = i >= d, c = i - w * d;
+        float sum = 0.0f;
+#pragma unroll
+        for (int q = 0; q < NW; q += 4) sum += (red[q][w][c] + red[q + 1][w][c]) + (red[q + 2][w][c] + red[q + 3][w][c]);
+        out[i] = sum;
     }
 }
 
 
 // ---- rows of 64, 128 or 256 values: LPR = d / 8 lanes per row, 64 / LPR rows of one wavefront side by side ----
 // (one row per wavefront would leave three quarters or more of the lanes idle)
-template <int LPR> __device__ __forceinline__ float row_sum(float x) {
-#pragma unroll
-    for (int m = 1; m < LPR; m <<= 1) x += __shfl_xor(x, m, 64);
-    return x;
-}
 // x (this lane's eight values of its row) -> x - mean for LayerNorm; returns 1 / sqrt(mean((x - mean)^2) + eps)
 template <int LPR> __device__ __forceinline__ float center_packed(float (&x)[8], int kind, float eps) {
     constexpr float invd = 1.0f / (float)(LPR * 8);
@@ -229,38 +247,41 @@ template <int LPR> __device__ __forceinline__ float center_packed(float (&x)[8],
         float sm = 0.0f;
 #pragma unroll
         for (int e = 0; e < 8; ++e) sm += x[e];
-        const float mu = row_sum<LPR>(sm) * invd;
+        const float mu = lanes_sum<LPR>(sm) * invd;
 #pragma unroll
         for (int e = 0; e < 8; ++e) x[e] -= mu;
     }
     float ss = 0.0f;
 #pragma unroll
     for (int e = 0; e < 8; ++e) ss += x[e] * x[e];
-    return 1.0f / sqrtf(row_sum<LPR>(ss) * invd + eps);
+    return 1.0f / sqrtf(lanes_sum<LPR>(ss) * invd + eps);
 }
 
 template <typename DT, int LPR>
-__global__ void __launch_bounds__(256) norm_gate_fwd_packed_kernel(NormArgs a) {
+__global__ void __launch_bounds__(256) norm_gate_fwd_packed_kernel(NormArgs a, int rpb) {
     constexpr int R = 64 / LPR, d = LPR * 8;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, sub = lane / LPR, c = (lane % LPR) * 8;
-    const long row = ((long)blockIdx.x * 4 + wave) * R + sub;
-    const bool live = row < a.rows;
-    const long rr = live ? row : a.rows - 1;            // (lanes past the end repeat the last row and store nothing)
-    const int head = (int)((rr / a.T) % a.NH);
-    float x[8], g[8], be[8], o[8], y[8];
+    const int bh = blockIdx.y, head = bh % a.NH;
+    const int t_end = min(a.T, ((int)blockIdx.x + 1) * rpb);
+    float g[8], be[8];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) { g[e] = 1.0f; be[e] = 0.0f; o[e] = 0.0f; }
-    Row8<DT>::load(a.h, rr * d + c, x);
+    for (int e = 0; e < 8; ++e) { g[e] = 1.0f; be[e] = 0.0f; }
     if (a.gamma) load8f(a.gamma + (long)head * d + c, g);
     if (a.beta && a.kind == 1) load8f(a.beta + (long)head * d + c, be);
-    if (a.o_pre) Row8<DT>::load(a.o_pre, rr * d + c, o);
-    const float rstd = center_packed<LPR>(x, a.kind, a.eps);
+    for (int t0 = blockIdx.x * rpb + wave * R; t0 < t_end; t0 += (blockDim.x >> 6) * R) {
+        const bool live = t0 + sub < t_end;             // (lanes past the end repeat the last row and store nothing)
+        const long row = (long)bh * a.T + (live ? t0 + sub : t_end - 1);
+        float x[8], o[8], y[8];
+        Row8<DT>::load(a.h, row * d + c, x);
+        if (a.o_pre) Row8<DT>::load(a.o_pre, row * d + c, o);
+        const float rstd = center_packed<LPR>(x, a.kind, a.eps);
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        const float n = x[e] * rstd * g[e] + be[e];
-        y[e] = a.o_pre ? n * sigmoidf_(o[e]) : n;
+        for (int e = 0; e < 8; ++e) {
+            const float n = x[e] * rstd * g[e] + be[e];
+            y[e] = a.o_pre ? n * sigmoid_row<DT>(o[e]) : n;
+        }
+        if (live) Row8<DT>::store_stream(a.y, row * d + c, y);
     }
-    if (live) Row8<DT>::store_stream(a.y, row * d + c, y);
 }
 
 template <typename DT, int LPR>
@@ -292,7 +313,7 @@ __global__ void __launch_bounds__(256) norm_gate_bwd_packed_kernel(NormBwdArgs a
             x[e] = xh;
             float dn = dy[e];
             if (a.o_pre) {
-                const float og = sigmoidf_(o[e]);
+                const float og = sigmoid_row<DT>(o[e]);
                 dop[e] = dy[e] * (xh * g[e] + be[e]) * og * (1.0f - og);
                 dn = dy[e] * og;
             }
@@ -302,8 +323,8 @@ __global__ void __launch_bounds__(256) norm_gate_bwd_packed_kernel(NormBwdArgs a
             s2 += dx[e] * xh;
         }
         constexpr float invd = 1.0f / (float)d;
-        s1 = a.kind == 1 ? row_sum<LPR>(s1) * invd : 0.0f;
-        s2 = row_sum<LPR>(s2) * invd;
+        s1 = a.kind == 1 ? lanes_sum<LPR>(s1) * invd : 0.0f;
+        s2 = lanes_sum<LPR>(s2) * invd;
         if (live) {
             if (a.o_pre && a.do_pre) Row8<DT>::store_stream(a.do_pre, row * d + c, dop);
             float dh[8];
@@ -356,7 +377,7 @@ __global__ void __launch_bounds__(NPG_WAVES * 64) norm_param_grad_kernel(NormPar
 #pragma unroll
         for (int w = 0; w < NPG_WAVES; ++w) { sg += red[w][0][lane]; sb += red[w][1][lane]; }
         if (a.dgamma) a.dgamma[(long)head * a.d + c] = (float)sg;
-        if (a.dbeta) a.dbeta[(long)head * a.d + c] = (float)sb;
+        if (a.dbeta) a.dbeta[(long)head * a.d + c] = a.kind == 1 ? (float)sb : 0.0f;
     }
 }
 
@@ -394,19 +415,29 @@ __global__ void __launch_bounds__(256) transfer_gain_kernel(GainArgs a) {
     }
 }
 
+// Rows per workgroup of the forward kernels: `side` rows of a wavefront side by side, four wavefronts, and so many rounds
+// (at most eight) that the launch still has 8192 wavefronts, the 256 CUs' full occupancy.
+int fwd_rows_per_block(const NormArgs& a, int side) {
+    const long waves = (a.rows + side - 1) / side;
+    int rounds = 1;
+    while (rounds < 8 && waves / (2 * rounds) >= 8192) rounds *= 2;
+    return 4 * side * rounds;
+}
 template <typename DT, int LPR> hipError_t norm_fwd_packed(const NormArgs& a, hipStream_t s) {
-    const long rpb = 4 * (64 / LPR);      // rows per workgroup
-    hipLaunchKernelGGL((norm_gate_fwd_packed_kernel<DT, LPR>), dim3((unsigned)((a.rows + rpb - 1) / rpb)), dim3(256), 0, s, a);
+    const int rpb = fwd_rows_per_block(a, 64 / LPR);
+    const dim3 grid((a.T + rpb - 1) / rpb, (unsigned)(a.rows / a.T));
+    // (one wavefront is enough for a generation step, T = 1)
+    hipLaunchKernelGGL((norm_gate_fwd_packed_kernel<DT, LPR>), grid, dim3(a.T <= 64 / LPR ? 64 : 256), 0, s, a, rpb);
     return hipGetLastError();
 }
 template <typename DT> hipError_t norm_fwd_dt(const NormArgs& a, hipStream_t s) {
     if (a.d == 64) return norm_fwd_packed<DT, 8>(a, s);
     if (a.d == 128) return norm_fwd_packed<DT, 16>(a, s);
     if (a.d == 256) return norm_fwd_packed<DT, 32>(a, s);
-    const dim3 grid((unsigned)((a.rows + 3) / 4));
-    if (a.d <= 512) hipLaunchKernelGGL((norm_gate_fwd_kernel<DT, 1>), grid, dim3(256), 0, s, a);
-    else if (a.d <= 1024) hipLaunchKernelGGL((norm_gate_fwd_kernel<DT, 2>), grid, dim3(256), 0, s, a);
-    else hipLaunchKernelGGL((norm_gate_fwd_kernel<DT, 4>), grid, dim3(256), 0, s, a);
+    const int rpb = fwd_rows_per_block(a, 1);
+    const dim3 grid((a.T + rpb - 1) / rpb, (unsigned)(a.rows / a.T)), block(a.T < 4 ? 64 * a.T : 256);
+    if (a.d <= 512) hipLaunchKernelGGL((norm_gate_fwd_kernel<DT, 1>), grid, block, 0, s, a, rpb);
+    else hipLaunchKernelGGL((norm_gate_fwd_kernel<DT, 2>), grid, block, 0, s, a, rpb);
     return hipGetLastError();
 }
 template <typename DT> hipError_t norm_bwd_dt(const NormBwdArgs& a, int BH, hipStream_t s) {
@@ -417,9 +448,8 @@ template <typename DT> hipError_t norm_bwd_dt(const NormBwdArgs& a, int BH, hipS
         else hipLaunchKernelGGL((norm_gate_bwd_packed_kernel<DT, 32>), grid, dim3(256), 0, s, a);
         return hipGetLastError();
     }
-    if (a.d <= 512) hipLaunchKernelGGL((norm_gate_bwd_kernel<DT, 1>), grid, dim3(256), 0, s, a);
-    else if (a.d <= 1024) hipLaunchKernelGGL((norm_gate_bwd_kernel<DT, 2>), grid, dim3(256), 0, s, a);
-    else hipLaunchKernelGGL((norm_gate_bwd_kernel<DT, 4>), grid, dim3(256), 0, s, a);
+    if (a.d <= 512) hipLaunchKernelGGL((norm_gate_bwd_kernel<DT, 1, NORM_BW1>), grid, dim3(64 * NORM_BW1), 0, s, a);
+    else hipLaunchKernelGGL((norm_gate_bwd_kernel<DT, 2, 8>), grid, dim3(512), 0, s, a);
     return hipGetLastError();
 }
 template <typename DT> hipError_t gain_dt(const GainArgs& a, int BH, hipStream_t s) {

@@ -26,6 +26,11 @@ __device__ __forceinline__ int acc_row(int v, int grp) { return 8 * (v >> 2) + 4
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 __device__ __forceinline__ float fast_log2(float x) { return __builtin_amdgcn_logf(x); }
 
+// sigma(x) from the hardware's exp2 and reciprocal (relative error about 1e-7, 5e-6 at x = -80; 0 / 1 / NaN at -inf / +inf / NaN)
+__device__ __forceinline__ float fast_sigmoid(float x) {
+    return __builtin_amdgcn_rcpf(1.0f + fast_exp2(-1.4426950408889634f * x));
+}
+
 __device__ __forceinline__ uint32_t bf16_bits_rne(float x) {
     // round-to-nearest-even conversion, as bits in the low half
     bf16_t b = (bf16_t)x;
@@ -371,6 +376,30 @@ __device__ __forceinline__ unsigned xcd_remap(unsigned hw, unsigned total) {
 // ---------------------------------------------------------------------------------------
 // Wavefront helpers (64 lanes)
 // ---------------------------------------------------------------------------------------
+// Sum over groups of N neighbouring lanes (N = 2 ... 64, aligned), in every lane, without going through LDS (a shuffle by
+// ds_bpermute is a round trip of some hundred clocks): lanes 1 and 2 apart by quad permutations, the other half of a
+// group of 8 and of 16 by mirroring it (its lanes all hold the same sum by then), rows of 16 and halves of 32 by the
+// swap instructions, which given the same value twice return the two sides of each pair.
+template <int CTRL> __device__ __forceinline__ float dpp_move(float x) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xf, 0xf, true));
+}
+template <int N> __device__ __forceinline__ float lanes_sum(float x) {
+    if constexpr (N >= 2) x += dpp_move<0xb1>(x);       // quad_perm [1, 0, 3, 2]
+    if constexpr (N >= 4) x += dpp_move<0x4e>(x);       // quad_perm [2, 3, 0, 1]
+    if constexpr (N >= 8) x += dpp_move<0x141>(x);      // row_half_mirror
+    if constexpr (N >= 16) x += dpp_move<0x140>(x);     // row_mirror
+    if constexpr (N >= 32) {
+        const auto p = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(unsigned, x), __builtin_bit_cast(unsigned, x), false, false);
+        const unsigned lo = p[0], hi = p[1];
+        x = __builtin_bit_cast(float, lo) + __builtin_bit_cast(float, hi);
+    }
+    if constexpr (N >= 64) {
+        const auto p = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, x), __builtin_bit_cast(unsigned, x), false, false);
+        const unsigned lo = p[0], hi = p[1];
+        x = __builtin_bit_cast(float, lo) + __builtin_bit_cast(float, hi);
+    }
+    return x;
+}
 __device__ __forceinline__ float wave_sum(float x) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);

@@ -58,7 +58,6 @@ struct GateGradArgs {
 };
 hipError_t launch_gate_grads(const GateGradArgs& a, int BH, hipStream_t s);
 
-hipError_t launch_fill_zero(float* p, long n, hipStream_t s);
 struct FillList { float* p[4]; long n[4]; };     // n[q] = 0: slot unused
 hipError_t launch_fill_zero4(const FillList& f, hipStream_t s);
 // out[bh] = <A[bh], Bm[bh]>; A (BH, *, lda), Bm (BH, d1, d2): the first d2 columns of the first d1 rows of A's `perA` values
@@ -110,6 +109,7 @@ int norm_row_blocks(int T);
 struct NormParamGradArgs {
     const float* part; float* dgamma; float* dbeta;   // outputs (NH, d), either may be NULL
     int B, NH, nblk, d;
+    int kind;                                         // 0 = RMS norm: dbeta is zero
 };
 hipError_t launch_norm_param_grad(const NormParamGradArgs& a, hipStream_t s);
 struct GainArgs {

@@ -706,18 +706,14 @@ __global__ void __launch_bounds__(NW * 64, OCC) tile_kernel_bf16(TileArgs a) {
                 float sm = 0.0f;
 #pragma unroll
                 for (int e = 0; e < 8; ++e) sm += x[e];
-#pragma unroll
-                for (int m = 1; m < OCPR; m <<= 1) sm += __shfl_xor(sm, m, 64);
-                const float mu = sm * invd;
+                const float mu = lanes_sum<OCPR>(sm) * invd;
 #pragma unroll
                 for (int e = 0; e < 8; ++e) x[e] -= mu;
             }
             float ss = 0.0f;
 #pragma unroll
             for (int e = 0; e < 8; ++e) ss += x[e] * x[e];
-#pragma unroll
-            for (int m = 1; m < OCPR; m <<= 1) ss += __shfl_xor(ss, m, 64);
-            const float rstd = 1.0f / sqrtf(ss * invd + a.fz_eps);
+            const float rstd = 1.0f / sqrtf(lanes_sum<OCPR>(ss) * invd + a.fz_eps);
             float y[8];
 #pragma unroll
             for (int e = 0; e < 8; ++e) y[e] = x[e] * rstd * fz_g[e] + fz_b[e];
@@ -726,9 +722,8 @@ __global__ void __launch_bounds__(NW * 64, OCC) tile_kernel_bf16(TileArgs a) {
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     const float o0 = bf16_lo_to_f32(ow[e]), o1 = bf16_hi_to_f32(ow[e]);
-                    const float e0 = expf(-fabsf(o0)), e1 = expf(-fabsf(o1));
-                    y[2 * e] *= o0 >= 0.0f ? 1.0f / (1.0f + e0) : e0 / (1.0f + e0);
-                    y[2 * e + 1] *= o1 >= 0.0f ? 1.0f / (1.0f + e1) : e1 / (1.0f + e1);
+                    y[2 * e] *= fast_sigmoid(o0);
+                    y[2 * e + 1] *= fast_sigmoid(o1);
                 }
             }
             u32x4 yw;

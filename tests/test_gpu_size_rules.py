@@ -66,3 +66,42 @@ def test_wide_output_blocks(variant, B, NH, T, dqk, dhv, chunk):
 def test_tensors_that_end_inside_a_block(keep, variant, dtype, T, dqk, dhv, chunk):
     w = wl.small(variant, dtype, B=1, NH=3, T=T, dqk=dqk, dhv=dhv, chunk=chunk, seed=800 + T + dqk)
     _check_slices(w, dCn=True, keep=keep)
+
+
+# the row kernels of the layer: one and two groups of 512 columns per wavefront, several rows side by side, row blocks that
+# end early, one row only; forward through the layer's own entry point against the fp64 norm of the rounded cell output
+@pytest.mark.parametrize("dtype", [wl.BF16, wl.F32])
+@pytest.mark.parametrize("kind", [0, 1])
+@pytest.mark.parametrize("B,NH,T,dhv", [(1, 1, 1, 512), (1, 2, 129, 264), (2, 1, 33, 1024), (1, 3, 77, 128), (8, 16, 1030, 256)])
+def test_layer_rows(dtype, kind, B, NH, T, dhv):
+    import paper_2503_14376_amd as tfla
+    if dtype == wl.F32 and dhv > 512:
+        dhv = 512
+    g = torch.Generator(device="cuda").manual_seed(900 + T + dhv)
+    td = torch.bfloat16 if dtype == wl.BF16 else torch.float32
+    mk = lambda *s: torch.randn(s, device="cuda", generator=g)
+    q, k, v, o, dY = mk(B, NH, T, 64).to(td), mk(B, NH, T, 64).to(td), *(mk(B, NH, T, dhv).to(td) for _ in range(3))
+    o = o * 8                                   # gates from closed to open
+    ip, fp, gamma, beta = mk(B, NH, T), mk(B, NH, T) + 3, 1 + 0.1 * mk(NH, dhv), 0.1 * mk(NH, dhv)
+    print("rows", dtype, kind, (B, NH, T, dhv), flush=True)
+    kw = dict(chunk=64, norm_kind=kind, norm_eps=1e-6)
+    f = tfla.mlstm_layer_fwd(q, k, v, ip, fp, o, gamma, beta, **kw)
+    b = tfla.mlstm_layer_bwd(q, k, v, ip, fp, f["H"], dY, o, gamma, beta, f["n_out"], f["m_out"], fwd_workspace=f["workspace"], **kw)
+    torch.cuda.synchronize()
+    h, od, gd, bd, dy = (t.double().cpu() for t in (f["H"], o, gamma, beta, dY))
+    od.requires_grad_(); gd.requires_grad_(); bd.requires_grad_()
+    x = h - h.mean(-1, keepdim=True) if kind == 1 else h
+    y = torch.sigmoid(od) * (x / torch.sqrt((x * x).mean(-1, keepdim=True) + 1e-6) * gd[None, :, None] + (bd[None, :, None] if kind else 0))
+    (y * dy).sum().backward()
+    # one rounding to the element type (2^-9, 2^-24) of the largest value, and for the sums over B T rows of products of
+    # rounded operands the fp32 spacing times sqrt(rows); a factor of four on each
+    tol = 4 * 2.0 ** -9 if dtype == wl.BF16 else 4e-6
+    err = lambda a, r: float((a.double().cpu() - r).abs().max() / r.abs().max().clamp_min(1e-30))
+    errs = {"Y": err(f["Y"], y.detach()), "do": err(b["do_pre"], od.grad), "dgamma": err(b["dgamma"], gd.grad)}
+    if kind == 1:
+        errs["dbeta"] = err(b["dbeta"], bd.grad)
+    else:
+        assert float(b["dbeta"].abs().max()) == 0.0
+    print("   ", errs, flush=True)
+    for key, e in errs.items():
+        assert e <= (tol if key in ("Y", "do") else 4e-6 * max(1.0, (B * T) ** 0.5 / 8)), (key, errs)
