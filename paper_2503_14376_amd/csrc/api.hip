@@ -617,15 +617,9 @@ static int step_impl(const void* q, const void* k, const void* v, const float* i
     StepArgs a;
     a.q = q; a.k = k; a.v = v; a.i_pre = i_pre; a.f_pre = f_pre;
     a.C = C; a.n = variant == TFLA_EXP ? n : nullptr; a.m = variant == TFLA_EXP ? m : nullptr;
-    a.C_out = C_out; a.n_out = variant == TFLA_EXP ? n_out : nullptr; a.m_out = variant == TFLA_EXP ? m_out : nullptr;
+    a.C_out = C_out; a.n_out = n_out; a.m_out = m_out;     // (zero-filled for mLSTMsig)
     a.h = h; a.dqk = dqk; a.dhv = dhv; a.variant = variant; a.dtype = dtype; a.eps = eps; a.softcap = softcap;
     TFLA_LAUNCH(K_STEP, launch_step(a, B * NH, s));
-    if (variant == TFLA_SIG) {
-        FillList fl{};
-        if (n_out) { fl.p[0] = n_out; fl.n[0] = (long)B * NH * dqk; }
-        if (m_out) { fl.p[1] = m_out; fl.n[1] = (long)B * NH; }
-        if (n_out || m_out) TFLA_LAUNCH(K_FILL, launch_fill_zero4(fl, s));
-    }
     return TFLA_OK;
 }
 

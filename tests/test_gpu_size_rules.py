@@ -105,3 +105,29 @@ def test_layer_rows(dtype, kind, B, NH, T, dhv):
     print("   ", errs, flush=True)
     for key, e in errs.items():
         assert e <= (tol if key in ("Y", "do") else 4e-6 * max(1.0, (B * T) ** 0.5 / 8)), (key, errs)
+
+
+# generation step: both slab widths (64 columns from 2^24 state values on), batches of 64, 128 and 256 rows and row counts
+# that end inside a batch; one step against the fp64 recurrence on the first and the last head, fp32 bar on the state
+@pytest.mark.parametrize("variant", [wl.EXP, wl.SIG])
+@pytest.mark.parametrize("B,NH,dqk,dhv", [(1, 1, 64, 64), (16, 8, 256, 512), (2, 3, 192, 64), (64, 64, 64, 64), (3, 64, 320, 320),
+                                          (16, 64, 128, 128), (1, 2, 576, 960), (17, 1, 1024, 1024)])
+def test_step_slabs(variant, B, NH, dqk, dhv):
+    import paper_2503_14376_amd as tfla
+    g = torch.Generator(device="cuda").manual_seed(950 + dqk + dhv)
+    mk = lambda *s: torch.randn(s, device="cuda", generator=g)
+    q, k, v = mk(B, NH, dqk), mk(B, NH, dqk), mk(B, NH, dhv)
+    ip, fp, C, n, m = mk(B, NH), mk(B, NH) + 3, mk(B, NH, dqk, dhv), mk(B, NH, dqk), mk(B, NH)
+    print("step slabs", variant, (B, NH, dqk, dhv), flush=True)
+    o = tfla.mlstm_step(q, k, v, ip, fp, C, n, m, variant=variant, eps=1e-6)
+    torch.cuda.synchronize()
+    for b, h in ((0, 0), (B - 1, NH - 1)):
+        s = lambda t: t[b, h].double().cpu().numpy()[None]
+        r = orc.recurrent_fwd(s(q)[:, None], s(k)[:, None], s(v)[:, None], s(ip)[:, None], s(fp)[:, None], s(C), s(n), s(m),
+                              variant=variant, eps=1e-6)
+        from tests import gpu_util as gu
+        for key, ref in (("h", r["H"][0, 0]), ("C", r["Cn"][0])) + ((("n", r["nn"][0]),) if variant == wl.EXP else ()):
+            e = gu.rel_err(o[key][b, h], ref)
+            assert e <= gu.TOL[wl.F32], (key, e)
+    if variant == wl.SIG:
+        assert float(o["n"].abs().max()) == 0.0 and float(o["m"].abs().max()) == 0.0
