@@ -29,6 +29,7 @@ template <int KIND, int CPR> __device__ __forceinline__ int swz_mask(int r) {
         if (CPR == 8) return (r >> 1) & 7;
         return (r >> 2) & 3;
     }
+    static_assert(KIND == SWZ_K || CPR >= 8, "a transposed tile has at least 64 columns: the mask moves a chunk by four");
     if (CPR >= 16) return 4 * (r & 3);
     return 4 * ((r >> 1) & 1);
 }
@@ -136,6 +137,15 @@ __device__ __forceinline__ void dma4(const void* gbase_uniform, uint32_t voff, u
     const uint64_t gu = (uint64_t)glo | ((uint64_t)ghi << 32);
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tglobal_load_lds_dword %1, %2"
                  :: "s"(la), "v"(voff), "s"(gu) : "memory", "m0");
+}
+
+// a 16-bit store (low half of `data`) that the compiler's own wait counts know nothing of
+__device__ __forceinline__ void store16_uncounted(const void* gbase_uniform, uint32_t voff, uint32_t data) {
+    const uint64_t gb = (uint64_t)(uintptr_t)gbase_uniform;
+    const uint32_t glo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)gb);
+    const uint32_t ghi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(gb >> 32));
+    const uint64_t gu = (uint64_t)glo | ((uint64_t)ghi << 32);
+    asm volatile("s_nop 4\n\tglobal_store_short %0, %1, %2" :: "v"(voff), "v"(data), "s"(gu) : "memory");
 }
 
 // workgroup barrier without the fence a __syncthreads() carries (that fence would wait for
@@ -258,6 +268,12 @@ template <int COLS> struct TFragReader {
 #pragma unroll
         for (int j = 1; j < NJ; ++j) o = (nb % NJ == j) ? off[j] : o;
         return o + (uint32_t)(nb / NJ) * 256u;
+    }
+    // the same for a run-time nb without the table
+    static __device__ __forceinline__ uint32_t offset_of(int lane, int rowg, int nb) {
+        const int i = lane & 15, m = lane >> 4, g = lane >> 5;
+        const int row = rowg * g + (i >> 2), f = swz_mask<SWZ_T, CPR>(i >> 2);
+        return (uint32_t)(row * RB + (((4 * (nb % NJ)) ^ f) + 2 * (m & 1) + ((i & 3) >> 1)) * 16 + (i & 1) * 8) + (uint32_t)(nb / NJ) * 256u;
     }
     // the same fragment read from a precomputed block_offset()
     static __device__ __forceinline__ bf16x8 load_at(const char* tile, uint32_t boff, int rowA, int rowB) {

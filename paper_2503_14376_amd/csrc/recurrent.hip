@@ -11,6 +11,7 @@
 #include "tfla_device.h"
 #include "tfla_internal.h"
 #include "recurrent_fast.h"
+#include "recurrent_narrow.h"
 
 namespace tfla {
 
@@ -203,26 +204,28 @@ static hipError_t launch_rec_t(const RecArgs& a, int BH, hipStream_t s) {
     return hipGetLastError();
 }
 
-template <int WN>
+template <bool PAD>
 static hipError_t launch_rec_bf16(const RecArgs& a, int BH, hipStream_t s) {
-    dim3 grid(a.d2 / (WN * 32), a.d1 / 64, BH);
-    // pieces of 128 rows (half as many workgroup barriers) whenever the chunk size allows
-    const bool wide = a.L % 128 == 0;
-    if (a.padded()) {
-        if (wide) hipLaunchKernelGGL((recurrent_kernel_bf16<WN, 128, true>), grid, dim3(WN * 128), 0, s, a);
-        else hipLaunchKernelGGL((recurrent_kernel_bf16<WN, 64, true>), grid, dim3(WN * 128), 0, s, a);
+    // 64 x 128 state tiles where they are whole and 64 x 64 ones would not fit the 256 CUs in one round (see
+    // recurrent_narrow.h for both sides); pieces of 128 rows (half as many barriers) where the chunk size allows
+    const bool narrow = a.d2 % 128 != 0 || (long)BH * (a.d1 / 64) * (a.d2 / 64) <= 256;
+    const bool wide_pieces = a.L % 128 == 0;
+    const dim3 grid(a.d2 / (narrow ? 64 : 128), a.d1 / 64, BH), block(512);
+    if (narrow) {
+        if (wide_pieces) hipLaunchKernelGGL((recurrent_narrow_kernel_bf16<128, PAD>), grid, block, 0, s, a);
+        else hipLaunchKernelGGL((recurrent_narrow_kernel_bf16<64, PAD>), grid, block, 0, s, a);
     } else {
-        if (wide) hipLaunchKernelGGL((recurrent_kernel_bf16<WN, 128>), grid, dim3(WN * 128), 0, s, a);
-        else hipLaunchKernelGGL((recurrent_kernel_bf16<WN, 64>), grid, dim3(WN * 128), 0, s, a);
+        if (wide_pieces) hipLaunchKernelGGL((recurrent_kernel_bf16<4, 128, PAD>), grid, block, 0, s, a);
+        else hipLaunchKernelGGL((recurrent_kernel_bf16<4, 64, PAD>), grid, block, 0, s, a);
     }
     return hipGetLastError();
 }
 
 hipError_t launch_recurrent(const RecArgs& a, int BH, int dtype, hipStream_t s) {
     if (dtype == 1) {
-        // the bf16 kernel writes the chunk states as (d2, d1) only
+        // the bf16 kernels write the chunk states as (d2, d1) only
         if (a.stN) return hipErrorInvalidValue;
-        return a.d2 % 128 == 0 ? launch_rec_bf16<4>(a, BH, s) : launch_rec_bf16<2>(a, BH, s);
+        return a.padded() ? launch_rec_bf16<true>(a, BH, s) : launch_rec_bf16<false>(a, BH, s);
     }
     // fp32: 128x128 state tiles when that still fills the chip, 64x64 tiles otherwise
     const bool big_ok = (a.d1 % 128 == 0) && (a.d2 % 128 == 0);

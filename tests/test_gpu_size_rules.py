@@ -131,3 +131,18 @@ def test_step_slabs(variant, B, NH, dqk, dhv):
             assert e <= gu.TOL[wl.F32], (key, e)
     if variant == wl.SIG:
         assert float(o["n"].abs().max()) == 0.0 and float(o["m"].abs().max()) == 0.0
+
+
+# the two recurrent kernels: 64 x 64 state tiles up to 256 of them, 64 x 128 beyond (where d_hv is a multiple of 128), with
+# 64- and 128-row pieces, piece counts that are no multiple of the four a producer keeps on its way, whole and ragged
+@pytest.mark.parametrize("variant,B,NH,T,dqk,dhv,chunk", [
+    (wl.EXP, 2, 8, 320, 256, 256, 64),          # exactly 256 tiles of 64 x 64, five 64-row pieces
+    (wl.SIG, 1, 17, 384, 256, 256, 128),        # 272: 64 x 128 tiles, three 128-row pieces
+    (wl.EXP, 3, 7, 200, 256, 256, 64),          # 336, ragged
+    (wl.SIG, 4, 8, 700, 248, 200, 256),         # 512, ragged in every direction, 128-row pieces
+    (wl.EXP, 8, 40, 130, 64, 64, 64),           # 320 tiles, d_hv = 64: 64 x 64 whatever their number
+    (wl.EXP, 1, 1, 64, 64, 64, 64),             # one piece
+])
+def test_recurrent_tiles(variant, B, NH, T, dqk, dhv, chunk):
+    w = wl.small(variant, wl.BF16, B=B, NH=NH, T=T, dqk=dqk, dhv=dhv, chunk=chunk, seed=1000 + T + dqk)
+    _check_slices(w, dCn=True)
