@@ -111,10 +111,10 @@ FwdWs carve_fwd(const Dims& d, void* ws) {
 }
 
 struct BwdWs {
-    float *wrow, *ucol, *sH, *aK, *gbar, *mout, *tmp, *csum, *wrowB, *sQ, *partQ, *partK, *cdot, *Cfinal, *anchor, *pacc, *ancC;
+    float *wrow, *ucol, *sH, *aK, *gbar, *mout, *tmp, *csum, *wrowB, *sQ, *partQ, *partK, *Cfinal, *anchor, *pacc, *ancC;
     float *wrow_lo, *ucol_lo, *wrowB_lo;   // fp32 kernels: rounding remainders of the exponents (NULL for bf16)
-    double* bsum;
-    void *cN, *dcT, *dcN, *E, *E2;
+    double *bsum, *cdot;
+    void *cN, *dcT, *E, *E2;
     int nbQ, nbK;
     size_t bytes;
 };
@@ -133,12 +133,11 @@ BwdWs carve_bwd(const Dims& d, void* ws) {
     w.wrowB = c.take<float>(d.BHT); w.sQ = c.take<float>(d.BHT);
     w.nbQ = w.nbK = d.dqk / tile_bd2(d.dhv, d.dqk, d.dtype, d.L, d.BHT);
     w.partQ = c.take<float>((size_t)w.nbQ * d.BHT); w.partK = c.take<float>((size_t)w.nbK * d.BHT);
-    w.cdot = c.take<float>(d.BH);
+    w.cdot = c.take<double>((size_t)d.BH * STATE_DOT_PARTS);
     w.Cfinal = c.take<float>((size_t)d.BH * d.dqk * d.dhv);
     const size_t st = (size_t)d.BH * d.Nc * d.dqk * d.dhv * d.esz;
-    // bf16: C_{k-1} and dC_k, both as (d_hv, d_qk); fp32 additionally dC_k as (d_qk, d_hv)
+    // C_{k-1} and dC_k, both as (d_hv, d_qk)
     w.cN = c.take_bytes(st); w.dcT = c.take_bytes(st);
-    w.dcN = d.dtype == TFLA_BF16 ? nullptr : c.take_bytes(st);
     // bf16: the weighted intra-chunk matrix shared by dQ and dK, (BH, Nc, L, L)
     w.E = (d.dtype == TFLA_BF16 && tile_shares_E(d.dhv)) ? c.take_bytes((size_t)d.BHT * d.L * d.esz) : nullptr;
     // head dimensions above 512: fp32 partial results of the gradient kernels' first half, and the second
@@ -279,7 +278,7 @@ int fwd_impl(const void* q, const void* k, const void* v, const float* i_pre, co
     // 2. recurrent kernel: C_{k-1} (transposed, element type of q/k/v) and n_{k-1} for every chunk
     RecArgs r;
     r.X = k; r.Y = v; r.rs = w.aK; r.gbar = w.gbar; r.S0 = C0;
-    r.stT = w.stT; r.stN = nullptr; r.Sfinal = Cn; r.Sfinal2 = w.Cfin;
+    r.stT = w.stT; r.Sfinal = Cn; r.Sfinal2 = w.Cfin;
     r.n0 = is_exp ? n0 : nullptr; r.nst = is_exp ? w.nst : nullptr; r.nfinal = is_exp ? nn : nullptr;
     r.T = d.T; r.L = chunk; r.Nc = d.Nc; r.d1 = d.dqk; r.d2 = d.dhv; r.reverse = 0;
     r.T_in = T; r.d1_in = dqk; r.d2_in = dhv;
@@ -349,10 +348,8 @@ int bwd_impl(const void* q, const void* k, const void* v, const float* i_pre, co
         fw = carve_fwd(d, const_cast<void*>(fwd_workspace));
         if (fwd_workspace_bytes < fw.bytes) return TFLA_ERR_WORKSPACE;
     }
-    // the generic fp32 kernels read the states of dQ / dK as (d_qk, d_hv); the bf16 kernels read
-    // (d_hv, d_qk) everywhere, so only that layout is ever written on the bf16 path
-    const bool tonly = dtype == TFLA_BF16;
-    const bool reuse_states = reuse && tonly;
+    // (the forget-gate scan is anchored on the bf16 path only)
+    const bool anchored = dtype == TFLA_BF16;
     const float* wrow = reuse ? fw.wrow : w.wrow;
     const float* ucol = reuse ? fw.ucol : w.ucol;
     const float* sH = reuse ? fw.sH : w.sH;
@@ -385,12 +382,12 @@ int bwd_impl(const void* q, const void* k, const void* v, const float* i_pre, co
     }
 
     // 2. the chunk states C_{k-1}
-    const void* cstates = reuse_states ? fw.stT : w.cN;
-    const float* Cfinal = reuse_states ? fw.Cfin : w.Cfinal;
-    if (!reuse_states) {
+    const void* cstates = reuse ? fw.stT : w.cN;
+    const float* Cfinal = reuse ? fw.Cfin : w.Cfinal;
+    if (!reuse) {
         RecArgs r;
         r.X = k; r.Y = v; r.rs = aK; r.gbar = gbar; r.S0 = C0;
-        r.stT = tonly ? w.cN : nullptr; r.stN = tonly ? nullptr : w.cN;
+        r.stT = w.cN;
         r.Sfinal = nullptr; r.Sfinal2 = dCn ? w.Cfinal : nullptr;
         r.n0 = nullptr; r.nst = nullptr; r.nfinal = nullptr;
         r.T = d.T; r.L = chunk; r.Nc = d.Nc; r.d1 = d.dqk; r.d2 = d.dhv; r.reverse = 0;
@@ -402,13 +399,13 @@ int bwd_impl(const void* q, const void* k, const void* v, const float* i_pre, co
     // 3. backward recurrence: dC_k for every chunk, dC_0 at the end
     RecArgs rb;
     rb.X = q; rb.Y = dH; rb.rs = sQ; rb.gbar = gbar; rb.S0 = dCn;
-    rb.stT = w.dcT; rb.stN = tonly ? nullptr : w.dcN; rb.Sfinal = dC0; rb.Sfinal2 = nullptr;
+    rb.stT = w.dcT; rb.Sfinal = dC0; rb.Sfinal2 = nullptr;
     rb.n0 = nullptr; rb.nst = nullptr; rb.nfinal = nullptr;
     rb.T = d.T; rb.L = chunk; rb.Nc = d.Nc; rb.d1 = d.dqk; rb.d2 = d.dhv; rb.reverse = 1;
     rb.T_in = T; rb.d1_in = dqk; rb.d2_in = dhv;
     // bf16: the reversed launch also forms <C, dC> at the block boundaries of the forget-gate gradient scan, from the
     // fp32 copies of C that the forward launch left there and its own fp32 accumulators
-    rb.anc = nullptr; rb.anc_in = tonly ? (reuse_states ? fw.anc : w.ancC) : nullptr; rb.anc_part = tonly ? w.anchor : nullptr;
+    rb.anc = nullptr; rb.anc_in = anchored ? (reuse ? fw.anc : w.ancC) : nullptr; rb.anc_part = anchored ? w.anchor : nullptr;
     rb.anc_G = anchor_G(d);
     TFLA_LAUNCH(K_REC_BWD, launch_recurrent(rb, (int)d.BH, dtype, s));
 
@@ -425,7 +422,7 @@ int bwd_impl(const void* q, const void* k, const void* v, const float* i_pre, co
     t.d1 = d.dhv; t.d2 = d.dqk; t.dotwith = q; t.dotpart = w.partQ;
     TFLA_LAUNCH(K_TILE_DQ, launch_tile_mode<MODE_DQ>(t, (int)d.BH, dtype, s));
     // dK: rows = kv index j
-    t.X = v; t.Y = dH; t.Z = q; t.Out = dk; t.wrow_lo = ucol_lo; t.wcol_lo = wrowB_lo; t.wrow = ucol; t.wcol = wrowB; t.srow = aK; t.St = tonly ? w.dcT : w.dcN;
+    t.X = v; t.Y = dH; t.Z = q; t.Out = dk; t.wrow_lo = ucol_lo; t.wcol_lo = wrowB_lo; t.wrow = ucol; t.wcol = wrowB; t.srow = aK; t.St = w.dcT;
     t.d1 = d.dhv; t.d2 = d.dqk; t.dotwith = k; t.dotpart = w.partK;
     TFLA_LAUNCH(K_TILE_DK, launch_tile_mode<MODE_DK>(t, (int)d.BH, dtype, s));
 
@@ -441,7 +438,7 @@ int bwd_impl(const void* q, const void* k, const void* v, const float* i_pre, co
     // terms per chunk, from the bf16 states) accumulates over one block instead of the whole sequence.  The anchors
     // themselves are exact to fp32: the forward recurrent launch leaves fp32 copies of the state at the block
     // boundaries and the reversed launch multiplies them with its fp32 accumulators (see RecArgs).
-    if (tonly) {
+    if (anchored) {
         gg.G = anchor_G(d);
         gg.anchor = w.anchor; gg.npart = rec_anchor_parts(d.dqk, d.dhv);
     }

@@ -304,6 +304,14 @@ hipError_t launch_gate_bwd_prep(const GateBwdPrepArgs& a, hipStream_t s) {
 // the blocks after it and scans its own steps (in fp64: the terms cancel heavily).
 static constexpr int GG_BLOCK = 1024;
 
+__device__ __forceinline__ double state_dot_sum(const GateGradArgs& a, int bh) {
+    double s = 0.0;
+    if (a.cdot) {
+#pragma unroll
+        for (int p = 0; p < STATE_DOT_PARTS; ++p) s += a.cdot[(long)bh * STATE_DOT_PARTS + p];
+    }
+    return s;
+}
 __device__ __forceinline__ void gate_grad_terms(const GateGradArgs& a, long idx, float& r, float& c) {
     r = 0.0f; c = 0.0f;
     for (int nb = 0; nb < a.nbQ; ++nb) r += a.partQ[(long)nb * a.BHT + idx];
@@ -343,7 +351,7 @@ __global__ void __launch_bounds__(256) gate_grads_kernel(GateGradArgs a) {
     for (int o = 32; o > 0; o >>= 1) later += __shfl_xor(later, o, 64);
     if (lane == 0) wt[wave] = later;
     __syncthreads();
-    if (tid == 0) after = wt[0] + wt[1] + wt[2] + wt[3] + (a.cdot ? (double)a.cdot[bh] : 0.0);
+    if (tid == 0) after = wt[0] + wt[1] + wt[2] + wt[3] + state_dot_sum(a, bh);
     __syncthreads();
     // thread tid owns GG_BLOCK / 256 consecutive steps
     constexpr int SEG = GG_BLOCK / 256;
@@ -416,7 +424,7 @@ __global__ void __launch_bounds__(256) gate_grads_anchored_kernel(GateGradArgs a
     __shared__ double wa[4];
     double anc = 0.0;
     if (kc1 == a.Nc) {
-        anc = a.cdot ? (double)a.cdot[bh] : 0.0;
+        anc = state_dot_sum(a, bh);
     } else {
         const int nslot = (a.Nc + a.G - 1) / a.G;
         const float* pp = a.anchor + ((long)bh * nslot + kc1 / a.G) * a.npart;
@@ -478,28 +486,26 @@ hipError_t launch_fill_zero4(const FillList& f, hipStream_t s) {
     return hipGetLastError();
 }
 
-// out[bh] = <A[bh], Bm[bh]> over the d1 x d2 values of Bm; A's rows are lda apart
-__global__ void __launch_bounds__(1024) state_dot_kernel(const float* A, long perA, int lda, const float* Bm, int d1, int d2, float* out) {
-    __shared__ double wt[16];
-    const int bh = blockIdx.x, tid = threadIdx.x;
-    const long per = (long)d1 * d2;
+// Part p of <A[bh], Bm[bh]> over the d1 x d2 values of Bm (A's rows are lda apart): rows p, p + STATE_DOT_PARTS, ...,
+// the wavefronts of the workgroup one row each.  (One workgroup per (batch, head) took 17 us for 32 heads of 96 x 192, 12
+// us for 16 of 128 x 256; now 6 and 6.)
+__global__ void __launch_bounds__(256) state_dot_kernel(const float* A, long perA, int lda, const float* Bm, int d1, int d2, double* out) {
+    __shared__ double wt[4];
+    const int bh = blockIdx.y, p = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     double acc = 0.0;
-    for (long i = tid; i < per; i += 1024) {
-        const long r = i / d2;
-        acc += (double)A[bh * perA + r * lda + (i - r * d2)] * (double)Bm[bh * per + i];
+    for (int r = p + STATE_DOT_PARTS * wave; r < d1; r += 4 * STATE_DOT_PARTS) {
+        const float* ar = A + bh * perA + (long)r * lda;
+        const float* br = Bm + ((long)bh * d1 + r) * d2;
+        for (int c = lane; c < d2; c += 64) acc += (double)ar[c] * (double)br[c];
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o, 64);
-    if ((tid & 63) == 0) wt[tid >> 6] = acc;
+    if (lane == 0) wt[wave] = acc;
     __syncthreads();
-    if (tid == 0) {
-        double t = 0.0;
-        for (int w = 0; w < 16; ++w) t += wt[w];
-        out[bh] = (float)t;
-    }
+    if (threadIdx.x == 0) out[(long)bh * STATE_DOT_PARTS + p] = (wt[0] + wt[1]) + (wt[2] + wt[3]);
 }
-hipError_t launch_state_dot(const float* A, long perA, int lda, const float* Bm, int d1, int d2, float* out, int BH, hipStream_t s) {
-    hipLaunchKernelGGL(state_dot_kernel, dim3(BH), dim3(1024), 0, s, A, perA, lda, Bm, d1, d2, out);
+hipError_t launch_state_dot(const float* A, long perA, int lda, const float* Bm, int d1, int d2, double* out, int BH, hipStream_t s) {
+    hipLaunchKernelGGL(state_dot_kernel, dim3(STATE_DOT_PARTS, BH), dim3(256), 0, s, A, perA, lda, Bm, d1, d2, out);
     return hipGetLastError();
 }
 

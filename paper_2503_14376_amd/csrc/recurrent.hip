@@ -6,8 +6,8 @@
 //
 // Forward:  X = K, Y = V, rs = a-bar, state = C;  backward: X = Q, Y = delta H,
 // rs = b-bar * qscale / h_denom, state = delta C, chunks visited last to first.  The state
-// before each update is written (in the element type of X/Y) to slot k in one or both of the
-// layouts the tiled kernels read: stT[k] = state^T (d2 x d1) and stN[k] = state (d1 x d2).
+// before each update is written (in the element type of X/Y) to slot k in the layout the tiled
+// kernels read: stT[k] = state^T (d2 x d1).
 #include "tfla_device.h"
 #include "tfla_internal.h"
 #include "recurrent_fast.h"
@@ -116,14 +116,6 @@ __global__ void __launch_bounds__(256) recurrent_kernel(RecArgs a) {
 #pragma unroll
                         for (int ni = 0; ni < NI; ++ni) {
                             const int n = n0 + wn * 32 * NI + 32 * ni + l32;
-                            if (a.stN) {
-                                DT* dst = reinterpret_cast<DT*>(a.stN) + slot * a.d1 * a.d2;
-#pragma unroll
-                                for (int v = 0; v < 16; ++v) {
-                                    const int m = m0 + wm * 32 * MI + 32 * mi + acc_row(v, g);
-                                    dst[(long)m * a.d2 + n] = E::from_f32(acc[mi][ni][v]);
-                                }
-                            }
                             if (a.stT) {
                                 // registers 4j..4j+3 hold four consecutive m: one packed store each
                                 DT* dst = reinterpret_cast<DT*>(a.stT) + slot * a.d1 * a.d2;
@@ -223,8 +215,6 @@ static hipError_t launch_rec_bf16(const RecArgs& a, int BH, hipStream_t s) {
 
 hipError_t launch_recurrent(const RecArgs& a, int BH, int dtype, hipStream_t s) {
     if (dtype == 1) {
-        // the bf16 kernels write the chunk states as (d2, d1) only
-        if (a.stN) return hipErrorInvalidValue;
         return a.padded() ? launch_rec_bf16<true>(a, BH, s) : launch_rec_bf16<false>(a, BH, s);
     }
     // fp32: 128x128 state tiles when that still fills the chip, 64x64 tiles otherwise

@@ -44,7 +44,7 @@ hipError_t launch_gate_bwd_prep(const GateBwdPrepArgs& a, hipStream_t s);
 struct GateGradArgs {
     const float* partQ; int nbQ;   // (nbQ, BH*T) partial q.dq
     const float* partK; int nbK;   // (nbK, BH*T) partial k.dk
-    const float* cdot;             // (BH) <C_T, dC_T> or NULL
+    const double* cdot;            // (BH, STATE_DOT_PARTS) partial sums of <C_T, dC_T>, or NULL
     const float* i_pre; const float* f_pre;
     float* d_i; float* d_f;
     double* bsum;                  // (BH, ceil(T / 1024)) scratch: block sums
@@ -61,7 +61,9 @@ hipError_t launch_gate_grads(const GateGradArgs& a, int BH, hipStream_t s);
 struct FillList { float* p[4]; long n[4]; };     // n[q] = 0: slot unused
 hipError_t launch_fill_zero4(const FillList& f, hipStream_t s);
 // out[bh] = <A[bh], Bm[bh]>; A (BH, *, lda), Bm (BH, d1, d2): the first d2 columns of the first d1 rows of A's `perA` values
-hipError_t launch_state_dot(const float* A, long perA, int lda, const float* Bm, int d1, int d2, float* out, int BH, hipStream_t s);
+// as STATE_DOT_PARTS partial sums each
+constexpr int STATE_DOT_PARTS = 16;
+hipError_t launch_state_dot(const float* A, long perA, int lda, const float* Bm, int d1, int d2, double* out, int BH, hipStream_t s);
 // Chunks per block of the anchored forget-gate gradient scan: four (a block has at most 2048 steps); two for heads
 // wider than 512, where a row's dot products run over so many terms that the noise of a few chunks already shows
 // (behind a norm layer the forget-gate gradient is what survives of an almost complete cancellation).
@@ -130,7 +132,6 @@ struct RecArgs {
     const float* gbar;    // (BH, Nc)
     const float* S0;      // (BH, d1_in, d2_in) fp32 or NULL (zero)
     void* stT;            // (BH, Nc, d2, d1) element type DT, or NULL
-    void* stN;            // (BH, Nc, d1, d2) element type DT, or NULL
     float* Sfinal;        // (BH, d1_in, d2_in) fp32 or NULL
     float* Sfinal2;       // second copy of the final state, (BH, d1, d2), or NULL
     const float* n0;      // (BH, d1_in) or NULL; normaliser vector, forward mLSTMexp only
@@ -172,7 +173,7 @@ struct TileArgs {
     const void* X; const void* Y;   // (BH, out_T, in_ld1)
     const void* Z; void* Out;       // (BH, out_T, out_ld), see below
     const float* wrow; const float* wcol; const float* srow;   // (BH, T)
-    const void* St;                 // (BH, Nc, d2, d1)
+    const void* St;                 // (BH, Nc, d_hv, d_qk): d2 x d1 for H and dV, d1 x d2 for dQ and dK
     int T, L, Nc, d1, d2;
     int kc_desc;                    // bf16 kernels: walk the chunks last to first (set by the launcher)
     // MODE_H, mLSTMexp: normaliser

@@ -73,7 +73,10 @@ __global__ void __launch_bounds__(NW * 64) tile_kernel(TileArgs a) {
     const int steps_left = PAD ? a.out_T - kc * a.L : 0, cols1 = PAD ? a.in_cols1 : 0, cols2 = PAD ? a.out_ld - nb2 * BD2 : 0;
     const DT* Y = reinterpret_cast<const DT*>(a.Y) + tin * xld;
     const DT* Z = reinterpret_cast<const DT*>(a.Z) + tin * zld + (long)nb2 * BD2;
-    const DT* St = reinterpret_cast<const DT*>(a.St) + (((long)bh * a.Nc + kc) * d2 + (long)nb2 * BD2) * ld1;
+    // the state of the chunk is (d_hv, d_qk): contraction-contiguous for H and dV, contraction-major for dQ and dK
+    constexpr bool STT = MODE == MODE_DQ || MODE == MODE_DK;
+    const DT* St = reinterpret_cast<const DT*>(a.St) + (STT ? ((long)bh * a.Nc + kc) * ld1 * d2 + (long)nb2 * BD2
+                                                            : (((long)bh * a.Nc + kc) * d2 + (long)nb2 * BD2) * ld1);
     const float* wcol = a.wcol + tbase;
     const float* wcol_lo = a.wcol_lo ? a.wcol_lo + tbase : nullptr;
 
@@ -101,20 +104,28 @@ __global__ void __launch_bounds__(NW * 64) tile_kernel(TileArgs a) {
     const int ct_lo = UPPER ? r0 / BC : 0;
     const int ct_hi = UPPER ? a.L / BC : (r0 + BR) / BC;
 
-    RowsPrefetch<DT, BD2, BC, NT> ps;          // state chunk  [BD2][BC]
+    typename std::conditional<STT, TrPrefetch<DT, BC, BD2, NT, false>, RowsPrefetch<DT, BD2, BC, NT>>::type ps;   // state slice [BD2][BC]
+    auto load_state = [&](int j) {
+        if constexpr (STT) ps.load(St + (long)j * BC * d2, d2, tid);
+        else ps.load(St + j * BC, ld1, tid);
+    };
+    auto store_state = [&](DT* dst) {
+        if constexpr (STT) ps.template store<false>(dst, ZS, nullptr, tid);
+        else ps.store(dst, ZS, tid);
+    };
     RowsPrefetch<DT, BC, D1, NT> py;           // Y tile       [BC][D1]
     TrPrefetch<DT, BC, BD2, NT, true> pz;      // Z tile       [BC][BD2] -> [BD2][BC]
     float pw = 0.0f, pwl = 0.0f;
     int buf = 0;
 
     // ---------------- inter-chunk part: acc = X_r St, BC columns of d1 per stage
-    ps.load(St, ld1, tid);
-    ps.store(ldsZ[0], ZS, tid);
+    load_state(0);
+    store_state(ldsZ[0]);
     __syncthreads();
 #pragma unroll
     for (int j = 0; j < NK; ++j) {
         if (j + 1 < NK) {
-            ps.load(St + (j + 1) * BC, ld1, tid);
+            load_state(j + 1);
         } else {
             py.template load<PAD>(Y + (long)ct_lo * BC * xld, xld, tid, steps_left - ct_lo * BC, cols1);
             pz.template load<PAD>(Z + (long)ct_lo * BC * zld, zld, tid, steps_left - ct_lo * BC, cols2);
@@ -127,7 +138,7 @@ __global__ void __launch_bounds__(NW * 64) tile_kernel(TileArgs a) {
             for (int nb = 0; nb < NB; ++nb)
                 acc[nb] = E::mma(xf[j * (BC / 16) + ks], E::load(zb + (nb * 32 + l32) * ZS + 16 * ks + 8 * g), acc[nb]);
         if (j + 1 < NK) {
-            ps.store(ldsZ[buf ^ 1], ZS, tid);
+            store_state(ldsZ[buf ^ 1]);
         } else {
             py.store(ldsY[buf ^ 1], YS, tid);
             pz.template store<false>(ldsZ[buf ^ 1], ZS, nullptr, tid);
@@ -404,7 +415,7 @@ hipError_t launch_tile_mode(const TileArgs& a0, int BH, int dtype, hipStream_t s
         h.X = reinterpret_cast<const float*>(a.X) + 256;
         h.in_cols1 = a.in_cols1 - 256;
         h.Y = reinterpret_cast<const float*>(a.Y) + 256;
-        h.St = reinterpret_cast<const float*>(a.St) + 256;
+        h.St = reinterpret_cast<const float*>(a.St) + ((MODE == MODE_DQ || MODE == MODE_DK) ? (long)256 * a.d2 : 256);
         if (a.nstate) h.nstate = a.nstate + 256;
         return launch_tile_d1<float, 256, MODE, 2>(h, BH, bd2, s);
     }
