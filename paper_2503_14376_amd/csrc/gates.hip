@@ -245,7 +245,107 @@ __global__ void __launch_bounds__(GATE_WAVES * 64) gates_step_kernel(GateArgs a)
     }
 }
 
+// Both kernels in one for short sequences: up to sixteen chunks, one wavefront each, in one workgroup per (batch, head);
+// the lane's E = L / 64 steps stay in registers from the scans to the results, and the chunk summaries meet in LDS.
+// Longer sequences keep the two launches, which spread one (batch, head) over the chip (a workgroup that walks 32 chunks
+// twice took 34 us where the two take 16).  us, two launches / one: 8 heads of 8 chunks of 128 11 / 5.6; 256 heads of 8
+// chunks of 256 23 / 12; 16 heads of 16 chunks of 256 17 / 13.
+constexpr int GATE_FUSED_CHUNKS = 16;
+template <int E, typename AT>
+__global__ void __launch_bounds__(GATE_FUSED_CHUNKS * 64) gates_fused_kernel(GateArgs a) {
+    __shared__ AT cg[GATE_FUSED_CHUNKS], camax[GATE_FUSED_CHUNKS];
+    const int bh = blockIdx.x, lane = threadIdx.x & 63, kc = threadIdx.x >> 6;
+    const bool is_exp = a.variant == 0;
+    const int t0 = kc * (64 * E) + lane * E;                       // first of this lane's steps
+    const long row = (long)bh * a.T + t0, urow = (long)bh * a.Tvalid + t0;
+    const AT log2e = (AT)1.4426950408889634;
+    AT fb[E], ib[E], b[E], cm[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        fb[e] = (AT)0; ib[e] = (AT)-1.0e30f;                       // (a step past the end of the sequence)
+        if (t0 + e < a.Tvalid) {
+            fb[e] = log_sigmoid_t<AT>(soft_cap_t<AT>((AT)a.f_pre[urow + e], a.softcap));
+            const AT ip = soft_cap_t<AT>((AT)a.i_pre[urow + e], a.softcap);
+            ib[e] = is_exp ? ip : log_sigmoid_t<AT>(ip);
+        }
+    }
+    AT fsum = (AT)0;
+#pragma unroll
+    for (int e = 0; e < E; ++e) fsum += fb[e];
+    const AT off = wave_excl_scan_add<AT>(fsum, lane), roff = wave_excl_rscan_add<AT>(fsum, lane);
+    AT run = off, cmx = (AT)-INFINITY;
+    float uh[E], ul[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        run += fb[e];
+        b[e] = run;
+        const AT u = ib[e] - run;
+        cmx = max_t<AT>(cmx, u);
+        cm[e] = cmx;
+        uh[e] = (float)(u * log2e);
+        ul[e] = (float)(u * log2e - (AT)uh[e]);
+    }
+    const AT cmoff = wave_excl_scan_max<AT>(cmx, lane);
+    // a_j = sum_{s>j} f-bar_s + i-bar_j
+    AT av[E], amax = (AT)-INFINITY;
+    run = roff;
+#pragma unroll
+    for (int e = E - 1; e >= 0; --e) {
+        av[e] = run + ib[e];
+        amax = max_t<AT>(amax, av[e]);
+        run += fb[e];
+    }
+    amax = wave_max_t<AT>(amax);
+    const AT gsum = wave_sum_t<AT>(fsum);
+    if (lane == 0) { cg[kc] = gsum; camax[kc] = amax; }
+    __syncthreads();
+    AT mprev = (is_exp && a.m0) ? (AT)a.m0[bh] : (AT)0;
+    if (is_exp)
+        for (int k = 0; k < kc; ++k) mprev = max_t<AT>(cg[k] + mprev, camax[k]);
+    const AT mk = is_exp ? max_t<AT>(gsum + mprev, amax) : (AT)0;
+    if (lane == 0) {
+        a.gbar[(long)bh * a.Nc + kc] = (float)exp_t<AT>(gsum + mprev - mk);
+        if (kc == a.Nc - 1 && a.mfinal) a.mfinal[bh] = (float)mk;
+    }
+    const AT lq = (AT)log2f(a.qscale);
+    typedef float vec __attribute__((ext_vector_type(E)));
+    vec wh, wl, sh, ak, uv, uvl;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        AT wr, s, mo = (AT)0;
+        if (is_exp) {
+            const AT M = max_t<AT>(mprev, max_t<AT>(cmoff, cm[e]));
+            wr = -M * log2e + lq;
+            s = exp_t<AT>(mprev - M) * (AT)a.qscale;
+            mo = b[e] + M;
+        } else {
+            wr = b[e] * log2e + lq;
+            s = exp_t<AT>(b[e]) * (AT)a.qscale;
+        }
+        wh[e] = (float)wr; wl[e] = (float)(wr - (AT)wh[e]);
+        sh[e] = (float)s;
+        ak[e] = (float)exp_t<AT>(av[e] - mk);
+        uv[e] = uh[e]; uvl[e] = ul[e];
+        a.mout[row + e] = (float)mo;
+        if (a.mout_user && t0 + e < a.Tvalid) a.mout_user[urow + e] = (float)mo;
+    }
+    *reinterpret_cast<vec*>(a.wrow + row) = wh;
+    *reinterpret_cast<vec*>(a.ucol + row) = uv;
+    *reinterpret_cast<vec*>(a.sH + row) = sh;
+    *reinterpret_cast<vec*>(a.aK + row) = ak;
+    if (a.wrow_lo) *reinterpret_cast<vec*>(a.wrow_lo + row) = wl;
+    if (a.ucol_lo) *reinterpret_cast<vec*>(a.ucol_lo + row) = uvl;
+}
+
 template <typename AT> static hipError_t launch_gates_t(const GateArgs& a, int BH, hipStream_t s) {
+    if (a.Nc <= GATE_FUSED_CHUNKS && (a.L == 64 || a.L == 128 || a.L == 256 || a.L == 512)) {
+        const dim3 grid(BH), block(64 * a.Nc);
+        if (a.L == 64) hipLaunchKernelGGL((gates_fused_kernel<1, AT>), grid, block, 0, s, a);
+        else if (a.L == 128) hipLaunchKernelGGL((gates_fused_kernel<2, AT>), grid, block, 0, s, a);
+        else if (a.L == 256) hipLaunchKernelGGL((gates_fused_kernel<4, AT>), grid, block, 0, s, a);
+        else hipLaunchKernelGGL((gates_fused_kernel<8, AT>), grid, block, 0, s, a);
+        return hipGetLastError();
+    }
     const dim3 grid((a.Nc + GATE_WAVES - 1) / GATE_WAVES, BH);
     // the log gates of a lane's steps stay in registers for every chunk size the library accepts (L <= 2048)
     if (a.L / 64 <= 8) hipLaunchKernelGGL((gates_chunk_kernel<8, AT>), grid, dim3(GATE_WAVES * 64), 0, s, a);

@@ -146,3 +146,12 @@ def test_step_slabs(variant, B, NH, dqk, dhv):
 def test_recurrent_tiles(variant, B, NH, T, dqk, dhv, chunk):
     w = wl.small(variant, wl.BF16, B=B, NH=NH, T=T, dqk=dqk, dhv=dhv, chunk=chunk, seed=1000 + T + dqk)
     _check_slices(w, dCn=True)
+
+
+# the gate pre-pass in one launch (up to 16 chunks of 64, 128, 256 or 512) and in two
+@pytest.mark.parametrize("dtype", [wl.BF16, wl.F32])
+@pytest.mark.parametrize("variant,T,chunk", [(wl.EXP, 1024, 64), (wl.EXP, 1025, 64), (wl.SIG, 2048, 128), (wl.EXP, 1000, 512),
+                                             (wl.EXP, 576, 192)])
+def test_gate_launches(dtype, variant, T, chunk):
+    w = wl.small(variant, dtype, B=1, NH=3, T=T, dqk=64, dhv=64, chunk=chunk, seed=1100 + T)
+    _check_slices(w)
