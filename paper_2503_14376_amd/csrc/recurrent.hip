@@ -15,17 +15,19 @@
 
 namespace tfla {
 
-// Generic kernel (any element type, operands staged transposed through registers); bf16 uses
-// recurrent_kernel_bf16 (recurrent_fast.h), this one serves fp32.
-
-template <typename DT, int MI, int NI, int BK, bool PAD>
-__global__ void __launch_bounds__(256) recurrent_kernel(RecArgs a) {
-    using E = Elem<DT>;
-    constexpr int BM = 64 * MI, BN = 64 * NI, NT = 256;
-    constexpr int LS = BK + E::PAD;
-    constexpr int D = 4;   // pieces (BK rows of X and Y) in flight from global memory
-    __shared__ __attribute__((aligned(16))) DT ldsX[2][BM * LS];
-    __shared__ __attribute__((aligned(16))) DT ldsY[2][BN * LS];
+// fp32 kernel.  Pieces of BK rows of X (scaled) and Y go through registers into LDS in their own row-major layout: the
+// fp32 matrix instructions take one value per lane and k, so the fragments are read from it as they are.  D pieces are on
+// their way in registers.  What bounds it: the matrix instructions, 1024 clocks per piece and wavefront in one chain, and
+// the staging around them in the same wavefronts.  (With both operands transposed on the way, a dword per load, and waits
+// that drained the pieces at every branch: 16 heads 128 x 256, 1024 steps, chunk 64 52 us per launch, now 43.)
+// PAD: the caller's tensors end before the pieces and tiles do (RecArgs::T_in, d1_in, d2_in); what lies past is zero.
+template <int MI, int NI, bool PAD>
+__global__ void __launch_bounds__(256) recurrent_kernel_f32(RecArgs a) {
+    constexpr int BM = 64 * MI, BN = 64 * NI, NT = 256, BK = 32, D = 4;
+    constexpr int LX = BM + 4, LY = BN + 4;
+    __shared__ __attribute__((aligned(16))) float ldsX[2][BK * LX];
+    __shared__ __attribute__((aligned(16))) float ldsY[2][BK * LY];
+    __shared__ float ldsG[4096];                // gbar of every chunk
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l32 = lane & 31, g = lane >> 5;
     const int wm = wave >> 1, wn = wave & 1;
@@ -38,11 +40,12 @@ __global__ void __launch_bounds__(256) recurrent_kernel(RecArgs a) {
     // the caller's tensors: row strides, and (PAD) what exists of them from this tile's first column on
     const int xld = PAD ? a.d1_in : a.d1, yld = PAD ? a.d2_in : a.d2, tld = PAD ? a.T_in : a.T;
     const int xcols = PAD ? a.d1_in - m0 : 0, ycols = PAD ? a.d2_in - n0 : 0;
-    const DT* X = reinterpret_cast<const DT*>(a.X) + (long)bh * tld * xld + m0;
-    const DT* Y = reinterpret_cast<const DT*>(a.Y) + (long)bh * tld * yld + n0;
+    const float* X = reinterpret_cast<const float*>(a.X) + (long)bh * tld * xld + m0;
+    const float* Y = reinterpret_cast<const float*>(a.Y) + (long)bh * tld * yld + n0;
     const float* rs = a.rs + (long)bh * a.T;
     const bool with_n = (a.nst != nullptr) && bx == 0;
 
+    for (int k = tid; k < a.Nc; k += NT) ldsG[k] = a.gbar[(long)bh * a.Nc + k];
     f32x16 acc[MI][NI];
 #pragma unroll
     for (int mi = 0; mi < MI; ++mi)
@@ -59,58 +62,56 @@ __global__ void __launch_bounds__(256) recurrent_kernel(RecArgs a) {
     float nacc = 0.0f;
     if (with_n && tid < BM && a.n0 && (!PAD || tid < xcols)) nacc = a.n0[(long)bh * xld + m0 + tid];
 
-    // The sequence is consumed as P pieces of BK rows; piece i belongs to chunk step i / PPC.
+    // The sequence is consumed as P pieces of BK rows; piece i belongs to chunk step i / PPC.  Past the last piece it is
+    // requested again, and the loop runs whole groups of D pieces: the compiler's waits for the pieces on their way are
+    // exact only if every path has the same loads.
     const int PPC = a.L / BK, P = a.Nc * PPC;
-    auto piece_row = [&](int i) -> long {
-        const int stepc = i / PPC;
-        const int kc = a.reverse ? a.Nc - 1 - stepc : stepc;
-        return (long)kc * a.L + (long)(i % PPC) * BK;
-    };
-    using PX = TrPrefetch<DT, BK, BM, NT, false>;
-    using PY = TrPrefetch<DT, BK, BN, NT, false>;
+    using PX = RowsPrefetch<float, BK, BM, NT>;
+    using PY = RowsPrefetch<float, BK, BN, NT>;
     PX px[D];
     PY py[D];
-    float prs[D][PX::N][8];
+    float prs[D][PX::N];
+    auto request = [&](int slot, int i0) {
+        const int i = i0 < P ? i0 : P - 1;
+        const int stepc = i / PPC, kc = a.reverse ? a.Nc - 1 - stepc : stepc;
+        const long tr = (long)kc * a.L + (long)(i - stepc * PPC) * BK;
 #pragma unroll
-    for (int d = 0; d < D; ++d)
-        if (d < P) {
-            const long tr = piece_row(d);
-            px[d].template load<PAD>(X + tr * xld, xld, tid, tld - (int)tr, xcols);
-            py[d].template load<PAD>(Y + tr * yld, yld, tid, tld - (int)tr, ycols);
-            px[d].load_scales(prs[d], rs + tr, tid);
+        for (int j = 0; j < PX::N; ++j) prs[slot][j] = rs[tr + (tid + j * NT) / PX::CPR];
+        px[slot].template load<PAD>(X + tr * xld, xld, tid, tld - (int)tr, xcols);
+        py[slot].template load<PAD>(Y + tr * yld, yld, tid, tld - (int)tr, ycols);
+    };
+    auto stage = [&](int slot, int buf) {
+#pragma unroll
+        for (int j = 0; j < PX::N; ++j) {
+            f32x4 w = __builtin_bit_cast(f32x4, px[slot].r[j]);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) w[e] *= prs[slot][j];
+            px[slot].r[j] = __builtin_bit_cast(u32x4, w);
         }
-    px[0].store_scaled(ldsX[0], LS, prs[0], tid);
-    py[0].template store<false>(ldsY[0], LS, nullptr, tid);
-    if (D < P) {
-        const long tr = piece_row(D);
-        px[0].template load<PAD>(X + tr * xld, xld, tid, tld - (int)tr, xcols);
-        py[0].template load<PAD>(Y + tr * yld, yld, tid, tld - (int)tr, ycols);
-        px[0].load_scales(prs[0], rs + tr, tid);
-    }
+        px[slot].store(ldsX[buf], LX, tid);
+        py[slot].store(ldsY[buf], LY, tid);
+    };
+#pragma unroll
+    for (int d = 0; d < D; ++d) request(d, d);
+    stage(0, 0);
     __syncthreads();
 
     for (int i0 = 0; i0 < P; i0 += D) {
 #pragma unroll
         for (int dd = 0; dd < D; ++dd) {
             const int i = i0 + dd;
+            // ---- request piece i + D into the registers of piece i, stage piece i + 1 into the other LDS buffer
+            request(dd, i + D);
+            stage((dd + 1) % D, (i + 1) & 1);
+            const float* xb = ldsX[i & 1] + wm * 32 * MI + l32;
+            const float* yb = ldsY[i & 1] + wn * 32 * NI + l32;
             if (i < P) {
-                const int r = (dd + 1) % D;   // ring slot that holds piece i+1
-                // ---- stage piece i+1 into the other LDS buffer, refill its ring slot
-                if (i + 1 < P) {
-                    px[r].store_scaled(ldsX[(i + 1) & 1], LS, prs[r], tid);
-                    py[r].template store<false>(ldsY[(i + 1) & 1], LS, nullptr, tid);
-                    if (i + 1 + D < P) {
-                        const long tr = piece_row(i + 1 + D);
-                        px[r].template load<PAD>(X + tr * xld, xld, tid, tld - (int)tr, xcols);
-                        py[r].template load<PAD>(Y + tr * yld, yld, tid, tld - (int)tr, ycols);
-                        px[r].load_scales(prs[r], rs + tr, tid);
-                    }
-                }
                 // ---- chunk boundary: emit the state before this chunk's update, then decay
                 if (i % PPC == 0) {
                     const int stepc = i / PPC;
                     const int kc = a.reverse ? a.Nc - 1 - stepc : stepc;
                     const long slot = (long)bh * a.Nc + kc;
+                    const float gb = ldsG[kc];
 #pragma unroll
                     for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
@@ -118,7 +119,7 @@ __global__ void __launch_bounds__(256) recurrent_kernel(RecArgs a) {
                             const int n = n0 + wn * 32 * NI + 32 * ni + l32;
                             if (a.stT) {
                                 // registers 4j..4j+3 hold four consecutive m: one packed store each
-                                DT* dst = reinterpret_cast<DT*>(a.stT) + slot * a.d1 * a.d2;
+                                float* dst = reinterpret_cast<float*>(a.stT) + slot * a.d1 * a.d2;
 #pragma unroll
                                 for (int j = 0; j < 4; ++j) {
                                     const int m = m0 + wm * 32 * MI + 32 * mi + acc_row(4 * j, g);
@@ -126,47 +127,34 @@ __global__ void __launch_bounds__(256) recurrent_kernel(RecArgs a) {
                                            acc[mi][ni][4 * j + 2], acc[mi][ni][4 * j + 3]);
                                 }
                             }
-                        }
-                    if (with_n && tid < BM) a.nst[slot * a.d1 + m0 + tid] = nacc;
-                    const float gb = a.gbar[(long)bh * a.Nc + kc];
-#pragma unroll
-                    for (int mi = 0; mi < MI; ++mi)
-#pragma unroll
-                        for (int ni = 0; ni < NI; ++ni)
 #pragma unroll
                             for (int v = 0; v < 16; ++v) acc[mi][ni][v] *= gb;
+                        }
+                    if (with_n && tid < BM) a.nst[slot * a.d1 + m0 + tid] = nacc;
                     nacc *= gb;
                 }
                 // ---- multiply piece i
-                const DT* xb = ldsX[i & 1];
-                const DT* yb = ldsY[i & 1];
 #pragma unroll
-                for (int ks = 0; ks < BK / 16; ++ks) {
-                    typename E::frag af[MI], bf[NI];
+                for (int k = 0; k < BK; k += 2) {
+                    float af[MI], bf[NI];
 #pragma unroll
-                    for (int mi = 0; mi < MI; ++mi)
-                        af[mi] = E::load(xb + (wm * 32 * MI + 32 * mi + l32) * LS + 16 * ks + 8 * g);
+                    for (int mi = 0; mi < MI; ++mi) af[mi] = xb[(k + g) * LX + 32 * mi];
 #pragma unroll
-                    for (int ni = 0; ni < NI; ++ni)
-                        bf[ni] = E::load(yb + (wn * 32 * NI + 32 * ni + l32) * LS + 16 * ks + 8 * g);
+                    for (int ni = 0; ni < NI; ++ni) bf[ni] = yb[(k + g) * LY + 32 * ni];
 #pragma unroll
                     for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
-                        for (int ni = 0; ni < NI; ++ni) acc[mi][ni] = E::mma(af[mi], bf[ni], acc[mi][ni]);
+                        for (int ni = 0; ni < NI; ++ni) acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[mi], bf[ni], acc[mi][ni], 0, 0, 0);
                 }
                 if (with_n && tid < BM) {
                     // n += column sums of the staged (a-bar (.) K) piece, from the same rounded values
                     float sacc = 0.0f;
 #pragma unroll
-                    for (int c = 0; c < BK; c += 8) {
-                        const typename E::frag f = E::load(xb + tid * LS + c);
-#pragma unroll
-                        for (int e = 0; e < 8; ++e) sacc += E::frag_elem(f, e);
-                    }
+                    for (int c = 0; c < BK; ++c) sacc += ldsX[i & 1][c * LX + tid];
                     nacc += sacc;
                 }
-                __syncthreads();
             }
+            __syncthreads();
         }
     }
     // ---- final state
@@ -187,12 +175,11 @@ __global__ void __launch_bounds__(256) recurrent_kernel(RecArgs a) {
     if (with_n && tid < BM && a.nfinal && (!PAD || tid < xcols)) a.nfinal[(long)bh * xld + m0 + tid] = nacc;
 }
 
-template <typename DT, int MI, int NI>
-static hipError_t launch_rec_t(const RecArgs& a, int BH, hipStream_t s) {
-    constexpr int BK = sizeof(DT) == 2 ? 64 : 32;
+template <int MI, int NI>
+static hipError_t launch_rec_f32(const RecArgs& a, int BH, hipStream_t s) {
     dim3 grid(a.d2 / (64 * NI), a.d1 / (64 * MI), BH);
-    if (a.padded()) hipLaunchKernelGGL((recurrent_kernel<DT, MI, NI, BK, true>), grid, dim3(256), 0, s, a);
-    else hipLaunchKernelGGL((recurrent_kernel<DT, MI, NI, BK, false>), grid, dim3(256), 0, s, a);
+    if (a.padded()) hipLaunchKernelGGL((recurrent_kernel_f32<MI, NI, true>), grid, dim3(256), 0, s, a);
+    else hipLaunchKernelGGL((recurrent_kernel_f32<MI, NI, false>), grid, dim3(256), 0, s, a);
     return hipGetLastError();
 }
 
@@ -221,7 +208,7 @@ hipError_t launch_recurrent(const RecArgs& a, int BH, int dtype, hipStream_t s) 
     const bool big_ok = (a.d1 % 128 == 0) && (a.d2 % 128 == 0);
     const long wg_big = (long)BH * (a.d1 / 128) * (a.d2 / 128);
     const bool big = big_ok && wg_big >= 192;
-    return big ? launch_rec_t<float, 2, 2>(a, BH, s) : launch_rec_t<float, 1, 1>(a, BH, s);
+    return big ? launch_rec_f32<2, 2>(a, BH, s) : launch_rec_f32<1, 1>(a, BH, s);
 }
 
 }  // namespace tfla
