@@ -242,7 +242,8 @@ inline int tile_bd2(int d1, int d2, int dtype, int L, long rows) {
     const int ov = tile_width_override;
     if (dtype == 1 && (ov == 64 || ov == 128) && d2 % ov == 0) return ov;
     if (dtype == 1 && d1 >= 512 && d2 % 256 == 0 && L % 128 == 0 && (rows / 128) * (d2 / 256) >= 256) return 256;
-    if (d2 % 128 == 0) return 128;
+    // fp32: 64 columns while 128 would leave fewer than 512 workgroups of two wavefronts
+    if (d2 % 128 == 0 && (dtype == 1 || (rows / 64) * (d2 / 128) >= 512)) return 128;
     return 64;
 }
 // the fused layer output needs whole rows of h~ in one workgroup of the H kernel

@@ -40,11 +40,14 @@ __global__ void __launch_bounds__(NW * 64) tile_kernel(TileArgs a) {
     constexpr int KS1 = D1 / 16, NB = BD2 / 32, NK = D1 / BC;
     constexpr int YS = D1 + E::PAD, ZS = BC + E::PAD;
     constexpr int ld1 = SPLIT ? 2 * D1 : D1;    // row stride of the state's rows over the contraction index
-    // two stages of (Y tile, Z tile, column weights): one is multiplied while the other is filled
-    __shared__ __attribute__((aligned(16))) DT ldsY[2][BC * YS];
-    __shared__ __attribute__((aligned(16))) DT ldsZ[2][BD2 * ZS];
-    __shared__ float ldsW[2][BC];
-    __shared__ float ldsWl[2][BC];     // rounding remainders of the column exponents (zeros when there are none)
+    // Two stages of (Y tile, Z tile, column weights), one multiplied while the other is filled -- or, where two would
+    // leave a CU with one workgroup (wide Y tiles), a single one behind a second barrier: the next tile waits in
+    // registers meanwhile, and the other workgroups of the CU fill the gap.
+    constexpr int NSTG = 2 * (BC * YS + BD2 * ZS) * (int)sizeof(DT) <= 78 * 1024 ? 2 : 1;
+    __shared__ __attribute__((aligned(16))) DT ldsY[NSTG][BC * YS];
+    __shared__ __attribute__((aligned(16))) DT ldsZ[NSTG][BD2 * ZS];
+    __shared__ float ldsW[NSTG][BC];
+    __shared__ float ldsWl[NSTG][BC];  // rounding remainders of the column exponents (zeros when there are none)
     __shared__ float ldsR[NW * 32];
     __shared__ float ldsN[(MODE == MODE_H) ? D1 : 1];
 
@@ -117,6 +120,8 @@ __global__ void __launch_bounds__(NW * 64) tile_kernel(TileArgs a) {
     TrPrefetch<DT, BC, BD2, NT, true> pz;      // Z tile       [BC][BD2] -> [BD2][BC]
     float pw = 0.0f, pwl = 0.0f;
     int buf = 0;
+    auto other = [&]() { return NSTG == 2 ? buf ^ 1 : 0; };
+    auto left = [&]() { if constexpr (NSTG == 1) __syncthreads(); };     // everyone has left the only stage
 
     // ---------------- inter-chunk part: acc = X_r St, BC columns of d1 per stage
     load_state(0);
@@ -137,15 +142,16 @@ __global__ void __launch_bounds__(NW * 64) tile_kernel(TileArgs a) {
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb)
                 acc[nb] = E::mma(xf[j * (BC / 16) + ks], E::load(zb + (nb * 32 + l32) * ZS + 16 * ks + 8 * g), acc[nb]);
+        left();
         if (j + 1 < NK) {
-            store_state(ldsZ[buf ^ 1]);
+            store_state(ldsZ[other()]);
         } else {
-            py.store(ldsY[buf ^ 1], YS, tid);
-            pz.template store<false>(ldsZ[buf ^ 1], ZS, nullptr, tid);
-            if (tid < BC) { ldsW[buf ^ 1][tid] = pw; ldsWl[buf ^ 1][tid] = pwl; }
+            py.store(ldsY[other()], YS, tid);
+            pz.template store<false>(ldsZ[other()], ZS, nullptr, tid);
+            if (tid < BC) { ldsW[other()][tid] = pw; ldsWl[other()][tid] = pwl; }
         }
         __syncthreads();
-        buf ^= 1;
+        buf = other();
     }
     {
         float sr[16];
@@ -219,13 +225,14 @@ __global__ void __launch_bounds__(NW * 64) tile_kernel(TileArgs a) {
                 acc[nb] = E::mma(p1, E::load(zrow + 16), acc[nb]);
             }
         }
+        left();
         if (more) {
-            py.store(ldsY[buf ^ 1], YS, tid);
-            pz.template store<false>(ldsZ[buf ^ 1], ZS, nullptr, tid);
-            if (tid < BC) { ldsW[buf ^ 1][tid] = pw; ldsWl[buf ^ 1][tid] = pwl; }
+            py.store(ldsY[other()], YS, tid);
+            pz.template store<false>(ldsZ[other()], ZS, nullptr, tid);
+            if (tid < BC) { ldsW[other()][tid] = pw; ldsWl[other()][tid] = pwl; }
         }
         __syncthreads();
-        buf ^= 1;
+        buf = other();
     }
 
     // ---------------- epilogue
