@@ -97,14 +97,14 @@ __global__ void __launch_bounds__(512) recurrent_narrow_kernel_bf16(RecArgs a) {
         static_assert(AH * CPC <= 63, "the counter holds the pieces on their way");
         for (int p = 0; p < NS - 1 && p < P; ++p) request();
         auto await = [&](int younger) {     // pieces requested after the awaited one
-            if (younger >= AH) wait_vmcnt<(AH * CPC <= 63 ? AH * CPC : 63)>();
-            else wait_vmcnt_dyn(younger * CPC > 63 ? 63 : younger * CPC);
+            if (younger >= AH) wait_vmcnt<AH * CPC>();
+            else wait_vmcnt_dyn(younger * CPC);
         };
         await((P < NS - 1 ? P : NS - 1) - 1);
         int i = 0;
         for (; i < P; ++i) {
             barrier_nofence();
-            // piece i + 2 goes into the stage of piece i - 1, which every consumer has left; piece i + 1 must have landed
+            // piece i + NS - 1 goes into the stage of piece i - 1, which every consumer has left; piece i + 1 must have landed
             // before the next barrier
             if (i + NS - 1 < P) { request(); await(AH); }
             else await(P - 2 - i > 0 ? P - 2 - i : 0);

@@ -100,23 +100,6 @@ template <> struct Elem<float> {
     static __device__ __forceinline__ float frag_elem(const frag& f, int e) { return f.v[e]; }
 };
 
-// ---------------------------------------------------------------------------------------
-// Natural staging: copy a [ROWS][COLS] tile (row stride gstride elements in global memory)
-// into LDS with row stride lstride, 16 bytes per thread and step.
-// ---------------------------------------------------------------------------------------
-template <typename DT, int ROWS, int COLS, int NT>
-__device__ __forceinline__ void stage_rows(DT* lds, int lstride, const DT* g, long gstride, int tid) {
-    constexpr int EPC = 16 / (int)sizeof(DT);   // elements per 16-byte chunk
-    constexpr int CPR = COLS / EPC;             // chunks per row
-    constexpr int TOTAL = ROWS * CPR;
-#pragma unroll
-    for (int c = tid; c < TOTAL; c += NT) {
-        const int r = c / CPR, cc = c % CPR;
-        const u32x4 w = *reinterpret_cast<const u32x4*>(g + (long)r * gstride + cc * EPC);
-        *reinterpret_cast<u32x4*>(lds + r * lstride + cc * EPC) = w;
-    }
-}
-
 // Source row of slot (8*u + e) of a transposed tile.  With PERM the eight rows of a group
 // are those that registers 8c..8c+7 of a 32x32 MFMA result hold for lane group g, so that a
 // result tile can be fed back as an operand against this tile without leaving registers.
@@ -127,63 +110,8 @@ template <bool PERM> __device__ __forceinline__ int tr_src_row(int u, int e) {
 }
 
 // ---------------------------------------------------------------------------------------
-// Transposed staging: global tile [ROWS][COLS] (ROWS = contraction index, contiguous COLS)
-// -> LDS [COLS][ROWS (+pad)], i.e. contraction index contiguous per LDS row.  Optional
-// per-source-row scale (fp32 multiply, rounded back to the element type).
-// ---------------------------------------------------------------------------------------
-template <int ROWS, int COLS, int NT, bool PERM, bool SCALE>
-__device__ __forceinline__ void stage_transposed(bf16_t* lds, int lstride, const bf16_t* g, long gstride,
-                                                 const float* rowscale, int tid) {
-    constexpr int UNITS = (ROWS / 8) * (COLS / 2);
-#pragma unroll
-    for (int idx = tid; idx < UNITS; idx += NT) {
-        const int cp = idx % (COLS / 2), u = idx / (COLS / 2);
-        uint32_t w[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e)
-            w[e] = *reinterpret_cast<const uint32_t*>(g + (long)tr_src_row<PERM>(u, e) * gstride + 2 * cp);
-        if (SCALE) {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const float s = rowscale[tr_src_row<PERM>(u, e)];
-                const uint32_t lo = bf16_bits_rne(bf16_lo_to_f32(w[e]) * s);
-                const uint32_t hi = bf16_bits_rne(bf16_hi_to_f32(w[e]) * s);
-                w[e] = lo | (hi << 16);
-            }
-        }
-        u32x4 lo, hi;
-#pragma unroll
-        for (int d = 0; d < 4; ++d) {
-            lo[d] = (w[2 * d] & 0xffffu) | (w[2 * d + 1] << 16);
-            hi[d] = (w[2 * d] >> 16) | (w[2 * d + 1] & 0xffff0000u);
-        }
-        *reinterpret_cast<u32x4*>(lds + (2 * cp) * lstride + 8 * u) = lo;
-        *reinterpret_cast<u32x4*>(lds + (2 * cp + 1) * lstride + 8 * u) = hi;
-    }
-}
-
-template <int ROWS, int COLS, int NT, bool PERM, bool SCALE>
-__device__ __forceinline__ void stage_transposed(float* lds, int lstride, const float* g, long gstride,
-                                                 const float* rowscale, int tid) {
-    constexpr int UNITS = (ROWS / 8) * COLS;
-#pragma unroll
-    for (int idx = tid; idx < UNITS; idx += NT) {
-        const int col = idx % COLS, u = idx / COLS;
-        float w[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            w[e] = g[(long)tr_src_row<PERM>(u, e) * gstride + col];
-            if (SCALE) w[e] *= rowscale[tr_src_row<PERM>(u, e)];
-        }
-        f32x4 a = {w[0], w[1], w[2], w[3]}, b = {w[4], w[5], w[6], w[7]};
-        *reinterpret_cast<f32x4*>(lds + col * lstride + 8 * u) = a;
-        *reinterpret_cast<f32x4*>(lds + col * lstride + 8 * u + 4) = b;
-    }
-}
-
-// ---------------------------------------------------------------------------------------
-// Split (prefetching) forms of the two stagers: load() issues the global loads into
-// registers, store() writes them to LDS later, so the loads of the next tile are in flight
+// Staging of the fp32 kernels' tiles, in their own row-major layout or transposed (contraction index contiguous per
+// LDS row): load() issues the global loads into registers, store() writes them to LDS later, so the loads of the next tile are in flight
 // while the current tile is being multiplied.
 // ---------------------------------------------------------------------------------------
 template <typename DT, int ROWS, int COLS, int NT> struct RowsPrefetch {
@@ -214,85 +142,6 @@ template <typename DT, int ROWS, int COLS, int NT> struct RowsPrefetch {
 
 template <typename DT, int ROWS, int COLS, int NT, bool PERM> struct TrPrefetch;
 
-template <int ROWS, int COLS, int NT, bool PERM> struct TrPrefetch<bf16_t, ROWS, COLS, NT, PERM> {
-    static constexpr int UNITS = (ROWS / 8) * (COLS / 2), N = (UNITS + NT - 1) / NT;
-    uint32_t w[N][8];
-    __device__ __forceinline__ void load(const bf16_t* g, long gstride, int tid) {
-#pragma unroll
-        for (int i = 0; i < N; ++i) {
-            const int idx = tid + i * NT;
-            if (UNITS % NT == 0 || idx < UNITS) {
-                const int cp = idx % (COLS / 2), u = idx / (COLS / 2);
-#pragma unroll
-                for (int e = 0; e < 8; ++e)
-                    w[i][e] = *reinterpret_cast<const uint32_t*>(g + (long)tr_src_row<PERM>(u, e) * gstride + 2 * cp);
-            }
-        }
-    }
-    // per-unit row scales held in registers (rs[i][e] = scale of source row 8u+e; PERM = false)
-    __device__ __forceinline__ void load_scales(float (&rs)[N][8], const float* g, int tid) const {
-#pragma unroll
-        for (int i = 0; i < N; ++i) {
-            const int idx = tid + i * NT;
-            if (UNITS % NT == 0 || idx < UNITS) {
-                const int u = idx / (COLS / 2);
-                const f32x4 a = *reinterpret_cast<const f32x4*>(g + 8 * u), b = *reinterpret_cast<const f32x4*>(g + 8 * u + 4);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) { rs[i][e] = a[e]; rs[i][4 + e] = b[e]; }
-            }
-        }
-    }
-    __device__ __forceinline__ void store_scaled(bf16_t* lds, int lstride, const float (&rs)[N][8], int tid) const {
-#pragma unroll
-        for (int i = 0; i < N; ++i) {
-            const int idx = tid + i * NT;
-            if (UNITS % NT == 0 || idx < UNITS) {
-                const int cp = idx % (COLS / 2), u = idx / (COLS / 2);
-                uint32_t x[8];
-#pragma unroll
-                for (int e = 0; e < 8; ++e)
-                    x[e] = bf16_bits_rne(bf16_lo_to_f32(w[i][e]) * rs[i][e]) | (bf16_bits_rne(bf16_hi_to_f32(w[i][e]) * rs[i][e]) << 16);
-                u32x4 lo, hi;
-#pragma unroll
-                for (int d = 0; d < 4; ++d) {
-                    lo[d] = (x[2 * d] & 0xffffu) | (x[2 * d + 1] << 16);
-                    hi[d] = (x[2 * d] >> 16) | (x[2 * d + 1] & 0xffff0000u);
-                }
-                *reinterpret_cast<u32x4*>(lds + (2 * cp) * lstride + 8 * u) = lo;
-                *reinterpret_cast<u32x4*>(lds + (2 * cp + 1) * lstride + 8 * u) = hi;
-            }
-        }
-    }
-    // rowscale (LDS or global, indexed by source row) may be null
-    template <bool SCALE>
-    __device__ __forceinline__ void store(bf16_t* lds, int lstride, const float* rowscale, int tid) const {
-#pragma unroll
-        for (int i = 0; i < N; ++i) {
-            const int idx = tid + i * NT;
-            if (UNITS % NT == 0 || idx < UNITS) {
-                const int cp = idx % (COLS / 2), u = idx / (COLS / 2);
-                uint32_t x[8];
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    x[e] = w[i][e];
-                    if (SCALE) {
-                        const float s = rowscale[tr_src_row<PERM>(u, e)];
-                        x[e] = bf16_bits_rne(bf16_lo_to_f32(x[e]) * s) | (bf16_bits_rne(bf16_hi_to_f32(x[e]) * s) << 16);
-                    }
-                }
-                u32x4 lo, hi;
-#pragma unroll
-                for (int d = 0; d < 4; ++d) {
-                    lo[d] = (x[2 * d] & 0xffffu) | (x[2 * d + 1] << 16);
-                    hi[d] = (x[2 * d] >> 16) | (x[2 * d + 1] & 0xffff0000u);
-                }
-                *reinterpret_cast<u32x4*>(lds + (2 * cp) * lstride + 8 * u) = lo;
-                *reinterpret_cast<u32x4*>(lds + (2 * cp + 1) * lstride + 8 * u) = hi;
-            }
-        }
-    }
-};
-
 template <int ROWS, int COLS, int NT, bool PERM> struct TrPrefetch<float, ROWS, COLS, NT, PERM> {
     static constexpr int UNITS = (ROWS / 8) * COLS, N = (UNITS + NT - 1) / NT;
     float w[N][8];
@@ -311,42 +160,13 @@ template <int ROWS, int COLS, int NT, bool PERM> struct TrPrefetch<float, ROWS, 
             }
         }
     }
-    __device__ __forceinline__ void load_scales(float (&rs)[N][8], const float* g, int tid) const {
-#pragma unroll
-        for (int i = 0; i < N; ++i) {
-            const int idx = tid + i * NT;
-            if (UNITS % NT == 0 || idx < UNITS) {
-                const int u = idx / COLS;
-                const f32x4 a = *reinterpret_cast<const f32x4*>(g + 8 * u), b = *reinterpret_cast<const f32x4*>(g + 8 * u + 4);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) { rs[i][e] = a[e]; rs[i][4 + e] = b[e]; }
-            }
-        }
-    }
-    __device__ __forceinline__ void store_scaled(float* lds, int lstride, const float (&rs)[N][8], int tid) const {
+    __device__ __forceinline__ void store(float* lds, int lstride, int tid) const {
 #pragma unroll
         for (int i = 0; i < N; ++i) {
             const int idx = tid + i * NT;
             if (UNITS % NT == 0 || idx < UNITS) {
                 const int col = idx % COLS, u = idx / COLS;
-                f32x4 a = {w[i][0] * rs[i][0], w[i][1] * rs[i][1], w[i][2] * rs[i][2], w[i][3] * rs[i][3]};
-                f32x4 b = {w[i][4] * rs[i][4], w[i][5] * rs[i][5], w[i][6] * rs[i][6], w[i][7] * rs[i][7]};
-                *reinterpret_cast<f32x4*>(lds + col * lstride + 8 * u) = a;
-                *reinterpret_cast<f32x4*>(lds + col * lstride + 8 * u + 4) = b;
-            }
-        }
-    }
-    template <bool SCALE>
-    __device__ __forceinline__ void store(float* lds, int lstride, const float* rowscale, int tid) const {
-#pragma unroll
-        for (int i = 0; i < N; ++i) {
-            const int idx = tid + i * NT;
-            if (UNITS % NT == 0 || idx < UNITS) {
-                const int col = idx % COLS, u = idx / COLS;
-                float x[8];
-#pragma unroll
-                for (int e = 0; e < 8; ++e) x[e] = SCALE ? w[i][e] * rowscale[tr_src_row<PERM>(u, e)] : w[i][e];
-                f32x4 a = {x[0], x[1], x[2], x[3]}, b = {x[4], x[5], x[6], x[7]};
+                f32x4 a = {w[i][0], w[i][1], w[i][2], w[i][3]}, b = {w[i][4], w[i][5], w[i][6], w[i][7]};
                 *reinterpret_cast<f32x4*>(lds + col * lstride + 8 * u) = a;
                 *reinterpret_cast<f32x4*>(lds + col * lstride + 8 * u + 4) = b;
             }
@@ -354,13 +174,7 @@ template <int ROWS, int COLS, int NT, bool PERM> struct TrPrefetch<float, ROWS, 
     }
 };
 
-// four consecutive elements as one store (8 bytes of bf16, 16 bytes of fp32)
-__device__ __forceinline__ void store4(bf16_t* p, float a, float b, float c, float d) {
-    uint2 w;
-    w.x = bf16_bits_rne(a) | (bf16_bits_rne(b) << 16);
-    w.y = bf16_bits_rne(c) | (bf16_bits_rne(d) << 16);
-    *reinterpret_cast<uint2*>(p) = w;
-}
+// four consecutive values as one store
 __device__ __forceinline__ void store4(float* p, float a, float b, float c, float d) {
     f32x4 w = {a, b, c, d};
     *reinterpret_cast<f32x4*>(p) = w;

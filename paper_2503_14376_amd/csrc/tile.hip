@@ -113,7 +113,7 @@ __global__ void __launch_bounds__(NW * 64) tile_kernel(TileArgs a) {
         else ps.load(St + j * BC, ld1, tid);
     };
     auto store_state = [&](DT* dst) {
-        if constexpr (STT) ps.template store<false>(dst, ZS, nullptr, tid);
+        if constexpr (STT) ps.store(dst, ZS, tid);
         else ps.store(dst, ZS, tid);
     };
     RowsPrefetch<DT, BC, D1, NT> py;           // Y tile       [BC][D1]
@@ -147,7 +147,7 @@ __global__ void __launch_bounds__(NW * 64) tile_kernel(TileArgs a) {
             store_state(ldsZ[other()]);
         } else {
             py.store(ldsY[other()], YS, tid);
-            pz.template store<false>(ldsZ[other()], ZS, nullptr, tid);
+            pz.store(ldsZ[other()], ZS, tid);
             if (tid < BC) { ldsW[other()][tid] = pw; ldsWl[other()][tid] = pwl; }
         }
         __syncthreads();
@@ -228,7 +228,7 @@ __global__ void __launch_bounds__(NW * 64) tile_kernel(TileArgs a) {
         left();
         if (more) {
             py.store(ldsY[other()], YS, tid);
-            pz.template store<false>(ldsZ[other()], ZS, nullptr, tid);
+            pz.store(ldsZ[other()], ZS, tid);
             if (tid < BC) { ldsW[other()][tid] = pw; ldsWl[other()][tid] = pwl; }
         }
         __syncthreads();
