@@ -57,11 +57,9 @@ __device__ __forceinline__ void load8f(const float* p, float (&x)[8]) {
     x[0] = a.x; x[1] = a.y; x[2] = a.z; x[3] = a.w; x[4] = b.x; x[5] = b.y; x[6] = b.z; x[7] = b.w;
 }
 
-// sigma(x) as accurate as the rows' element type asks for.  bf16 rows: the hardware's exp2 and reciprocal (about 1e-7
-// relative, 5e-6 at x = -80, against the 4e-3 of a bf16 value); with the library's exponential and an IEEE division the
-// row kernels are bound by their vector instructions and not by memory.
+// sigma(x) to the accuracy of an exponential and an IEEE division, for rows of either type
 template <typename DT> __device__ __forceinline__ float sigmoid_row(float x);
-template <> __device__ __forceinline__ float sigmoid_row<bf16_t>(float x) { return fast_sigmoid(x); }
+template <> __device__ __forceinline__ float sigmoid_row<bf16_t>(float x) { return sigmoid_bf16(x); }
 template <> __device__ __forceinline__ float sigmoid_row<float>(float x) {
     const float e = expf(-fabsf(x));
     return (x >= 0.0f ? 1.0f : e) / (1.0f + e);

@@ -26,9 +26,21 @@ __device__ __forceinline__ int acc_row(int v, int grp) { return 8 * (v >> 2) + 4
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 __device__ __forceinline__ float fast_log2(float x) { return __builtin_amdgcn_logf(x); }
 
-// sigma(x) from the hardware's exp2 and reciprocal (relative error about 1e-7, 5e-6 at x = -80; 0 / 1 / NaN at -inf / +inf / NaN)
-__device__ __forceinline__ float fast_sigmoid(float x) {
-    return __builtin_amdgcn_rcpf(1.0f + fast_exp2(-1.4426950408889634f * x));
+// sigma(x) of a bf16 value, as close as the library's exponential and an IEEE division come (over all 65536 values at most
+// 1.59 ulp of fp32 and 0.064 on average, both ways) in two thirds of their instructions.
+// e = exp(-|x|) = 2^n 2^f with f in [-1/2, 1/2] from a two-term product with log2 e; below -128, where e is zero, the
+// argument stays finite.  The denominator lies in [1, 2], so the division needs none of the scaling and special cases of the
+// general one: the quotient by the hardware's reciprocal, and its remainder once more.
+// (The hardware's exp2 of -x log2 e and its reciprocal alone are three instructions, but their relative error grows with
+// |x|, to 5e-6 at x = -80, and nothing is left below -88.)
+__device__ __forceinline__ float sigmoid_bf16(float x) {
+    float a = -fabsf(x);
+    a = a < -128.0f ? -128.0f : a;
+    const float n = rintf(a * 1.44269502e+00f);
+    const float f = __builtin_fmaf(a, 1.92596299e-08f, __builtin_fmaf(a, 1.44269502e+00f, -n));
+    const float e = __builtin_amdgcn_ldexpf(fast_exp2(f), (int)n);
+    const float d = 1.0f + e, m = x >= 0.0f ? 1.0f : e, r = __builtin_amdgcn_rcpf(d), q = m * r;
+    return __builtin_fmaf(__builtin_fmaf(-d, q, m), r, q);
 }
 
 __device__ __forceinline__ uint32_t bf16_bits_rne(float x) {

@@ -721,9 +721,8 @@ __global__ void __launch_bounds__(NW * 64, OCC) tile_kernel_bf16(TileArgs a) {
                 const u32x4 ow = *reinterpret_cast<const u32x4*>(wtile + toff);
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    const float o0 = bf16_lo_to_f32(ow[e]), o1 = bf16_hi_to_f32(ow[e]);
-                    y[2 * e] *= fast_sigmoid(o0);
-                    y[2 * e + 1] *= fast_sigmoid(o1);
+                    y[2 * e] *= sigmoid_bf16(bf16_lo_to_f32(ow[e]));
+                    y[2 * e + 1] *= sigmoid_bf16(bf16_hi_to_f32(ow[e]));
                 }
             }
             u32x4 yw;

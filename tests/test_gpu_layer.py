@@ -231,3 +231,33 @@ def test_layer_steps_continue_a_layer_forward(variant, dtype):
     ref = lo.layer_fwd(d["q"], d["k"], d["v"], d["i_pre"], d["f_pre"], d["o_pre"], d["gamma"], d["beta"], variant=variant,
                        eps=1e-6, gate_softcap=15.0, kind=lo.LAYER, norm_eps=1e-6)
     assert gu.rel_err(y, ref["y"]) <= gu.TOL[dtype]
+
+
+# fused into the H kernel; separate NORM kernel with several rows of a wavefront side by side (ragged length); one and two
+# groups of 512 columns per wavefront
+@pytest.mark.parametrize("T,dhv,chunk", [(1024, 64, 64), (1024, 64, 192), (128, 512, 64), (64, 1024, 64)])
+def test_output_gate_of_every_bf16_value(T, dhv, chunk):
+    """sigma(o~) for all 65536 bf16 values: scale zero and shift one make y the gate alone.  The exponential (1 ulp), the sum
+    1 + e and the division (half an ulp each) leave a relative error of 2^-22, that is 2^-14 of a bf16 spacing, doubled here;
+    then one rounding to bf16, subnormal results included."""
+    import paper_2503_14376_amd as tfla
+    assert T * dhv == 1 << 16
+    g = torch.Generator(device="cuda").manual_seed(71)
+    mk = lambda *s: torch.randn(s, device="cuda", generator=g)
+    q, k, v = mk(1, 1, T, 64).bfloat16(), mk(1, 1, T, 64).bfloat16(), mk(1, 1, T, dhv).bfloat16()
+    o = torch.arange(1 << 16, device="cuda", dtype=torch.int32).to(torch.int16).view(torch.bfloat16).reshape(1, 1, T, dhv)
+    gamma, beta = torch.zeros(1, dhv, device="cuda"), torch.ones(1, dhv, device="cuda")
+    kw = dict(chunk=chunk, norm_kind=lo.LAYER)
+    f = tfla.mlstm_layer_fwd(q, k, v, mk(1, 1, T), mk(1, 1, T) + 3, o, gamma, beta, **kw)
+    torch.cuda.synchronize()
+    x = o.cpu().double().flatten()
+    y = f["Y"].cpu().double().flatten()
+    nan = torch.isnan(x)
+    assert torch.equal(torch.isnan(y), nan)
+    x, y = x[~nan], y[~nan]
+    e = torch.exp(-x.abs())
+    ref = torch.where(x >= 0, torch.ones_like(e), e) / (1 + e)
+    spacing = torch.exp2(torch.floor(torch.log2(ref.clamp_min(2.0 ** -126))) - 7)
+    err = (y - ref).abs() / spacing
+    print("gate", (T, dhv, chunk), "worst error in bf16 spacings", float(err.max()), "at", float(x[err.argmax()]), flush=True)
+    assert float(err.max()) <= 0.5 + 2.0 ** -13
