@@ -253,7 +253,7 @@ __global__ void __launch_bounds__(GATE_WAVES * 64) gates_step_kernel(GateArgs a)
 constexpr int GATE_FUSED_CHUNKS = 16;
 template <int E, typename AT>
 __global__ void __launch_bounds__(GATE_FUSED_CHUNKS * 64) gates_fused_kernel(GateArgs a) {
-    __shared__ AT cg[GATE_FUSED_CHUNKS], camax[GATE_FUSED_CHUNKS];
+    __shared__ AT cg[GATE_FUSED_CHUNKS], camax[GATE_FUSED_CHUNKS], m_init;
     const int bh = blockIdx.x, lane = threadIdx.x & 63, kc = threadIdx.x >> 6;
     const bool is_exp = a.variant == 0;
     const int t0 = kc * (64 * E) + lane * E;                       // first of this lane's steps
@@ -298,8 +298,11 @@ __global__ void __launch_bounds__(GATE_FUSED_CHUNKS * 64) gates_fused_kernel(Gat
     amax = wave_max_t<AT>(amax);
     const AT gsum = wave_sum_t<AT>(fsum);
     if (lane == 0) { cg[kc] = gsum; camax[kc] = amax; }
+    // (read once, before the barrier: the caller's final state may be the buffer of its initial state, and the last chunk's
+    // wavefront writes it without waiting for the others)
+    if (threadIdx.x == 0) m_init = (is_exp && a.m0) ? (AT)a.m0[bh] : (AT)0;
     __syncthreads();
-    AT mprev = (is_exp && a.m0) ? (AT)a.m0[bh] : (AT)0;
+    AT mprev = m_init;
     if (is_exp)
         for (int k = 0; k < kc; ++k) mprev = max_t<AT>(cg[k] + mprev, camax[k]);
     const AT mk = is_exp ? max_t<AT>(gsum + mprev, amax) : (AT)0;

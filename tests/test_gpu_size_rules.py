@@ -155,3 +155,23 @@ def test_recurrent_tiles(variant, B, NH, T, dqk, dhv, chunk):
 def test_gate_launches(dtype, variant, T, chunk):
     w = wl.small(variant, dtype, B=1, NH=3, T=T, dqk=64, dhv=64, chunk=chunk, seed=1100 + T)
     _check_slices(w)
+
+
+# a state that is continued in place (the final state's buffers are the initial state's): up to 16 chunks the gate pre-pass
+# is one workgroup per (batch, head), whose wavefronts all need the initial max state that one of them replaces
+@pytest.mark.parametrize("dtype", [wl.BF16, wl.F32])
+@pytest.mark.parametrize("T,chunk", [(64, 64), (128, 64), (250, 64), (512, 128), (1024, 64)])
+def test_state_continued_in_place(dtype, T, chunk):
+    import paper_2503_14376_amd as tfla
+    from tests import gpu_util as gu
+    w = wl.small(wl.EXP, dtype, B=2, NH=3, T=T, dqk=64, dhv=64, chunk=chunk, seed=1200 + T)
+    dev = gu.dev_inputs(w, wl.make_inputs(w))
+    args = [dev[x] for x in ("q", "k", "v", "i_pre", "f_pre")]
+    st = [dev[x] for x in ("C0", "n0", "m0")]
+    st[2] = st[2] + 40.0                        # an initial max state that decides the stabilisation of every chunk
+    two = tfla.mlstm_fwd(*args, *st, chunk=chunk, eps=1e-6)
+    cur = [t.clone() for t in st]
+    one = tfla.mlstm_fwd(*args, *cur, chunk=chunk, eps=1e-6, out=dict(zip(("Cn", "nn", "mn"), cur)))
+    torch.cuda.synchronize()
+    for key in ("H", "Cn", "nn", "mn", "n_out", "m_out"):
+        assert torch.equal(one[key], two[key]), key
