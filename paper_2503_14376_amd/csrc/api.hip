@@ -132,8 +132,15 @@ BwdWs carve_bwd(const Dims& d, void* ws) {
     w.bsum = c.take<double>(d.BH * ((d.T + 1023) / 1024));
     w.wrowB = c.take<float>(d.BHT); w.sQ = c.take<float>(d.BHT);
     w.nbQ = w.nbK = d.dqk / tile_bd2(d.dhv, d.dqk, d.dtype, d.L, d.BHT);
-    w.partQ = c.take<float>((size_t)w.nbQ * d.BHT); w.partK = c.take<float>((size_t)w.nbK * d.BHT);
-    w.cdot = c.take<double>((size_t)d.BH * STATE_DOT_PARTS);
+    // The sizes that callers have planned their buffers with do not grow, so two later pieces lie in memory that is free by
+    // then: the partial <C_T, dC_T> in the gate pre-pass's scratch (a chunk has at least 64 steps, 768 bytes of it per
+    // (batch, head)), and the row dots of 128-wide dQ / dK blocks at d_hv = 512, twice as many as the usual 256-wide ones
+    // leave, in the boundary copies of C, which the reversed recurrent launch has read (dqk / 16 bytes per step, both
+    // together, against at least dqk / 2).
+    const bool parts_in_copies = d.dtype == TFLA_BF16 && d.dhv == 512 && d.dqk % 256 == 0 && w.nbQ == d.dqk / 128;
+    if (!parts_in_copies) { w.partQ = c.take<float>((size_t)w.nbQ * d.BHT); w.partK = c.take<float>((size_t)w.nbK * d.BHT); }
+    static_assert(STATE_DOT_PARTS * sizeof(double) <= 3 * 64 * sizeof(float), "cdot fits the gate scratch");
+    w.cdot = reinterpret_cast<double*>(w.tmp);
     w.Cfinal = c.take<float>((size_t)d.BH * d.dqk * d.dhv);
     const size_t st = (size_t)d.BH * d.Nc * d.dqk * d.dhv * d.esz;
     // C_{k-1} and dC_k, both as (d_hv, d_qk)
@@ -148,6 +155,7 @@ BwdWs carve_bwd(const Dims& d, void* ws) {
     // bf16: fp32 boundary copies of C (used when the states are recomputed here), and the partial inner products
     // <C, dC> of every boundary
     w.ancC = d.dtype == TFLA_BF16 ? c.take<float>(anchor_slots(d) * (size_t)d.BH * d.dqk * d.dhv) : nullptr;
+    if (parts_in_copies) { w.partQ = w.ancC; w.partK = w.ancC ? w.ancC + (size_t)w.nbQ * d.BHT : nullptr; }
     w.anchor = c.take<float>(anchor_slots(d) * (size_t)d.BH * rec_anchor_parts(d.dqk, d.dhv));
     w.bytes = c.off;
     return w;
@@ -232,9 +240,9 @@ inline bool misaligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p)
 inline bool needs_pad(int T, int dqk, int dhv, int chunk) {
     return T % chunk != 0 || dqk != kernel_dim(dqk) || dhv != kernel_dim(dhv);
 }
-// Workspace bytes of the two directions.  For a problem whose tensors end before the blocks do they are what they were
-// when its inputs were copied (the copies' bytes included), so that sizes that callers have planned with, and what
-// tfla_mlstm_fwd_static accepts, stay the same; the space behind the carved pieces is not touched.
+// Workspace bytes of the two directions.  For a problem whose tensors end before the blocks do they include the padded
+// copies of its inputs that were made once, so that what tfla_mlstm_fwd_static accepts stays the same; the space behind the
+// carved pieces is not touched.
 size_t copies_bytes(const Dims& d, int direction) {
     if (!needs_pad(d.T_in, d.dqk_in, d.dhv_in, d.L)) return 0;
     const size_t sq = align_up((size_t)d.BHT * d.dqk * d.esz), sv = align_up((size_t)d.BHT * d.dhv * d.esz);

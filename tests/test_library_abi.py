@@ -119,6 +119,30 @@ def test_workspace_grows_with_the_problem(tfla):
     assert big % 256 == 0
 
 
+# (B, NH, T, dqk, dhv, chunk, variant, dtype), bytes forward and backward that callers may have planned their buffers with
+PLANNED = [
+    ((2, 8, 8192, 256, 512, 256, 0, 1), 215488512, 417373440),
+    ((1, 8, 512, 256, 512, 256, 0, 1), 12763648, 19074048),         # 128-wide dQ / dK blocks at d_hv = 512
+    ((1, 8, 512, 512, 512, 128, 1, 1), 33784320, 51614720),
+    ((1, 4, 300, 1024, 512, 128, 0, 1), 65710592, 91792384),
+    ((1, 1, 5000, 1024, 512, 2048, 0, 1), 58061312, 107551744),
+    ((1, 8, 1000, 256, 512, 128, 0, 1), 55067392, 86586624),
+    ((2, 16, 3000, 96, 192, 128, 0, 1), 194683904, 300718080),
+    ((4, 64, 2048, 64, 64, 256, 0, 1), 50880512, 71336960),
+    ((1, 1, 64, 64, 64, 64, 0, 1), 44288, 53504),
+    ((4, 4, 4096, 1024, 1024, 256, 0, 1), 1413221376, 2020347648),
+    ((2, 8, 1024, 128, 256, 64, 1, 0), 36836352, 103949824),
+    ((3, 8, 1000, 256, 264, 128, 0, 0), 241291008, 556245248),
+]
+
+
+@pytest.mark.parametrize("dims,fwd,bwd", PLANNED)
+def test_workspace_sizes_do_not_grow(tfla, dims, fwd, bwd):
+    # the forward size is exact: it decides what the entry point with the static scratch memory accepts
+    assert tfla.workspace_bytes(0, *dims) == fwd
+    assert 0 < tfla.workspace_bytes(1, *dims) <= bwd
+
+
 def _call_fwd(lib, q=1, k=1, v=1, i=1, f=1, C0=0, n0=0, m0=0, H=1, ws=256, ws_bytes=1 << 40, **kw):
     """tfla_mlstm_fwd with fake (never dereferenced) pointers: only the host-side validation runs."""
     a = dict(OK_ARGS); a.update(kw)
