@@ -270,7 +270,8 @@ __global__ void __launch_bounds__(NW * 64) tile_kernel(TileArgs a) {
     if (MODE == MODE_H) {
         if (a.variant == 0) {
             const long t = tbase + wr0 + l32;
-            const float den = fmaxf(fabsf(nrm), expf(-a.mout[t])) + a.eps;
+            float den = fmaxf(fabsf(nrm), expf(-a.mout[t])) + a.eps;
+            if (PAD && wr0 + l32 >= steps_left) den = 1.0f;     // (no q there: with eps = 0 and a large max state it would be 0)
             if (g == 0) {
                 ldsR[wave * 32 + l32] = 1.0f / den;
                 if (a.nout && nb2 == 0 && (!PAD || wr0 + l32 < steps_left)) a.nout[tin + wr0 + l32] = nrm;

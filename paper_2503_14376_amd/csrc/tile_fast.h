@@ -602,12 +602,13 @@ __global__ void __launch_bounds__(NW * 64, OCC) tile_kernel_bf16(TileArgs a) {
     float inv = 1.0f;
     if (MODE == MODE_H) {
         if (a.variant == 0) {
-            const float den = fmaxf(fabsf(nrm), expf(-ldsM[wave][l32])) + a.eps;
-            inv = 1.0f / den;
+            float den = fmaxf(fabsf(nrm), expf(-ldsM[wave][l32])) + a.eps;
             if constexpr (PAD) {
                 const int ts = wr0 + l32;
+                if (ts >= steps_left) den = 1.0f;       // (no q there: with eps = 0 and a large max state it would be 0)
                 if (g == 0 && a.nout && nb2 == 0 && ts < steps_left) a.nout[tin + ts] = nrm;
             } else if (g == 0 && a.nout && nb2 == 0) a.nout[t] = nrm;
+            inv = 1.0f / den;
             if (g == 0 && a.wrowB_out && nb2 == 0) {
                 a.wrowB_out[t] = wr - log2f(den);
                 a.sQ_out[t] = srl / den;

@@ -175,3 +175,26 @@ def test_state_continued_in_place(dtype, T, chunk):
     torch.cuda.synchronize()
     for key in ("H", "Cn", "nn", "mn", "n_out", "m_out"):
         assert torch.equal(one[key], two[key]), key
+
+
+# steps past the end of a ragged sequence have no q: with eps = 0 and a max state above 104, where exp(-m) is zero in fp32,
+# their denominator is no number, and what the H kernel leaves for them must not reach the gradients.  The backward pass from
+# the forward call's workspace against the one that recomputes everything (same operands; the suite's bar)
+@pytest.mark.parametrize("dtype,dqk,dhv,chunk", [(wl.BF16, 64, 64, 64), (wl.BF16, 256, 512, 128), (wl.BF16, 1024, 64, 128), (wl.F32, 64, 64, 64), (wl.F32, 512, 64, 128)])
+def test_ragged_length_without_epsilon(dtype, dqk, dhv, chunk):
+    import paper_2503_14376_amd as tfla
+    from tests import gpu_util as gu
+    w = wl.small(wl.EXP, dtype, B=1, NH=2, T=chunk + 37, dqk=dqk, dhv=dhv, chunk=chunk, seed=1300 + dqk, init_state=False)
+    dev = gu.dev_inputs(w, wl.make_inputs(w))
+    # q, k of positive mean: the normalisers of the true steps stay away from zero
+    q, k = (0.25 * dev[x] + 1.0 for x in ("q", "k"))
+    ip = dev["i_pre"] + 115.0
+    f = tfla.mlstm_fwd(q, k, dev["v"], ip, dev["f_pre"], chunk=chunk, eps=0.0)
+    assert float(f["m_out"].min()) > 104.0
+    args = (q, k, dev["v"], ip, dev["f_pre"], dev["dH"], f["n_out"], f["m_out"])
+    kept = tfla.mlstm_bwd(*args, chunk=chunk, eps=0.0, fwd_workspace=f["workspace"])
+    again = tfla.mlstm_bwd(*args, chunk=chunk, eps=0.0)
+    torch.cuda.synchronize()
+    for key in ("dq", "dk", "dv", "d_i_pre", "d_f_pre", "dC0"):
+        e = gu.rel_err(kept[key], again[key].double().cpu().numpy())
+        assert e <= gu.TOL[dtype], (key, e)
