@@ -123,7 +123,7 @@ __global__ void __launch_bounds__(WN * 128) recurrent_kernel_bf16(RecArgs a) {
         int lsub = 0, lslot = 0;
         uint32_t lst = smem_a;
         auto request = [&]() {
-            if constexpr (PAD) dx.template issue_bounded<false, true>(xreq, bounded_bytes(xleft, xcols, 2 * xld), xcols, lst, ptid);
+            if constexpr (PAD) dx.template issue_bounded<true>(xreq, bounded_bytes(xleft, xcols, 2 * xld), xcols, lst, ptid);
             else dx.issue(xreq, lst, ptid);
             // every producer fetches the same 64 row scales and gbar to the same place: identical
             // data, and each wavefront's own counter then covers what it reads
@@ -268,7 +268,7 @@ __global__ void __launch_bounds__(WN * 128) recurrent_kernel_bf16(RecArgs a) {
         int lsub = 0, lslot = 0;
         uint32_t lst = smem_a + XB;
         auto request_part = [&](int q) {
-            if constexpr (PAD) dy.template issue_bounded<false, true>(yreq, bounded_bytes(yleft, ycols, 2 * yld), ycols, lst, tid, q, CPC);
+            if constexpr (PAD) dy.template issue_bounded<true>(yreq, bounded_bytes(yleft, ycols, 2 * yld), ycols, lst, tid, q, CPC);
             else dma16(yreq, dy.goff[q], lst + (wc + q * WN) * 1024);
         };
         auto request_end = [&]() {

@@ -85,7 +85,7 @@ __global__ void __launch_bounds__(512) recurrent_narrow_kernel_bf16(RecArgs a) {
         const uint32_t ya = lds_addr(smemY);
         uint32_t lst = ya;
         auto request = [&]() {
-            if constexpr (PAD) dy.template issue_bounded<false, true>(yreq, bounded_bytes(yleft, ycols, 2 * yld), ycols, lst, rtid);
+            if constexpr (PAD) dy.template issue_bounded<true>(yreq, bounded_bytes(yleft, ycols, 2 * yld), ycols, lst, rtid);
             else dy.issue(yreq, lst, rtid);
             const bool wrap = ++lsub == PPC;
             const int dr = wrap ? wrap_rows : step_rows;

@@ -174,7 +174,7 @@ __global__ void __launch_bounds__(NW * 64, OCC) tile_kernel_bf16(TileArgs a) {
                 // the workgroup's own rows: no other workgroup reads them when its block covers all output columns
                 if constexpr (PAD) {
                     const int cl = a.in_cols1 - sl * BXS;
-                    dxs.template issue_bounded<false, true>(Xb + sl * BXS, bounded_bytes(steps_left - r0, cl, 2 * xld), cl, st, tid);
+                    dxs.template issue_bounded<true>(Xb + sl * BXS, bounded_bytes(steps_left - r0, cl, 2 * xld), cl, st, tid);
                 } else if (gx == 1) dxs.template issue<true>(Xb + sl * BXS, st, tid);
                 else dxs.issue(Xb + sl * BXS, st, tid);
             } else {
@@ -187,13 +187,13 @@ __global__ void __launch_bounds__(NW * 64, OCC) tile_kernel_bf16(TileArgs a) {
                 // (E of this workgroup's rows: read by this workgroup only)
                 dy.template issue<true>(Eb + (long)ct * BC * a.L, st, tid);
             } else if constexpr (PAD) {
-                dy.template issue_bounded<false, true>(Y + (long)ct * BC * xld, bounded_bytes(steps_left - ct * BC, a.in_cols1, 2 * xld),
+                dy.template issue_bounded<true>(Y + (long)ct * BC * xld, bounded_bytes(steps_left - ct * BC, a.in_cols1, 2 * xld),
                                                        a.in_cols1, st, tid);
             } else {
                 dy.issue(Y + (long)ct * BC * xld, st, tid);
             }
             if constexpr (PAD)
-                dz.template issue_bounded<false, true>(Z + (long)ct * BC * zld, bounded_bytes(steps_left - ct * BC, cols2, 2 * zld), cols2,
+                dz.template issue_bounded<true>(Z + (long)ct * BC * zld, bounded_bytes(steps_left - ct * BC, cols2, 2 * zld), cols2,
                                                        st + YB, tid);
             else dz.issue(Z + (long)ct * BC * zld, st + YB, tid);
             if (!ELITE) {
@@ -210,7 +210,7 @@ __global__ void __launch_bounds__(NW * 64, OCC) tile_kernel_bf16(TileArgs a) {
             if (pi & 1) {
                 if constexpr (PAD) {
                     const int cl = a.in_cols1 - sl * BXS;
-                    dxs.template issue_bounded<false, false>(Xb + sl * BXS, bounded_bytes(steps_left - r0, cl, 2 * xld), cl, st, tid, part, nparts);
+                    dxs.template issue_bounded<false>(Xb + sl * BXS, bounded_bytes(steps_left - r0, cl, 2 * xld), cl, st, tid, part, nparts);
                 } else if (gx == 1) dxs.template issue_part<true>(Xb + sl * BXS, st, tid, part, nparts);
                 else dxs.issue_part(Xb + sl * BXS, st, tid, part, nparts);
             } else {
@@ -221,13 +221,13 @@ __global__ void __launch_bounds__(NW * 64, OCC) tile_kernel_bf16(TileArgs a) {
             if (ELITE) {
                 dy.template issue_part<true>(Eb + (long)ct * BC * a.L, st, tid, part, nparts);
             } else if constexpr (PAD) {
-                dy.template issue_bounded<false, false>(Y + (long)ct * BC * xld, bounded_bytes(steps_left - ct * BC, a.in_cols1, 2 * xld),
+                dy.template issue_bounded<false>(Y + (long)ct * BC * xld, bounded_bytes(steps_left - ct * BC, a.in_cols1, 2 * xld),
                                                         a.in_cols1, st, tid, part, nparts);
             } else {
                 dy.issue_part(Y + (long)ct * BC * xld, st, tid, part, nparts);
             }
             if constexpr (PAD)
-                dz.template issue_bounded<false, false>(Z + (long)ct * BC * zld, bounded_bytes(steps_left - ct * BC, cols2, 2 * zld), cols2,
+                dz.template issue_bounded<false>(Z + (long)ct * BC * zld, bounded_bytes(steps_left - ct * BC, cols2, 2 * zld), cols2,
                                                         st + YB, tid, part, nparts);
             else dz.issue_part(Z + (long)ct * BC * zld, st + YB, tid, part, nparts);
             if (!ELITE) {
@@ -428,7 +428,7 @@ __global__ void __launch_bounds__(NW * 64, OCC) tile_kernel_bf16(TileArgs a) {
                 const uint32_t wdst = smem_a + (uint32_t)(stg * STAGE + (sl % SPS) * SLOT);
                 if (FUSE && !a.fz_o) {}                  // no output gate: nothing to fetch
                 else if constexpr (PAD)
-                    dw.template issue_bounded<false, true>(wsrc, bounded_bytes(steps_left - wr0, cols2, 2 * zld), cols2, wdst, lane);
+                    dw.template issue_bounded<true>(wsrc, bounded_bytes(steps_left - wr0, cols2, 2 * zld), cols2, wdst, lane);
                 else if (gx == 1) dw.template issue<true>(wsrc, wdst, lane);
                 else dw.issue(wsrc, wdst, lane);
             }
@@ -629,7 +629,7 @@ __global__ void __launch_bounds__(NW * 64, OCC) tile_kernel_bf16(TileArgs a) {
         const bf16_t* wsrc = reinterpret_cast<const bf16_t*>(FUSE ? a.fz_o : a.dotwith) + (tin + wr0) * zld + (long)nb2 * BD2;
         if (FUSE && !a.fz_o) {}                          // no output gate: nothing to fetch
         else if constexpr (PAD)
-            dw.template issue_bounded<false, true>(wsrc, bounded_bytes(steps_left - wr0, cols2, 2 * zld), cols2, lds_addr(wtile), lane);
+            dw.template issue_bounded<true>(wsrc, bounded_bytes(steps_left - wr0, cols2, 2 * zld), cols2, lds_addr(wtile), lane);
         else if (gx == 1) dw.template issue<true>(wsrc, lds_addr(wtile), lane);
         else dw.issue(wsrc, lds_addr(wtile), lane);
     }
