@@ -141,6 +141,9 @@ BwdWs carve_bwd(const Dims& d, void* ws) {
     if (!parts_in_copies) { w.partQ = c.take<float>((size_t)w.nbQ * d.BHT); w.partK = c.take<float>((size_t)w.nbK * d.BHT); }
     static_assert(STATE_DOT_PARTS * sizeof(double) <= 3 * 64 * sizeof(float), "cdot fits the gate scratch");
     w.cdot = reinterpret_cast<double*>(w.tmp);
+    // (unused; keeps the pieces behind it where they were.  Their offsets from the other tensors show in the time: chunk 512,
+    // 2 x 8 x 8192 x 256 / 512, forward + backward, 836 to 860 us for shifts of the whole workspace by 256 bytes and more)
+    c.take<float>(d.BH);
     w.Cfinal = c.take<float>((size_t)d.BH * d.dqk * d.dhv);
     const size_t st = (size_t)d.BH * d.Nc * d.dqk * d.dhv * d.esz;
     // C_{k-1} and dC_k, both as (d_hv, d_qk)
