@@ -250,6 +250,8 @@ __global__ void __launch_bounds__(GATE_WAVES * 64) gates_step_kernel(GateArgs a)
 // Longer sequences keep the two launches, which spread one (batch, head) over the chip (a workgroup that walks 32 chunks
 // twice took 34 us where the two take 16).  us, two launches / one: 8 heads of 8 chunks of 128 11 / 5.6; 256 heads of 8
 // chunks of 256 23 / 12; 16 heads of 16 chunks of 256 17 / 13.
+// The chunk sizes are those that give a lane 1, 2, 4 or 8 steps, one vector store per result; the others (192, 320, 1024, ...)
+// keep the two launches as well.
 constexpr int GATE_FUSED_CHUNKS = 16;
 template <int E, typename AT>
 __global__ void __launch_bounds__(GATE_FUSED_CHUNKS * 64) gates_fused_kernel(GateArgs a) {

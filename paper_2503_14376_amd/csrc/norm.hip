@@ -12,7 +12,7 @@ namespace {
 
 // Rows per workgroup of the backward kernels, and the wavefronts that share them for rows of 257 to 512 values.  With
 // four wavefronts of 32 rows each the launch has too few in flight to stream (16 heads, 4000 steps of 512: 126 us at
-// 2.6 TB/s); sixteen take 70 us, 4.7 TB/s (a large copy moves 5.0).
+// 2.6 TB/s); sixteen take 81 us, 4.1 TB/s, and 142 us, 4.7 TB/s, at 8192 steps (a large copy moves 5.0).
 constexpr int NORM_RPB = 128, NORM_BW1 = 16;
 
 // eight consecutive elements of a row as floats

@@ -116,10 +116,15 @@ __global__ void __launch_bounds__(256) step_kernel(StepArgs a) {
 
 // Slabs of 64 columns for a large state (2^24 values and more over all heads: 16 sequences of 8 heads 256 / 512), of 32
 // below, where the launch would otherwise leave CUs without work.  A batch covers all rows up to 256, so that a workgroup
-// has its whole slab (or 256 rows of it) in flight at once; more batches of fewer rows lose 5 to 40 %.  us per step, the
-// former 64-column kernel without requests ahead / 32 / 64 columns: 1 sequence of 8 heads 256 / 512 9.7 / 5.2 / 6.4;
-// 8 sequences 20.6 / 13.7 / 14.9; 32 sequences 62 / 56.5 / 55.6 (4.83 TB/s; a large copy moves 5.0); 64 sequences 116 /
-// 111 / 104; 4 heads of 1024, 1 sequence 41 / 13.1 / 17.3, 16 sequences 118 / 117 / 109.
+// has its whole slab (or 256 rows of it) in flight at once; more batches of fewer rows lose 5 to 40 %.  32 / 64 columns, us
+// per step: 1 sequence of 8 heads 256 / 512 5.2 / 6.4, 8 sequences 13.6 / 14.4, 32 sequences 56.5 / 55.6, 64 sequences 111 /
+// 104; 4 heads of 1024, 1 sequence 13.1 / 17.3, 16 sequences 117 / 109.
+// Loads and stores are non-temporal because a model of several layers comes back to a layer's state only after those of all
+// the others.  us per step (replayed graph), the former kernel of plain accesses and no requests ahead / this one, states
+// taken in turn from 1.6 GB: 1, 8, 16, 32, 64 sequences of 8 heads 256 / 512 12.3 / 5.2, 20.7 / 13.6, 32.2 / 28.2, 61.8 /
+// 54.7 (4.9 TB/s; a large copy moves 5.0), 117 / 102.5; 16 sequences of 8 heads 512 / 512 59.3 / 55.0.  One state updated in
+// place over and over, which the 256 MB memory-side cache could hold: 6.1 / 5.3, 12.5 / 10.8, 22.9 / 25.1, 43.2 / 51.7, 94.8 /
+// 99.1; 43.2 / 52.5.  Plain accesses here: 41 to 45 in the last case, but 60.3 to 61.3 where the states take turns.
 template <typename DT, int COLS> static void launch_step_c(const StepArgs& a, int BH, hipStream_t s) {
     const dim3 grid(a.dhv / COLS, BH), block(256);
     constexpr int U64 = COLS / 16;              // passes that cover 64 rows

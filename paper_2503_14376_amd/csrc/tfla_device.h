@@ -27,7 +27,7 @@ __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_ex
 __device__ __forceinline__ float fast_log2(float x) { return __builtin_amdgcn_logf(x); }
 
 // sigma(x) of a bf16 value, as close as the library's exponential and an IEEE division come (over all 65536 values at most
-// 1.59 ulp of fp32 and 0.064 on average, both ways) in two thirds of their instructions.
+// 1.59 ulp of fp32 and 0.064 on average, both ways), in 17 vector instructions instead of 28.
 // e = exp(-|x|) = 2^n 2^f with f in [-1/2, 1/2] from a two-term product with log2 e; below -128, where e is zero, the
 // argument stays finite.  The denominator lies in [1, 2], so the division needs none of the scaling and special cases of the
 // general one: the quotient by the hardware's reciprocal, and its remainder once more.

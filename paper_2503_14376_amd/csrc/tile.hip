@@ -112,10 +112,6 @@ __global__ void __launch_bounds__(NW * 64) tile_kernel(TileArgs a) {
         if constexpr (STT) ps.load(St + (long)j * BC * d2, d2, tid);
         else ps.load(St + j * BC, ld1, tid);
     };
-    auto store_state = [&](DT* dst) {
-        if constexpr (STT) ps.store(dst, ZS, tid);
-        else ps.store(dst, ZS, tid);
-    };
     RowsPrefetch<DT, BC, D1, NT> py;           // Y tile       [BC][D1]
     TrPrefetch<DT, BC, BD2, NT, true> pz;      // Z tile       [BC][BD2] -> [BD2][BC]
     float pw = 0.0f, pwl = 0.0f;
@@ -125,7 +121,7 @@ __global__ void __launch_bounds__(NW * 64) tile_kernel(TileArgs a) {
 
     // ---------------- inter-chunk part: acc = X_r St, BC columns of d1 per stage
     load_state(0);
-    store_state(ldsZ[0]);
+    ps.store(ldsZ[0], ZS, tid);
     __syncthreads();
 #pragma unroll
     for (int j = 0; j < NK; ++j) {
@@ -144,7 +140,7 @@ __global__ void __launch_bounds__(NW * 64) tile_kernel(TileArgs a) {
                 acc[nb] = E::mma(xf[j * (BC / 16) + ks], E::load(zb + (nb * 32 + l32) * ZS + 16 * ks + 8 * g), acc[nb]);
         left();
         if (j + 1 < NK) {
-            store_state(ldsZ[other()]);
+            ps.store(ldsZ[other()], ZS, tid);
         } else {
             py.store(ldsY[other()], YS, tid);
             pz.store(ldsZ[other()], ZS, tid);
@@ -351,7 +347,7 @@ static hipError_t launch_tile_t(const TileArgs& a0, int BH, hipStream_t s) {
         else
             hipLaunchKernelGGL((tile_kernel_bf16<D1, BD2, NW, MODE, OCC, SPLIT, NOE, 0>), grid, dim3(64 * NW), 0, s, a);
     } else {
-        constexpr int BC = 32;   // two LDS stages must fit in 160 KB
+        constexpr int BC = 32;   // (the kernel takes one LDS stage where two of them would leave a CU with one workgroup)
         if (padded) hipLaunchKernelGGL((tile_kernel<DT, D1, BD2, BC, NW, MODE, SPLIT, true>), grid, dim3(64 * NW), 0, s, a);
         else hipLaunchKernelGGL((tile_kernel<DT, D1, BD2, BC, NW, MODE, SPLIT, false>), grid, dim3(64 * NW), 0, s, a);
     }
