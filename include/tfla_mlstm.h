@@ -84,7 +84,8 @@ enum {
  * Forward pass (Sec. 2.2 / App. B.2 for the mathematics, Sec. 3 / App. C for the tiling).
  *   in : q, k, v, i_pre, f_pre; optional initial state C0, n0, m0 (all three NULL = zero
  *        state with m0 = 0; for TFLA_SIG only C0 is read and n0/m0 may be NULL)
- *   out: H (required); optional final state Cn, nn, mn (each may be NULL);
+ *   out: H (required); optional final state Cn, nn, mn (each may be NULL, and each may be the buffer of the
+ *        initial state that it replaces; a matching backward call needs the initial state, though);
  *        optional n_out, m_out (B, NH, T): the signed normaliser n_t^T q~_t and the max state
  *        m_t of every step, which tfla_mlstm_bwd needs for TFLA_EXP.
  *   workspace: device scratch of at least tfla_mlstm_workspace_bytes(TFLA_FWD, ...) bytes,

@@ -282,9 +282,13 @@ int fwd_impl(const void* q, const void* k, const void* v, const float* i_pre, co
     // (m_out goes to the caller's tensor; the kernels that read it back count in whole chunks)
     const bool own_mout = is_exp && m_out && d.T == d.T_in;
     float* mout = own_mout ? m_out : w.mout;
-    int st = run_gates(d, i_pre, f_pre, m0, w.wrow, w.ucol, w.sH, w.aK, w.gbar, mout, (is_exp && !own_mout) ? m_out : nullptr, is_exp ? mn : nullptr,
-                       w.tmp, w.csum, w.wrow_lo, w.ucol_lo, softcap, s);
+    // A state continued in place (mn is m0): the second of two gate launches reads m0 in every workgroup, so the final max
+    // state waits in the memory of n_{k-1}, which the recurrent kernel writes later, until all of them have.
+    const bool m_waits = is_exp && mn && mn == m0 && !gates_in_one_launch(d.Nc, chunk);
+    int st = run_gates(d, i_pre, f_pre, m0, w.wrow, w.ucol, w.sH, w.aK, w.gbar, mout, (is_exp && !own_mout) ? m_out : nullptr,
+                       !is_exp ? nullptr : (m_waits ? w.nst : mn), w.tmp, w.csum, w.wrow_lo, w.ucol_lo, softcap, s);
     if (st != TFLA_OK) return st;
+    if (m_waits) TFLA_LAUNCH(K_GATES, launch_copy(w.nst, mn, (int)d.BH, s));
 
     // 2. recurrent kernel: C_{k-1} (transposed, element type of q/k/v) and n_{k-1} for every chunk
     RecArgs r;

@@ -245,14 +245,13 @@ __global__ void __launch_bounds__(GATE_WAVES * 64) gates_step_kernel(GateArgs a)
     }
 }
 
-// Both kernels in one for short sequences: up to sixteen chunks, one wavefront each, in one workgroup per (batch, head);
+// Both kernels in one for short sequences (gates_in_one_launch): up to sixteen chunks, one wavefront each, in one workgroup per (batch, head);
 // the lane's E = L / 64 steps stay in registers from the scans to the results, and the chunk summaries meet in LDS.
 // Longer sequences keep the two launches, which spread one (batch, head) over the chip (a workgroup that walks 32 chunks
 // twice took 34 us where the two take 16).  us, two launches / one: 8 heads of 8 chunks of 128 11 / 5.6; 256 heads of 8
 // chunks of 256 23 / 12; 16 heads of 16 chunks of 256 17 / 13.
 // The chunk sizes are those that give a lane 1, 2, 4 or 8 steps, one vector store per result; the others (192, 320, 1024, ...)
 // keep the two launches as well.
-constexpr int GATE_FUSED_CHUNKS = 16;
 template <int E, typename AT>
 __global__ void __launch_bounds__(GATE_FUSED_CHUNKS * 64) gates_fused_kernel(GateArgs a) {
     __shared__ AT cg[GATE_FUSED_CHUNKS], camax[GATE_FUSED_CHUNKS], m_init;
@@ -343,7 +342,7 @@ __global__ void __launch_bounds__(GATE_FUSED_CHUNKS * 64) gates_fused_kernel(Gat
 }
 
 template <typename AT> static hipError_t launch_gates_t(const GateArgs& a, int BH, hipStream_t s) {
-    if (a.Nc <= GATE_FUSED_CHUNKS && (a.L == 64 || a.L == 128 || a.L == 256 || a.L == 512)) {
+    if (gates_in_one_launch(a.Nc, a.L)) {
         const dim3 grid(BH), block(64 * a.Nc);
         if (a.L == 64) hipLaunchKernelGGL((gates_fused_kernel<1, AT>), grid, block, 0, s, a);
         else if (a.L == 128) hipLaunchKernelGGL((gates_fused_kernel<2, AT>), grid, block, 0, s, a);
@@ -579,6 +578,14 @@ __global__ void __launch_bounds__(256) fill_zero4_kernel(FillList f) {
         if (i < f.n[q]) { f.p[q][i] = 0.0f; return; }
         i -= f.n[q];
     }
+}
+__global__ void __launch_bounds__(256) copy_kernel(const float* from, float* to, int n) {
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i < n) to[i] = from[i];
+}
+hipError_t launch_copy(const float* from, float* to, int n, hipStream_t s) {
+    hipLaunchKernelGGL(copy_kernel, dim3((n + 255) / 256), dim3(256), 0, s, from, to, n);
+    return hipGetLastError();
 }
 hipError_t launch_fill_zero4(const FillList& f, hipStream_t s) {
     long total = 0;

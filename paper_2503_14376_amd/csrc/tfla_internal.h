@@ -32,6 +32,9 @@ struct GateArgs {
 };
 hipError_t launch_gates(const GateArgs& a, int BH, hipStream_t s);
 
+// the pre-pass is one workgroup per (batch, head) instead of two launches (gates.hip has both sides)
+constexpr int GATE_FUSED_CHUNKS = 16;
+inline bool gates_in_one_launch(int Nc, int L) { return Nc <= GATE_FUSED_CHUNKS && (L == 64 || L == 128 || L == 256 || L == 512); }
 struct GateBwdPrepArgs {
     const float* wrow; const float* sH; const float* n_out; const float* m_out;
     float* wrowB; float* sQ;
@@ -60,6 +63,7 @@ hipError_t launch_gate_grads(const GateGradArgs& a, int BH, hipStream_t s);
 
 struct FillList { float* p[4]; long n[4]; };     // n[q] = 0: slot unused
 hipError_t launch_fill_zero4(const FillList& f, hipStream_t s);
+hipError_t launch_copy(const float* from, float* to, int n, hipStream_t s);
 // out[bh] = <A[bh], Bm[bh]>; A (BH, *, lda), Bm (BH, d1, d2): the first d2 columns of the first d1 rows of A's `perA` values
 // as STATE_DOT_PARTS partial sums each
 constexpr int STATE_DOT_PARTS = 16;

@@ -179,9 +179,10 @@ def test_gate_launches(dtype, variant, T, chunk):
 
 
 # a state that is continued in place (the final state's buffers are the initial state's): up to 16 chunks the gate pre-pass
-# is one workgroup per (batch, head), whose wavefronts all need the initial max state that one of them replaces
+# is one workgroup per (batch, head), whose wavefronts all need the initial max state that one of them replaces; beyond, and at
+# other chunk sizes, all workgroups of a second launch do
 @pytest.mark.parametrize("dtype", [wl.BF16, wl.F32])
-@pytest.mark.parametrize("T,chunk", [(64, 64), (128, 64), (250, 64), (512, 128), (1024, 64)])
+@pytest.mark.parametrize("T,chunk", [(64, 64), (128, 64), (250, 64), (512, 128), (1024, 64), (1088, 64), (4000, 64), (1100, 192), (5000, 1024)])
 def test_state_continued_in_place(dtype, T, chunk):
     import paper_2503_14376_amd as tfla
     from tests import gpu_util as gu
