@@ -23,7 +23,9 @@ UNITS = [("api.hip", "api.o", []), ("gates.hip", "gates.o", []), ("step.hip", "s
     # index registers by compile-time constants); with the widest shapes its body exceeds the default size limit
     # (accumulators in ordinary VGPRs as for recurrent.hip: the dK kernel then needs no accumulation registers at all)
     ("tile_inst.hip", "tile_mode%d.o" % m, ["-DTFLA_TILE_MODE=%d" % m, "-mllvm", "-pragma-unroll-threshold=200000",
-                                            "-mllvm", "-amdgpu-mfma-vgpr-form"]) for m in range(4)]
+                                            "-mllvm", "-amdgpu-mfma-vgpr-form"]) for m in range(4)] + [
+    ("tile_grads.hip", "tile_grads%d.o" % w, ["-DTFLA_GRADS_DQK=%d" % w, "-mllvm", "-pragma-unroll-threshold=200000",
+                                              "-mllvm", "-amdgpu-mfma-vgpr-form"]) for w in (64, 128, 256)]
 
 
 def _compile(unit):

@@ -172,10 +172,10 @@ BwdWs carve_bwd(const Dims& d, void* ws) {
 
 // ---- optional per-kernel timing with HIP events on the caller's stream -------------------
 enum { K_GATES = 0, K_BWD_PREP, K_REC_FWD, K_REC_BWD, K_TILE_H, K_TILE_DV, K_TILE_DQ, K_TILE_DK, K_GATE_GRADS,
-       K_STATE_DOT, K_FILL, K_STEP, K_NORM_FWD, K_NORM_BWD, K_GAIN, K_COUNT };
+       K_STATE_DOT, K_FILL, K_STEP, K_NORM_FWD, K_NORM_BWD, K_GAIN, K_TILE_GRADS, K_COUNT };
 const char* const kKernelNames[K_COUNT] = {"gates", "gate_bwd_prep", "recurrent_fwd", "recurrent_bwd", "tile_H",
                                            "tile_dV", "tile_dQ", "tile_dK", "gate_grads", "state_dot", "fill_zero",
-                                           "recurrent_step", "norm_gate_fwd", "norm_gate_bwd", "transfer_gain"};
+                                           "recurrent_step", "norm_gate_fwd", "norm_gate_bwd", "transfer_gain", "tile_grads"};
 struct Profiler {
     bool on = false;
     int cap = 0, used = 0;
@@ -431,15 +431,21 @@ int bwd_impl(const void* q, const void* k, const void* v, const float* i_pre, co
     // dV: rows = kv index j
     t.X = k; t.Y = q; t.Z = dH; t.Out = dv; t.out_T = T; t.out_ld = dhv; t.in_ld1 = t.in_cols1 = dqk; t.wrow_lo = ucol_lo; t.wcol_lo = wrowB_lo; t.wrowB_lo_out = nullptr; t.wrow = ucol; t.wcol = wrowB; t.srow = aK; t.St = w.dcT;
     t.d1 = d.dqk; t.d2 = d.dhv; t.dotwith = nullptr; t.dotpart = nullptr;
-    TFLA_LAUNCH(K_TILE_DV, launch_tile_mode<MODE_DV>(t, (int)d.BH, dtype, s));
+    const TileArgs tv = t;
     // dQ: rows = query index i
     t.X = dH; t.Y = v; t.Z = k; t.Out = dq; t.out_ld = dqk; t.in_ld1 = t.in_cols1 = dhv; t.wrow_lo = wrowB_lo; t.wcol_lo = ucol_lo; t.wrow = wrowB; t.wcol = ucol; t.srow = sQ; t.St = cstates;
     t.d1 = d.dhv; t.d2 = d.dqk; t.dotwith = q; t.dotpart = w.partQ;
-    TFLA_LAUNCH(K_TILE_DQ, launch_tile_mode<MODE_DQ>(t, (int)d.BH, dtype, s));
+    const TileArgs tq = t;
     // dK: rows = kv index j
     t.X = v; t.Y = dH; t.Z = q; t.Out = dk; t.wrow_lo = ucol_lo; t.wcol_lo = wrowB_lo; t.wrow = ucol; t.wcol = wrowB; t.srow = aK; t.St = w.dcT;
-    t.d1 = d.dhv; t.d2 = d.dqk; t.dotwith = k; t.dotpart = w.partK;
-    TFLA_LAUNCH(K_TILE_DK, launch_tile_mode<MODE_DK>(t, (int)d.BH, dtype, s));
+    t.dotwith = k; t.dotpart = w.partK;
+    if (grads_in_one_launch(d.dqk, d.dhv, dtype, chunk, d.BHT)) {
+        TFLA_LAUNCH(K_TILE_GRADS, launch_grads(tv, tq, t, (int)d.BH, s));
+    } else {
+        TFLA_LAUNCH(K_TILE_DV, launch_tile_mode<MODE_DV>(tv, (int)d.BH, dtype, s));
+        TFLA_LAUNCH(K_TILE_DQ, launch_tile_mode<MODE_DQ>(tq, (int)d.BH, dtype, s));
+        TFLA_LAUNCH(K_TILE_DK, launch_tile_mode<MODE_DK>(t, (int)d.BH, dtype, s));
+    }
 
     // 5. gate gradients
     if (dCn) TFLA_LAUNCH(K_STATE_DOT, launch_state_dot(Cfinal, (long)d.dqk * d.dhv, d.dhv, dCn, dqk, dhv, w.cdot, (int)d.BH, s));

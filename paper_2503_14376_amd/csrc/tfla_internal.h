@@ -250,6 +250,23 @@ inline int tile_bd2(int d1, int d2, int dtype, int L, long rows) {
     if (d2 % 128 == 0 && (dtype == 1 || (rows / 64) * (d2 / 128) >= 512)) return 128;
     return 64;
 }
+// dV, dQ and dK in one launch (tile_grads.hip): bf16, where dQ and dK need not hand E over (d_hv up to 256) and every part
+// fits two workgroups per CU (contractions up to 256 columns; wider ones hold their X rows in half of the register file),
+// with the block widths that kernel is built for (tile_width_override may ask for others).  Faster at every size measured,
+// 6 to 37 % of forward + backward, from one sequence of 777 steps to 128 heads of 32.
+inline bool grads_in_one_launch(int dqk, int dhv, int dtype, int L, long rows) {
+    return dtype == 1 && dqk <= 256 && dhv <= 256 && tile_bd2(dqk, dhv, dtype, L, rows) == (dhv >= 128 ? 128 : 64) &&
+           tile_bd2(dhv, dqk, dtype, L, rows) == (dqk >= 128 ? 128 : 64);
+}
+template <int DQK> hipError_t launch_tile_grads(const TileArgs& dv, const TileArgs& dq, const TileArgs& dk, int BH, hipStream_t s);
+inline hipError_t launch_grads(const TileArgs& dv, const TileArgs& dq, const TileArgs& dk, int BH, hipStream_t s) {
+    switch (dv.d1) {
+        case 64: return launch_tile_grads<64>(dv, dq, dk, BH, s);
+        case 128: return launch_tile_grads<128>(dv, dq, dk, BH, s);
+        case 256: return launch_tile_grads<256>(dv, dq, dk, BH, s);
+        default: return hipErrorInvalidValue;
+    }
+}
 // the fused layer output needs whole rows of h~ in one workgroup of the H kernel
 inline bool layer_fusion_applies(int dqk, int dhv, int dtype, int L, long rows) {
     return dtype == 1 && (dhv == 64 || dhv == 128) && tile_bd2(dqk, dhv, dtype, L, rows) == dhv;

@@ -42,6 +42,13 @@ __host__ __device__ constexpr int pre_item(int item, int BXS, int BCS) {
     return w < Q ? 2 * (grp * Q + w) + 1 : 2 * grp;
 }
 
+// quotient and remainder by a divisor whose log2 the launcher supplies when it has one (else -1)
+__device__ __forceinline__ unsigned tile_divmod(unsigned n, unsigned d, int sh, unsigned& rem) {
+    const unsigned q = sh >= 0 ? n >> sh : n / d;
+    rem = n - q * d;
+    return q;
+}
+
 // SPLIT: 0 = the whole contraction over D1 in this launch; 1 / 2 = the first / second 512-wide half of a
 // contraction over 1024 columns (rows of the D1-wide operands are 2 D1 apart): the first half stores its raw fp32
 // accumulators, the second adds them to its own before the epilogue.
@@ -51,82 +58,95 @@ __host__ __device__ constexpr int pre_item(int item, int BXS, int BCS) {
 // end leave zeros in LDS (dma16_bounded) and only the true steps and columns are stored; 0 = whole blocks.
 // FUSE: 1 = MODE_H also stores the layer output y = sigma(o~) (.) NORM(h~) (Sec. 2.1, hidden-state output equation) of
 // its rows; the column block covers all of d2 (the launcher checks), nothing is padded.
-template <int D1, int BD2, int NW, int MODE, int OCC, int SPLIT = 0, int NOE = 0, int PAD = 0, int FUSE = 0>
-__global__ void __launch_bounds__(NW * 64, OCC) tile_kernel_bf16(TileArgs a) {
-    static_assert(!FUSE || (MODE == MODE_H && SPLIT == 0 && !PAD), "the fused layer output belongs to the plain H kernel");
-    using E = Elem<bf16_t>;
-    using frag = E::frag;
-    constexpr bool UPPER = (MODE & 1) != 0;
-    constexpr bool STT = (MODE == MODE_DQ || MODE == MODE_DK);   // state slices are contraction-major
-    constexpr bool ELITE = MODE == MODE_DK && !NOE;              // column tiles carry E instead of Y
-    constexpr bool EWRITE = MODE == MODE_DQ && !NOE;
-    constexpr int NT = NW * 64, BR = NW * 32, BC = 32;
-    constexpr int KS1 = D1 / 16, NB = BD2 / 32;
-    constexpr int YB = ELITE ? BC * BR * 2 : BC * D1 * 2, ZB = BC * BD2 * 2;         // bytes
-    constexpr int XSMIN = BR * (D1 < 128 ? D1 : 128) * 2;       // room for wide X slices when the tiles are small
-    constexpr int STAGE = (ELITE && YB + ZB < XSMIN) ? XSMIN : YB + ZB;
-    constexpr int ESTG = EWRITE ? NW * 2048 : 0;                // per-wave staging of E tiles
+// Sizes of a workgroup's pieces of LDS and of what it streams through them.
+template <int D1, int BD2, int NW, int MODE, int OCC, int SPLIT, int NOE, int FUSE> struct TileShape {
+    static constexpr bool UPPER = (MODE & 1) != 0;
+    static constexpr bool STT = (MODE == MODE_DQ || MODE == MODE_DK);   // state slices are contraction-major
+    static constexpr bool ELITE = MODE == MODE_DK && !NOE;              // column tiles carry E instead of Y
+    static constexpr bool EWRITE = MODE == MODE_DQ && !NOE;
+    static constexpr int NT = NW * 64, BR = NW * 32, BC = 32;
+    static constexpr int KS1 = D1 / 16, NB = BD2 / 32;
+    static constexpr int YB = ELITE ? BC * BR * 2 : BC * D1 * 2, ZB = BC * BD2 * 2;         // bytes
+    static constexpr int XSMIN = BR * (D1 < 128 ? D1 : 128) * 2;       // room for wide X slices when the tiles are small
+    static constexpr int STAGE = (ELITE && YB + ZB < XSMIN) ? XSMIN : YB + ZB;
+    static constexpr int ESTG = EWRITE ? NW * 2048 : 0;                // per-wave staging of E tiles
     // LDS budget of one workgroup: 160 KB shared by OCC resident workgroups, minus the small arrays
-    constexpr int BUDGET = (OCC >= 2 ? 80 : 160) * 1024 - 6144 - ESTG;
-    constexpr int NS = STAGE * 4 <= BUDGET ? 4 : (STAGE * 3 <= BUDGET ? 3 : 2);
+    static constexpr int BUDGET = (OCC >= 2 ? 80 : 160) * 1024 - 6144 - ESTG;
+    static constexpr int NS = STAGE * 4 <= BUDGET ? 4 : (STAGE * 3 <= BUDGET ? 3 : 2);
     static_assert(NS * STAGE <= BUDGET, "ring does not fit");
-    constexpr int BCS_RAW = STAGE / (BD2 * 2);
-    constexpr int BCS = BCS_RAW >= 64 ? 64 : 32;                                    // state slice width
-    constexpr int NKS = D1 / BCS;
+    static constexpr int BCS_RAW = STAGE / (BD2 * 2);
+    static constexpr int BCS = BCS_RAW >= 64 ? 64 : 32;                                    // state slice width
+    static constexpr int NKS = D1 / BCS;
     // the workgroup's rows of X arrive in [BR][BXS] slices
-    constexpr int BXS_RAW = STAGE / (BR * 2);
-    constexpr int BXS = BXS_RAW >= 128 ? 128 : (BXS_RAW >= 64 ? 64 : 32);
-    constexpr int NXS = D1 / BXS, NPRE = NXS + NKS;
+    static constexpr int BXS_RAW = STAGE / (BR * 2);
+    static constexpr int BXS = BXS_RAW >= 128 ? 128 : (BXS_RAW >= 64 ? 64 : 32);
+    static constexpr int NXS = D1 / BXS, NPRE = NXS + NKS;
     static_assert(BR * BXS * 2 <= STAGE && BXS <= D1 && D1 % BXS == 0, "X slice must fit a stage");
     static_assert(BD2 * BCS * 2 <= STAGE && BCS <= 64 && D1 % BCS == 0, "state slice must fit a stage");
 
     // after the loops the ring's memory holds the output block (and the dot operand) of each wave
-    constexpr bool WTILE = MODE == MODE_DQ || MODE == MODE_DK || FUSE;   // the epilogue reads a second per-wave tile
-    constexpr int EPI = (WTILE ? 2 : 1) * NW * 32 * BD2 * 2;
-    constexpr int SMEM = NS * STAGE > EPI ? NS * STAGE : EPI;
+    static constexpr bool WTILE = MODE == MODE_DQ || MODE == MODE_DK || FUSE;   // the epilogue reads a second per-wave tile
+    static constexpr int EPI = (WTILE ? 2 : 1) * NW * 32 * BD2 * 2;
+    static constexpr int SMEM = NS * STAGE > EPI ? NS * STAGE : EPI;
     static_assert(SMEM <= BUDGET, "LDS budget");
     // The epilogue's per-wave tiles ([32][BD2] bf16: the output block on its way out and, for dQ / dK, the wave's rows
     // of the dot operand -- for the fused layer output, of the gate pre-activations) live in slots of the ring's memory.  Slots are numbered from the stage after the one that
     // holds the last ring item: the first (NS - 1) SPS of them are free while that item is being multiplied, so the dot
     // operand (slots 0 .. NW-1) is requested then and its latency hides behind the last tile; the output tiles take
     // the slots NW .. 2 NW - 1 once every wave has left the ring.
-    constexpr int SLOT = 32 * BD2 * 2, SPS = STAGE / SLOT >= 1 ? STAGE / SLOT : 1;
+    static constexpr int SLOT = 32 * BD2 * 2, SPS = STAGE / SLOT >= 1 ? STAGE / SLOT : 1;
     // (not where a slot is larger than a stage, and not in the first half of a split contraction, which has no epilogue)
-    constexpr bool WPRE = WTILE && SPLIT != 1 && STAGE >= SLOT && (NS - 1) * SPS >= NW && NS * SPS >= 2 * NW;
-    __shared__ __attribute__((aligned(1024))) char smem[SMEM];
-    __shared__ __attribute__((aligned(1024))) char ldsE[EWRITE ? ESTG : 16];
-    __shared__ __attribute__((aligned(256))) float ldsW[NS][NW][64];   // column weights of a tile, one copy per wave
-    // per-row scalars of each wave's 32 rows (two copies side by side), fetched like the tiles
-    __shared__ __attribute__((aligned(256))) float ldsS[NW][64];    // inter-chunk row scale
-    __shared__ __attribute__((aligned(256))) float ldsWr[NW][64];   // row term of the weights
-    __shared__ __attribute__((aligned(256))) float ldsM[(MODE == MODE_H) ? NW : 1][64];  // max state (mLSTMexp forward)
-    __shared__ __attribute__((aligned(256))) float ldsN[(MODE == MODE_H) ? D1 : 64];     // n_{k-1}
+    static constexpr bool WPRE = WTILE && SPLIT != 1 && STAGE >= SLOT && (NS - 1) * SPS >= NW && NS * SPS >= 2 * NW;
+    // bytes of everything, for callers that lay the pieces out themselves
+    static constexpr int AT_E = SMEM, AT_W = AT_E + (EWRITE ? ESTG : 0), AT_S = AT_W + NS * NW * 256, AT_WR = AT_S + NW * 256,
+                         AT_M = AT_WR + NW * 256, AT_N = AT_M + (MODE == MODE_H ? NW : 1) * 256,
+                         BYTES = AT_N + (MODE == MODE_H ? D1 : 64) * 4;
+};
+
+// Where a workgroup's pieces of LDS are.
+struct TileLds {
+    char* smem;             // the ring
+    char* ldsE;             // staging of E tiles (dQ)
+    float* ldsW;            // [NS][NW][64] column weights of a tile, one copy per wave
+    // per-row scalars of each wave's 32 rows (two copies side by side), fetched like the tiles; [NW][64] each
+    float* ldsS;            // inter-chunk row scale
+    float* ldsWr;           // row term of the weights
+    float* ldsM;            // max state (mLSTMexp forward)
+    float* ldsN;            // n_{k-1}, D1 values (H)
+};
+
+// One workgroup: output rows rbi and columns nb2 (block indices) of the chunk with the linear id wg.
+// ALONE: no other workgroup of the launch but those of the same mode reads the operands (they may carry the
+// non-temporal hint where exactly one workgroup reads them).
+template <int D1, int BD2, int NW, int MODE, int OCC, int SPLIT, int NOE, int PAD, int FUSE, bool ALONE>
+__device__ __forceinline__ void tile_body_bf16(const TileArgs& a, const TileLds& lds, int nb2, int rbi, unsigned wg) {
+    static_assert(!FUSE || (MODE == MODE_H && SPLIT == 0 && !PAD), "the fused layer output belongs to the plain H kernel");
+    using E = Elem<bf16_t>;
+    using frag = E::frag;
+    using SH = TileShape<D1, BD2, NW, MODE, OCC, SPLIT, NOE, FUSE>;
+    constexpr bool UPPER = SH::UPPER, STT = SH::STT, ELITE = SH::ELITE, EWRITE = SH::EWRITE, WTILE = SH::WTILE, WPRE = SH::WPRE;
+    constexpr int NT = SH::NT, BR = SH::BR, BC = SH::BC, KS1 = SH::KS1, NB = SH::NB, YB = SH::YB, STAGE = SH::STAGE, NS = SH::NS,
+                  BCS = SH::BCS, NKS = SH::NKS, BXS = SH::BXS, NPRE = SH::NPRE, SLOT = SH::SLOT, SPS = SH::SPS;
+    char* const smem = lds.smem;
+    char* const ldsE = lds.ldsE;
+    auto ldsW = reinterpret_cast<float (*)[NW][64]>(lds.ldsW);
+    auto ldsS = reinterpret_cast<float (*)[64]>(lds.ldsS);
+    auto ldsWr = reinterpret_cast<float (*)[64]>(lds.ldsWr);
+    auto ldsM = reinterpret_cast<float (*)[64]>(lds.ldsM);
+    float* const ldsN = lds.ldsN;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l32 = lane & 31, g = lane >> 5;
     TFLA_TL(0);
-    // one-dimensional launch (the number of workgroups can exceed what the y and z grid dimensions hold):
-    // linear id -> (column block, row block, chunk, batch*head), column blocks fastest
-    const unsigned nwg = gridDim.x, gx = (unsigned)a.d2 / BD2, gy = (unsigned)a.L / (32 * NW);
-    unsigned wg = xcd_remap(blockIdx.x, nwg);
-    // quotient and remainder by a divisor whose log2 the launcher supplies when it has one
-    auto divmod = [](unsigned n, unsigned d, int sh, unsigned& rem) {
-        const unsigned q = sh >= 0 ? n >> sh : n / d;
-        rem = n - q * d;
-        return q;
-    };
+    const unsigned gx = (unsigned)a.d2 / BD2, gy = (unsigned)a.L / (32 * NW);
     unsigned rem;
-    wg = divmod(wg, gx, a.sh_gx, rem);
-    const int nb2 = __builtin_amdgcn_readfirstlane((int)rem);
-    wg = divmod(wg, gy, a.sh_gy, rem);
-    const int rbi = __builtin_amdgcn_readfirstlane((int)rem);
     const int rb = UPPER ? rbi : (int)gy - 1 - rbi;      // row blocks with more column tiles first
     // Order in time: every XCD walks the chunks of its own (batch, head) slices together, chunk by chunk, in
     // the direction a.kc_desc gives (the launcher's choice, by measurement).
     // bpx = slices per XCD (the XCD's contiguous range of ids then covers exactly its slices)
     const unsigned bhn = (unsigned)a.dec_bh, bpx = (unsigned)a.dec_bpx;
-    wg = divmod(wg, bpx, a.sh_bpx, rem);
+    wg = tile_divmod(wg, bpx, a.sh_bpx, rem);
     const unsigned bl = rem;
-    wg = divmod(wg, (unsigned)a.Nc, a.sh_nc, rem);
+    wg = tile_divmod(wg, (unsigned)a.Nc, a.sh_nc, rem);
     const int kci = __builtin_amdgcn_readfirstlane((int)rem);
     const int kc = a.kc_desc ? a.Nc - 1 - kci : kci;
     const int bh = __builtin_amdgcn_readfirstlane((int)(wg * bpx + bl));
@@ -175,11 +195,11 @@ __global__ void __launch_bounds__(NW * 64, OCC) tile_kernel_bf16(TileArgs a) {
                 if constexpr (PAD) {
                     const int cl = a.in_cols1 - sl * BXS;
                     dxs.template issue_bounded<true>(Xb + sl * BXS, bounded_bytes(steps_left - r0, cl, 2 * xld), cl, st, tid);
-                } else if (gx == 1) dxs.template issue<true>(Xb + sl * BXS, st, tid);
+                } else if (ALONE && gx == 1) dxs.template issue<true>(Xb + sl * BXS, st, tid);
                 else dxs.issue(Xb + sl * BXS, st, tid);
             } else {
                 // (state slices of the dQ / dK kernels carry the hint too: measured, -3 us on dQ)
-                ds.template issue<STT>(St + (STT ? (long)sl * BCS * d2 : (long)sl * BCS), st, tid);
+                ds.template issue<STT && ALONE>(St + (STT ? (long)sl * BCS * d2 : (long)sl * BCS), st, tid);
             }
         } else {
             const int ct = ct_lo + item - NPRE;
@@ -211,10 +231,10 @@ __global__ void __launch_bounds__(NW * 64, OCC) tile_kernel_bf16(TileArgs a) {
                 if constexpr (PAD) {
                     const int cl = a.in_cols1 - sl * BXS;
                     dxs.template issue_bounded<false>(Xb + sl * BXS, bounded_bytes(steps_left - r0, cl, 2 * xld), cl, st, tid, part, nparts);
-                } else if (gx == 1) dxs.template issue_part<true>(Xb + sl * BXS, st, tid, part, nparts);
+                } else if (ALONE && gx == 1) dxs.template issue_part<true>(Xb + sl * BXS, st, tid, part, nparts);
                 else dxs.issue_part(Xb + sl * BXS, st, tid, part, nparts);
             } else {
-                ds.template issue_part<STT>(St + (STT ? (long)sl * BCS * d2 : (long)sl * BCS), st, tid, part, nparts);
+                ds.template issue_part<STT && ALONE>(St + (STT ? (long)sl * BCS * d2 : (long)sl * BCS), st, tid, part, nparts);
             }
         } else {
             const int ct = ct_lo + item - NPRE;
@@ -429,7 +449,7 @@ __global__ void __launch_bounds__(NW * 64, OCC) tile_kernel_bf16(TileArgs a) {
                 if (FUSE && !a.fz_o) {}                  // no output gate: nothing to fetch
                 else if constexpr (PAD)
                     dw.template issue_bounded<true>(wsrc, bounded_bytes(steps_left - wr0, cols2, 2 * zld), cols2, wdst, lane);
-                else if (gx == 1) dw.template issue<true>(wsrc, wdst, lane);
+                else if (ALONE && gx == 1) dw.template issue<true>(wsrc, wdst, lane);
                 else dw.issue(wsrc, wdst, lane);
             }
         }
@@ -630,7 +650,7 @@ __global__ void __launch_bounds__(NW * 64, OCC) tile_kernel_bf16(TileArgs a) {
         if (FUSE && !a.fz_o) {}                          // no output gate: nothing to fetch
         else if constexpr (PAD)
             dw.template issue_bounded<true>(wsrc, bounded_bytes(steps_left - wr0, cols2, 2 * zld), cols2, lds_addr(wtile), lane);
-        else if (gx == 1) dw.template issue<true>(wsrc, lds_addr(wtile), lane);
+        else if (ALONE && gx == 1) dw.template issue<true>(wsrc, lds_addr(wtile), lane);
         else dw.issue(wsrc, lds_addr(wtile), lane);
     }
     // fused layer output: this lane's eight columns of the per-head scale and shift (requested here, ahead of the
@@ -755,6 +775,23 @@ __global__ void __launch_bounds__(NW * 64, OCC) tile_kernel_bf16(TileArgs a) {
     wait_vmcnt<0>();
     TFLA_TL(6);
 #endif
+}
+
+template <int D1, int BD2, int NW, int MODE, int OCC, int SPLIT = 0, int NOE = 0, int PAD = 0, int FUSE = 0>
+__global__ void __launch_bounds__(NW * 64, OCC) tile_kernel_bf16(TileArgs a) {
+    using SH = TileShape<D1, BD2, NW, MODE, OCC, SPLIT, NOE, FUSE>;
+    __shared__ __attribute__((aligned(1024))) char smem[SH::SMEM];
+    __shared__ __attribute__((aligned(1024))) char ldsE[SH::EWRITE ? SH::ESTG : 16];
+    __shared__ __attribute__((aligned(256))) float ldsW[SH::NS * NW * 64], ldsS[NW * 64], ldsWr[NW * 64];
+    __shared__ __attribute__((aligned(256))) float ldsM[(MODE == MODE_H ? NW : 1) * 64], ldsN[MODE == MODE_H ? D1 : 64];
+    // one-dimensional launch (the number of workgroups can exceed what the y and z grid dimensions hold):
+    // linear id -> (column block, row block, chunk, batch*head), column blocks fastest
+    unsigned rem;
+    unsigned wg = tile_divmod(xcd_remap(blockIdx.x, gridDim.x), (unsigned)a.d2 / BD2, a.sh_gx, rem);
+    const int nb2 = __builtin_amdgcn_readfirstlane((int)rem);
+    wg = tile_divmod(wg, (unsigned)a.L / (32 * NW), a.sh_gy, rem);
+    const int rbi = __builtin_amdgcn_readfirstlane((int)rem);
+    tile_body_bf16<D1, BD2, NW, MODE, OCC, SPLIT, NOE, PAD, FUSE, true>(a, TileLds{smem, ldsE, ldsW, ldsS, ldsWr, ldsM, ldsN}, nb2, rbi, wg);
 }
 
 }  // namespace tfla

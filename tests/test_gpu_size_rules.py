@@ -73,6 +73,19 @@ def test_wide_output_blocks(variant, B, NH, T, dqk, dhv, chunk):
     _check_slices(w)
 
 
+# dV, dQ and dK in one launch: all kernel widths up to 256 on either side, two- and four-wavefront workgroups, several row
+# blocks, a number of heads that is no multiple of the XCDs, tensors that end inside a block; and the first shape past the rule
+@pytest.mark.parametrize("variant,NH,T,dqk,dhv,chunk", [
+    (wl.EXP, 3, 512, 64, 64, 256), (wl.SIG, 8, 192, 64, 128, 64), (wl.EXP, 2, 300, 64, 256, 128),
+    (wl.SIG, 5, 384, 128, 64, 384), (wl.EXP, 8, 130, 120, 128, 64), (wl.EXP, 1, 1000, 128, 200, 512),
+    (wl.EXP, 3, 256, 256, 64, 64), (wl.SIG, 2, 449, 256, 128, 128), (wl.EXP, 8, 512, 256, 256, 256),
+    (wl.EXP, 3, 256, 256, 264, 128),
+])
+def test_gradients_in_one_launch(variant, NH, T, dqk, dhv, chunk):
+    w = wl.small(variant, wl.BF16, B=1, NH=NH, T=T, dqk=dqk, dhv=dhv, chunk=chunk, seed=600 + T + dqk)
+    _check_slices(w, dCn=True)
+
+
 # tensors that end before the kernels' blocks do: whole row blocks, pieces and column blocks past the end, odd remainders,
 # initial state and upstream state gradient, both ways of the backward pass (kept and recomputed states)
 @pytest.mark.parametrize("keep", [True, False])
