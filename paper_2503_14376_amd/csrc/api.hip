@@ -439,8 +439,9 @@ int bwd_impl(const void* q, const void* k, const void* v, const float* i_pre, co
     // dK: rows = kv index j
     t.X = v; t.Y = dH; t.Z = q; t.Out = dk; t.wrow_lo = ucol_lo; t.wcol_lo = wrowB_lo; t.wrow = ucol; t.wcol = wrowB; t.srow = aK; t.St = w.dcT;
     t.dotwith = k; t.dotpart = w.partK;
-    if (grads_in_one_launch(d.dqk, d.dhv, dtype, chunk, d.BHT)) {
-        TFLA_LAUNCH(K_TILE_GRADS, launch_grads(tv, tq, t, (int)d.BH, s));
+    const bool one = grads_in_one_launch(d.dqk, d.dhv, dtype, chunk, d.BHT);
+    if (one) {
+        TFLA_LAUNCH(K_TILE_GRADS, launch_grads(tv, tq, t, (int)d.BH, dtype, s));
     } else {
         TFLA_LAUNCH(K_TILE_DV, launch_tile_mode<MODE_DV>(tv, (int)d.BH, dtype, s));
         TFLA_LAUNCH(K_TILE_DQ, launch_tile_mode<MODE_DQ>(tq, (int)d.BH, dtype, s));
@@ -450,7 +451,9 @@ int bwd_impl(const void* q, const void* k, const void* v, const float* i_pre, co
     // 5. gate gradients
     if (dCn) TFLA_LAUNCH(K_STATE_DOT, launch_state_dot(Cfinal, (long)d.dqk * d.dhv, d.dhv, dCn, dqk, dhv, w.cdot, (int)d.BH, s));
     GateGradArgs gg;
-    gg.partQ = w.partQ; gg.nbQ = w.nbQ; gg.partK = w.partK; gg.nbK = w.nbK; gg.cdot = dCn ? w.cdot : nullptr;
+    // (the fp32 kernel for all three may take wider blocks than the workspace was sized for)
+    const int nb = dtype != TFLA_BF16 && one && grads_f32_wide(d.dqk, d.dhv, d.BHT) && d.dqk >= 128 ? d.dqk / 128 : w.nbQ;
+    gg.partQ = w.partQ; gg.nbQ = nb; gg.partK = w.partK; gg.nbK = nb; gg.cdot = dCn ? w.cdot : nullptr;
     gg.i_pre = i_pre; gg.f_pre = f_pre; gg.d_i = d_i_pre; gg.d_f = d_f_pre; gg.T = d.T; gg.Tvalid = T; gg.variant = variant;
     gg.BHT = d.BHT; gg.bsum = w.bsum; gg.softcap = softcap;
     gg.anchor = nullptr; gg.L = chunk; gg.Nc = d.Nc; gg.G = 1; gg.npart = 0;

@@ -250,20 +250,29 @@ inline int tile_bd2(int d1, int d2, int dtype, int L, long rows) {
     if (d2 % 128 == 0 && (dtype == 1 || (rows / 64) * (d2 / 128) >= 512)) return 128;
     return 64;
 }
-// dV, dQ and dK in one launch (tile_grads.hip): bf16, where dQ and dK need not hand E over (d_hv up to 256) and every part
-// fits two workgroups per CU (contractions up to 256 columns; wider ones hold their X rows in half of the register file),
-// with the block widths that kernel is built for (tile_width_override may ask for others).  Faster at every size measured,
-// 6 to 37 % of forward + backward, from one sequence of 777 steps to 128 heads of 32.
+// dV, dQ and dK in one launch (tile_grads.hip), where dQ and dK need not hand E over.
+// bf16: d_hv up to 256, and every part fits two workgroups per CU (contractions up to 256 columns; wider ones hold their X rows
+// in half of the register file), with the block widths that kernel is built for (tile_width_override may ask for others).
+// Faster at every size measured, 6 to 37 % of forward + backward, from one sequence of 777 steps to 128 heads of 32.
+// fp32: the same widths.  What the kernels wait for there is the matrix unit, and what one launch gains is the chip filled
+// once instead of three times: 44 % of forward + backward for one head of 64 and 256 steps, 24 % for 8 heads of 256 and 500
+// steps, 2 to 12 % where each launch fills it many times over.  In the middle, two-wavefront workgroups (chunk sizes that are
+// no multiple of 128) of a 256-wide d_hv and a narrow d_qk lose 6 to 8 % from 32768 rows on (16 heads of 128 / 256, batch 2,
+// 1024 steps 334 -> 354 us; with batch 3 and 8 heads, 24576 rows, 353 -> 298), and wide heads are not worth it from 65536 on.
 inline bool grads_in_one_launch(int dqk, int dhv, int dtype, int L, long rows) {
-    return dtype == 1 && dqk <= 256 && dhv <= 256 && tile_bd2(dqk, dhv, dtype, L, rows) == (dhv >= 128 ? 128 : 64) &&
-           tile_bd2(dhv, dqk, dtype, L, rows) == (dqk >= 128 ? 128 : 64);
+    if (dqk > 256 || dhv > 256) return false;
+    if (dtype != 1) return (dqk <= 128 && dhv <= 128) || rows < (L % 128 != 0 && dhv > 128 && dqk <= 128 ? 32768 : 65536);
+    return tile_bd2(dqk, dhv, dtype, L, rows) == (dhv >= 128 ? 128 : 64) && tile_bd2(dhv, dqk, dtype, L, rows) == (dqk >= 128 ? 128 : 64);
 }
-template <int DQK> hipError_t launch_tile_grads(const TileArgs& dv, const TileArgs& dq, const TileArgs& dk, int BH, hipStream_t s);
-inline hipError_t launch_grads(const TileArgs& dv, const TileArgs& dq, const TileArgs& dk, int BH, hipStream_t s) {
+// fp32, all three in one launch: 64-column blocks while 128 would leave fewer than 512 workgroups of two wavefronts (never
+// narrower than tile_bd2(), whose launches have the chip to themselves: 16 heads of 128 / 256, 1024 steps 128 wide)
+inline bool grads_f32_wide(int dqk, int dhv, long rows) { return (rows / 64) * (dhv / 128 + 2 * (dqk / 128)) >= 512; }
+template <int DQK> hipError_t launch_tile_grads(const TileArgs& dv, const TileArgs& dq, const TileArgs& dk, int BH, int dtype, hipStream_t s);
+inline hipError_t launch_grads(const TileArgs& dv, const TileArgs& dq, const TileArgs& dk, int BH, int dtype, hipStream_t s) {
     switch (dv.d1) {
-        case 64: return launch_tile_grads<64>(dv, dq, dk, BH, s);
-        case 128: return launch_tile_grads<128>(dv, dq, dk, BH, s);
-        case 256: return launch_tile_grads<256>(dv, dq, dk, BH, s);
+        case 64: return launch_tile_grads<64>(dv, dq, dk, BH, dtype, s);
+        case 128: return launch_tile_grads<128>(dv, dq, dk, BH, dtype, s);
+        case 256: return launch_tile_grads<256>(dv, dq, dk, BH, dtype, s);
         default: return hipErrorInvalidValue;
     }
 }

@@ -81,8 +81,25 @@ def test_wide_output_blocks(variant, B, NH, T, dqk, dhv, chunk):
     (wl.EXP, 3, 256, 256, 64, 64), (wl.SIG, 2, 449, 256, 128, 128), (wl.EXP, 8, 512, 256, 256, 256),
     (wl.EXP, 3, 256, 256, 264, 128),
 ])
-def test_gradients_in_one_launch(variant, NH, T, dqk, dhv, chunk):
-    w = wl.small(variant, wl.BF16, B=1, NH=NH, T=T, dqk=dqk, dhv=dhv, chunk=chunk, seed=600 + T + dqk)
+@pytest.mark.parametrize("dtype", [wl.BF16, wl.F32])
+def test_gradients_in_one_launch(dtype, variant, NH, T, dqk, dhv, chunk):
+    w = wl.small(variant, dtype, B=1, NH=NH, T=T, dqk=dqk, dhv=dhv, chunk=chunk, seed=600 + T + dqk)
+    _check_slices(w, dCn=True)
+
+
+# fp32: 128-wide blocks in the one launch (512 workgroups of two wavefronts and more), and both sides of the rules that keep
+# three launches
+@pytest.mark.parametrize("variant,B,NH,T,dqk,dhv,chunk", [
+    (wl.SIG, 2, 8, 1024, 128, 256, 64),         # one launch, 128-wide blocks
+    (wl.EXP, 2, 8, 512, 128, 256, 64),          # exactly 512 workgroups
+    (wl.EXP, 1, 15, 512, 128, 256, 64),         # 480
+    (wl.EXP, 2, 8, 500, 256, 104, 128),
+    (wl.SIG, 2, 16, 1024, 128, 256, 64),        # 32768 rows: three launches
+    (wl.EXP, 4, 16, 1024, 256, 64, 256),        # 65536 rows
+    (wl.EXP, 4, 16, 1024, 128, 128, 64),        # 65536 rows of narrow heads: one launch
+])
+def test_gradients_in_one_launch_fp32_rules(variant, B, NH, T, dqk, dhv, chunk):
+    w = wl.small(variant, wl.F32, B=B, NH=NH, T=T, dqk=dqk, dhv=dhv, chunk=chunk, seed=650 + T + dqk)
     _check_slices(w, dCn=True)
 
 
