@@ -288,4 +288,38 @@ template <int COLS> struct TFragReader {
     }
 };
 
+// Prefetch into the XCD's L2 for the recurrent kernels: the workgroups that hold the state tiles of one (batch, head) read the
+// same rows of X and Y at about the same time, so all their requests together wait for one trip to memory per line, and what is
+// on its way is a fraction of what the rings hold.  Here every one of them requests its share of the 128-byte lines of a piece
+// AHEAD pieces ahead, four bytes per line, into a scrap of LDS that nobody reads.
+template <int BK, int AHEAD> struct LinePrefetch {
+    bool on = false;
+    const char* base;
+    uint32_t vo, dst;
+    int row, sub = 0, left, rows, ld2;
+    // T: one of the two tensors (rows of `ld` values, `steps` of them per (batch, head)) of whose `width` columns the
+    // `sharers` workgroups read all; this one is number `index`.  P pieces, the first at row0.
+    __device__ __forceinline__ void init(const void* T, long bh, int ld, int steps, int width, int sharers, int index, int P, long row0, int lane,
+                                         uint32_t scrap) {
+        const int lpr = width / 64, per = BK * lpr / sharers;         // lines per row, lines per workgroup
+        // Whole shares of at most one line per lane.  With eight sharers (heads of 256, of 128 / 256) and on short sequences
+        // there is nothing to gain: 64 heads of 256, 2048 steps 65 / 58 us per launch without, 67 / 60 with.
+        on = sharers >= 16 && P >= 4 * AHEAD && per >= 1 && per <= 64 && per * sharers == BK * lpr && steps >= BK && ((uintptr_t)T & 3) == 0;
+        base = reinterpret_cast<const char*>(T) + bh * steps * (long)ld * 2;
+        const int q = index * per + (lane < per ? lane : per - 1);
+        const int col = (q % lpr) * 128;
+        vo = (uint32_t)((q / lpr) * ld * 2 + (col < ld * 2 ? col : ld * 2 - 16));
+        dst = scrap; row = (int)row0; left = P - 1; rows = steps; ld2 = ld * 2;
+    }
+    __device__ __forceinline__ void advance(int PPC, int step_rows, int wrap_rows) {
+        if (left <= 0) return;
+        --left;
+        const bool wrap = ++sub == PPC;
+        row += wrap ? wrap_rows : step_rows;
+        if (wrap) sub = 0;
+    }
+    // one load per call, also where the piece is not there to prefetch: callers count them
+    __device__ __forceinline__ void issue() const { dma4(base + (long)(row + BK <= rows ? row : 0) * ld2, vo, dst); }
+};
+
 }  // namespace tfla

@@ -63,8 +63,12 @@ __global__ void __launch_bounds__(WN * 128) recurrent_kernel_bf16(RecArgs a) {
     constexpr int CPP = DX::N + BK / 64 + 1;        // loads per producer and piece (X, row scales, gbar)
     constexpr int CPC = DY::N;                      // loads per consumer and piece (Y)
     constexpr int NST = 4;                          // state stores per consumer at a chunk boundary
+    // pieces that the lines of X and Y are brought into L2 ahead (LinePrefetch).  16 heads 256 / 512, chunk 256, 8192 steps: 113 / 107.5
+    // us per launch forward / reversed without, 105.8 / 104.7 with 3, 104.6 / 103.7 with 4, 108.1 / 106.3 with 6; 64 heads and
+    // 4096 steps 218 / 203, 205 / 198, 205 / 197, 215 / 204.
+    constexpr int AHEAD = 4;
     constexpr int STEADY = (NS - 2) * CPP, STEADY_C = (NS - 2) * CPC;
-    static_assert(STEADY + 2 * (NH + 1) <= 63 && STEADY_C + (NH + 1) * NST <= 63, "wait counts must fit the 6-bit counter");
+    static_assert(STEADY + NS - 1 + 2 * (NH + 1) <= 63 && STEADY_C + (NH + 1) * NST <= 63, "wait counts must fit the 6-bit counter");
     static_assert(CPC % KS == 0, "Y requests are spread evenly over the k steps");
 
     __shared__ __attribute__((aligned(1024))) char smem[NS * STAGE];
@@ -72,6 +76,7 @@ __global__ void __launch_bounds__(WN * 128) recurrent_kernel_bf16(RecArgs a) {
     __shared__ __attribute__((aligned(256))) float ldsRs[NS][BK];
     __shared__ __attribute__((aligned(256))) float ldsG[NS][64];
     __shared__ __attribute__((aligned(256))) float ldsNx[2][WN][BM];            // column sums of scaled X, per producer
+    __shared__ __attribute__((aligned(256))) float ldsPf[2][64];                // where the prefetches go
     TFLA_RTL_DECL
 
     const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, g = lane >> 5;
@@ -120,6 +125,15 @@ __global__ void __launch_bounds__(WN * 128) recurrent_kernel_bf16(RecArgs a) {
         const float* greq = a.gbar + (long)bh * a.Nc + (a.reverse ? a.Nc - 1 : 0);
         const long step_rows = BK, wrap_rows = a.reverse ? (long)BK - 2L * a.L : (long)BK;
         const long gstep = a.reverse ? -1 : 1;
+        // producer 0 prefetches X, producer 1 Y
+        LinePrefetch<BK, AHEAD> pf;
+        if (!PAD && wc < 2) {       // (tensors that end inside a piece: 58.4 us without, 58.6 with, 16 heads and 4000 steps)
+            pf.init(wc == 0 ? a.X : a.Y, bh, wc == 0 ? xld : yld, tld, wc == 0 ? a.d1 : a.d2, (int)(gridDim.x * gridDim.y), by * (int)gridDim.x + bx, P,
+                    row0, lane, lds_addr(ldsPf) + 256u * wc);
+            if (pf.on)
+                for (int p = 0; p < AHEAD; ++p) pf.advance(PPC, (int)step_rows, (int)wrap_rows);
+        }
+        const int cpp = CPP + (pf.on ? 1 : 0), own = pf.on ? 1 : 0;    // loads per piece; its own prefetch, issued last, need not have landed
         int lsub = 0, lslot = 0;
         uint32_t lst = smem_a;
         auto request = [&]() {
@@ -136,12 +150,14 @@ __global__ void __launch_bounds__(WN * 128) recurrent_kernel_bf16(RecArgs a) {
             xreq += dr * xld; rsreq += dr; xleft -= (int)dr;
             if (wrap) { lsub = 0; greq += gstep; }
             if (++lslot == NS) { lslot = 0; lst = smem_a; } else lst += STAGE;
+            if (pf.on) { pf.issue(); pf.advance(PPC, (int)step_rows, (int)wrap_rows); }
         };
         // Rescale, in place, this wave's own chunks of the X piece in `slot` (piece of chunk step
         // `stp`, last piece of its chunk if `closes`), after waiting until at most `pending` younger
         // operations of this wave are outstanding.
         auto rescale = [&](int slot, int stp, bool closes, int pending, int tl = -1) {
             if (pending == STEADY) wait_vmcnt<STEADY>();
+            else if (pending == STEADY + NS - 1) wait_vmcnt<STEADY + NS - 1>();
             else wait_vmcnt_dyn(pending);
             TFLA_RTL(tl);
             char* xt = smem + slot * STAGE;
@@ -184,7 +200,7 @@ __global__ void __launch_bounds__(WN * 128) recurrent_kernel_bf16(RecArgs a) {
 #pragma unroll
         for (int p = 0; p < NS - 1; ++p)
             if (p < P) { request(); ++requested; }
-        rescale(0, 0, PPC == 1, (requested - 1) * CPP);
+        rescale(0, 0, PPC == 1, (requested - 1) * cpp + own);
 
         // Iteration i (consumers multiply piece i): request piece i + NS - 1 into the slot of piece
         // i - 1, which the consumers have left; rescale piece i + 1.  (sub, step, slot) describe
@@ -223,7 +239,7 @@ __global__ void __launch_bounds__(WN * 128) recurrent_kernel_bf16(RecArgs a) {
                 // issued since (this iteration's and those of the NS - 3 iterations before)
                 int ahead = P - 2 - i;
                 ahead = ahead > NS - 2 ? NS - 2 : ahead;
-                int pending = ahead * CPP + st0;
+                int pending = ahead * cpp + own + st0;
 #pragma unroll
                 for (int h = 0; h < NH; ++h) pending += sth[h];
                 rescale(slot1, step1, sub1 == PPC - 1, pending, 4 * i + 3);
@@ -235,6 +251,7 @@ __global__ void __launch_bounds__(WN * 128) recurrent_kernel_bf16(RecArgs a) {
             sth[0] = st0;
         }
         if (n_owner && a.nfinal && (!PAD || lane < xcols)) a.nfinal[(long)bh * xld + m0 + lane] = nacc;
+        wait_vmcnt<0>();                                // (nothing is on its way into LDS when the workgroup ends)
     } else {
         // =============================== consumers ===========================================
         f32x16 acc[MI];

@@ -103,6 +103,18 @@ def test_gradients_in_one_launch_fp32_rules(variant, B, NH, T, dqk, dhv, chunk):
     _check_slices(w, dCn=True)
 
 
+# recurrent kernels that bring the lines of later pieces into L2: sequences of fewer, as many and more pieces than it reaches
+# ahead four times, both piece sizes, both tile widths, sequences and head dimensions that end inside a piece
+@pytest.mark.parametrize("variant,B,NH,T,dqk,dhv,chunk", [
+    (wl.EXP, 1, 8, 2944, 256, 512, 128), (wl.SIG, 1, 8, 3072, 256, 512, 128), (wl.EXP, 1, 3, 1600, 256, 512, 192),
+    (wl.EXP, 1, 4, 3500, 256, 320, 256), (wl.SIG, 3, 8, 1920, 256, 512, 128), (wl.EXP, 3, 8, 2048, 256, 512, 128),
+    (wl.EXP, 3, 8, 1100, 200, 456, 192), (wl.SIG, 1, 4, 1024, 1024, 1024, 64),
+])
+def test_recurrent_prefetch(variant, B, NH, T, dqk, dhv, chunk):
+    w = wl.small(variant, wl.BF16, B=B, NH=NH, T=T, dqk=dqk, dhv=dhv, chunk=chunk, seed=680 + T + dqk)
+    _check_slices(w)
+
+
 # tensors that end before the kernels' blocks do: whole row blocks, pieces and column blocks past the end, odd remainders,
 # initial state and upstream state gradient, both ways of the backward pass (kept and recomputed states)
 @pytest.mark.parametrize("keep", [True, False])
