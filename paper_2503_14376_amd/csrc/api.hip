@@ -221,8 +221,9 @@ void prof_collect() {
 
 int run_gates(const Dims& d, const float* i_pre, const float* f_pre, const float* m0, float* wrow, float* ucol,
               float* sH, float* aK, float* gbar, float* mout, float* mout_user, float* mfinal, float* tmp, float* csum, float* wrow_lo,
-              float* ucol_lo, float softcap, hipStream_t s) {
+              float* ucol_lo, float softcap, const FillList& zero, hipStream_t s) {
     GateArgs g;
+    g.zero = zero;
     g.softcap = softcap; g.Tvalid = d.T_in;
     g.i_pre = i_pre; g.f_pre = f_pre; g.m0 = d.variant == TFLA_EXP ? m0 : nullptr;
     g.T = d.T; g.L = d.L; g.Nc = d.Nc; g.variant = d.variant;
@@ -285,8 +286,16 @@ int fwd_impl(const void* q, const void* k, const void* v, const float* i_pre, co
     // A state continued in place (mn is m0): the second of two gate launches reads m0 in every workgroup, so the final max
     // state waits in the memory of n_{k-1}, which the recurrent kernel writes later, until all of them have.
     const bool m_waits = is_exp && mn && mn == m0 && !gates_in_one_launch(d.Nc, chunk);
+    FillList zero{};
+    if (!is_exp) {
+        // the outputs that mLSTMsig does not have
+        if (nn) { zero.p[0] = nn; zero.n[0] = d.BH * dqk; }
+        if (mn) { zero.p[1] = mn; zero.n[1] = d.BH; }
+        if (n_out) { zero.p[2] = n_out; zero.n[2] = d.BH * T; }
+        if (m_out) { zero.p[3] = m_out; zero.n[3] = d.BH * T; }
+    }
     int st = run_gates(d, i_pre, f_pre, m0, w.wrow, w.ucol, w.sH, w.aK, w.gbar, mout, (is_exp && !own_mout) ? m_out : nullptr,
-                       !is_exp ? nullptr : (m_waits ? w.nst : mn), w.tmp, w.csum, w.wrow_lo, w.ucol_lo, softcap, s);
+                       !is_exp ? nullptr : (m_waits ? w.nst : mn), w.tmp, w.csum, w.wrow_lo, w.ucol_lo, softcap, zero, s);
     if (st != TFLA_OK) return st;
     if (m_waits) TFLA_LAUNCH(K_GATES, launch_copy(w.nst, mn, (int)d.BH, s));
 
@@ -317,15 +326,6 @@ int fwd_impl(const void* q, const void* k, const void* v, const float* i_pre, co
     }
     TFLA_LAUNCH(K_TILE_H, launch_tile_mode<MODE_H>(t, (int)d.BH, dtype, s));
 
-    if (!is_exp) {
-        // the outputs that mLSTMsig does not have, zero-filled in one launch
-        FillList fl{};
-        if (nn) { fl.p[0] = nn; fl.n[0] = d.BH * dqk; }
-        if (mn) { fl.p[1] = mn; fl.n[1] = d.BH; }
-        if (n_out) { fl.p[2] = n_out; fl.n[2] = d.BH * T; }
-        if (m_out) { fl.p[3] = m_out; fl.n[3] = d.BH * T; }
-        if (nn || mn || n_out || m_out) TFLA_LAUNCH(K_FILL, launch_fill_zero4(fl, s));
-    }
     return TFLA_OK;
 }
 
@@ -375,7 +375,7 @@ int bwd_impl(const void* q, const void* k, const void* v, const float* i_pre, co
 
     // 1. gates as in the forward pass, then fold 1/h_denom into the backward weights
     if (!reuse) {
-        int st = run_gates(d, i_pre, f_pre, m0, w.wrow, w.ucol, w.sH, w.aK, w.gbar, w.mout, nullptr, nullptr, w.tmp, w.csum, w.wrow_lo, w.ucol_lo, softcap, s);
+        int st = run_gates(d, i_pre, f_pre, m0, w.wrow, w.ucol, w.sH, w.aK, w.gbar, w.mout, nullptr, nullptr, w.tmp, w.csum, w.wrow_lo, w.ucol_lo, softcap, FillList{}, s);
         if (st != TFLA_OK) return st;
     }
     // mLSTMsig has no denominator (the weights are the forward pass's own); for mLSTMexp the forward call has left

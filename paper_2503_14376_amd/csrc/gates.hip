@@ -39,6 +39,13 @@ template <typename AT> __device__ __forceinline__ AT exp_t(AT x);
 template <> __device__ __forceinline__ float exp_t<float>(float x) { return expf(x); }
 template <> __device__ __forceinline__ double exp_t<double>(double x) { return exp(x); }
 
+// this thread's share of the arrays to zero, of `threads` in the launch
+__device__ __forceinline__ void zero_share(const FillList& f, long thread, long threads) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+        for (long i = thread; i < f.n[q]; i += threads) f.p[q][i] = 0.0f;
+}
+
 template <typename AT> __device__ __forceinline__ AT wave_excl_scan_add(AT v, int lane) {
     AT x = v;
 #pragma unroll
@@ -174,6 +181,7 @@ __global__ void __launch_bounds__(GATE_WAVES * 64) gates_chunk_kernel(GateArgs a
 
 template <typename AT>
 __global__ void __launch_bounds__(GATE_WAVES * 64) gates_step_kernel(GateArgs a) {
+    zero_share(a.zero, ((long)blockIdx.y * gridDim.x + blockIdx.x) * blockDim.x + threadIdx.x, (long)gridDim.x * gridDim.y * blockDim.x);
     extern __shared__ double cm_raw[];   // [Nc + 1] values of type AT: m before chunk k
     AT* cm = reinterpret_cast<AT*>(cm_raw);
     const int bh = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -254,6 +262,7 @@ __global__ void __launch_bounds__(GATE_WAVES * 64) gates_step_kernel(GateArgs a)
 // keep the two launches as well.
 template <int E, typename AT>
 __global__ void __launch_bounds__(GATE_FUSED_CHUNKS * 64) gates_fused_kernel(GateArgs a) {
+    zero_share(a.zero, (long)blockIdx.x * blockDim.x + threadIdx.x, (long)gridDim.x * blockDim.x);
     __shared__ AT cg[GATE_FUSED_CHUNKS], camax[GATE_FUSED_CHUNKS], m_init;
     const int bh = blockIdx.x, lane = threadIdx.x & 63, kc = threadIdx.x >> 6;
     const bool is_exp = a.variant == 0;
@@ -404,9 +413,10 @@ hipError_t launch_gate_bwd_prep(const GateBwdPrepArgs& a, hipStream_t s) {
 //   d i-bar_j = k_j . dk_j ,   d f-bar_s = sum_{t>=s} (q_t . dq_t - k_t . dk_t) + <C_T, dC_T>.
 // This regroups the cumulative-gate gradients of App. B.3 (delta g, delta a, delta b and the
 // row/column sums of the intra-chunk gate-matrix gradient) into one reverse cumulative sum.
-// Two kernels over blocks of GG_BLOCK steps: block sums first, then every block adds the sums of
-// the blocks after it and scans its own steps (in fp64: the terms cancel heavily).
-static constexpr int GG_BLOCK = 1024;
+// Over blocks of GG_BLOCK steps: every block adds the sums of the blocks after it and scans its own steps (in fp64: the
+// terms cancel heavily).  Up to GG_ONE blocks the block forms those sums itself; beyond, a launch before it leaves them
+// in memory once (the launch is 4 to 7 us, the terms of three blocks are read in one).
+static constexpr int GG_BLOCK = 1024, GG_ONE = 4;
 
 __device__ __forceinline__ double state_dot_sum(const GateGradArgs& a, int bh) {
     double s = 0.0;
@@ -422,11 +432,10 @@ __device__ __forceinline__ void gate_grad_terms(const GateGradArgs& a, long idx,
     for (int nb = 0; nb < a.nbK; ++nb) c += a.partK[(long)nb * a.BHT + idx];
 }
 
-__global__ void __launch_bounds__(256) gate_grads_sum_kernel(GateGradArgs a) {
-    __shared__ double wt[4];
-    const int bh = blockIdx.y, blk = blockIdx.x, tid = threadIdx.x;
-    const long row = (long)bh * a.T;
+// this thread's part of the sum over block blk
+__device__ __forceinline__ double gate_grad_block_part(const GateGradArgs& a, long row, int blk, int tid) {
     double tot = 0.0;
+#pragma unroll
     for (int e = 0; e < GG_BLOCK / 256; ++e) {
         const int t = blk * GG_BLOCK + e * 256 + tid;
         if (t < a.T) {
@@ -435,6 +444,13 @@ __global__ void __launch_bounds__(256) gate_grads_sum_kernel(GateGradArgs a) {
             tot += (double)r - (double)c;
         }
     }
+    return tot;
+}
+
+__global__ void __launch_bounds__(256) gate_grads_sum_kernel(GateGradArgs a) {
+    __shared__ double wt[4];
+    const int bh = blockIdx.y, blk = blockIdx.x, tid = threadIdx.x;
+    double tot = gate_grad_block_part(a, (long)bh * a.T, blk, tid);
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) tot += __shfl_xor(tot, o, 64);
     if ((tid & 63) == 0) wt[tid >> 6] = tot;
@@ -450,7 +466,11 @@ __global__ void __launch_bounds__(256) gate_grads_kernel(GateGradArgs a) {
     const long row = (long)bh * a.T;
     // sum of the blocks after this one
     double later = 0.0;
-    for (int b2 = blk + 1 + tid; b2 < nblk; b2 += 256) later += a.bsum[(long)bh * nblk + b2];
+    if (nblk <= GG_ONE) {
+        for (int b2 = blk + 1; b2 < nblk; ++b2) later += gate_grad_block_part(a, row, b2, tid);
+    } else {
+        for (int b2 = blk + 1 + tid; b2 < nblk; b2 += 256) later += a.bsum[(long)bh * nblk + b2];
+    }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) later += __shfl_xor(later, o, 64);
     if (lane == 0) wt[wave] = later;
@@ -563,22 +583,15 @@ hipError_t launch_gate_grads(const GateGradArgs& a, int BH, hipStream_t s) {
         return hipGetLastError();
     }
     const dim3 grid((a.T + GG_BLOCK - 1) / GG_BLOCK, BH);
-    hipLaunchKernelGGL(gate_grads_sum_kernel, grid, dim3(256), 0, s, a);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
+    if (grid.x > GG_ONE) {
+        hipLaunchKernelGGL(gate_grads_sum_kernel, grid, dim3(256), 0, s, a);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
     hipLaunchKernelGGL(gate_grads_kernel, grid, dim3(256), 0, s, a);
     return hipGetLastError();
 }
 
-// up to four arrays in one launch: element i of the concatenation belongs to the first array whose end lies beyond i
-__global__ void __launch_bounds__(256) fill_zero4_kernel(FillList f) {
-    long i = (long)blockIdx.x * 256 + threadIdx.x;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        if (i < f.n[q]) { f.p[q][i] = 0.0f; return; }
-        i -= f.n[q];
-    }
-}
 __global__ void __launch_bounds__(256) copy_kernel(const float* from, float* to, int n) {
     const int i = blockIdx.x * 256 + threadIdx.x;
     if (i < n) to[i] = from[i];
@@ -587,17 +600,6 @@ hipError_t launch_copy(const float* from, float* to, int n, hipStream_t s) {
     hipLaunchKernelGGL(copy_kernel, dim3((n + 255) / 256), dim3(256), 0, s, from, to, n);
     return hipGetLastError();
 }
-hipError_t launch_fill_zero4(const FillList& f, hipStream_t s) {
-    long total = 0;
-    for (int q = 0; q < 4; ++q) {
-        if (f.n[q] < 0 || (f.n[q] > 0 && !f.p[q])) return hipErrorInvalidValue;
-        total += f.n[q];
-    }
-    if (total == 0) return hipSuccess;
-    hipLaunchKernelGGL(fill_zero4_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, f);
-    return hipGetLastError();
-}
-
 // Part p of <A[bh], Bm[bh]> over the d1 x d2 values of Bm (A's rows are lda apart): rows p, p + STATE_DOT_PARTS, ...,
 // the wavefronts of the workgroup one row each.  (One workgroup per (batch, head) took 17 us for 32 heads of 96 x 192, 12
 // us for 16 of 128 x 256; now 6 and 6.)

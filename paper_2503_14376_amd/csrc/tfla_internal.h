@@ -6,6 +6,8 @@
 
 namespace tfla {
 
+struct FillList { float* p[4]; long n[4]; };     // arrays to zero; n[q] = 0: slot unused
+
 // ---- chunkwise gates (App. B.2 "Chunkwise Gates", App. B.2 inter-chunk max state) ----------
 struct GateArgs {
     const float* i_pre;   // (BH, Tvalid)
@@ -29,6 +31,8 @@ struct GateArgs {
     // ucol + ucol_lo are the exponents to double accuracy); csum then holds doubles as well.  NULL / 0 otherwise.
     float* wrow_lo; float* ucol_lo; int precise;
     float* csum;          // (BH, 2, Nc) scratch: per-chunk sum of f-bar and max of a
+    // the outputs that mLSTMsig does not have, zeroed on the way (a launch of its own for them took 5 us)
+    FillList zero;
 };
 hipError_t launch_gates(const GateArgs& a, int BH, hipStream_t s);
 
@@ -61,8 +65,6 @@ struct GateGradArgs {
 };
 hipError_t launch_gate_grads(const GateGradArgs& a, int BH, hipStream_t s);
 
-struct FillList { float* p[4]; long n[4]; };     // n[q] = 0: slot unused
-hipError_t launch_fill_zero4(const FillList& f, hipStream_t s);
 hipError_t launch_copy(const float* from, float* to, int n, hipStream_t s);
 // out[bh] = <A[bh], Bm[bh]>; A (BH, *, lda), Bm (BH, d1, d2): the first d2 columns of the first d1 rows of A's `perA` values
 // as STATE_DOT_PARTS partial sums each

@@ -103,6 +103,12 @@ def test_gradients_in_one_launch_fp32_rules(variant, B, NH, T, dqk, dhv, chunk):
     _check_slices(w, dCn=True)
 
 
+# fp32 forget-gate scan: the blocks of 1024 steps after a block summed by itself (up to four blocks) or by a launch before it
+@pytest.mark.parametrize("variant,T", [(wl.EXP, 1024), (wl.SIG, 1100), (wl.EXP, 4096), (wl.SIG, 4097)])
+def test_fp32_gate_gradient_blocks(variant, T):
+    _check_slices(wl.small(variant, wl.F32, B=1, NH=2, T=T, dqk=64, dhv=64, chunk=64, seed=640 + T), dCn=True)
+
+
 # recurrent kernels that bring the lines of later pieces into L2: sequences of fewer, as many and more pieces than it reaches
 # ahead four times, both piece sizes, both tile widths, sequences and head dimensions that end inside a piece
 @pytest.mark.parametrize("variant,B,NH,T,dqk,dhv,chunk", [
