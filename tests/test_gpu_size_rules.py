@@ -109,6 +109,18 @@ def test_fp32_gate_gradient_blocks(variant, T):
     _check_slices(wl.small(variant, wl.F32, B=1, NH=2, T=T, dqk=64, dhv=64, chunk=64, seed=640 + T), dCn=True)
 
 
+# fp32 recurrent kernels: 256 state tiles of 64 x 64 and fewer (split pieces), more of them, and 128 x 128 ones; two and more
+# pieces per chunk, one chunk, numbers of pieces that are no multiple of four, tensors that end inside a tile and a piece
+@pytest.mark.parametrize("keep", [True, False])
+@pytest.mark.parametrize("variant,B,NH,T,dqk,dhv,chunk", [
+    (wl.EXP, 1, 1, 64, 64, 64, 64), (wl.SIG, 1, 3, 300, 72, 40, 192), (wl.EXP, 1, 16, 256, 256, 256, 128),
+    (wl.EXP, 1, 17, 200, 256, 256, 64), (wl.SIG, 1, 64, 128, 128, 128, 64), (wl.EXP, 2, 24, 130, 256, 256, 64),
+])
+def test_fp32_state_tiles(keep, variant, B, NH, T, dqk, dhv, chunk):
+    w = wl.small(variant, wl.F32, B=B, NH=NH, T=T, dqk=dqk, dhv=dhv, chunk=chunk, seed=660 + T + dqk, init_state=True)
+    _check_slices(w, dCn=True, keep=keep)
+
+
 # recurrent kernels that bring the lines of later pieces into L2: sequences of fewer, as many and more pieces than it reaches
 # ahead four times, both piece sizes, both tile widths, sequences and head dimensions that end inside a piece
 @pytest.mark.parametrize("variant,B,NH,T,dqk,dhv,chunk", [
