@@ -172,9 +172,9 @@ BwdWs carve_bwd(const Dims& d, void* ws) {
 
 // ---- optional per-kernel timing with HIP events on the caller's stream -------------------
 enum { K_GATES = 0, K_BWD_PREP, K_REC_FWD, K_REC_BWD, K_TILE_H, K_TILE_DV, K_TILE_DQ, K_TILE_DK, K_GATE_GRADS,
-       K_STATE_DOT, K_FILL, K_STEP, K_NORM_FWD, K_NORM_BWD, K_GAIN, K_TILE_GRADS, K_COUNT };
+       K_STATE_DOT, K_STEP, K_NORM_FWD, K_NORM_BWD, K_GAIN, K_TILE_GRADS, K_COUNT };
 const char* const kKernelNames[K_COUNT] = {"gates", "gate_bwd_prep", "recurrent_fwd", "recurrent_bwd", "tile_H",
-                                           "tile_dV", "tile_dQ", "tile_dK", "gate_grads", "state_dot", "fill_zero",
+                                           "tile_dV", "tile_dQ", "tile_dK", "gate_grads", "state_dot",
                                            "recurrent_step", "norm_gate_fwd", "norm_gate_bwd", "transfer_gain", "tile_grads"};
 struct Profiler {
     bool on = false;
@@ -439,7 +439,8 @@ int bwd_impl(const void* q, const void* k, const void* v, const float* i_pre, co
     // dK: rows = kv index j
     t.X = v; t.Y = dH; t.Z = q; t.Out = dk; t.wrow_lo = ucol_lo; t.wcol_lo = wrowB_lo; t.wrow = ucol; t.wcol = wrowB; t.srow = aK; t.St = w.dcT;
     t.dotwith = k; t.dotpart = w.partK;
-    const bool one = grads_in_one_launch(d.dqk, d.dhv, dtype, chunk, d.BHT);
+    // (bf16 dK may be written over K: the launches of dV and dQ, which read K, have to be over then)
+    const bool one = dk != k && grads_in_one_launch(d.dqk, d.dhv, dtype, chunk, d.BHT);
     if (one) {
         TFLA_LAUNCH(K_TILE_GRADS, launch_grads(tv, tq, t, (int)d.BH, dtype, s));
     } else {

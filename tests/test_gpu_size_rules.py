@@ -87,6 +87,25 @@ def test_gradients_in_one_launch(dtype, variant, NH, T, dqk, dhv, chunk):
     _check_slices(w, dCn=True)
 
 
+# bf16: dK written over K, which dV and dQ read, takes three launches and gives the same bits
+@pytest.mark.parametrize("dqk,dhv", [(64, 64), (256, 128)])
+def test_key_gradient_in_place(dqk, dhv):
+    import paper_2503_14376_amd as tfla
+    from tests import gpu_util as gu
+    w = wl.small(wl.EXP, wl.BF16, B=4, NH=16, T=1024, dqk=dqk, dhv=dhv, chunk=128, seed=630 + dqk)
+    dev = gu.dev_inputs(w, wl.make_inputs(w))
+    x = [dev[n] for n in ("q", "k", "v", "i_pre", "f_pre")]
+    f = tfla.mlstm_fwd(*x, chunk=128, variant=w.variant, eps=1e-6)
+    call = lambda out: tfla.mlstm_bwd(*x, dev["dH"], f["n_out"], f["m_out"], chunk=128, variant=w.variant, eps=1e-6,
+                                      fwd_workspace=f["workspace"], out=out)
+    apart = call(None)
+    over = call(dict({n: torch.empty_like(apart[n]) for n in ("dq", "dv", "d_i_pre", "d_f_pre", "dC0")}, dk=x[1]))
+    torch.cuda.synchronize()
+    assert over["dk"].data_ptr() == x[1].data_ptr()
+    for n in ("dq", "dk", "dv", "d_i_pre", "d_f_pre", "dC0"):
+        assert torch.equal(apart[n], over[n]), n
+
+
 # fp32: 128-wide blocks in the one launch (512 workgroups of two wavefronts and more), and both sides of the rules that keep
 # three launches
 @pytest.mark.parametrize("variant,B,NH,T,dqk,dhv,chunk", [
