@@ -181,7 +181,7 @@ __global__ void __launch_bounds__(GATE_WAVES * 64) gates_chunk_kernel(GateArgs a
 
 template <typename AT>
 __global__ void __launch_bounds__(GATE_WAVES * 64) gates_step_kernel(GateArgs a) {
-    zero_share(a.zero, ((long)blockIdx.y * gridDim.x + blockIdx.x) * blockDim.x + threadIdx.x, (long)gridDim.x * gridDim.y * blockDim.x);
+    if (a.variant != 0) zero_share(a.zero, ((long)blockIdx.y * gridDim.x + blockIdx.x) * blockDim.x + threadIdx.x, (long)gridDim.x * gridDim.y * blockDim.x);
     extern __shared__ double cm_raw[];   // [Nc + 1] values of type AT: m before chunk k
     AT* cm = reinterpret_cast<AT*>(cm_raw);
     const int bh = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -262,7 +262,7 @@ __global__ void __launch_bounds__(GATE_WAVES * 64) gates_step_kernel(GateArgs a)
 // keep the two launches as well.
 template <int E, typename AT>
 __global__ void __launch_bounds__(GATE_FUSED_CHUNKS * 64) gates_fused_kernel(GateArgs a) {
-    zero_share(a.zero, (long)blockIdx.x * blockDim.x + threadIdx.x, (long)gridDim.x * blockDim.x);
+    if (a.variant != 0) zero_share(a.zero, (long)blockIdx.x * blockDim.x + threadIdx.x, (long)gridDim.x * blockDim.x);
     __shared__ AT cg[GATE_FUSED_CHUNKS], camax[GATE_FUSED_CHUNKS], m_init;
     const int bh = blockIdx.x, lane = threadIdx.x & 63, kc = threadIdx.x >> 6;
     const bool is_exp = a.variant == 0;

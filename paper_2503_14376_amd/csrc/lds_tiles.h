@@ -304,7 +304,9 @@ template <int BK, int AHEAD> struct LinePrefetch {
         const int lpr = width / 64, per = BK * lpr / sharers;         // lines per row, lines per workgroup
         // Whole shares of at most one line per lane.  With eight sharers (heads of 256, of 128 / 256) and on short sequences
         // there is nothing to gain: 64 heads of 256, 2048 steps 65 / 58 us per launch without, 67 / 60 with.
-        on = sharers >= 16 && P >= 4 * AHEAD && per >= 1 && per <= 64 && per * sharers == BK * lpr && steps >= BK && ((uintptr_t)T & 3) == 0;
+        // Nor with more than an XCD runs at a time (32), whose shares come too late or into other L2s: 4 sequences of 4 heads of
+        // 1024, 128 sharers, 4096 steps, forward + backward 2745 us without, 2774 with.
+        on = sharers >= 16 && sharers <= 32 && P >= 4 * AHEAD && per >= 1 && per <= 64 && per * sharers == BK * lpr && steps >= BK && ((uintptr_t)T & 3) == 0;
         base = reinterpret_cast<const char*>(T) + bh * steps * (long)ld * 2;
         const int q = index * per + (lane < per ? lane : per - 1);
         const int col = (q % lpr) * 128;

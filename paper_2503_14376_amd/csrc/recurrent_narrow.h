@@ -91,11 +91,13 @@ __global__ void __launch_bounds__(512) recurrent_narrow_kernel_bf16(RecArgs a) {
         uint32_t lst = ya;
         // requester 0 prefetches X, requester 1 Y
         LinePrefetch<BK, AHEAD> pf;
-        const int rw = __builtin_amdgcn_readfirstlane(rtid >> 6);
-        pf.init(rw == 0 ? a.X : a.Y, bh, rw == 0 ? xld : yld, tld, rw == 0 ? a.d1 : a.d2, (int)(gridDim.x * gridDim.y), by * (int)gridDim.x + bx, P, row0,
-                lane, lds_addr(ldsPf) + 256u * rw);
-        if (pf.on)
-            for (int p = 0; p < AHEAD; ++p) pf.advance(PPC, step_rows, wrap_rows);
+        if constexpr (!PAD) {       // (tensors that end inside a piece are left as they were: 8 heads, 1000 steps with layer 39.4 us without, 40.3 with)
+            const int rw = __builtin_amdgcn_readfirstlane(rtid >> 6);
+            pf.init(rw == 0 ? a.X : a.Y, bh, rw == 0 ? xld : yld, tld, rw == 0 ? a.d1 : a.d2, (int)(gridDim.x * gridDim.y),
+                    by * (int)gridDim.x + bx, P, row0, lane, lds_addr(ldsPf) + 256u * rw);
+            if (pf.on)
+                for (int p = 0; p < AHEAD; ++p) pf.advance(PPC, step_rows, wrap_rows);
+        }
         auto request = [&]() {
             if constexpr (PAD) dy.template issue_bounded<true>(yreq, bounded_bytes(yleft, ycols, 2 * yld), ycols, lst, rtid);
             else dy.issue(yreq, lst, rtid);
