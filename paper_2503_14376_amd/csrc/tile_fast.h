@@ -176,6 +176,10 @@ __device__ __forceinline__ void tile_body_bf16(const TileArgs& a, const TileLds&
     using DYT = typename std::conditional<ELITE, DmaTile<BC, BR, NT, SWZ_T>, DmaTile<BC, D1, NT, SWZ_K>>::type;
     DYT dy;    dy.init(ELITE ? a.L : xld, tid);
     DmaTile<BC, BD2, NT, SWZ_T> dz;   dz.init(zld, tid);
+    if constexpr (PAD) {
+        if constexpr (!ELITE) dy.bound_columns(a.in_cols1, tid);
+        dz.bound_columns(cols2, tid);
+    }
     // E of this chunk: (L, L), rows = query index; the dK kernel reads the columns of its own rows
     const bf16_t* Eb = reinterpret_cast<const bf16_t*>(a.E) + ((long)bh * a.Nc + kc) * a.L * a.L + (ELITE ? r0 : 0);
     constexpr int CS = DS::N;
@@ -208,12 +212,12 @@ __device__ __forceinline__ void tile_body_bf16(const TileArgs& a, const TileLds&
                 dy.template issue<true>(Eb + (long)ct * BC * a.L, st, tid);
             } else if constexpr (PAD) {
                 dy.template issue_bounded<true>(Y + (long)ct * BC * xld, bounded_bytes(steps_left - ct * BC, a.in_cols1, 2 * xld),
-                                                       a.in_cols1, st, tid);
+                                                       D1, st, tid);
             } else {
                 dy.issue(Y + (long)ct * BC * xld, st, tid);
             }
             if constexpr (PAD)
-                dz.template issue_bounded<true>(Z + (long)ct * BC * zld, bounded_bytes(steps_left - ct * BC, cols2, 2 * zld), cols2,
+                dz.template issue_bounded<true>(Z + (long)ct * BC * zld, bounded_bytes(steps_left - ct * BC, cols2, 2 * zld), BD2,
                                                        st + YB, tid);
             else dz.issue(Z + (long)ct * BC * zld, st + YB, tid);
             if (!ELITE) {
@@ -242,12 +246,12 @@ __device__ __forceinline__ void tile_body_bf16(const TileArgs& a, const TileLds&
                 dy.template issue_part<true>(Eb + (long)ct * BC * a.L, st, tid, part, nparts);
             } else if constexpr (PAD) {
                 dy.template issue_bounded<false>(Y + (long)ct * BC * xld, bounded_bytes(steps_left - ct * BC, a.in_cols1, 2 * xld),
-                                                        a.in_cols1, st, tid, part, nparts);
+                                                        D1, st, tid, part, nparts);
             } else {
                 dy.issue_part(Y + (long)ct * BC * xld, st, tid, part, nparts);
             }
             if constexpr (PAD)
-                dz.template issue_bounded<false>(Z + (long)ct * BC * zld, bounded_bytes(steps_left - ct * BC, cols2, 2 * zld), cols2,
+                dz.template issue_bounded<false>(Z + (long)ct * BC * zld, bounded_bytes(steps_left - ct * BC, cols2, 2 * zld), BD2,
                                                         st + YB, tid, part, nparts);
             else dz.issue_part(Z + (long)ct * BC * zld, st + YB, tid, part, nparts);
             if (!ELITE) {
