@@ -137,6 +137,10 @@ TFLA_API size_t tfla_static_scratch_bytes(void);
  *        dCn (B, NH, dqk, dhv) gradient w.r.t. the returned final state, or NULL for zero.
  *   out: dq, dk (B, NH, T, dqk), dv (B, NH, T, dhv) in `dtype`; d_i_pre, d_f_pre (B, NH, T)
  *        float; dC0 (B, NH, dqk, dhv) float or NULL.  No gradient is produced for n0, m0.
+ *        dq, dk and dv must not overlap q, k, v or dH, except that dk may be the whole buffer of
+ *          k (bf16 only);
+ *          v, where dqk = dhv is at most 128 (bf16) or 64 (fp32);
+ *          q or (dqk = dhv) dH, within the same widths and where the chunk is 64 or 128.
  *   fwd_workspace, fwd_workspace_bytes: NULL / 0, or the workspace of the forward call with
  *        exactly these inputs, dimensions, chunk, variant and dtype, unmodified since that call
  *        (read only here).  With NULL the gate vectors and the chunk states are recomputed

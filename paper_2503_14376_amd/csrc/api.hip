@@ -234,6 +234,11 @@ int run_gates(const Dims& d, const float* i_pre, const float* f_pre, const float
     return TFLA_OK;
 }
 
+// whether two of the caller's tensors share memory
+inline bool overlap(const void* a, size_t na, const void* b, size_t nb) {
+    const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+    return a && b && x < y + nb && y < x + na;
+}
 inline bool misaligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) != 0; }
 // whether the caller's tensors end before the kernels' blocks do.  The kernels then read and write them in place, with
 // everything past their end taken as zero: a zero k, v (and upstream gradient) row or column adds nothing to any state,
@@ -439,8 +444,11 @@ int bwd_impl(const void* q, const void* k, const void* v, const float* i_pre, co
     // dK: rows = kv index j
     t.X = v; t.Y = dH; t.Z = q; t.Out = dk; t.wrow_lo = ucol_lo; t.wcol_lo = wrowB_lo; t.wrow = ucol; t.wcol = wrowB; t.srow = aK; t.St = w.dcT;
     t.dotwith = k; t.dotpart = w.partK;
-    // (bf16 dK may be written over K: the launches of dV and dQ, which read K, have to be over then)
-    const bool one = dk != k && grads_in_one_launch(d.dqk, d.dhv, dtype, chunk, d.BHT);
+    // (dK over an input: the launches of dV and dQ, which read all four, have to be over then.  dK's own workgroups read just
+    // their rows of K and V before they store them.)
+    const size_t nqk = (size_t)d.BH * T * dqk * d.esz, nhv = (size_t)d.BH * T * dhv * d.esz;
+    const bool dk_over_input = overlap(dk, nqk, k, nqk) || overlap(dk, nqk, v, nhv) || overlap(dk, nqk, q, nqk) || overlap(dk, nqk, dH, nhv);
+    const bool one = !dk_over_input && grads_in_one_launch(d.dqk, d.dhv, dtype, chunk, d.BHT);
     if (one) {
         TFLA_LAUNCH(K_TILE_GRADS, launch_grads(tv, tq, t, (int)d.BH, dtype, s));
     } else {

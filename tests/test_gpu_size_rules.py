@@ -87,21 +87,28 @@ def test_gradients_in_one_launch(dtype, variant, NH, T, dqk, dhv, chunk):
     _check_slices(w, dCn=True)
 
 
-# bf16: dK written over K, which dV and dQ read, takes three launches and gives the same bits
-@pytest.mark.parametrize("dqk,dhv", [(64, 64), (256, 128)])
-def test_key_gradient_in_place(dqk, dhv):
+# dK written over an input that dV and dQ read takes three launches and gives the same bits (what the header allows: over K in
+# bf16; over V where a workgroup reads its own rows only; over Q and dH where a chunk is one row block)
+@pytest.mark.parametrize("dtype,T,dqk,dhv,chunk,name", [
+    (wl.BF16, 1024, 64, 64, 128, "k"), (wl.BF16, 1024, 256, 128, 128, "k"),
+    (wl.BF16, 1024, 64, 64, 256, "v"), (wl.BF16, 1024, 128, 128, 256, "v"), (wl.BF16, 1000, 96, 96, 128, "v"), (wl.F32, 1024, 64, 64, 128, "v"),
+    (wl.BF16, 1024, 128, 128, 128, "q"), (wl.BF16, 1000, 64, 256, 64, "q"), (wl.F32, 1024, 64, 64, 64, "q"),
+    (wl.BF16, 1024, 64, 64, 64, "dH"), (wl.BF16, 1024, 128, 128, 128, "dH"), (wl.F32, 1000, 64, 64, 128, "dH"),
+])
+def test_key_gradient_in_place(dtype, T, dqk, dhv, chunk, name):
     import paper_2503_14376_amd as tfla
     from tests import gpu_util as gu
-    w = wl.small(wl.EXP, wl.BF16, B=4, NH=16, T=1024, dqk=dqk, dhv=dhv, chunk=128, seed=630 + dqk)
+    w = wl.small(wl.EXP, dtype, B=4, NH=16, T=T, dqk=dqk, dhv=dhv, chunk=chunk, seed=630 + dqk)
+    print("dK over", name, (dtype, T, dqk, dhv, chunk), flush=True)
     dev = gu.dev_inputs(w, wl.make_inputs(w))
     x = [dev[n] for n in ("q", "k", "v", "i_pre", "f_pre")]
-    f = tfla.mlstm_fwd(*x, chunk=128, variant=w.variant, eps=1e-6)
-    call = lambda out: tfla.mlstm_bwd(*x, dev["dH"], f["n_out"], f["m_out"], chunk=128, variant=w.variant, eps=1e-6,
+    f = tfla.mlstm_fwd(*x, chunk=chunk, variant=w.variant, eps=1e-6)
+    call = lambda out: tfla.mlstm_bwd(*x, dev["dH"], f["n_out"], f["m_out"], chunk=chunk, variant=w.variant, eps=1e-6,
                                       fwd_workspace=f["workspace"], out=out)
     apart = call(None)
-    over = call(dict({n: torch.empty_like(apart[n]) for n in ("dq", "dv", "d_i_pre", "d_f_pre", "dC0")}, dk=x[1]))
+    over = call(dict({n: torch.empty_like(apart[n]) for n in ("dq", "dv", "d_i_pre", "d_f_pre", "dC0")}, dk=dev[name]))
     torch.cuda.synchronize()
-    assert over["dk"].data_ptr() == x[1].data_ptr()
+    assert over["dk"].data_ptr() == dev[name].data_ptr()
     for n in ("dq", "dk", "dv", "d_i_pre", "d_f_pre", "dC0"):
         assert torch.equal(apart[n], over[n]), n
 
