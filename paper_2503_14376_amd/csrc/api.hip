@@ -291,13 +291,24 @@ int fwd_impl(const void* q, const void* k, const void* v, const float* i_pre, co
     // A state continued in place (mn is m0): the second of two gate launches reads m0 in every workgroup, so the final max
     // state waits in the memory of n_{k-1}, which the recurrent kernel writes later, until all of them have.
     const bool m_waits = is_exp && mn && mn == m0 && !gates_in_one_launch(d.Nc, chunk);
-    FillList zero{};
+    FillList zero{}, zero_last{};
     if (!is_exp) {
-        // the outputs that mLSTMsig does not have
-        if (nn) { zero.p[0] = nn; zero.n[0] = d.BH * dqk; }
-        if (mn) { zero.p[1] = mn; zero.n[1] = d.BH; }
-        if (n_out) { zero.p[2] = n_out; zero.n[2] = d.BH * T; }
-        if (m_out) { zero.p[3] = m_out; zero.n[3] = d.BH * T; }
+        // the outputs that mLSTMsig does not have: zeroed by the gate kernels on the way; by a launch of their own at the end
+        // where one of them lies over an input, which others read meanwhile
+        float* const p[4] = {nn, mn, n_out, m_out};
+        const size_t n[4] = {(size_t)d.BH * dqk, (size_t)d.BH, (size_t)d.BH * T, (size_t)d.BH * T};
+        const size_t row = (size_t)d.BH * T, vb = row * dhv * d.esz;
+        for (int i = 0; i < 4; ++i) {
+            if (!p[i]) continue;
+            const size_t b = n[i] * sizeof(float);
+            const bool read = overlap(p[i], b, i_pre, row * sizeof(float)) || overlap(p[i], b, f_pre, row * sizeof(float)) ||
+                              overlap(p[i], b, q, row * dqk * d.esz) || overlap(p[i], b, k, row * dqk * d.esz) || overlap(p[i], b, v, vb) ||
+                              overlap(p[i], b, C0, n[0] * dhv * sizeof(float)) || (fz && overlap(p[i], b, fz->o_pre, vb)) ||
+                              (fz && overlap(p[i], b, fz->gamma, (size_t)NH * dhv * sizeof(float))) ||
+                              (fz && overlap(p[i], b, fz->beta, (size_t)NH * dhv * sizeof(float)));
+            FillList& f = read ? zero_last : zero;
+            f.p[i] = p[i]; f.n[i] = (long)n[i];
+        }
     }
     int st = run_gates(d, i_pre, f_pre, m0, w.wrow, w.ucol, w.sH, w.aK, w.gbar, mout, (is_exp && !own_mout) ? m_out : nullptr,
                        !is_exp ? nullptr : (m_waits ? w.nst : mn), w.tmp, w.csum, w.wrow_lo, w.ucol_lo, softcap, zero, s);
@@ -330,7 +341,7 @@ int fwd_impl(const void* q, const void* k, const void* v, const float* i_pre, co
         t.fz_kind = fz->kind; t.fz_NH = fz->NH; t.fz_eps = fz->eps;
     }
     TFLA_LAUNCH(K_TILE_H, launch_tile_mode<MODE_H>(t, (int)d.BH, dtype, s));
-
+    if (zero_last.n[0] + zero_last.n[1] + zero_last.n[2] + zero_last.n[3] > 0) TFLA_LAUNCH(K_GATES, launch_zero(zero_last, s));
     return TFLA_OK;
 }
 

@@ -592,6 +592,12 @@ hipError_t launch_gate_grads(const GateGradArgs& a, int BH, hipStream_t s) {
     return hipGetLastError();
 }
 
+// (the shares stride through the arrays: any number of workgroups does)
+__global__ void __launch_bounds__(256) zero_kernel(FillList f) { zero_share(f, (long)blockIdx.x * 256 + threadIdx.x, (long)gridDim.x * 256); }
+hipError_t launch_zero(const FillList& f, hipStream_t s) {
+    hipLaunchKernelGGL(zero_kernel, dim3(256), dim3(256), 0, s, f);
+    return hipGetLastError();
+}
 __global__ void __launch_bounds__(256) copy_kernel(const float* from, float* to, int n) {
     const int i = blockIdx.x * 256 + threadIdx.x;
     if (i < n) to[i] = from[i];

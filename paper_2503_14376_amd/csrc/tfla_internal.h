@@ -65,6 +65,7 @@ struct GateGradArgs {
 };
 hipError_t launch_gate_grads(const GateGradArgs& a, int BH, hipStream_t s);
 
+hipError_t launch_zero(const FillList& f, hipStream_t s);
 hipError_t launch_copy(const float* from, float* to, int n, hipStream_t s);
 // out[bh] = <A[bh], Bm[bh]>; A (BH, *, lda), Bm (BH, d1, d2): the first d2 columns of the first d1 rows of A's `perA` values
 // as STATE_DOT_PARTS partial sums each

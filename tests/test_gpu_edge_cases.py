@@ -321,7 +321,7 @@ def test_tile_width_override_gives_the_same_results(width):
 
 
 def test_sigmoid_variant_zero_fills_the_outputs_it_does_not_have():
-    """mLSTMsig has no normaliser and no max state: nn, mn, n_out, m_out come back as zeros (one fill launch for
+    """mLSTMsig has no normaliser and no max state: nn, mn, n_out, m_out come back as zeros (the gate kernels write
     all of them), whatever the buffers held before; likewise n and m of the generation step."""
     import paper_2503_14376_amd as tfla
     from tests import gpu_util as gu
@@ -346,3 +346,24 @@ def test_sigmoid_variant_zero_fills_the_outputs_it_does_not_have():
                          variant=w.variant, out=s)
     torch.cuda.synchronize()
     assert float(s2["n"].abs().max()) == 0.0 and float(s2["m"].abs().max()) == 0.0
+
+
+@pytest.mark.parametrize("dtype", [wl.BF16, wl.F32])
+@pytest.mark.parametrize("T", [512, 1280, 500])         # gates in one launch (up to sixteen chunks) and in two
+def test_sigmoid_variant_zero_outputs_over_inputs(dtype, T):
+    """The outputs that mLSTMsig does not have may lie over inputs that the caller no longer needs: they are zeroed when
+    everything has been read, and the other results are what they are with buffers of their own."""
+    import paper_2503_14376_amd as tfla
+    from tests import gpu_util as gu
+    w = wl.small(wl.SIG, dtype, B=2, NH=16, T=T, dqk=64, dhv=64, chunk=64, seed=98)
+    dev = gu.dev_inputs(w, wl.make_inputs(w))
+    call = lambda out: tfla.mlstm_fwd(dev["q"], dev["k"], dev["v"], dev["i_pre"], dev["f_pre"], dev["C0"], None, None,
+                                      chunk=w.chunk, variant=w.variant, eps=1e-6, out=out)
+    apart = call({})
+    C0 = dev["C0"].view(-1)
+    out = call({"n_out": dev["i_pre"], "m_out": dev["f_pre"], "Cn": torch.empty_like(dev["C0"]),
+                "nn": C0[:2 * 16 * 64].view(2, 16, 64), "mn": C0[-2 * 16:].view(2, 16)})
+    torch.cuda.synchronize()
+    assert torch.equal(apart["H"], out["H"]) and torch.equal(apart["Cn"], out["Cn"])
+    for key in ("nn", "mn", "n_out", "m_out"):
+        assert float(out[key].abs().max()) == 0.0, key
