@@ -170,6 +170,16 @@ BwdWs carve_bwd(const Dims& d, void* ws) {
         if (e_ != hipSuccess) return (int)e_;  \
     } while (0)
 
+// (here, out of sight of the units that define launch_tile_grads(): named in one of them, every width would be built there)
+hipError_t launch_grads(const TileArgs& dv, const TileArgs& dq, const TileArgs& dk, int BH, int dtype, hipStream_t s) {
+    switch (dv.d1) {
+        case 64: return launch_tile_grads<64>(dv, dq, dk, BH, dtype, s);
+        case 128: return launch_tile_grads<128>(dv, dq, dk, BH, dtype, s);
+        case 256: return launch_tile_grads<256>(dv, dq, dk, BH, dtype, s);
+        default: return hipErrorInvalidValue;
+    }
+}
+
 // ---- optional per-kernel timing with HIP events on the caller's stream -------------------
 enum { K_GATES = 0, K_BWD_PREP, K_REC_FWD, K_REC_BWD, K_TILE_H, K_TILE_DV, K_TILE_DQ, K_TILE_DK, K_GATE_GRADS,
        K_STATE_DOT, K_STEP, K_NORM_FWD, K_NORM_BWD, K_GAIN, K_TILE_GRADS, K_COUNT };

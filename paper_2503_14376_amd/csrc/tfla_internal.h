@@ -270,15 +270,8 @@ inline bool grads_in_one_launch(int dqk, int dhv, int dtype, int L, long rows) {
 // fp32, all three in one launch: 64-column blocks while 128 would leave fewer than 512 workgroups of two wavefronts (never
 // narrower than tile_bd2(), whose launches have the chip to themselves: 16 heads of 128 / 256, 1024 steps 128 wide)
 inline bool grads_f32_wide(int dqk, int dhv, long rows) { return (rows / 64) * (dhv / 128 + 2 * (dqk / 128)) >= 512; }
+// (defined for DQK = 64, 128 and 256, each in a unit of its own that holds that width's kernels)
 template <int DQK> hipError_t launch_tile_grads(const TileArgs& dv, const TileArgs& dq, const TileArgs& dk, int BH, int dtype, hipStream_t s);
-inline hipError_t launch_grads(const TileArgs& dv, const TileArgs& dq, const TileArgs& dk, int BH, int dtype, hipStream_t s) {
-    switch (dv.d1) {
-        case 64: return launch_tile_grads<64>(dv, dq, dk, BH, dtype, s);
-        case 128: return launch_tile_grads<128>(dv, dq, dk, BH, dtype, s);
-        case 256: return launch_tile_grads<256>(dv, dq, dk, BH, dtype, s);
-        default: return hipErrorInvalidValue;
-    }
-}
 // the fused layer output needs whole rows of h~ in one workgroup of the H kernel
 inline bool layer_fusion_applies(int dqk, int dhv, int dtype, int L, long rows) {
     return dtype == 1 && (dhv == 64 || dhv == 128) && tile_bd2(dqk, dhv, dtype, L, rows) == dhv;

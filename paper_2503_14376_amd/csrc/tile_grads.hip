@@ -12,7 +12,7 @@
 // the body of its own kernel (tile_fast.h) in the same LDS; registers and LDS are those of the widest, which still
 // leaves two workgroups per CU.
 //
-// Compiled once per TFLA_GRADS_DQK (kernel width of q and k).
+// Compiled once per TFLA_GRADS_DQK (kernel width of q and k); a unit holds the kernels of that width only.
 #include "tfla_device.h"
 #include "tfla_internal.h"
 #include "tile_f32.h"

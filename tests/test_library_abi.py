@@ -41,6 +41,17 @@ def test_library_exports_every_declared_symbol(tfla):
     assert sorted(binding.EXPORTS) == declared_symbols()
 
 
+def test_every_kernel_is_built_once(tfla):
+    # A kernel descriptor's name stands in its code object a fixed number of times; a kernel that more than one unit
+    # instantiates is there in as many copies.
+    with open(tfla.lib_path(), "rb") as f:
+        names = re.findall(rb"_ZN4tfla\w+?\.kd", f.read())
+    count = {n: names.count(n) for n in set(names)}
+    assert any(b"grads_kernel_bf16" in n for n in count)
+    least = min(count.values())
+    assert [n for n, c in count.items() if c != least] == []
+
+
 def test_missing_library_fails_loudly(tfla, monkeypatch):
     from paper_2503_14376_amd import binding
     monkeypatch.setattr(binding, "_lib", None)
