@@ -478,6 +478,11 @@ __device__ __forceinline__ void tile_body_bf16(const TileArgs& a, const TileLds&
         f32x16 s;
 #pragma unroll
         for (int v = 0; v < 16; ++v) s[v] = 0.0f;
+        f32x4 wc[4];                            // this lane's column weights: wc[v / 4][v % 4] = wb[acc_row(v, g)]
+        auto read_weights = [&]() {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) wc[q] = *reinterpret_cast<const f32x4*>(wb + 8 * q + 4 * g);
+        };
         if constexpr (SPREAD) {
             constexpr int G = 4, KG = KS1 / G;
 #pragma unroll
@@ -499,12 +504,14 @@ __device__ __forceinline__ void tile_body_bf16(const TileArgs& a, const TileLds&
                 for (int q = 0; q < PF; ++q) __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
                 if (req) issue_part(i + NS - 1, gq, G);
             }
+            read_weights();
         } else {
             frag ya[KS1];
 #pragma unroll
             for (int ks = 0; ks < KS1; ++ks) ya[ks].v = ry.load(yb, ks, 0);
 #pragma unroll
             for (int ks = 0; ks < KS1; ++ks) s = E::mma(ya[ks], xf[ks], s);
+            read_weights();
             // LDS reads run PF fragments ahead of the MFMAs that consume them
             constexpr int PF = KS1 < 4 ? KS1 : 4;
 #pragma unroll
@@ -514,21 +521,30 @@ __device__ __forceinline__ void tile_body_bf16(const TileArgs& a, const TileLds&
                 __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
                 __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
             }
+            // ... and behind the last PF products, the column weights.  Left to the compiler they are read once the products are
+            // over, into the score tile's registers, which is two more trips to LDS per tile.  On one box, read late ->
+            // here: 8 heads 256 / 512, 1000 steps, forward with its layer 40.3 -> 39.4 us; 32768 steps, chunk 512 614 -> 607; batch 2,
+            // 8192 steps, forward + backward 742 -> 732; 64 heads of 64, batch 4, 2048 steps 381 -> 375; 4 heads of 1024, batch
+            // 4, 4096 steps 2818 -> 2791.  Without the barrier the sums of the exponents move up among the products and wait
+            // for the weights there: 378 against 367 for the heads of 64 on another box.
 #pragma unroll
-            for (int q = 0; q < PF; ++q) __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+            for (int q = 0; q < PF; ++q) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
         }
         float p[16];
+#pragma unroll
+        for (int v = 0; v < 16; ++v) p[v] = s[v] * fast_exp2(wr + wc[v >> 2][v & 3]);
         if (diag) {
+            // the tile on the diagonal (cs == wr0): one value per lane against compile-time offsets, compared once per workgroup
+            const int rel = l32 - 4 * g;
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
-                const int cl = acc_row(v, g);
-                const float w = fast_exp2(wr + wb[cl]);
-                const bool keep = UPPER ? (cs + cl >= wr0 + l32) : (cs + cl <= wr0 + l32);
-                p[v] = keep ? s[v] * w : 0.0f;
+                const int off = acc_row(v, 0);
+                p[v] = (UPPER ? off >= rel : off <= rel) ? p[v] : 0.0f;
             }
-        } else {
-#pragma unroll
-            for (int v = 0; v < 16; ++v) p[v] = s[v] * fast_exp2(wr + wb[acc_row(v, g)]);
         }
         if (MODE == MODE_H) {
 #pragma unroll
