@@ -538,8 +538,12 @@ __device__ __forceinline__ void tile_body_bf16(const TileArgs& a, const TileLds&
 #pragma unroll
         for (int v = 0; v < 16; ++v) p[v] = s[v] * fast_exp2(wr + wc[v >> 2][v & 3]);
         if (diag) {
-            // the tile on the diagonal (cs == wr0): one value per lane against compile-time offsets, compared once per workgroup
-            const int rel = l32 - 4 * g;
+            // the tile on the diagonal (cs == wr0), one per wavefront: one value per lane against compile-time offsets.  The
+            // compares move ahead of the loop, into the wait for the first tiles, and hold 32 scalar registers from there (done
+            // here, the ragged prompt above takes 39.6 us instead of 39.1 and 16 heads of 96 / 192 205 instead of 204); the
+            // widest kernels, which would spill 5 to 19 others for them, do them here.
+            int rel = l32 - 4 * g;
+            if constexpr (OCC == 1) asm volatile("" : "+v"(rel));
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
                 const int off = acc_row(v, 0);
