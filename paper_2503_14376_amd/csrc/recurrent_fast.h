@@ -66,7 +66,13 @@ __global__ void __launch_bounds__(WN * 128) recurrent_kernel_bf16(RecArgs a) {
     // pieces that the lines of X and Y are brought into L2 ahead (LinePrefetch).  16 heads 256 / 512, chunk 256, 8192 steps: 113 / 107.5
     // us per launch forward / reversed without, 105.8 / 104.7 with 3, 104.6 / 103.7 with 4, 108.1 / 106.3 with 6; 64 heads and
     // 4096 steps 218 / 203, 205 / 198, 205 / 197, 215 / 204.
+    // Where four workgroups or more read a line of X (d2 from 512 on), and pieces of 128 rows, whose ring holds fewer bytes on their
+    // way.  Forward + backward in us, without -> with: 8 heads 256 / 512, batch 4, 2048 steps, chunk 128 425 -> 419; heads of 512, batch
+    // 4, 2048 steps, chunk 128 756 -> 735, one sequence of 8192, chunk 256 661 -> 641; 256 / 1024 764 -> 755.  d2 = 256: 16
+    // heads 512 / 256, batch 2, 2048 steps, chunk 128 419 -> 421, 8192 steps, chunk 512 1779 -> 1781.  Pieces of 64 rows: 256 / 512, batch 2,
+    // 8192 steps, chunk 64 1169 -> 1179, heads of 512 630 -> 628, 512 / 256, chunk 192 587 -> 595.
     constexpr int AHEAD = 4;
+    constexpr bool PREFETCH = !PAD && BK == 128;
     constexpr int STEADY = (NS - 2) * CPP, STEADY_C = (NS - 2) * CPC;
     static_assert(STEADY + NS - 1 + 2 * (NH + 1) <= 63 && STEADY_C + (NH + 1) * NST <= 63, "wait counts must fit the 6-bit counter");
     static_assert(CPC % KS == 0, "Y requests are spread evenly over the k steps");
@@ -127,7 +133,7 @@ __global__ void __launch_bounds__(WN * 128) recurrent_kernel_bf16(RecArgs a) {
         const long gstep = a.reverse ? -1 : 1;
         // producer 0 prefetches X, producer 1 Y
         LinePrefetch<BK, AHEAD> pf;
-        if (!PAD && wc < 2) {       // (tensors that end inside a piece: 58.4 us without, 58.6 with, 16 heads and 4000 steps)
+        if (PREFETCH && gridDim.x >= 4 && wc < 2) {     // (tensors that end inside a piece: 58.4 us without, 58.6 with, 16 heads and 4000 steps)
             pf.init(wc == 0 ? a.X : a.Y, bh, wc == 0 ? xld : yld, tld, wc == 0 ? a.d1 : a.d2, (int)(gridDim.x * gridDim.y), by * (int)gridDim.x + bx, P,
                     row0, lane, lds_addr(ldsPf) + 256u * wc);
             if (pf.on)

@@ -147,12 +147,16 @@ def test_fp32_state_tiles(keep, variant, B, NH, T, dqk, dhv, chunk):
     _check_slices(w, dCn=True, keep=keep)
 
 
-# recurrent kernels that bring the lines of later pieces into L2: sequences of fewer, as many and more pieces than it reaches
-# ahead four times, both piece sizes, both tile widths, sequences and head dimensions that end inside a piece
+# recurrent kernels that bring the lines of later pieces into L2.  On: 64 x 64 state tiles, 16 and 32 sharers, pieces of 64 and
+# 128 rows, one and more per chunk (from 24 on), and 64 x 128 ones, d_hv from 512 on, pieces of 128 rows (from 16 on).  Off: a piece
+# too few, pieces of 64 rows or d_hv = 256 with 64 x 128 tiles, 128 sharers, sequences and head dimensions that end inside a piece
 @pytest.mark.parametrize("variant,B,NH,T,dqk,dhv,chunk", [
-    (wl.EXP, 1, 8, 2944, 256, 512, 128), (wl.SIG, 1, 8, 3072, 256, 512, 128), (wl.EXP, 1, 3, 1600, 256, 512, 192),
-    (wl.EXP, 1, 4, 3500, 256, 320, 256), (wl.SIG, 3, 8, 1920, 256, 512, 128), (wl.EXP, 3, 8, 2048, 256, 512, 128),
-    (wl.EXP, 3, 8, 1100, 200, 456, 192), (wl.SIG, 1, 4, 1024, 1024, 1024, 64),
+    (wl.SIG, 1, 8, 3072, 256, 512, 128), (wl.EXP, 1, 8, 3072, 256, 512, 256), (wl.EXP, 1, 8, 1536, 256, 512, 64),
+    (wl.SIG, 1, 8, 1728, 256, 512, 192), (wl.EXP, 1, 5, 1600, 256, 256, 64), (wl.EXP, 1, 3, 3200, 128, 512, 128),
+    (wl.EXP, 3, 8, 2048, 256, 512, 128), (wl.SIG, 3, 8, 2304, 256, 512, 256), (wl.EXP, 1, 8, 2560, 512, 512, 512),
+    (wl.EXP, 1, 8, 2944, 256, 512, 128), (wl.SIG, 3, 8, 1920, 256, 512, 128), (wl.EXP, 3, 8, 1152, 256, 512, 192),
+    (wl.EXP, 2, 16, 2048, 512, 256, 128), (wl.SIG, 1, 4, 1024, 1024, 1024, 64),
+    (wl.EXP, 1, 3, 1600, 256, 512, 192), (wl.EXP, 1, 4, 3500, 256, 320, 256), (wl.EXP, 3, 8, 1100, 200, 456, 192),
 ])
 def test_recurrent_prefetch(variant, B, NH, T, dqk, dhv, chunk):
     w = wl.small(variant, wl.BF16, B=B, NH=NH, T=T, dqk=dqk, dhv=dhv, chunk=chunk, seed=680 + T + dqk)
