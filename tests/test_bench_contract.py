@@ -34,3 +34,23 @@ def test_algorithmic_flops_match_the_count_model():
     assert abs(per_kernel["tile_H"] - (2 * w.dqk * w.dhv + 0.5 * 2 * w.chunk * (w.dqk + w.dhv)) * units) < 1.0
     # the generation benchmark prices its kernel with the recurrent formulation's memory operations (App. F.2)
     assert cm.bytes_recurrent_step_exp(256, 512) > 2 * 256 * 512 * 4
+
+
+def test_every_timing_family_of_the_library_is_priced_or_known_to_be_small():
+    sys.path.insert(0, ROOT)
+    import bench
+    import paper_2503_14376_amd as tfla
+    if not os.path.exists(tfla.lib_path()):
+        from paper_2503_14376_amd import build
+        build.build(verbose=False)
+    priced = [f for fams in bench.KERNEL_GROUPS.values() for f in fams]
+    assert sorted(priced + list(bench.OTHER_FAMILIES)) == sorted(tfla.profile_read())
+    flops = bench.algorithmic_flops(wl.CONFIGS["c4"])[0]
+    byts = bench.algorithmic_bytes(wl.CONFIGS["c4"], 2)
+    assert sorted(flops) == sorted(byts) == sorted(priced)
+    # one gradient launch: the products of all three, fewer bytes than three launches (their operands are the same tensors)
+    three = ("tile_dV", "tile_dQ", "tile_dK")
+    assert flops["tile_grads"] == sum(flops[f] for f in three)
+    w = wl.small(wl.EXP, wl.BF16, B=4, NH=64, T=2048, dqk=64, dhv=64, chunk=256)
+    narrow = bench.algorithmic_bytes(w, 2)
+    assert narrow["tile_grads"] < 0.7 * sum(narrow[f] for f in three)
