@@ -260,8 +260,10 @@ inline int tile_bd2(int d1, int d2, int dtype, int L, long rows) {
 // fp32: the same widths.  What the kernels wait for there is the matrix unit, and what one launch gains is the chip filled
 // once instead of three times: 44 % of forward + backward for one head of 64 and 256 steps, 24 % for 8 heads of 256 and 500
 // steps, 2 to 12 % where each launch fills it many times over.  In the middle, two-wavefront workgroups (chunk sizes that are
-// no multiple of 128) of a 256-wide d_hv and a narrow d_qk lose 6 to 8 % from 32768 rows on (16 heads of 128 / 256, batch 2,
-// 1024 steps 334 -> 354 us; with batch 3 and 8 heads, 24576 rows, 353 -> 298), and wide heads are not worth it from 65536 on.
+// no multiple of 128) of a 256-wide d_hv and a narrow d_qk: from 32768 rows on the three launches have 128-wide blocks for a
+// d_qk of 128 as well (tile_bd2), and how full each launch's last round of workgroups is decides.  us, three launches / one:
+// 128 / 256, 24576 rows 353 / 298, 32768 rows 317 / 337, 49152 rows 523 / 514, chunk 192 and 36864 rows 521 / 470; 64 / 256, 32768 rows
+// 228 / 242, 49152 rows 356 / 348, 57344 rows 395 / 404.  They keep the three there; wide heads do from 65536 rows on.
 inline bool grads_in_one_launch(int dqk, int dhv, int dtype, int L, long rows) {
     if (dqk > 256 || dhv > 256) return false;
     if (dtype != 1) return (dqk <= 128 && dhv <= 128) || rows < (L % 128 != 0 && dhv > 128 && dqk <= 128 ? 32768 : 65536);

@@ -3,14 +3,16 @@
 // The three gradient kernels of a chunk read the same tensors (K, Q and dH in all of them, V and the states in two), and
 // where dQ and dK form their weighted matrix each for itself (tile_shares_E()) none waits for another.  One after another,
 // each streams its operands from memory again; side by side on one XCD they find them in its L2: 64 heads of 64, batch 4,
-// 2048 steps: 318 MB fetched of 790 MB of operands (the chunks that are under way on an XCD at a time have 1.5 MB of them
+// 2048 steps: 316 MB fetched, 302 MB of operands counted once, 788 MB as each part reads them (the chunks that are under way on an XCD at a time have 1.5 MB of them
 // there, 4 MB at heads of 256).  Forward + backward, three launches -> one: that shape with its layer 415 -> 374 us, 32 heads
 // of 128 345 -> 305, 16 heads of 256 440 -> 413, 16 heads of 96 / 192 and 3000 steps 234 -> 209, one sequence of 777 steps
 // and 8 heads of 64 / 128, where two launches fewer count, 71 -> 52.  fp32: one head of 64 and 256 steps 87 -> 60 us (three
 // launches of 11 - 16 us on four CUs -> one of 15), 16 heads of 128 / 256 and 1024 steps 243 -> 229.
 // Linear workgroup id: (chunk of a head, row block, {column blocks of dV, of dQ, of dK}), the last fastest.  Every part is
-// the body of its own kernel (tile_fast.h) in the same LDS; registers and LDS are those of the widest, which still
-// leaves two workgroups per CU.
+// the body of its own kernel (tile_fast.h, tile_f32.h) in the same LDS; registers and LDS are those of the widest.  In bf16 that
+// still leaves two workgroups per CU; in fp32 most of the wide ones take more than 256 registers and run one wavefront per SIMD,
+// as the kernels of their own do there, and 40 of the 68 spill scalar registers (up to 179, the ragged and 128-wide ones most):
+// the argument blocks of three parts are live at once.
 //
 // Compiled once per TFLA_GRADS_DQK (kernel width of q and k); a unit holds the kernels of that width only.
 #include "tfla_device.h"
