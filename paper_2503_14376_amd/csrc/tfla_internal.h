@@ -276,7 +276,7 @@ inline bool grads_f32_wide(int dqk, int dhv, long rows) { return (rows / 64) * (
 template <int DQK> hipError_t launch_tile_grads(const TileArgs& dv, const TileArgs& dq, const TileArgs& dk, int BH, int dtype, hipStream_t s);
 // the fused layer output needs whole rows of h~ in one workgroup of the H kernel
 inline bool layer_fusion_applies(int dqk, int dhv, int dtype, int L, long rows) {
-    return dtype == 1 && (dhv == 64 || dhv == 128) && tile_bd2(dqk, dhv, dtype, L, rows) == dhv;
+    return dtype == 1 && dqk <= 512 && (dhv == 64 || dhv == 128) && tile_bd2(dqk, dhv, dtype, L, rows) == dhv;
 }
 
 }  // namespace tfla

@@ -90,6 +90,13 @@ def test_layer_output_formed_by_the_h_kernel(shape, kind, gate):
     run_layer(w, kind=kind, softcap=15.0, gate=gate, backward=dqk < 512)
 
 
+@pytest.mark.parametrize("dqk,dhv", [(1024, 64), (1024, 128)])
+def test_layer_narrow_rows_of_a_wide_contraction(dqk, dhv):
+    # rows of h~ that one workgroup could hold, behind a contraction that the fused kernel is not built for
+    w = wl.small(wl.EXP, wl.BF16, B=1, NH=2, T=256, dqk=dqk, dhv=dhv, chunk=64, seed=61, init_state=False)
+    run_layer(w, lo.RMS, softcap=15.0, gate=True)
+
+
 def test_layer_output_same_with_and_without_the_separate_norm_kernel():
     """The column-block override (a measurement aid) splits the rows of h~ over two workgroups, which sends the same
     problem through the separate NORM kernel: both paths normalise the same rounded h~, so the outputs agree to the
