@@ -244,6 +244,10 @@ template <int MODE> hipError_t launch_tile_mode(const TileArgs& a, int BH, int d
 // described above; 64 / 128 force that width wherever it divides d2; 256 changes nothing (it is already taken
 // wherever it is built).  The workspace layout depends on the width, so it must not change between the
 // workspace query, the forward call and the backward call of one step.
+// A contraction over 1024 columns (bf16): whether the weighted matrix of H or dV, L values per row, and the sums of its rows (H),
+// one per 64 columns at most, fit where the fp32 partial results of a split contraction would lie: d_hv values per row, the wider
+// head dimension's in the backward workspace.  (dQ and dK have memory of their own for it.)
+inline bool weights_fit(int L, int d2, int mode) { return mode != MODE_H || 2 * L + L / 16 <= 4 * d2; }
 extern int tile_width_override;
 inline int tile_bd2(int d1, int d2, int dtype, int L, long rows) {
     const int ov = tile_width_override;

@@ -24,10 +24,31 @@
 #include "tfla_internal.h"
 #include "tile_f32.h"
 #include "tile_fast.h"
+#include "tile_weights.h"
 
 namespace tfla {
 
 // ------------------------------------------------------------------------------------------
+// what the bf16 kernels' decomposition of the linear workgroup id divides by
+static void set_divisors(TileArgs& a, int BH, int gx, int gy) {
+    auto log2_or_neg = [](int v) { return (v > 0 && (v & (v - 1)) == 0) ? __builtin_ctz((unsigned)v) : -1; };
+    a.dec_bh = BH;
+    a.dec_bpx = BH % 8 == 0 ? BH / 8 : 1;
+    a.sh_gx = log2_or_neg(gx); a.sh_gy = log2_or_neg(gy);
+    a.sh_bpx = log2_or_neg(a.dec_bpx); a.sh_nc = log2_or_neg(a.Nc);
+}
+
+// the weighted matrix of a mode into a.E (tile_weights.h); for H of mLSTMexp the row sums into a.nrm_out
+template <int NW, int MODE>
+static hipError_t launch_weights(TileArgs a, int BH, hipStream_t s) {
+    const int gy = a.L / (32 * NW);
+    set_divisors(a, BH, 1, gy);
+    const dim3 grid((unsigned)((long)(gy * (gy + 1) / 2) * BH * a.Nc));
+    if (a.out_T != a.T || a.in_ld1 != a.d1) hipLaunchKernelGGL((weights_kernel_bf16<NW, MODE, 1>), grid, dim3(64 * NW), 0, s, a);
+    else hipLaunchKernelGGL((weights_kernel_bf16<NW, MODE, 0>), grid, dim3(64 * NW), 0, s, a);
+    return hipGetLastError();
+}
+
 template <typename DT, int D1, int BD2, int NW, int MODE, int SPLIT = 0>
 static hipError_t launch_tile_t(const TileArgs& a0, int BH, hipStream_t s) {
     TileArgs a = a0;
@@ -35,17 +56,12 @@ static hipError_t launch_tile_t(const TileArgs& a0, int BH, hipStream_t s) {
     // the caller's tensors may end before the kernels' blocks do
     const bool padded = a.out_T != a.T || a.out_ld != a.d2 || a.in_ld1 != (SPLIT ? 2 * D1 : D1);
     if constexpr (sizeof(DT) == 2) {
-        // what the kernel's decomposition of the linear workgroup id divides by
-        auto log2_or_neg = [](int v) { return (v > 0 && (v & (v - 1)) == 0) ? __builtin_ctz((unsigned)v) : -1; };
-        a.dec_bh = BH;
-        a.dec_bpx = BH % 8 == 0 ? BH / 8 : 1;
-        a.sh_gx = log2_or_neg(a.d2 / BD2); a.sh_gy = log2_or_neg(a.L / (32 * NW));
-        a.sh_bpx = log2_or_neg(a.dec_bpx); a.sh_nc = log2_or_neg(a.Nc);
+        set_divisors(a, BH, a.d2 / BD2, a.L / (32 * NW));
         // two workgroups per CU when the accumulator is narrow enough for 256 registers per lane
         constexpr int OCC = (BD2 <= 128 && D1 <= 256) ? 2 : 1;
         // dQ / dK share the weighted matrix E through memory only where the contraction that forms it is wide
-        constexpr int NOE = ((MODE == MODE_DQ || MODE == MODE_DK) && D1 <= TFLA_NOE_MAX_D1) ? 1 : 0;
-        if constexpr (MODE == MODE_H && SPLIT == 0 && BD2 <= 128) {
+        constexpr int NOE = D1 > 512 ? 2 : ((MODE == MODE_DQ || MODE == MODE_DK) && D1 <= TFLA_NOE_MAX_D1) ? 1 : 0;
+        if constexpr (MODE == MODE_H && SPLIT == 0 && D1 <= 512 && BD2 <= 128) {
             // the layer output next to h~: whole rows in one workgroup, nothing padded (the entry point has checked)
             if (a.fz_y) {
                 if (padded || a.d2 != BD2) return hipErrorInvalidValue;
@@ -95,12 +111,6 @@ static hipError_t launch_tile_m(const TileArgs& a, int BH, int bd2, hipStream_t 
     return hipErrorInvalidValue;
 }
 
-// one 512-wide half (SPLIT = 1, 2) of a bf16 contraction over 1024 columns
-template <int MODE, int SPLIT>
-static hipError_t launch_tile_half(const TileArgs& a, int BH, int bd2, hipStream_t s) {
-    return launch_tile_d1<bf16_t, 512, MODE, SPLIT>(a, BH, bd2, s);
-}
-
 template <int MODE>
 hipError_t launch_tile_mode(const TileArgs& a0, int BH, int dtype, hipStream_t s) {
     TileArgs a = a0;
@@ -119,7 +129,7 @@ hipError_t launch_tile_mode(const TileArgs& a0, int BH, int dtype, hipStream_t s
     if (dtype != 1) {
         if (a.d1 <= 256) return launch_tile_m<float, MODE>(a, BH, bd2, s);
         // fp32, d1 = 512: a wavefront's rows of X fill the register file at 256 fp32 columns, so the contraction runs
-        // as two 256-wide launches that meet in fp32, exactly like the 1024-wide bf16 case below
+        // as two 256-wide launches that meet in fp32, like H of bf16 below in its last case
         if (a.d1 != 512 || !a.part_acc || (nrm && !a.part_nrm)) return hipErrorInvalidValue;
         TileArgs h = a;
         h.d1 = 256;
@@ -136,28 +146,50 @@ hipError_t launch_tile_mode(const TileArgs& a0, int BH, int dtype, hipStream_t s
         return launch_tile_d1<float, 256, MODE, 2>(h, BH, bd2, s);
     }
     if (a.d1 <= 512) return launch_tile_m<bf16_t, MODE>(a, BH, bd2, s);
-    // d1 = 1024: the kernels hold a workgroup's X rows in registers, which ends at 512 columns.  Every term of
-    // the result is linear in the products over d1 (the weights depend on the gates only), so the contraction
-    // runs as two launches over 512 columns each: the first leaves its unnormalised accumulators (and its share
-    // of the normaliser) in fp32, the second adds them to its own before the epilogue.  dQ writes one matrix E
-    // per half (its products run over the halves of d_hv); dK reads the matching one in each of its launches.
+    // d1 = 1024: the kernels hold a workgroup's X rows in registers where they form the weighted matrix, which ends at 512
+    // columns.  So a launch before them leaves the matrix in memory (dK reads what dQ's has left) and they read it.  It takes the
+    // memory of the fp32 partial results below, for dQ and dK that of E.
+    // 16 heads of 1024, 4096 steps, chunk 256, us per mode H / dV / dQ / dK, split contraction -> this: 454 / 461 / 501 / 421 ->
+    // 312 / 280 / 316 / 249 (65 of the first three the weights), forward + backward 2758 -> 2087; chunk 128, 3000 steps of 8 heads
+    // 1310 -> 1040; chunk 64, 2048 steps of 4 heads 848 -> 706.
+    if (a.d1 != 1024) return hipErrorInvalidValue;
     constexpr bool STT = (MODE == MODE_DQ || MODE == MODE_DK);
-    if (a.d1 != 1024 || !a.part_acc || (nrm && !a.part_nrm) || (STT && a.E && !a.E2)) return hipErrorInvalidValue;
-    TileArgs h = a;
-    h.d1 = 512;
-    h.acc_out = a.part_acc; h.nrm_out = a.part_nrm;
-    hipError_t e = launch_tile_half<MODE, 1>(h, BH, bd2, s);
-    if (e != hipSuccess) return e;
-    h.acc_out = nullptr; h.nrm_out = nullptr;
-    h.acc_in = a.part_acc; h.nrm_in = a.part_nrm;
-    h.X = reinterpret_cast<const bf16_t*>(a.X) + 512;
-    h.in_cols1 = a.in_cols1 - 512;
-    if (MODE != MODE_DK) h.Y = reinterpret_cast<const bf16_t*>(a.Y) + 512;
-    h.St = reinterpret_cast<const bf16_t*>(a.St) + (STT ? (long)512 * a.d2 : 512);
-    // (n_{k-1} is stored as bf16 rows: 512 columns are 1024 bytes)
-    if (a.nstate) h.nstate = reinterpret_cast<const float*>(reinterpret_cast<const char*>(a.nstate) + 1024);
-    if (STT) h.E = a.E2;
-    return launch_tile_half<MODE, 2>(h, BH, bd2, s);
+    if (STT || weights_fit(a.L, a.d2, MODE)) {
+        if (!STT) {
+            if (!a.part_acc) return hipErrorInvalidValue;
+            a.E = a.part_acc;
+            a.nrm_out = reinterpret_cast<float*>(reinterpret_cast<char*>(a.part_acc) + (size_t)BH * a.T * a.L * 2);
+            a.nrm_in = a.nrm_out;
+        }
+        if (!a.E) return hipErrorInvalidValue;
+        if (MODE != MODE_DK) {
+            hipError_t e = a.L % 128 == 0 ? launch_weights<4, MODE>(a, BH, s) : launch_weights<2, MODE>(a, BH, s);
+            if (e != hipSuccess) return e;
+        }
+        return launch_tile_d1<bf16_t, 1024, MODE>(a, BH, bd2, s);
+    }
+    // H where d_hv is so narrow against the chunk that the matrix is larger than the memory for it: every term of the result is
+    // linear in the products over d1 (the weights depend on the gates only), so the contraction runs as two launches over 512
+    // columns each: the first leaves its unnormalised accumulators (and its share of the normaliser) in fp32, the second adds
+    // them to its own before the epilogue.
+    if constexpr (MODE == MODE_H) {
+        if (!a.part_acc || (nrm && !a.part_nrm)) return hipErrorInvalidValue;
+        TileArgs h = a;
+        h.d1 = 512;
+        h.acc_out = a.part_acc; h.nrm_out = a.part_nrm;
+        hipError_t e = launch_tile_d1<bf16_t, 512, MODE, 1>(h, BH, bd2, s);
+        if (e != hipSuccess) return e;
+        h.acc_out = nullptr; h.nrm_out = nullptr;
+        h.acc_in = a.part_acc; h.nrm_in = a.part_nrm;
+        h.X = reinterpret_cast<const bf16_t*>(a.X) + 512;
+        h.in_cols1 = a.in_cols1 - 512;
+        h.Y = reinterpret_cast<const bf16_t*>(a.Y) + 512;
+        h.St = reinterpret_cast<const bf16_t*>(a.St) + 512;
+        // (n_{k-1} is stored as bf16 rows: 512 columns are 1024 bytes)
+        if (a.nstate) h.nstate = reinterpret_cast<const float*>(reinterpret_cast<const char*>(a.nstate) + 1024);
+        return launch_tile_d1<bf16_t, 512, MODE, 2>(h, BH, bd2, s);
+    }
+    return hipErrorInvalidValue;
 }
 
 // One translation unit per (mode, element type) keeps compile times parallel: tile_inst.hip

@@ -53,7 +53,9 @@ __device__ __forceinline__ unsigned tile_divmod(unsigned n, unsigned d, int sh, 
 // contraction over 1024 columns (rows of the D1-wide operands are 2 D1 apart): the first half stores its raw fp32
 // accumulators, the second adds them to its own before the epilogue.
 // NOE: 1 = the dQ kernel does not store the weighted matrix E and the dK kernel recomputes it from dH and V
-// like every other mode (narrow contractions: E, L x L per chunk, is then more bytes than the operands it replaces).
+// like every other mode (narrow contractions: E, L x L per chunk, is then more bytes than the operands it replaces);
+// 2 = the weighted matrix of this mode is in memory (TileArgs::E, left by weights_kernel_bf16 or, for dK, by the launches for
+// dQ), and no product of X and Y is formed here: X is needed for the state's products only, slice by slice, whatever its width.
 // PAD: 1 = the caller's tensors end before the kernel's blocks do (TileArgs::out_T, out_ld, in_ld1): loads past their
 // end leave zeros in LDS (dma16_bounded) and only the true steps and columns are stored; 0 = whole blocks.
 // FUSE: 1 = MODE_H also stores the layer output y = sigma(o~) (.) NORM(h~) (Sec. 2.1, hidden-state output equation) of
@@ -62,8 +64,9 @@ __device__ __forceinline__ unsigned tile_divmod(unsigned n, unsigned d, int sh, 
 template <int D1, int BD2, int NW, int MODE, int OCC, int SPLIT, int NOE, int FUSE> struct TileShape {
     static constexpr bool UPPER = (MODE & 1) != 0;
     static constexpr bool STT = (MODE == MODE_DQ || MODE == MODE_DK);   // state slices are contraction-major
-    static constexpr bool ELITE = MODE == MODE_DK && !NOE;              // column tiles carry E instead of Y
-    static constexpr bool EWRITE = MODE == MODE_DQ && !NOE;
+    static constexpr bool ELITE = (MODE == MODE_DK && NOE == 0) || NOE == 2;    // column tiles carry E instead of Y
+    static constexpr bool EROWS = ELITE && MODE != MODE_DK;             // ... whose rows are this mode's own (dK reads what dQ's rows left)
+    static constexpr bool EWRITE = MODE == MODE_DQ && NOE == 0;
     static constexpr int NT = NW * 64, BR = NW * 32, BC = 32;
     static constexpr int KS1 = D1 / 16, NB = BD2 / 32;
     static constexpr int YB = ELITE ? BC * BR * 2 : BC * D1 * 2, ZB = BC * BD2 * 2;         // bytes
@@ -124,7 +127,7 @@ __device__ __forceinline__ void tile_body_bf16(const TileArgs& a, const TileLds&
     using E = Elem<bf16_t>;
     using frag = E::frag;
     using SH = TileShape<D1, BD2, NW, MODE, OCC, SPLIT, NOE, FUSE>;
-    constexpr bool UPPER = SH::UPPER, STT = SH::STT, ELITE = SH::ELITE, EWRITE = SH::EWRITE, WTILE = SH::WTILE, WPRE = SH::WPRE;
+    constexpr bool UPPER = SH::UPPER, STT = SH::STT, ELITE = SH::ELITE, EROWS = SH::EROWS, EWRITE = SH::EWRITE, WTILE = SH::WTILE, WPRE = SH::WPRE;
     constexpr int NT = SH::NT, BR = SH::BR, BC = SH::BC, KS1 = SH::KS1, NB = SH::NB, YB = SH::YB, STAGE = SH::STAGE, NS = SH::NS,
                   BCS = SH::BCS, NKS = SH::NKS, BXS = SH::BXS, NPRE = SH::NPRE, SLOT = SH::SLOT, SPS = SH::SPS;
     char* const smem = lds.smem;
@@ -173,15 +176,17 @@ __device__ __forceinline__ void tile_body_bf16(const TileArgs& a, const TileLds&
 
     using DS = typename std::conditional<STT, DmaTile<BCS, BD2, NT, SWZ_T>, DmaTile<BD2, BCS, NT, SWZ_K>>::type;
     DS ds;  ds.init(STT ? d2 : ld1, tid);
-    using DYT = typename std::conditional<ELITE, DmaTile<BC, BR, NT, SWZ_T>, DmaTile<BC, D1, NT, SWZ_K>>::type;
+    using DYT = typename std::conditional<EROWS, DmaTile<BR, BC, NT, SWZ_K>,
+                                          typename std::conditional<ELITE, DmaTile<BC, BR, NT, SWZ_T>, DmaTile<BC, D1, NT, SWZ_K>>::type>::type;
     DYT dy;    dy.init(ELITE ? a.L : xld, tid);
     DmaTile<BC, BD2, NT, SWZ_T> dz;   dz.init(zld, tid);
     if constexpr (PAD) {
         if constexpr (!ELITE) dy.bound_columns(a.in_cols1, tid);
         dz.bound_columns(cols2, tid);
     }
-    // E of this chunk: (L, L), rows = query index; the dK kernel reads the columns of its own rows
-    const bf16_t* Eb = reinterpret_cast<const bf16_t*>(a.E) + ((long)bh * a.Nc + kc) * a.L * a.L + (ELITE ? r0 : 0);
+    // E of this chunk: (L, L), rows = query index (of dV's: key index); the dK kernel reads the columns of its own rows
+    const bf16_t* Eb = reinterpret_cast<const bf16_t*>(a.E) + ((long)bh * a.Nc + kc) * a.L * a.L + (EROWS ? (long)r0 * a.L : ELITE ? r0 : 0);
+    const long etile = EROWS ? BC : (long)BC * a.L;      // from one column tile of it to the next
     constexpr int CS = DS::N;
     DmaTile<BR, BXS, NT, SWZ_K> dxs;  dxs.init(xld, tid);
     constexpr int CX = DmaTile<BR, BXS, NT, SWZ_K>::N;
@@ -208,8 +213,8 @@ __device__ __forceinline__ void tile_body_bf16(const TileArgs& a, const TileLds&
         } else {
             const int ct = ct_lo + item - NPRE;
             if (ELITE) {
-                // (E of this workgroup's rows: read by this workgroup only)
-                dy.template issue<true>(Eb + (long)ct * BC * a.L, st, tid);
+                // (E of this workgroup's rows: read by this workgroup only, where its block covers all output columns)
+                dy.template issue<NOE == 0>(Eb + ct * etile, st, tid);
             } else if constexpr (PAD) {
                 dy.template issue_bounded<true>(Y + (long)ct * BC * xld, bounded_bytes(steps_left - ct * BC, a.in_cols1, 2 * xld),
                                                        D1, st, tid);
@@ -243,7 +248,7 @@ __device__ __forceinline__ void tile_body_bf16(const TileArgs& a, const TileLds&
         } else {
             const int ct = ct_lo + item - NPRE;
             if (ELITE) {
-                dy.template issue_part<true>(Eb + (long)ct * BC * a.L, st, tid, part, nparts);
+                dy.template issue_part<NOE == 0>(Eb + ct * etile, st, tid, part, nparts);
             } else if constexpr (PAD) {
                 dy.template issue_bounded<false>(Y + (long)ct * BC * xld, bounded_bytes(steps_left - ct * BC, a.in_cols1, 2 * xld),
                                                         D1, st, tid, part, nparts);
@@ -433,10 +438,12 @@ __device__ __forceinline__ void tile_body_bf16(const TileArgs& a, const TileLds&
     const float wr = ldsWr[wave][l32];
     float rowsum = 0.0f;
     uint32_t eoff = 0;
-    if constexpr (ELITE) {
+    if constexpr (ELITE && !EROWS) {
         TFragReader<BR> re;  re.init(lane, 4);
         eoff = re.block_offset(wave);
     }
+    KFragReader<BC> ren;
+    if constexpr (EROWS) ren.init(l32, g);
     for (int ct = ct_lo; ct < ct_hi; ++ct) {
         const int i = NPRE + ct - ct_lo;
         __builtin_assume(i >= NPRE);            // (column tiles only from here on: lets the item-kind tests fold)
@@ -470,7 +477,11 @@ __device__ __forceinline__ void tile_body_bf16(const TileArgs& a, const TileLds&
         const char* zb = yb + YB;
         const float* wb = &ldsW[i % NS][wave][0];
         frag p0, p1;
-        if constexpr (ELITE) {
+        if constexpr (EROWS) {
+            // E of this wave's rows: the tile is [BR rows of this workgroup][32 columns]
+            p0.v = ren.load(yb, 0, wave);
+            p1.v = ren.load(yb, 1, wave);
+        } else if constexpr (ELITE) {
             // E^T of this wave's rows: the tile is [32 query rows][BR rows of this workgroup]
             p0.v = TFragReader<BR>::load_at(yb, eoff, 0, 8);
             p1.v = TFragReader<BR>::load_at(yb, eoff, 16, 24);
@@ -582,8 +593,9 @@ __device__ __forceinline__ void tile_body_bf16(const TileArgs& a, const TileLds&
             frag z[NB][2];
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb) {
-                z[nb][0].v = rz.load(zb, nb, 0, 8);
-                z[nb][1].v = rz.load(zb, nb, 16, 24);
+                // (in the order of k that the weights have: natural where they come from memory row by row)
+                z[nb][0].v = EROWS ? rzn.load(zb, nb, 0, 4) : rz.load(zb, nb, 0, 8);
+                z[nb][1].v = EROWS ? rzn.load(zb, nb, 16, 20) : rz.load(zb, nb, 16, 24);
             }
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb) {
@@ -628,6 +640,11 @@ __device__ __forceinline__ void tile_body_bf16(const TileArgs& a, const TileLds&
             asm volatile("" ::: "memory");      // one block's loads at a time: no register pile-up
         }
         if (MODE == MODE_H && a.variant == 0) nrm += a.nrm_in[t];
+    }
+    if constexpr (MODE == MODE_H && NOE == 2) {
+        // the row's weights, added up by the blocks of weights_kernel_bf16 that hold them
+        if (a.variant == 0)
+            for (int cb = 0; cb <= rb; ++cb) nrm += a.nrm_in[(long)cb * (long)bhn * a.T + t];
     }
     if constexpr (SPLIT == 1) {
         float* pout = a.acc_out + t * d2 + (long)nb2 * BD2 + 4 * g;

@@ -294,8 +294,8 @@ def test_optional_outputs_may_be_omitted(variant):
 @pytest.mark.parametrize("dqk,dhv,chunk", [(1024, 1024, 256), (1024, 1024, 64), (512, 1024, 128), (1024, 256, 192),
                                            (64, 1024, 64), (1024, 64, 256)])
 def test_head_dimensions_up_to_1024(variant, dqk, dhv, chunk):
-    """Head dimensions above 512 (the head-dimension benchmark of App. E.3 ends at 1024): the tiled kernels contract
-    over a 1024-wide dimension in two halves that meet in fp32; initial state given, so that every term is present."""
+    """Head dimensions above 512 (the head-dimension benchmark of App. E.3 ends at 1024): the tiled kernels of a
+    1024-wide contraction read their weights from memory (or contract in two halves that meet in fp32); initial state given, so that every term is present."""
     w = wl.small(variant, wl.BF16, B=1, NH=2, T=576 if chunk == 192 else 512, dqk=dqk, dhv=dhv, chunk=chunk,
                  seed=300 + dqk // 64 + dhv // 8 + chunk)
     _fwd_bwd(w, wl.make_inputs(w))

@@ -137,7 +137,7 @@ def test_layer_7b_head_shape(variant):
 
 @pytest.mark.parametrize("kind", [lo.RMS, lo.LAYER])
 def test_layer_head_dimension_1024(kind):
-    # the widest head: 1024-wide contractions in the cell (two 512-wide launches) and the norm kernels' widest rows
+    # the widest head: 1024-wide contractions in the cell (weights from memory) and the norm kernels' widest rows
     w = wl.small(wl.EXP, wl.BF16, B=1, NH=2, T=384, dqk=512, dhv=1024, chunk=128, seed=59, init_state=False)
     run_layer(w, kind, softcap=15.0, gate=True, gate_scale=2.0)
 

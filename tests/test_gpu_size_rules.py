@@ -60,9 +60,26 @@ def _check_slices(w, dCn=False, keep=True, scan=False):
         assert e <= tol, (k, e, errs)
 
 
+# contractions over 1024 columns.  The weighted matrix lies where a split contraction would leave its partial results, if it fits:
+# for H up to chunk 448 at d_hv = 256 and 960 at 512; several blocks per chunk on and off the diagonal, of 64 and of 128 rows,
+# whole and ragged
+@pytest.mark.parametrize("keep", [True, False])
+@pytest.mark.parametrize("variant,B,NH,T,dqk,dhv,chunk", [
+    (wl.EXP, 1, 2, 900, 1024, 256, 448),
+    (wl.EXP, 1, 2, 1024, 1024, 256, 512),       # does not fit
+    (wl.EXP, 1, 1, 2000, 1000, 512, 960),
+    (wl.SIG, 1, 1, 2048, 1024, 504, 1024),      # does not fit
+    (wl.EXP, 2, 1, 640, 520, 1000, 320),
+    (wl.SIG, 1, 3, 1152, 264, 1024, 384),
+])
+def test_wide_contractions(keep, variant, B, NH, T, dqk, dhv, chunk):
+    w = wl.small(variant, wl.BF16, B=B, NH=NH, T=T, dqk=dqk, dhv=dhv, chunk=chunk, seed=1500 + T + dqk)
+    _check_slices(w, dCn=True, keep=keep, scan=True)
+
+
 # 256-wide output blocks of the tiled kernels: rows / 128 * (columns / 256) >= 256 workgroups, chunk a multiple of 128
 @pytest.mark.parametrize("variant,B,NH,T,dqk,dhv,chunk", [
-    (wl.EXP, 1, 4, 2048, 1024, 1024, 256),      # exactly 256 workgroups in every mode (split contraction)
+    (wl.EXP, 1, 4, 2048, 1024, 1024, 256),      # exactly 256 workgroups in every mode (weights from memory)
     (wl.SIG, 1, 4, 1920, 1024, 1024, 128),      # 240: below the line
     (wl.EXP, 1, 8, 2048, 512, 512, 256),        # exactly 256, one launch per mode
     (wl.EXP, 3, 5, 2304, 512, 512, 384),        # an odd number of heads, three row blocks per chunk
@@ -320,7 +337,7 @@ def test_ragged_length_without_epsilon(dtype, dqk, dhv, chunk):
 @pytest.mark.parametrize("variant,dtype,B,NH,T,dqk,dhv,chunk", [
     (wl.EXP, wl.BF16, 2, 8, 2000, 256, 512, 256),       # 256 workgroups of dQ and dK
     (wl.SIG, wl.BF16, 1, 8, 2000, 504, 512, 256),       # 256 of every mode
-    (wl.EXP, wl.BF16, 1, 4, 2000, 1000, 1024, 256),     # the same with split contractions
+    (wl.EXP, wl.BF16, 1, 4, 2000, 1000, 1024, 256),     # the same with weights from memory
     (wl.SIG, wl.F32, 2, 8, 1024, 128, 256, 64),         # H and dV: 512 workgroups of 128 columns, two stages
     (wl.EXP, wl.F32, 2, 8, 1024, 256, 128, 128),        # dQ and dK
     (wl.EXP, wl.F32, 2, 8, 1024, 256, 256, 64),         # every mode, one stage
