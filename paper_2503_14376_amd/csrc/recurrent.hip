@@ -340,7 +340,17 @@ static hipError_t launch_rec_f32(const RecArgs& a, int BH, hipStream_t s) {
 template <bool PAD>
 static hipError_t launch_rec_bf16(const RecArgs& a, int BH, hipStream_t s) {
     // 64 x 128 state tiles where they are whole and 64 x 64 ones would not fit the 256 CUs in one round (see
-    // recurrent_narrow.h for both sides); pieces of 128 rows (half as many barriers) where the chunk size allows
+    // recurrent_narrow.h for both sides); pieces of 128 rows (half as many barriers) where the chunk size allows.
+    // Many tiles: 128 x 256 ones (in pieces of 64 rows), which fetch half as many bytes of X and Y per state value; a
+    // round of workgroups of them lasts about 8/3 rounds of the others.  Forward + backward in us, 64 x 128 -> 128 x 256,
+    // by the number of 128 x 256 tiles (heads of 512, 2048 steps, chunk 256): 128 346 -> 361, 160 485 -> 457, 192 503 -> 481, 224 639 -> 587,
+    // 256 656 -> 597, 288 808 -> 816, 320 838 -> 842, 352 973 -> 937, 512 1278 -> 1173, 576 1449 -> 1406; 256 / 512, 256 tiles
+    // 732 -> 670; heads of 256, 256 tiles 782 -> 746; 16 heads of 1024, 4096 steps 2040 -> 1797 (launches 471 -> 342).
+    const long tall_tiles = a.d1 % 128 == 0 && a.d2 % 256 == 0 ? (long)BH * (a.d1 / 128) * (a.d2 / 256) : 0;
+    if (tall_tiles > 0 && 8 * ((tall_tiles + 255) / 256) <= 3 * ((4 * tall_tiles + 255) / 256)) {
+        hipLaunchKernelGGL((recurrent_kernel_bf16<8, 64, PAD, 128, 4>), dim3(a.d2 / 256, a.d1 / 128, BH), dim3(768), 0, s, a);
+        return hipGetLastError();
+    }
     const bool narrow = a.d2 % 128 != 0 || (long)BH * (a.d1 / 64) * (a.d2 / 64) <= 256;
     const bool wide_pieces = a.L % 128 == 0;
     const dim3 grid(a.d2 / (narrow ? 64 : 128), a.d1 / 64, BH), block(512);

@@ -2,17 +2,18 @@
 //
 //   state <- gbar_k * state + (rs (.) X_k)^T Y_k        (contraction over the rows of a chunk)
 //
-// A workgroup owns a 64 x (32 WN) tile of the state for the whole sequence and consumes the
-// sequence in pieces of 64 rows.  Its 2 WN wavefronts have two roles that run side by side
-// between the workgroup barriers (one barrier per piece):
+// A workgroup owns a BM x (32 WN) tile of the state for the whole sequence (64 x 128, or
+// 128 x 256 where there are many, see recurrent.hip) and consumes the sequence in pieces of BK
+// rows.  Its WN + NP wavefronts have two roles that run side by side between the workgroup
+// barriers (one barrier per piece):
 //   * WN consumer wavefronts: wavefront c keeps the columns [32 c, 32 c + 32) of the tile in
 //     MFMA accumulators, multiplies piece i into them, requests the Y part of piece
 //     i + NS - 1 between its matrix instructions, and at chunk boundaries writes the state out
 //     and applies the decay;
-//   * WN producer wavefronts: they request the X part (and the scalars) of piece i + NS - 1
+//   * NP producer wavefronts: they request the X part (and the scalars) of piece i + NS - 1
 //     and rescale the X part of piece i + 1.
 // Both operands are contracted over their row index, so both stay in their natural row-major
-// layout in LDS and are read through the transposing LDS read.  X and Y pieces, the 64 row
+// layout in LDS and are read through the transposing LDS read.  X and Y pieces, the row
 // scales and gbar of the piece's chunk all arrive by asynchronous global->LDS loads in a ring
 // of NS stages that runs across chunk boundaries, so the sequential dependence between chunks
 // never drains the pipeline.
@@ -47,22 +48,29 @@ static __device__ unsigned long long tfla_rec_timeline[8192];
 #define TFLA_RTL_FLUSH
 #endif
 
+// What bounds the 128 x 256 tiles: 16 heads of 1024, 4096 steps, chunk 256 store 0.54 GB of states and 0.47 GB of anchors and fetch
+// 1.6 GB from L2 in 342 us, where the stores alone would take 150; with the Y part requested by the producers as well, so that the
+// consumers' stores are never waited for, 341.  Eight consumers, because 64 accumulators, the fragments of two k steps and the 64
+// values of an anchor fit 168 registers; the anchor's loads ahead of the state's stores spill 35 (505 us).  Tiles of 128 x 128 in the
+// same pieces lose to 64 x 128 (24 heads of 512, 2048 steps, forward + backward 508 -> 563 us).
 // PAD: the caller's tensors end before the kernel's pieces and tiles do (RecArgs::T_in, d1_in, d2_in): loads past their
 // end leave zeros in LDS, and only what exists of the caller's states is read and written.
-template <int WN, int BK, bool PAD = false>
-__global__ void __launch_bounds__(WN * 128) recurrent_kernel_bf16(RecArgs a) {
+// WN consumer and NP producer wavefronts, a BM x (32 WN) tile of the state.
+template <int WN, int BK, bool PAD = false, int BM = 64, int NP = WN>
+__global__ void __launch_bounds__((WN + NP) * 64) recurrent_kernel_bf16(RecArgs a) {
     using E = Elem<bf16_t>;
     using frag = E::frag;
-    constexpr int NTP = WN * 64, BM = 64, BN = WN * 32, MI = 2, KS = BK / 16;
+    constexpr int NTC = WN * 64, NTP = NP * 64, BN = WN * 32, MI = BM / 32, KS = BK / 16;
     constexpr int XB = BK * BM * 2, YB = BK * BN * 2, STAGE = XB + YB;
-    constexpr int NS = BK == 64 ? 6 : 3;            // ring stages (the ring is 144 KB of LDS)
+    constexpr int NS = 144 * 1024 / STAGE;          // ring stages (the ring is 144 KB of LDS)
     constexpr int NH = NS - 3;                      // earlier iterations whose stores are younger than the awaited piece
     using DX = DmaTile<BK, BM, NTP, SWZ_T>;         // the producers' share of a piece
-    using DY = DmaTile<BK, BN, NTP, SWZ_T>;
+    using DY = DmaTile<BK, BN, NTC, SWZ_T>;
     constexpr int NX = DX::N;                       // 16-byte chunks of the X piece per producer lane
     constexpr int CPP = DX::N + BK / 64 + 1;        // loads per producer and piece (X, row scales, gbar)
     constexpr int CPC = DY::N;                      // loads per consumer and piece (Y)
-    constexpr int NST = 4;                          // state stores per consumer at a chunk boundary
+    constexpr int NST = BM / 16;                    // state stores per consumer at a chunk boundary
+    constexpr int SN = BM == 64 ? 16 : 8;           // state columns that go through LDS together (what is left beside the ring)
     // pieces that the lines of X and Y are brought into L2 ahead (LinePrefetch).  16 heads 256 / 512, chunk 256, 8192 steps: 113 / 107.5
     // us per launch forward / reversed without, 105.8 / 104.7 with 3, 104.6 / 103.7 with 4, 108.1 / 106.3 with 6; 64 heads and
     // 4096 steps 218 / 203, 205 / 198, 205 / 197, 215 / 204.
@@ -71,17 +79,18 @@ __global__ void __launch_bounds__(WN * 128) recurrent_kernel_bf16(RecArgs a) {
     // 4, 2048 steps, chunk 128 756 -> 735, one sequence of 8192, chunk 256 661 -> 641; 256 / 1024 764 -> 755.  d2 = 256: 16
     // heads 512 / 256, batch 2, 2048 steps, chunk 128 419 -> 421, 8192 steps, chunk 512 1779 -> 1781.  Pieces of 64 rows: 256 / 512, batch 2,
     // 8192 steps, chunk 64 1169 -> 1179, heads of 512 630 -> 628, 512 / 256, chunk 192 587 -> 595.
+    // Tiles of 128 x 256 (16 to 32 of them per head: widths around 1024), 16 heads of 1024, 4096 steps: 1840 -> 1797; forward, chunk 128 855 -> 809.
     constexpr int AHEAD = 4;
-    constexpr bool PREFETCH = !PAD && BK == 128;
+    constexpr bool PREFETCH = !PAD && (BK == 128 || BM == 128);
     constexpr int STEADY = (NS - 2) * CPP, STEADY_C = (NS - 2) * CPC;
     static_assert(STEADY + NS - 1 + 2 * (NH + 1) <= 63 && STEADY_C + (NH + 1) * NST <= 63, "wait counts must fit the 6-bit counter");
     static_assert(CPC % KS == 0, "Y requests are spread evenly over the k steps");
 
     __shared__ __attribute__((aligned(1024))) char smem[NS * STAGE];
-    __shared__ __attribute__((aligned(1024))) char stage_out[WN * 2048];        // per consumer: [32 n][32 m] bf16
+    __shared__ __attribute__((aligned(1024))) char stage_out[WN * SN * 128];    // per consumer: [SN n][64 m] bf16
     __shared__ __attribute__((aligned(256))) float ldsRs[NS][BK];
     __shared__ __attribute__((aligned(256))) float ldsG[NS][64];
-    __shared__ __attribute__((aligned(256))) float ldsNx[2][WN][BM];            // column sums of scaled X, per producer
+    __shared__ __attribute__((aligned(256))) float ldsNx[2][NP][BM];            // column sums of scaled X, per producer
     __shared__ __attribute__((aligned(256))) float ldsPf[2][64];                // where the prefetches go
     TFLA_RTL_DECL
 
@@ -100,7 +109,7 @@ __global__ void __launch_bounds__(WN * 128) recurrent_kernel_bf16(RecArgs a) {
     const int PPC = a.L / BK, P = a.Nc * PPC;
     const uint32_t smem_a = lds_addr(smem), rs_a = lds_addr(ldsRs), g_a = lds_addr(ldsG);
     // the normaliser vector n (one value per state row) is kept by the workgroups bx == 0:
-    // lane l of the first producer owns row m0 + l
+    // lane l of producer w, w < BM / 64, owns row m0 + 64 w + l
     const bool with_n = (a.nst != nullptr) && bx == 0;
     // the caller's tensors: row strides, steps per (batch, head), and (PAD) columns from this tile's first on
     const int xld = PAD ? a.d1_in : a.d1, yld = PAD ? a.d2_in : a.d2, tld = PAD ? a.T_in : a.T;
@@ -110,9 +119,10 @@ __global__ void __launch_bounds__(WN * 128) recurrent_kernel_bf16(RecArgs a) {
         // =============================== producers ===========================================
         // the wavefronts that feed the ring issue ahead of the consumer on their SIMD (1.5 % on the kernel)
         __builtin_amdgcn_s_setprio(3);
-        const int ptid = tid - NTP;
-        const bool n_owner = with_n && wc == 0;
-        float nacc = (n_owner && a.n0 && (!PAD || lane < xcols)) ? a.n0[(long)bh * xld + m0 + lane] : 0.0f;
+        const int ptid = tid - NTC;
+        const bool n_owner = with_n && wc < BM / 64;
+        const int nrow = 64 * wc + lane;            // (an owner's)
+        float nacc = (n_owner && a.n0 && (!PAD || nrow < xcols)) ? a.n0[(long)bh * xld + m0 + nrow] : 0.0f;
         // make the compiler wait for this plain load here: a wait that it places later, inside the
         // loop, would also wait for every global->LDS load in flight
         asm volatile("" : "+v"(nacc));
@@ -120,6 +130,7 @@ __global__ void __launch_bounds__(WN * 128) recurrent_kernel_bf16(RecArgs a) {
 #pragma unroll
         for (int e = 0; e < 8; ++e) nsum[e] = 0.0f;
         DX dx; dx.init(xld, ptid);
+        if constexpr (PAD) dx.bound_columns(xcols, ptid);
         // Pieces are requested in order.  The addresses of the next piece to request advance
         // incrementally (no multiplication or division in the loop): 64 rows per piece; when the
         // recurrence runs backwards the chunks are visited last to first, rows inside a chunk still
@@ -133,7 +144,7 @@ __global__ void __launch_bounds__(WN * 128) recurrent_kernel_bf16(RecArgs a) {
         const long gstep = a.reverse ? -1 : 1;
         // producer 0 prefetches X, producer 1 Y
         LinePrefetch<BK, AHEAD> pf;
-        if (PREFETCH && gridDim.x >= 4 && wc < 2) {     // (tensors that end inside a piece: 58.4 us without, 58.6 with, 16 heads and 4000 steps)
+        if (PREFETCH && (BM == 128 || gridDim.x >= 4) && wc < 2) {     // (tensors that end inside a piece: 58.4 us without, 58.6 with, 16 heads and 4000 steps)
             pf.init(wc == 0 ? a.X : a.Y, bh, wc == 0 ? xld : yld, tld, wc == 0 ? a.d1 : a.d2, (int)(gridDim.x * gridDim.y), by * (int)gridDim.x + bx, P,
                     row0, lane, lds_addr(ldsPf) + 256u * wc);
             if (pf.on)
@@ -143,7 +154,7 @@ __global__ void __launch_bounds__(WN * 128) recurrent_kernel_bf16(RecArgs a) {
         int lsub = 0, lslot = 0;
         uint32_t lst = smem_a;
         auto request = [&]() {
-            if constexpr (PAD) dx.template issue_bounded<true>(xreq, bounded_bytes(xleft, xcols, 2 * xld), xcols, lst, ptid);
+            if constexpr (PAD) dx.template issue_bounded<true>(xreq, bounded_bytes(xleft, xcols, 2 * xld), BM, lst, ptid);
             else dx.issue(xreq, lst, ptid);
             // every producer fetches the same 64 row scales and gbar to the same place: identical
             // data, and each wavefront's own counter then covers what it reads
@@ -169,8 +180,8 @@ __global__ void __launch_bounds__(WN * 128) recurrent_kernel_bf16(RecArgs a) {
             char* xt = smem + slot * STAGE;
 #pragma unroll
             for (int j = 0; j < NX; ++j) {
-                const int cidx = (wc + j * WN) * 64 + lane;            // 16-byte chunk of the tile
-                const float sc = ldsRs[slot][cidx >> 3];
+                const int cidx = (wc + j * NP) * 64 + lane;            // 16-byte chunk of the tile
+                const float sc = ldsRs[slot][cidx / (BM / 8)];
                 u32x4 w = *reinterpret_cast<const u32x4*>(xt + cidx * 16);
 #pragma unroll
                 for (int d = 0; d < 4; ++d) {
@@ -182,17 +193,22 @@ __global__ void __launch_bounds__(WN * 128) recurrent_kernel_bf16(RecArgs a) {
             }
             // the piece that closes a chunk also closes the chunk's column sums
             if (with_n && closes) {
-                // lanes whose chunks hold the same eight columns differ in lane bits 3 and 5, and in
-                // bits 2 and 4 together (the swizzle moves a chunk by four positions on odd row pairs)
+                // lanes whose chunks hold the same eight columns differ, with 64 columns, in lane bits 3 and 5, and in
+                // bits 2 and 4 together (the swizzle moves a chunk by four positions on odd row pairs); with 128, in
+                // bits 2 and 4 together and in bits 3 and 5 together (by four positions per row)
 #pragma unroll
                 for (int e = 0; e < 8; ++e) {
                     float s = nsum[e];
                     s += __shfl_xor(s, 20, 64);
-                    s += __shfl_xor(s, 8, 64);
-                    s += __shfl_xor(s, 32, 64);
+                    if constexpr (BM == 64) {
+                        s += __shfl_xor(s, 8, 64);
+                        s += __shfl_xor(s, 32, 64);
+                    } else {
+                        s += __shfl_xor(s, 40, 64);
+                    }
                     nsum[e] = s;
                 }
-                if (lane < 8) {
+                if (lane < BM / 8) {
                     float* dst = &ldsNx[stp & 1][wc][8 * lane];
 #pragma unroll
                     for (int e = 0; e < 8; ++e) dst[e] = nsum[e];
@@ -225,13 +241,13 @@ __global__ void __launch_bounds__(WN * 128) recurrent_kernel_bf16(RecArgs a) {
                 // n before this chunk leaves as two bf16 rows of d1: the rounded value and the rounding
                 // remainder (together good to 2^-17), the form in which the parallel kernel feeds it to the
                 // matrix unit next to the state
-                uint16_t* np = reinterpret_cast<uint16_t*>(a.nst) + ((long)bh * a.Nc + kc) * 2 * a.d1 + m0 + lane;
+                uint16_t* np = reinterpret_cast<uint16_t*>(a.nst) + ((long)bh * a.Nc + kc) * 2 * a.d1 + m0 + nrow;
                 const uint32_t nhi = bf16_bits_rne(nacc);
                 np[0] = (uint16_t)nhi;
                 np[a.d1] = (uint16_t)bf16_bits_rne(nacc - bf16_lo_to_f32(nhi));
                 float s = 0.0f;
 #pragma unroll
-                for (int w = 0; w < WN; ++w) s += ldsNx[step & 1][w][lane];
+                for (int w = 0; w < NP; ++w) s += ldsNx[step & 1][w][nrow];
                 nacc = ldsG[slot][lane] * nacc + s;
                 st0 = 2;
             }
@@ -256,20 +272,26 @@ __global__ void __launch_bounds__(WN * 128) recurrent_kernel_bf16(RecArgs a) {
             for (int h = NH; h > 0; --h) sth[h] = sth[h - 1];
             sth[0] = st0;
         }
-        if (n_owner && a.nfinal && (!PAD || lane < xcols)) a.nfinal[(long)bh * xld + m0 + lane] = nacc;
+        if (n_owner && a.nfinal && (!PAD || nrow < xcols)) a.nfinal[(long)bh * xld + m0 + nrow] = nacc;
         wait_vmcnt<0>();                                // (nothing is on its way into LDS when the workgroup ends)
     } else {
         // =============================== consumers ===========================================
         f32x16 acc[MI];
 #pragma unroll
-        for (int mi = 0; mi < MI; ++mi)
+        for (int mi = 0; mi < MI; ++mi) {
+            // (one row block's addresses and masks at a time: all at once were 60 scalar registers spilled with 64 rows, 246
+            // vector registers with 128; with that and the columns bounded once, below, 16 heads 256 / 512, 4000 steps, forward
+            // + backward 413 -> 403 us)
+            int mb = m0 + mi * 32;
+            asm volatile("" : "+s"(mb));
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
-                const int m = m0 + mi * 32 + acc_row(v, g);
+                const int m = mb + acc_row(v, g);
                 const int n = n0 + wc * 32 + l32;
                 const bool there = !PAD || (m < a.d1_in && n < a.d2_in);
                 acc[mi][v] = (a.S0 && there) ? a.S0[((long)bh * xld + m) * yld + n] : 0.0f;
             }
+        }
         // make the compiler wait for these plain loads here rather than inside the loop, where its
         // wait would also cover the state stores in flight
 #pragma unroll
@@ -284,6 +306,7 @@ __global__ void __launch_bounds__(WN * 128) recurrent_kernel_bf16(RecArgs a) {
         asm volatile("" : "+v"(boff));
         // the consumers fetch the Y pieces (same order and address stepping as the producers' X)
         DY dy; dy.init(yld, tid);
+        if constexpr (PAD) dy.bound_columns(ycols, tid);
         const long row0 = a.reverse ? (long)(a.Nc - 1) * a.L : 0;
         const bf16_t* yreq = reinterpret_cast<const bf16_t*>(a.Y) + ((long)bh * tld + row0) * yld + n0;
         int yleft = PAD ? a.T_in - (int)row0 : 0;
@@ -291,7 +314,7 @@ __global__ void __launch_bounds__(WN * 128) recurrent_kernel_bf16(RecArgs a) {
         int lsub = 0, lslot = 0;
         uint32_t lst = smem_a + XB;
         auto request_part = [&](int q) {
-            if constexpr (PAD) dy.template issue_bounded<true>(yreq, bounded_bytes(yleft, ycols, 2 * yld), ycols, lst, tid, q, CPC);
+            if constexpr (PAD) dma16_bounded<true>(yreq, bounded_bytes(yleft, ycols, 2 * yld), dy.goff[q], lst + (wc + q * WN) * 1024);
             else dma16(yreq, dy.goff[q], lst + (wc + q * WN) * 1024);
         };
         auto request_end = [&]() {
@@ -318,34 +341,43 @@ __global__ void __launch_bounds__(WN * 128) recurrent_kernel_bf16(RecArgs a) {
             int st0 = 0;
             const char* xt = smem + slot * STAGE;
             const char* yt = xt + XB;
-            frag af[KS][MI], bfr[KS];
+            // the fragments of FK k steps at a time: all of them with two row blocks, two steps with four, whose registers
+            // the anchors below need
+            constexpr int FK = BM == 64 ? KS : 2;
+            frag af[FK][MI], bfr[FK];
+            auto fragments = [&](int ks) {
 #pragma unroll
-            for (int ks = 0; ks < KS; ++ks) {
+                for (int mi = 0; mi < MI; ++mi) af[ks % FK][mi].v = ra.load(xt, mi, 16 * ks, 16 * ks + 4);
+                bfr[ks % FK].v = TFragReader<BN>::load_at(yt, boff, 16 * ks, 16 * ks + 4);
+            };
+            if constexpr (FK == KS) {
 #pragma unroll
-                for (int mi = 0; mi < MI; ++mi) af[ks][mi].v = ra.load(xt, mi, 16 * ks, 16 * ks + 4);
-                bfr[ks].v = TFragReader<BN>::load_at(yt, boff, 16 * ks, 16 * ks + 4);
+                for (int ks = 0; ks < KS; ++ks) fragments(ks);
             }
             // chunk boundary: emit the state before this chunk's update, then decay
             if (sub == 0) {
                 const int kc = a.reverse ? a.Nc - 1 - step : step;
                 if (a.stT) {
                     st0 = NST;
-                    // through a private LDS tile [16 n][64 m] per half of the wave's 32 columns (16-byte chunks
+                    // through a private LDS tile [SN n][64 m] per part of the wave's 32 columns (16-byte chunks
                     // XOR-swizzled by the row) so that the state leaves in whole 128-byte lines
-                    char* ot = stage_out + wc * 2048;
+                    char* ot = stage_out + wc * SN * 128;
                     char* gdst = reinterpret_cast<char*>(a.stT) +
                                  ((((long)bh * a.Nc + kc) * a.d2 + n0 + wc * 32) * a.d1 + m0) * 2;
 #pragma unroll
-                    for (int h = 0; h < 2; ++h) {
-                        if ((l32 >> 4) == h) {
-                            const int n = l32 & 15;
+                    for (int mh = 0; mh < BM / 64; ++mh)
 #pragma unroll
-                            for (int mi = 0; mi < MI; ++mi)
+                    for (int h = 0; h < 32 / SN; ++h) {
+                        if ((l32 / SN) == h) {
+                            const int n = l32 % SN;
+#pragma unroll
+                            for (int mi = 0; mi < 2; ++mi)
 #pragma unroll
                                 for (int j = 0; j < 4; ++j) {
+                                    const f32x16& s = acc[2 * mh + mi];
                                     uint2 w;
-                                    w.x = pack_bf16x2(acc[mi][4 * j], acc[mi][4 * j + 1]);
-                                    w.y = pack_bf16x2(acc[mi][4 * j + 2], acc[mi][4 * j + 3]);
+                                    w.x = pack_bf16x2(s[4 * j], s[4 * j + 1]);
+                                    w.y = pack_bf16x2(s[4 * j + 2], s[4 * j + 3]);
                                     *reinterpret_cast<uint2*>(ot + n * 128 + (((4 * mi + j) ^ (n & 7)) * 16) + 8 * g) = w;
                                 }
                         }
@@ -353,11 +385,11 @@ __global__ void __launch_bounds__(WN * 128) recurrent_kernel_bf16(RecArgs a) {
                         // one wavefront's LDS operations in order)
                         asm volatile("" ::: "memory");
 #pragma unroll
-                        for (int q = 0; q < 2; ++q) {
+                        for (int q = 0; q < SN / 8; ++q) {
                             const int n = q * 8 + (lane >> 3), c = lane & 7;
                             const u32x4 w = *reinterpret_cast<const u32x4*>(ot + n * 128 + ((c ^ (n & 7)) * 16));
                             // (non-temporal: measured slightly faster for the tiled kernels that follow)
-                            __builtin_nontemporal_store(w, reinterpret_cast<u32x4*>(gdst + ((long)(16 * h + n) * a.d1 + 8 * c) * 2));
+                            __builtin_nontemporal_store(w, reinterpret_cast<u32x4*>(gdst + ((long)(SN * h + n) * a.d1 + 64 * mh + 8 * c) * 2));
                         }
                         asm volatile("" ::: "memory");
                     }
@@ -387,21 +419,25 @@ __global__ void __launch_bounds__(WN * 128) recurrent_kernel_bf16(RecArgs a) {
                             f32x4 c[MI * 4];
 #pragma unroll
                             for (int q = 0; q < MI * 4; ++q) c[q] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(a.anc_in + off + (long)q * 256));
-                            float dot = 0.0f;
+                            float dot[MI / 2] = {};         // (one partial per 64 rows of the tile)
 #pragma unroll
                             for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
                                 for (int j = 0; j < 4; ++j)
 #pragma unroll
-                                    for (int e = 0; e < 4; ++e) dot += acc[mi][4 * j + e] * c[mi * 4 + j][e];
+                                    for (int e = 0; e < 4; ++e) dot[mi / 2] += acc[mi][4 * j + e] * c[mi * 4 + j][e];
                             // Everything this wavefront has in flight has landed once these plain loads have (the
                             // compiler's own wait for them may or may not say so; this one does).  Operations from
                             // before this point can then never be younger than a piece that is still awaited, so the
                             // wait counts below stay valid without knowing about the loads.
                             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-                            dot = wave_sum(dot);
-                            if (lane == 0) a.anc_part[((long)bh * nslot + kb / a.anc_G) * (gridDim.x * gridDim.y * WN) + part] = dot;
-                            st0 += 1;
+#pragma unroll
+                            for (int h = 0; h < MI / 2; ++h) {
+                                dot[h] = wave_sum(dot[h]);
+                                if (lane == 0)
+                                    a.anc_part[((long)bh * nslot + kb / a.anc_G) * (gridDim.x * gridDim.y * WN * (MI / 2)) + part * (MI / 2) + h] = dot[h];
+                            }
+                            st0 += MI / 2;
                         }
                         asm volatile("" ::: "memory");
                     }
@@ -416,10 +452,12 @@ __global__ void __launch_bounds__(WN * 128) recurrent_kernel_bf16(RecArgs a) {
             // the Y part of piece i + NS - 1 (into the slot of piece i - 1, which every consumer has
             // left) is requested between the matrix instructions
             const bool req = i + NS - 1 < P;
+            if constexpr (FK < KS) fragments(0);
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) {
+                if (FK < KS && ks + 1 < KS) fragments(ks + 1);
 #pragma unroll
-                for (int mi = 0; mi < MI; ++mi) acc[mi] = E::mma(af[ks][mi], bfr[ks], acc[mi]);
+                for (int mi = 0; mi < MI; ++mi) acc[mi] = E::mma(af[ks % FK][mi], bfr[ks % FK], acc[mi]);
                 if (req) {
 #pragma unroll
                     for (int q = ks * CPC / KS; q < (ks + 1) * CPC / KS; ++q) request_part(q);
@@ -448,15 +486,18 @@ __global__ void __launch_bounds__(WN * 128) recurrent_kernel_bf16(RecArgs a) {
         }
         if (a.Sfinal || a.Sfinal2) {
 #pragma unroll
-            for (int mi = 0; mi < MI; ++mi)
+            for (int mi = 0; mi < MI; ++mi) {
+                int mb = m0 + mi * 32;          // (as above)
+                asm volatile("" : "+s"(mb));
 #pragma unroll
                 for (int v = 0; v < 16; ++v) {
-                    const int m = m0 + mi * 32 + acc_row(v, g);
+                    const int m = mb + acc_row(v, g);
                     const int n = n0 + wc * 32 + l32;
                     const bool there = !PAD || (m < a.d1_in && n < a.d2_in);
                     if (a.Sfinal && there) a.Sfinal[((long)bh * xld + m) * yld + n] = acc[mi][v];
                     if (a.Sfinal2) a.Sfinal2[((long)bh * a.d1 + m) * a.d2 + n] = acc[mi][v];
                 }
+            }
         }
     }
     TFLA_RTL_FLUSH

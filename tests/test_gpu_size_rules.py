@@ -77,6 +77,26 @@ def test_wide_contractions(keep, variant, B, NH, T, dqk, dhv, chunk):
     _check_slices(w, dCn=True, keep=keep, scan=True)
 
 
+# 128 x 256 state tiles of the recurrent kernel: from 129 of them on, but not from 257 to 320; one piece and several per chunk,
+# fewer pieces than ring stages, anchors, whole and ragged
+@pytest.mark.parametrize("variant,B,NH,T,dqk,dhv,chunk,state", [
+    (wl.EXP, 3, 43, 320, 128, 256, 64, True),        # 129
+    (wl.EXP, 8, 16, 320, 128, 256, 64, True),        # 128: the smaller tiles
+    (wl.SIG, 13, 20, 128, 128, 256, 128, False),     # 260: the smaller tiles
+    (wl.EXP, 8, 41, 192, 128, 256, 192, False),      # 328
+    (wl.EXP, 19, 7, 64, 128, 256, 64, True),         # one piece
+    (wl.EXP, 19, 7, 100, 120, 248, 128, True),
+    (wl.EXP, 4, 8, 700, 456, 504, 128, True),
+    (wl.SIG, 4, 8, 1100, 512, 512, 256, True),
+    (wl.EXP, 2, 3, 900, 1000, 1024, 128, True),      # 32 workgroups per head: with the L2 prefetch where whole
+    (wl.EXP, 2, 3, 1152, 1024, 1024, 128, True),
+    (wl.SIG, 2, 3, 1152, 1024, 1024, 192, False),
+])
+def test_large_state_tiles(variant, B, NH, T, dqk, dhv, chunk, state):
+    w = wl.small(variant, wl.BF16, B=B, NH=NH, T=T, dqk=dqk, dhv=dhv, chunk=chunk, seed=1700 + T + dqk, init_state=state)
+    _check_slices(w, dCn=state, keep=T % 128 == 0, scan=True)
+
+
 # 256-wide output blocks of the tiled kernels: rows / 128 * (columns / 256) >= 256 workgroups, chunk a multiple of 128
 @pytest.mark.parametrize("variant,B,NH,T,dqk,dhv,chunk", [
     (wl.EXP, 1, 4, 2048, 1024, 1024, 256),      # exactly 256 workgroups in every mode (weights from memory)
