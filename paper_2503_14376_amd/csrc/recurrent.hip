@@ -355,8 +355,8 @@ static hipError_t launch_rec_bf16(const RecArgs& a, int BH, hipStream_t s) {
     const bool wide_pieces = a.L % 128 == 0;
     const dim3 grid(a.d2 / (narrow ? 64 : 128), a.d1 / 64, BH), block(512);
     if (narrow) {
-        if (wide_pieces) hipLaunchKernelGGL((recurrent_narrow_kernel_bf16<128, PAD>), grid, block, 0, s, a);
-        else hipLaunchKernelGGL((recurrent_narrow_kernel_bf16<64, PAD>), grid, block, 0, s, a);
+        if (wide_pieces) hipLaunchKernelGGL((recurrent_narrow_kernel_bf16<128, PAD>), grid, dim3(640), 0, s, a);
+        else hipLaunchKernelGGL((recurrent_narrow_kernel_bf16<64, PAD>), grid, dim3(640), 0, s, a);
     } else {
         if (wide_pieces) hipLaunchKernelGGL((recurrent_kernel_bf16<4, 128, PAD>), grid, block, 0, s, a);
         else hipLaunchKernelGGL((recurrent_kernel_bf16<4, 64, PAD>), grid, block, 0, s, a);

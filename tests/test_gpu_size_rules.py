@@ -97,6 +97,18 @@ def test_large_state_tiles(variant, B, NH, T, dqk, dhv, chunk, state):
     _check_slices(w, dCn=state, keep=T % 128 == 0, scan=True)
 
 
+# Few state tiles: the reversed launch's anchors arrive through a ring of LDS buffers.  The first one belongs to piece 1, 2, 3, 4, ...
+# (the chunks past the last whole block), the next to one four or (heads wider than 512) two chunks on, and there may be none
+@pytest.mark.parametrize("B,NH,T,dqk,dhv,chunk", [
+    (1, 2, 64 * n, 64, 64, 64) for n in (2, 4, 5, 6, 7, 8, 9)] + [(1, 2, 128 * n, 64, 128, 128) for n in (4, 5, 6, 7)] + [
+    (1, 1, 64 * n, 64, 1024, 64) for n in (2, 3, 4, 9)] + [(1, 1, 128 * n, 64, 1024, 128) for n in (3, 8)] + [
+    (1, 1, 256 * 5, 1024, 64, 256), (1, 3, 700, 64, 128, 64), (1, 3, 900, 120, 64, 128),
+])
+def test_anchors_through_lds(B, NH, T, dqk, dhv, chunk):
+    w = wl.small(wl.EXP, wl.BF16, B=B, NH=NH, T=T, dqk=dqk, dhv=dhv, chunk=chunk, seed=1900 + T + dqk)
+    _check_slices(w, keep=T % 256 == 0, scan=True)
+
+
 # 256-wide output blocks of the tiled kernels: rows / 128 * (columns / 256) >= 256 workgroups, chunk a multiple of 128
 @pytest.mark.parametrize("variant,B,NH,T,dqk,dhv,chunk", [
     (wl.EXP, 1, 4, 2048, 1024, 1024, 256),      # exactly 256 workgroups in every mode (weights from memory)
