@@ -1,6 +1,8 @@
 // Gate kernels: chunkwise log gates and max states (forward and backward preparation) and
 // the final gate-gradient reduction.  All scalar-per-step work of the method lives here;
 // it is VALU + wavefront-scan work on (B*NH*T) floats.
+#include <type_traits>
+
 #include "tfla_device.h"
 #include "tfla_internal.h"
 
@@ -46,37 +48,70 @@ __device__ __forceinline__ void zero_share(const FillList& f, long thread, long 
         for (long i = thread; i < f.n[q]; i += threads) f.p[q][i] = 0.0f;
 }
 
-template <typename AT> __device__ __forceinline__ AT wave_excl_scan_add(AT v, int lane) {
-    AT x = v;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) { const AT y = __shfl_up(x, o, 64); if (lane >= o) x += y; }
-    const AT p = __shfl_up(x, 1, 64);
-    return lane == 0 ? (AT)0 : p;
+// Scans over the wavefront: within the rows of 16 lanes by moves between lanes (DPP row shifts), across the four rows by
+// the rows' totals, read into scalar registers.  (A shuffle through LDS per step, six per scan and as many for a sum: us per
+// launch, shuffles / this, 8 heads of 8 chunks of 128 6.1 / 5.3; in double, 1 head of 4 chunks of 64 4.1 / 3.1.)
+// x of the lane CTRL says, `none` where there is no such lane in the row
+template <int CTRL, typename T> __device__ __forceinline__ T row_move(T x, T none) {
+    if constexpr (sizeof(T) == 4) {
+        return __builtin_bit_cast(T, __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, none), __builtin_bit_cast(int, x), CTRL, 0xf, 0xf, false));
+    } else {
+        typedef int i2 __attribute__((ext_vector_type(2)));
+        const i2 n = __builtin_bit_cast(i2, none), v = __builtin_bit_cast(i2, x);
+        const i2 r = {__builtin_amdgcn_update_dpp(n[0], v[0], CTRL, 0xf, 0xf, false), __builtin_amdgcn_update_dpp(n[1], v[1], CTRL, 0xf, 0xf, false)};
+        return __builtin_bit_cast(T, r);
+    }
+}
+template <typename T> __device__ __forceinline__ T lane_value(T x, int l) {
+    if constexpr (sizeof(T) == 4) {
+        return __builtin_bit_cast(T, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), l));
+    } else {
+        typedef int i2 __attribute__((ext_vector_type(2)));
+        const i2 v = __builtin_bit_cast(i2, x);
+        const i2 r = {__builtin_amdgcn_readlane(v[0], l), __builtin_amdgcn_readlane(v[1], l)};
+        return __builtin_bit_cast(T, r);
+    }
+}
+// the operands of op are in lane order: op(earlier lanes, later lanes)
+template <typename T, typename Op> __device__ __forceinline__ T wave_excl_scan(T x, T none, int lane, Op op, T* total = nullptr) {
+    x = op(row_move<0x111>(x, none), x);        // row_shr:1, 2, 4, 8
+    x = op(row_move<0x112>(x, none), x);
+    x = op(row_move<0x114>(x, none), x);
+    x = op(row_move<0x118>(x, none), x);
+    const T t0 = lane_value(x, 15), t1 = op(t0, lane_value(x, 31)), t2 = op(t1, lane_value(x, 47));
+    if (total) *total = op(t2, lane_value(x, 63));
+    const T before = lane < 16 ? none : lane < 32 ? t0 : lane < 48 ? t1 : t2;
+    return op(before, row_move<0x111>(x, none));
+}
+// the same over the lanes behind
+template <typename T, typename Op> __device__ __forceinline__ T wave_excl_rscan(T x, T none, int lane, Op op) {
+    x = op(x, row_move<0x101>(x, none));        // row_shl:1, 2, 4, 8
+    x = op(x, row_move<0x102>(x, none));
+    x = op(x, row_move<0x104>(x, none));
+    x = op(x, row_move<0x108>(x, none));
+    const T t3 = lane_value(x, 48), t2 = op(lane_value(x, 32), t3), t1 = op(lane_value(x, 16), t2);
+    const T after = lane >= 48 ? none : lane >= 32 ? t3 : lane >= 16 ? t2 : t1;
+    return op(row_move<0x101>(x, none), after);
+}
+template <typename AT> __device__ __forceinline__ AT wave_excl_scan_add(AT v, int lane, AT* total = nullptr) {
+    return wave_excl_scan(v, (AT)0, lane, [](AT x, AT y) { return x + y; }, total);
 }
 template <typename AT> __device__ __forceinline__ AT wave_excl_rscan_add(AT v, int lane) {
-    AT x = v;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) { const AT y = __shfl_down(x, o, 64); if (lane + o < 64) x += y; }
-    const AT p = __shfl_down(x, 1, 64);
-    return lane == 63 ? (AT)0 : p;
+    return wave_excl_rscan(v, (AT)0, lane, [](AT x, AT y) { return x + y; });
 }
 template <typename AT> __device__ __forceinline__ AT wave_excl_scan_max(AT v, int lane) {
-    AT x = v;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) { const AT y = __shfl_up(x, o, 64); if (lane >= o) x = max_t<AT>(x, y); }
-    const AT p = __shfl_up(x, 1, 64);
-    return lane == 0 ? (AT)-INFINITY : p;
+    return wave_excl_scan(v, (AT)-INFINITY, lane, [](AT x, AT y) { return max_t<AT>(x, y); });
 }
-template <typename AT> __device__ __forceinline__ AT wave_sum_t(AT x) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
-    return x;
+// (every lane gets the result)
+template <typename T, typename Op> __device__ __forceinline__ T wave_reduce(T x, Op op) {
+    x = op(x, row_move<0x128>(x, x));           // row_ror:8, 4, 2, 1
+    x = op(x, row_move<0x124>(x, x));
+    x = op(x, row_move<0x122>(x, x));
+    x = op(x, row_move<0x121>(x, x));
+    return op(op(lane_value(x, 0), lane_value(x, 16)), op(lane_value(x, 32), lane_value(x, 48)));
 }
-template <typename AT> __device__ __forceinline__ AT wave_max_t(AT x) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) x = max_t<AT>(x, __shfl_xor(x, o, 64));
-    return x;
-}
+template <typename AT> __device__ __forceinline__ AT wave_sum_t(AT x) { return wave_reduce(x, [](AT p, AT q) { return p + q; }); }
+template <typename AT> __device__ __forceinline__ AT wave_max_t(AT x) { return wave_reduce(x, [](AT p, AT q) { return max_t<AT>(p, q); }); }
 
 // The gate pre-pass runs as two kernels, each with one wavefront per chunk (four chunks per
 // workgroup), so that it fills the chip also when batch * heads is small.
@@ -94,15 +129,34 @@ template <typename AT> __device__ __forceinline__ AT wave_max_t(AT x) {
 // before any matrix product and no online rescaling is needed in the tiled kernel.
 static constexpr int GATE_WAVES = 4;
 
+// E consecutive values of a lane, one vector access.  What bounds these kernels is latency: few wavefronts, each with chains
+// of scans, logarithms and exponentials between its loads and stores, so the accesses are few and the loads come first.  us per
+// launch, value by value / as vectors, chunk and step kernel: 8 heads of 32 chunks of 256 8.6 / 6.8 and 5.4 / 4.9; 8 heads of 64 chunks
+// of 512 13.5 / 10.4 and 11.6 / 6.4; the anchored gradients, 8 heads of 8192 steps 8.6 / 6.6.
+template <int E, typename T> __device__ __forceinline__ void load_steps(T (&v)[E], const T* p) {
+    typedef T vec __attribute__((ext_vector_type(E)));
+    const vec w = *reinterpret_cast<const vec*>(p);
+#pragma unroll
+    for (int e = 0; e < E; ++e) v[e] = w[e];
+}
+template <int E, typename T> __device__ __forceinline__ void store_steps(T* p, const T (&v)[E]) {
+    typedef T vec __attribute__((ext_vector_type(E)));
+    vec w;
+#pragma unroll
+    for (int e = 0; e < E; ++e) w[e] = v[e];
+    *reinterpret_cast<vec*>(p) = w;
+}
+
+// WHOLE: a lane has exactly EC steps (chunks of 64, 128, 256 and 512), which move as vectors.
 // EC > 0: the lane's E <= EC steps keep their log gates in registers (one evaluation of the logarithms per
 // step instead of one per pass); EC = 0: any E, the log gates are evaluated again in every pass.
 // tmp and csum hold values of type AT.
-template <int EC, typename AT>
+template <int EC, typename AT, bool WHOLE>
 __global__ void __launch_bounds__(GATE_WAVES * 64) gates_chunk_kernel(GateArgs a) {
     const int bh = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int kc = blockIdx.x * GATE_WAVES + wave;
     if (kc >= a.Nc) return;
-    const int E = a.L / 64;
+    const int E = WHOLE ? EC : a.L / 64;
     const bool is_exp = a.variant == 0;
     const long row = (long)bh * a.T;
     AT* tb = reinterpret_cast<AT*>(a.tmp) + (long)bh * 3 * a.T;
@@ -136,7 +190,8 @@ __global__ void __launch_bounds__(GATE_WAVES * 64) gates_chunk_kernel(GateArgs a
 #pragma unroll
     for (int e = 0; e < EB; ++e)
         if (e < E) fsum += fbar(e);
-    const AT off = wave_excl_scan_add<AT>(fsum, lane);
+    AT gsum;
+    const AT off = wave_excl_scan_add<AT>(fsum, lane, &gsum);
     const AT roff = wave_excl_rscan_add<AT>(fsum, lane);
     // forward pass: b, u = i-bar - b, running max of u
     AT b = off, cmx = (AT)-INFINITY;
@@ -148,18 +203,24 @@ __global__ void __launch_bounds__(GATE_WAVES * 64) gates_chunk_kernel(GateArgs a
         }
     const AT cmoff = wave_excl_scan_max<AT>(cmx, lane);
     b = off; cmx = cmoff;
+    AT bv[NC], cv[NC], av_[NC];
+    float uhv[NC], ulv[NC];
 #pragma unroll
     for (int e = 0; e < EB; ++e)
         if (e < E) {
             b += fbar(e);
             const AT u = ibar(e) - b;
             cmx = max_t<AT>(cmx, u);
-            tb[t0 + e] = b;
-            tc[t0 + e] = cmx;
             const AT ul = u * log2e;
             const float uh = (float)ul;
-            a.ucol[row + t0 + e] = uh;
-            if (a.ucol_lo) a.ucol_lo[row + t0 + e] = (float)(ul - (AT)uh);
+            if constexpr (WHOLE) {
+                bv[e] = b; cv[e] = cmx; uhv[e] = uh; ulv[e] = (float)(ul - (AT)uh);
+            } else {
+                tb[t0 + e] = b;
+                tc[t0 + e] = cmx;
+                a.ucol[row + t0 + e] = uh;
+                if (a.ucol_lo) a.ucol_lo[row + t0 + e] = (float)(ul - (AT)uh);
+            }
         }
     // reverse pass: a_j = sum_{s>j} f-bar_s + i-bar_j
     AT run = roff, amax = (AT)-INFINITY;
@@ -167,19 +228,27 @@ __global__ void __launch_bounds__(GATE_WAVES * 64) gates_chunk_kernel(GateArgs a
     for (int e = EB - 1; e >= 0; --e)
         if (e < E) {
             const AT av = run + ibar(e);
-            ta[t0 + e] = av;
+            if constexpr (WHOLE) av_[e] = av;
+            else ta[t0 + e] = av;
             amax = max_t<AT>(amax, av);
             run += fbar(e);
         }
+    if constexpr (WHOLE) {
+        store_steps<EC>(tb + t0, bv);
+        store_steps<EC>(tc + t0, cv);
+        store_steps<EC>(ta + t0, av_);
+        store_steps<EC>(a.ucol + row + t0, uhv);
+        if (a.ucol_lo) store_steps<EC>(a.ucol_lo + row + t0, ulv);
+    }
     amax = wave_max_t<AT>(amax);
-    const AT gsum = wave_sum_t<AT>(fsum);
     if (lane == 0) {
         csum[((long)bh * 2 + 0) * a.Nc + kc] = gsum;
         csum[((long)bh * 2 + 1) * a.Nc + kc] = amax;
     }
 }
 
-template <typename AT>
+// EC > 0: a lane has exactly EC steps, which move as vectors and are requested before the recurrence over the chunks
+template <int EC, typename AT>
 __global__ void __launch_bounds__(GATE_WAVES * 64) gates_step_kernel(GateArgs a) {
     if (a.variant != 0) zero_share(a.zero, ((long)blockIdx.y * gridDim.x + blockIdx.x) * blockDim.x + threadIdx.x, (long)gridDim.x * gridDim.y * blockDim.x);
     extern __shared__ double cm_raw[];   // [Nc + 1] values of type AT: m before chunk k
@@ -188,6 +257,17 @@ __global__ void __launch_bounds__(GATE_WAVES * 64) gates_step_kernel(GateArgs a)
     const bool is_exp = a.variant == 0;
     const AT* cg = reinterpret_cast<const AT*>(a.csum) + ((long)bh * 2 + 0) * a.Nc;
     const AT* camax = reinterpret_cast<const AT*>(a.csum) + ((long)bh * 2 + 1) * a.Nc;
+    const int kc = blockIdx.x * GATE_WAVES + wave;
+    const int E = EC > 0 ? EC : a.L / 64;
+    const long row = (long)bh * a.T;
+    const AT* tb = reinterpret_cast<const AT*>(a.tmp) + (long)bh * 3 * a.T;
+    const AT* tc = tb + a.T;
+    const AT* ta = tc + a.T;
+    const long t0 = (long)kc * a.L + (long)lane * E;
+    constexpr int NC = EC > 0 ? EC : 1;
+    AT bv[NC], cv[NC], av_[NC];
+    if constexpr (EC > 0)
+        if (kc < a.Nc) { load_steps<EC>(bv, tb + t0); load_steps<EC>(cv, tc + t0); load_steps<EC>(av_, ta + t0); }
     if (wave == 0) {
         // lane l composes the maps of its segment of chunks, a wavefront scan composes the segments,
         // then every lane walks its segment again from its incoming m
@@ -195,15 +275,21 @@ __global__ void __launch_bounds__(GATE_WAVES * 64) gates_step_kernel(GateArgs a)
         const int k0 = lane * seg, k1 = min(a.Nc, k0 + seg);
         AT G = (AT)0, C = (AT)-INFINITY;
         for (int k = k0; k < k1; ++k) { C = max_t<AT>(C + cg[k], camax[k]); G += cg[k]; }
-        // inclusive scan of the composed maps over the lanes
-        AT Gs = G, Cs = C;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const AT Gp = __shfl_up(Gs, o, 64), Cp = __shfl_up(Cs, o, 64);
-            if (lane >= o) { Cs = max_t<AT>(Cp + Gs, Cs); Gs = Gp + Gs; }
-        }
-        // exclusive: the map of all chunks before this lane's segment, applied to m0
-        const AT Ge = __shfl_up(Gs, 1, 64), Ce = __shfl_up(Cs, 1, 64);
+        // exclusive scan over the lanes: the map of all chunks before this lane's segment, applied to m0
+        struct Map { AT g, c; };
+        const auto then = [](Map p, Map q) { return Map{p.g + q.g, max_t<AT>(p.c + q.g, q.c)}; };       // q after p
+        const auto moved = [](Map p, auto ctrl) { return Map{row_move<decltype(ctrl)::value>(p.g, (AT)0), row_move<decltype(ctrl)::value>(p.c, (AT)-INFINITY)}; };
+        const auto at = [](Map p, int l) { return Map{lane_value(p.g, l), lane_value(p.c, l)}; };
+        Map x{G, C};
+        x = then(moved(x, std::integral_constant<int, 0x111>()), x);
+        x = then(moved(x, std::integral_constant<int, 0x112>()), x);
+        x = then(moved(x, std::integral_constant<int, 0x114>()), x);
+        x = then(moved(x, std::integral_constant<int, 0x118>()), x);
+        const Map p0 = at(x, 15), p1 = then(p0, at(x, 31)), p2 = then(p1, at(x, 47));
+        Map before{(AT)0, (AT)-INFINITY};
+        if (lane >= 16) before = lane < 32 ? p0 : lane < 48 ? p1 : p2;
+        before = then(before, moved(x, std::integral_constant<int, 0x111>()));
+        const AT Ge = before.g, Ce = before.c;
         const AT m_init = (is_exp && a.m0) ? (AT)a.m0[bh] : (AT)0;
         AT m = lane == 0 ? m_init : max_t<AT>(m_init + Ge, Ce);
         if (!is_exp) m = (AT)0;
@@ -219,19 +305,11 @@ __global__ void __launch_bounds__(GATE_WAVES * 64) gates_step_kernel(GateArgs a)
         }
     }
     __syncthreads();
-    const int kc = blockIdx.x * GATE_WAVES + wave;
     if (kc >= a.Nc) return;
-    const int E = a.L / 64;
-    const long row = (long)bh * a.T;
-    const AT* tb = reinterpret_cast<const AT*>(a.tmp) + (long)bh * 3 * a.T;
-    const AT* tc = tb + a.T;
-    const AT* ta = tc + a.T;
     const AT log2e = (AT)1.4426950408889634;
     const AT lq = (AT)log2f(a.qscale);
-    const long t0 = (long)kc * a.L + (long)lane * E;
     const AT mprev = cm[kc], mk = cm[kc + 1];
-    for (int e = 0; e < E; ++e) {
-        const AT b = tb[t0 + e], cmx = tc[t0 + e], av = ta[t0 + e];
+    auto step = [&](AT b, AT cmx, AT av, float& wh, float& wl, float& shf, float& ak, float& mof) {
         AT wr, sh, mo;
         if (is_exp) {
             const AT M = max_t<AT>(mprev, cmx);
@@ -243,13 +321,37 @@ __global__ void __launch_bounds__(GATE_WAVES * 64) gates_step_kernel(GateArgs a)
             sh = exp_t<AT>(b) * (AT)a.qscale;
             mo = (AT)0;
         }
-        const float wh = (float)wr;
-        a.wrow[row + t0 + e] = wh;
-        if (a.wrow_lo) a.wrow_lo[row + t0 + e] = (float)(wr - (AT)wh);
-        a.sH[row + t0 + e] = (float)sh;
-        a.aK[row + t0 + e] = (float)exp_t<AT>(av - mk);
-        a.mout[row + t0 + e] = (float)mo;
-        if (a.mout_user && t0 + e < a.Tvalid) a.mout_user[(long)bh * a.Tvalid + t0 + e] = (float)mo;
+        wh = (float)wr;
+        wl = (float)(wr - (AT)wh);
+        shf = (float)sh;
+        ak = (float)exp_t<AT>(av - mk);
+        mof = (float)mo;
+    };
+    if constexpr (EC > 0) {
+        float wh[EC], wl[EC], sh[EC], ak[EC], mo[EC];
+#pragma unroll
+        for (int e = 0; e < EC; ++e) step(bv[e], cv[e], av_[e], wh[e], wl[e], sh[e], ak[e], mo[e]);
+        store_steps<EC>(a.wrow + row + t0, wh);
+        if (a.wrow_lo) store_steps<EC>(a.wrow_lo + row + t0, wl);
+        store_steps<EC>(a.sH + row + t0, sh);
+        store_steps<EC>(a.aK + row + t0, ak);
+        store_steps<EC>(a.mout + row + t0, mo);
+        if (a.mout_user) {
+#pragma unroll
+            for (int e = 0; e < EC; ++e)
+                if (t0 + e < a.Tvalid) a.mout_user[(long)bh * a.Tvalid + t0 + e] = mo[e];
+        }
+    } else {
+        for (int e = 0; e < E; ++e) {
+            float wh, wl, sh, ak, mo;
+            step(tb[t0 + e], tc[t0 + e], ta[t0 + e], wh, wl, sh, ak, mo);
+            a.wrow[row + t0 + e] = wh;
+            if (a.wrow_lo) a.wrow_lo[row + t0 + e] = wl;
+            a.sH[row + t0 + e] = sh;
+            a.aK[row + t0 + e] = ak;
+            a.mout[row + t0 + e] = mo;
+            if (a.mout_user && t0 + e < a.Tvalid) a.mout_user[(long)bh * a.Tvalid + t0 + e] = mo;
+        }
     }
 }
 
@@ -282,7 +384,8 @@ __global__ void __launch_bounds__(GATE_FUSED_CHUNKS * 64) gates_fused_kernel(Gat
     AT fsum = (AT)0;
 #pragma unroll
     for (int e = 0; e < E; ++e) fsum += fb[e];
-    const AT off = wave_excl_scan_add<AT>(fsum, lane), roff = wave_excl_rscan_add<AT>(fsum, lane);
+    AT gsum;
+    const AT off = wave_excl_scan_add<AT>(fsum, lane, &gsum), roff = wave_excl_rscan_add<AT>(fsum, lane);
     AT run = off, cmx = (AT)-INFINITY;
     float uh[E], ul[E];
 #pragma unroll
@@ -306,7 +409,6 @@ __global__ void __launch_bounds__(GATE_FUSED_CHUNKS * 64) gates_fused_kernel(Gat
         run += fb[e];
     }
     amax = wave_max_t<AT>(amax);
-    const AT gsum = wave_sum_t<AT>(fsum);
     if (lane == 0) { cg[kc] = gsum; camax[kc] = amax; }
     // (read once, before the barrier: the caller's final state may be the buffer of its initial state, and the last chunk's
     // wavefront writes it without waiting for the others)
@@ -360,15 +462,26 @@ template <typename AT> static hipError_t launch_gates_t(const GateArgs& a, int B
         return hipGetLastError();
     }
     const dim3 grid((a.Nc + GATE_WAVES - 1) / GATE_WAVES, BH);
+    const dim3 block(GATE_WAVES * 64);
+    const size_t lds = sizeof(AT) * (size_t)(a.Nc + 1);
+    auto both = [&](auto chunk_kernel, auto step_kernel) {
+        hipLaunchKernelGGL(chunk_kernel, grid, block, 0, s, a);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(step_kernel, grid, block, lds, s, a);
+        return hipGetLastError();
+    };
     // the log gates of a lane's steps stay in registers for every chunk size the library accepts (L <= 2048)
-    if (a.L / 64 <= 8) hipLaunchKernelGGL((gates_chunk_kernel<8, AT>), grid, dim3(GATE_WAVES * 64), 0, s, a);
-    else if (a.L / 64 <= 16) hipLaunchKernelGGL((gates_chunk_kernel<16, AT>), grid, dim3(GATE_WAVES * 64), 0, s, a);
-    else if (a.L / 64 <= 32) hipLaunchKernelGGL((gates_chunk_kernel<32, AT>), grid, dim3(GATE_WAVES * 64), 0, s, a);
-    else hipLaunchKernelGGL((gates_chunk_kernel<0, AT>), grid, dim3(GATE_WAVES * 64), 0, s, a);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(gates_step_kernel<AT>, grid, dim3(GATE_WAVES * 64), sizeof(AT) * (size_t)(a.Nc + 1), s, a);
-    return hipGetLastError();
+    switch (a.L) {
+        case 64: return both(gates_chunk_kernel<1, AT, true>, gates_step_kernel<1, AT>);
+        case 128: return both(gates_chunk_kernel<2, AT, true>, gates_step_kernel<2, AT>);
+        case 256: return both(gates_chunk_kernel<4, AT, true>, gates_step_kernel<4, AT>);
+        case 512: return both(gates_chunk_kernel<8, AT, true>, gates_step_kernel<8, AT>);
+    }
+    if (a.L / 64 <= 8) return both(gates_chunk_kernel<8, AT, false>, gates_step_kernel<0, AT>);
+    if (a.L / 64 <= 16) return both(gates_chunk_kernel<16, AT, false>, gates_step_kernel<0, AT>);
+    if (a.L / 64 <= 32) return both(gates_chunk_kernel<32, AT, false>, gates_step_kernel<0, AT>);
+    return both(gates_chunk_kernel<0, AT, false>, gates_step_kernel<0, AT>);
 }
 
 // a.precise: the fp32 kernels' pre-pass (double arithmetic, two-float exponents; tmp and csum then hold doubles)
@@ -450,9 +563,7 @@ __device__ __forceinline__ double gate_grad_block_part(const GateGradArgs& a, lo
 __global__ void __launch_bounds__(256) gate_grads_sum_kernel(GateGradArgs a) {
     __shared__ double wt[4];
     const int bh = blockIdx.y, blk = blockIdx.x, tid = threadIdx.x;
-    double tot = gate_grad_block_part(a, (long)bh * a.T, blk, tid);
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) tot += __shfl_xor(tot, o, 64);
+    const double tot = wave_sum_t<double>(gate_grad_block_part(a, (long)bh * a.T, blk, tid));
     if ((tid & 63) == 0) wt[tid >> 6] = tot;
     __syncthreads();
     if (tid == 0) a.bsum[(long)bh * gridDim.x + blk] = wt[0] + wt[1] + wt[2] + wt[3];
@@ -471,8 +582,7 @@ __global__ void __launch_bounds__(256) gate_grads_kernel(GateGradArgs a) {
     } else {
         for (int b2 = blk + 1 + tid; b2 < nblk; b2 += 256) later += a.bsum[(long)bh * nblk + b2];
     }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) later += __shfl_xor(later, o, 64);
+    later = wave_sum_t<double>(later);
     if (lane == 0) wt[wave] = later;
     __syncthreads();
     if (tid == 0) after = wt[0] + wt[1] + wt[2] + wt[3] + state_dot_sum(a, bh);
@@ -488,13 +598,9 @@ __global__ void __launch_bounds__(256) gate_grads_kernel(GateGradArgs a) {
         if (t0 + e < a.T) gate_grad_terms(a, row + t0 + e, r[e], c[e]);
         tot += (double)r[e] - (double)c[e];
     }
-    double x = tot;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) { const double y = __shfl_down(x, o, 64); if (lane + o < 64) x += y; }
-    double excl = __shfl_down(x, 1, 64);
-    if (lane == 63) excl = 0.0;
+    double excl = wave_excl_rscan_add<double>(tot, lane);
     __syncthreads();
-    if (lane == 0) wt[wave] = x;
+    if (lane == 0) wt[wave] = tot + excl;
     __syncthreads();
     for (int w = wave + 1; w < 4; ++w) excl += wt[w];
     double run = excl + after;
@@ -518,6 +624,8 @@ __global__ void __launch_bounds__(256) gate_grads_kernel(GateGradArgs a) {
 // then scans its own steps only, from the anchor at its end, and the rounding noise of the terms no longer
 // accumulates over the whole sequence (it grows with sqrt(T) in the unanchored scan).  One workgroup per
 // block (at most 2048 steps); a thread owns up to eight consecutive steps.
+// SC > 0: a thread owns exactly SC steps (a block is 256 SC steps), whose terms move as vectors; 0: any number up to eight.
+template <int SC>
 __global__ void __launch_bounds__(256) gate_grads_anchored_kernel(GateGradArgs a) {
     __shared__ double wt[4];
     const int bh = blockIdx.y, blk = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -525,22 +633,47 @@ __global__ void __launch_bounds__(256) gate_grads_anchored_kernel(GateGradArgs a
     const int kc0 = blk * a.G, kc1 = min(kc0 + a.G, a.Nc);      // chunks [kc0, kc1)
     const long tb = (long)kc0 * a.L;                            // first step of the block
     const int len = (kc1 - kc0) * a.L;                          // steps in this block
-    const int SEG = (a.G * a.L + 255) / 256;           // <= 8: G * L <= 2048
+    const int SEG = SC > 0 ? SC : (a.G * a.L + 255) / 256;     // <= 8: G * L <= 2048
+    constexpr int NE = SC > 0 ? SC : 8;
     const int l0 = tid * SEG;                          // first of this thread's steps within the block
-    float r[8], c[8];
+    float r[NE], c[NE], fpre[NE], ipre[NE];
     double tot = 0.0;
+    // (the gate pre-activations are requested ahead of the scan)
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        r[e] = 0.0f; c[e] = 0.0f;
-        if (e < SEG && l0 + e < len) gate_grad_terms(a, row + tb + l0 + e, r[e], c[e]);
-        tot += (double)r[e] - (double)c[e];
+    for (int e = 0; e < NE; ++e) {
+        const bool there = e < SEG && l0 + e < len && tb + l0 + e < a.Tvalid;
+        const long u = (long)bh * a.Tvalid + tb + l0 + e;
+        fpre[e] = there ? a.f_pre[u] : 0.0f;
+        ipre[e] = there ? a.i_pre[u] : 0.0f;
     }
-    double x = tot;
+    if constexpr (SC > 0) {
 #pragma unroll
-    for (int o = 1; o < 64; o <<= 1) { const double y = __shfl_down(x, o, 64); if (lane + o < 64) x += y; }
-    double excl = __shfl_down(x, 1, 64);
-    if (lane == 63) excl = 0.0;
-    if (lane == 0) wt[wave] = x;
+        for (int e = 0; e < NE; ++e) { r[e] = 0.0f; c[e] = 0.0f; }
+        if (l0 < len) {             // (whole segments: len is a multiple of SC)
+            float v[SC];
+            for (int nb = 0; nb < a.nbQ; ++nb) {
+                load_steps<SC>(v, a.partQ + (long)nb * a.BHT + row + tb + l0);
+#pragma unroll
+                for (int e = 0; e < SC; ++e) r[e] += v[e];
+            }
+            for (int nb = 0; nb < a.nbK; ++nb) {
+                load_steps<SC>(v, a.partK + (long)nb * a.BHT + row + tb + l0);
+#pragma unroll
+                for (int e = 0; e < SC; ++e) c[e] += v[e];
+            }
+        }
+#pragma unroll
+        for (int e = 0; e < NE; ++e) tot += (double)r[e] - (double)c[e];
+    } else {
+#pragma unroll
+        for (int e = 0; e < NE; ++e) {
+            r[e] = 0.0f; c[e] = 0.0f;
+            if (e < SEG && l0 + e < len) gate_grad_terms(a, row + tb + l0 + e, r[e], c[e]);
+            tot += (double)r[e] - (double)c[e];
+        }
+    }
+    double excl = wave_excl_rscan_add<double>(tot, lane);
+    if (lane == 0) wt[wave] = tot + excl;
     __syncthreads();
     for (int w = wave + 1; w < 4; ++w) excl += wt[w];
     // the anchor at the end of the block: <C_T, dC_T> (or nothing) at the end of the sequence, else <C, dC> at the
@@ -554,21 +687,20 @@ __global__ void __launch_bounds__(256) gate_grads_anchored_kernel(GateGradArgs a
         const float* pp = a.anchor + ((long)bh * nslot + kc1 / a.G) * a.npart;
         double ps = 0.0;
         for (int q = tid; q < a.npart; q += 256) ps += (double)pp[q];
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) ps += __shfl_xor(ps, o, 64);
+        ps = wave_sum_t<double>(ps);
         if (lane == 0) wa[wave] = ps;
         __syncthreads();
         anc = (wa[0] + wa[1]) + (wa[2] + wa[3]);
     }
     double run = excl + anc;
 #pragma unroll
-    for (int e = 7; e >= 0; --e) {
+    for (int e = NE - 1; e >= 0; --e) {
         if (e < SEG && l0 + e < len) {
             const long t = tb + l0 + e;
             run += (double)r[e] - (double)c[e];
             if (t < a.Tvalid) {
                 const long u = (long)bh * a.Tvalid + t;
-                const float fp = a.f_pre[u], ip = a.i_pre[u];
+                const float fp = fpre[e], ip = ipre[e];
                 a.d_f[u] = (float)run * sigmoid_neg(soft_cap(fp, a.softcap)) * soft_cap_grad(fp, a.softcap);
                 a.d_i[u] = (a.variant == 0 ? c[e] : c[e] * sigmoid_neg(soft_cap(ip, a.softcap))) * soft_cap_grad(ip, a.softcap);
             }
@@ -579,7 +711,15 @@ __global__ void __launch_bounds__(256) gate_grads_anchored_kernel(GateGradArgs a
 hipError_t launch_gate_grads(const GateGradArgs& a, int BH, hipStream_t s) {
     if (a.anchor) {
         if (a.G < 1 || (long)a.G * a.L > 2048) return hipErrorInvalidValue;
-        hipLaunchKernelGGL(gate_grads_anchored_kernel, dim3((a.Nc + a.G - 1) / a.G, BH), dim3(256), 0, s, a);
+        const dim3 grid((a.Nc + a.G - 1) / a.G, BH);
+        auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, a); };
+        switch (a.G * a.L) {
+            case 256: launch(gate_grads_anchored_kernel<1>); break;
+            case 512: launch(gate_grads_anchored_kernel<2>); break;
+            case 1024: launch(gate_grads_anchored_kernel<4>); break;
+            case 2048: launch(gate_grads_anchored_kernel<8>); break;
+            default: launch(gate_grads_anchored_kernel<0>);
+        }
         return hipGetLastError();
     }
     const dim3 grid((a.T + GG_BLOCK - 1) / GG_BLOCK, BH);
@@ -618,8 +758,7 @@ __global__ void __launch_bounds__(256) state_dot_kernel(const float* A, long per
         const float* br = Bm + ((long)bh * d1 + r) * d2;
         for (int c = lane; c < d2; c += 64) acc += (double)ar[c] * (double)br[c];
     }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o, 64);
+    acc = wave_sum_t<double>(acc);
     if (lane == 0) wt[wave] = acc;
     __syncthreads();
     if (threadIdx.x == 0) out[(long)bh * STATE_DOT_PARTS + p] = (wt[0] + wt[1]) + (wt[2] + wt[3]);

@@ -109,6 +109,18 @@ def test_anchors_through_lds(B, NH, T, dqk, dhv, chunk):
     _check_slices(w, keep=T % 256 == 0, scan=True)
 
 
+# Gate kernels of more than sixteen chunks: chunks of 64, 128, 256 and 512 move a lane's steps as vectors, others do not; several
+# chunks per lane of the recurrence over the chunks (more than 64), a last block of the gradient scan with fewer chunks, ragged ends
+@pytest.mark.parametrize("dtype", [wl.BF16, wl.F32])
+@pytest.mark.parametrize("variant,T,chunk", [
+    (wl.EXP, 64 * 19, 64), (wl.SIG, 64 * 67 - 3, 64), (wl.EXP, 64 * 131 - 1, 64), (wl.EXP, 128 * 17 - 100, 128), (wl.SIG, 256 * 18, 256),
+    (wl.EXP, 256 * 17 - 255, 256), (wl.EXP, 512 * 17 - 77, 512), (wl.EXP, 192 * 18 - 5, 192), (wl.SIG, 320 * 17, 320),
+])
+def test_gates_of_many_chunks(dtype, variant, T, chunk):
+    w = wl.small(variant, dtype, B=1, NH=2, T=T, dqk=64, dhv=64, chunk=chunk, seed=2100 + T)
+    _check_slices(w, keep=T % 2 == 0, scan=True)
+
+
 # 256-wide output blocks of the tiled kernels: rows / 128 * (columns / 256) >= 256 workgroups, chunk a multiple of 128
 @pytest.mark.parametrize("variant,B,NH,T,dqk,dhv,chunk", [
     (wl.EXP, 1, 4, 2048, 1024, 1024, 256),      # exactly 256 workgroups in every mode (weights from memory)
