@@ -86,6 +86,16 @@ template <typename DT, int D1, int MODE, int SPLIT = 0>
 static hipError_t launch_tile_d1(const TileArgs& a, int BH, int bd2, hipStream_t s) {
     if (a.L % 128 == 0) {
         if constexpr (sizeof(DT) == 2 && D1 > 256) {   // see tile_bd2()
+            if constexpr (D1 == 1024) {
+                // 256 rows per workgroup, eight wavefronts: a third less to bring into LDS per result, which is what these
+                // kernels wait for (7.5 TB/s with 128 rows).  16 heads of 1024, 4096 steps, chunk 256, H / dV / dQ / dK 268 / 239 /
+                // 274 / 286 -> 224 / 209 / 232 / 239 us.  A round of these workgroups lasts some 7/4 rounds of the others.  Forward +
+                // backward, 128 -> 256 rows, by the number of workgroups: 160 408 -> 342, 192 479 -> 425, 256 529 -> 496, 448 851 -> 798, 1024 1801 ->
+                // 1669; 320 646 -> 655 (H and dV alone) and 384 725 -> 708 stay with 128.
+                const long wgs = (long)BH * a.T / 256 * (a.d2 / 256);
+                if (bd2 == 256 && a.L % 256 == 0 && 7 * ((wgs + 255) / 256) <= 4 * ((2 * wgs + 255) / 256))
+                    return launch_tile_t<DT, D1, 256, 8, MODE, SPLIT>(a, BH, s);
+            }
             if (bd2 == 256) return launch_tile_t<DT, D1, 256, 4, MODE, SPLIT>(a, BH, s);
         }
         if (bd2 == 128) return launch_tile_t<DT, D1, 128, 4, MODE, SPLIT>(a, BH, s);

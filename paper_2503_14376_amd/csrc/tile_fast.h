@@ -70,7 +70,7 @@ template <int D1, int BD2, int NW, int MODE, int OCC, int SPLIT, int NOE, int FU
     static constexpr int NT = NW * 64, BR = NW * 32, BC = 32;
     static constexpr int KS1 = D1 / 16, NB = BD2 / 32;
     static constexpr int YB = ELITE ? BC * BR * 2 : BC * D1 * 2, ZB = BC * BD2 * 2;         // bytes
-    static constexpr int XSMIN = BR * (D1 < 128 ? D1 : 128) * 2;       // room for wide X slices when the tiles are small
+    static constexpr int XSMIN = BR * (D1 < 128 ? D1 : NW == 8 ? 64 : 128) * 2;    // room for wide X slices when the tiles are small
     static constexpr int STAGE = (ELITE && YB + ZB < XSMIN) ? XSMIN : YB + ZB;
     static constexpr int ESTG = EWRITE ? NW * 2048 : 0;                // per-wave staging of E tiles
     // LDS budget of one workgroup: 160 KB shared by OCC resident workgroups, minus the small arrays
@@ -89,7 +89,8 @@ template <int D1, int BD2, int NW, int MODE, int OCC, int SPLIT, int NOE, int FU
 
     // after the loops the ring's memory holds the output block (and the dot operand) of each wave
     static constexpr bool WTILE = MODE == MODE_DQ || MODE == MODE_DK || FUSE;   // the epilogue reads a second per-wave tile
-    static constexpr int EPI = (WTILE ? 2 : 1) * NW * 32 * BD2 * 2;
+    static constexpr bool WSEQ = WTILE && NW == 8;                              // ... in the place of the first, before that is written
+    static constexpr int EPI = (WTILE && !WSEQ ? 2 : 1) * NW * 32 * BD2 * 2;
     static constexpr int SMEM = NS * STAGE > EPI ? NS * STAGE : EPI;
     static_assert(SMEM <= BUDGET, "LDS budget");
     // The epilogue's per-wave tiles ([32][BD2] bf16: the output block on its way out and, for dQ / dK, the wave's rows
@@ -127,7 +128,7 @@ __device__ __forceinline__ void tile_body_bf16(const TileArgs& a, const TileLds&
     using E = Elem<bf16_t>;
     using frag = E::frag;
     using SH = TileShape<D1, BD2, NW, MODE, OCC, SPLIT, NOE, FUSE>;
-    constexpr bool UPPER = SH::UPPER, STT = SH::STT, ELITE = SH::ELITE, EROWS = SH::EROWS, EWRITE = SH::EWRITE, WTILE = SH::WTILE, WPRE = SH::WPRE;
+    constexpr bool UPPER = SH::UPPER, STT = SH::STT, ELITE = SH::ELITE, EROWS = SH::EROWS, EWRITE = SH::EWRITE, WTILE = SH::WTILE, WPRE = SH::WPRE, WSEQ = SH::WSEQ;
     constexpr int NT = SH::NT, BR = SH::BR, BC = SH::BC, KS1 = SH::KS1, NB = SH::NB, YB = SH::YB, STAGE = SH::STAGE, NS = SH::NS,
                   BCS = SH::BCS, NKS = SH::NKS, BXS = SH::BXS, NPRE = SH::NPRE, SLOT = SH::SLOT, SPS = SH::SPS;
     char* const smem = lds.smem;
@@ -644,7 +645,7 @@ __device__ __forceinline__ void tile_body_bf16(const TileArgs& a, const TileLds&
     if constexpr (MODE == MODE_H && NOE == 2) {
         // the row's weights, added up by the blocks of weights_kernel_bf16 that hold them
         if (a.variant == 0)
-            for (int cb = 0; cb <= rb; ++cb) nrm += a.nrm_in[(long)cb * (long)bhn * a.T + t];
+            for (int cb = 0; cb <= wr0 / (NW == 8 ? 128 : BR); ++cb) nrm += a.nrm_in[(long)cb * (long)bhn * a.T + t];     // (those blocks have 128 rows at most)
     }
     if constexpr (SPLIT == 1) {
         float* pout = a.acc_out + t * d2 + (long)nb2 * BD2 + 4 * g;
@@ -683,7 +684,7 @@ __device__ __forceinline__ void tile_body_bf16(const TileArgs& a, const TileLds&
     constexpr int OCPR = BD2 / 8, ORB = BD2 * 2;         // chunks and bytes per tile row
     auto slot_at = [&](int sl) { return smem + ((NI + sl / SPS) % NS) * STAGE + (sl % SPS) * SLOT; };
     char* otile = WPRE ? slot_at(NW + wave) : smem + wave * (32 * ORB);
-    char* wtile = WPRE ? slot_at(wave) : smem + NW * (32 * ORB) + wave * (32 * ORB);
+    char* wtile = WSEQ ? otile : WPRE ? slot_at(wave) : smem + NW * (32 * ORB) + wave * (32 * ORB);
     if (WTILE && !WPRE) {
         DmaTile<32, BD2, 64, SWZ_K> dw;                  // this wave's rows of the dot operand (of the gate pre-activations)
         dw.init(zld, lane);
@@ -714,6 +715,25 @@ __device__ __forceinline__ void tile_body_bf16(const TileArgs& a, const TileLds&
         }
     }
     const int fsw = swz_mask<SWZ_K, OCPR>(l32);
+    // dQ / dK: the row dots of the gate gradients
+    auto row_dots = [&]() {
+        float d = 0.0f;
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const uint2 w = *reinterpret_cast<const uint2*>(wtile + l32 * ORB + (((4 * nb + j) ^ fsw) * 16) + 8 * g);
+                d += acc[nb][4 * j] * bf16_lo_to_f32(w.x) + acc[nb][4 * j + 1] * bf16_hi_to_f32(w.x) +
+                     acc[nb][4 * j + 2] * bf16_lo_to_f32(w.y) + acc[nb][4 * j + 3] * bf16_hi_to_f32(w.y);
+            }
+        d += __shfl_xor(d, 32, 64);
+        if (g == 0) a.dotpart[(long)nb2 * (long)bhn * a.T + t] = d;
+    };
+    if constexpr (WSEQ) {
+        wait_vmcnt<0>();
+        row_dots();
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");      // (the output takes the operand's place)
+    }
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
@@ -793,23 +813,13 @@ __device__ __forceinline__ void tile_body_bf16(const TileArgs& a, const TileLds&
             __builtin_nontemporal_store(yw, reinterpret_cast<u32x4*>(ybase + (long)r * d2 * 2 + c * 16));
         }
     }
-    if (MODE == MODE_DQ || MODE == MODE_DK) {
+    if constexpr ((MODE == MODE_DQ || MODE == MODE_DK) && !WSEQ) {
         // the dot operand has landed: its loads are older than the output stores above (and than the E stores of the
         // last tile), which may still be on their way.  (A padded problem issues a store only where a lane has
         // something to store, so their number is not known here.)
         if constexpr (PAD) wait_vmcnt<0>();
         else wait_vmcnt<32 / (64 / OCPR)>();
-        float d = 0.0f;
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const uint2 w = *reinterpret_cast<const uint2*>(wtile + l32 * ORB + (((4 * nb + j) ^ fsw) * 16) + 8 * g);
-                d += acc[nb][4 * j] * bf16_lo_to_f32(w.x) + acc[nb][4 * j + 1] * bf16_hi_to_f32(w.x) +
-                     acc[nb][4 * j + 2] * bf16_lo_to_f32(w.y) + acc[nb][4 * j + 3] * bf16_hi_to_f32(w.y);
-            }
-        d += __shfl_xor(d, 32, 64);
-        if (g == 0) a.dotpart[(long)nb2 * (long)bhn * a.T + t] = d;
+        row_dots();
     }
     TFLA_TL(5);
 #ifdef TFLA_TIMELINE

@@ -121,6 +121,19 @@ def test_gates_of_many_chunks(dtype, variant, T, chunk):
     _check_slices(w, keep=T % 2 == 0, scan=True)
 
 
+# 256 rows per workgroup for contractions over 1024 columns: chunks of 256 and multiples, more than 128 workgroups, whole and ragged
+@pytest.mark.parametrize("variant,B,NH,T,dqk,dhv,chunk", [
+    (wl.EXP, 3, 3, 1024, 1024, 1024, 256),      # 144 workgroups
+    (wl.SIG, 2, 2, 2300, 1000, 1016, 256),      # 160 with the last chunk ragged
+    (wl.EXP, 2, 5, 1536, 1024, 768, 768),       # (three row blocks per chunk)
+    (wl.EXP, 1, 17, 1024, 1024, 512, 512),      # H and dV only, 136
+    (wl.EXP, 1, 17, 1000, 512, 1024, 512),      # dQ and dK only
+])
+def test_wide_contractions_256_rows(variant, B, NH, T, dqk, dhv, chunk):
+    w = wl.small(variant, wl.BF16, B=B, NH=NH, T=T, dqk=dqk, dhv=dhv, chunk=chunk, seed=2300 + T + dqk)
+    _check_slices(w, dCn=True, keep=T % 512 != 0, scan=True)
+
+
 # 256-wide output blocks of the tiled kernels: rows / 128 * (columns / 256) >= 256 workgroups, chunk a multiple of 128
 @pytest.mark.parametrize("variant,B,NH,T,dqk,dhv,chunk", [
     (wl.EXP, 1, 4, 2048, 1024, 1024, 256),      # exactly 256 workgroups in every mode (weights from memory)
