@@ -488,7 +488,7 @@ int bwd_impl(const void* q, const void* k, const void* v, const float* i_pre, co
     gg.BHT = d.BHT; gg.bsum = w.bsum; gg.softcap = softcap;
     gg.anchor = nullptr; gg.L = chunk; gg.Nc = d.Nc; gg.G = 1; gg.npart = 0;
     // bf16: the forget-gate scan is anchored with <C_k, dC_k> at the end of every block of anchor_chunks() chunks
-    // (a block has at most 2048 steps), so that the rounding noise of its terms (one part in 2^9 of the boundary
+    // (a block has at most 4096 steps), so that the rounding noise of its terms (one part in 2^9 of the boundary
     // terms per chunk, from the bf16 states) accumulates over one block instead of the whole sequence.  The anchors
     // themselves are exact to fp32: the forward recurrent launch leaves fp32 copies of the state at the block
     // boundaries and the reversed launch multiplies them with its fp32 accumulators (see RecArgs).

@@ -623,9 +623,9 @@ __global__ void __launch_bounds__(256) gate_grads_kernel(GateGradArgs a) {
 // use, so d f-bar there is <C_{k+1}, dC_{k+1}>, which needs no summation over time.  Every block of G chunks
 // then scans its own steps only, from the anchor at its end, and the rounding noise of the terms no longer
 // accumulates over the whole sequence (it grows with sqrt(T) in the unanchored scan).  One workgroup per
-// block (at most 2048 steps); a thread owns up to eight consecutive steps.
-// SC > 0: a thread owns exactly SC steps (a block is 256 SC steps), whose terms move as vectors; 0: any number up to eight.
-template <int SC>
+// block (at most 4096 steps, ANCHOR_STEPS); a thread owns up to sixteen consecutive steps.
+// SC > 0: a thread owns exactly SC steps (a block is 256 SC steps), whose terms move as vectors; 0: any number up to MOST.
+template <int SC, int MOST = SC>
 __global__ void __launch_bounds__(256) gate_grads_anchored_kernel(GateGradArgs a) {
     __shared__ double wt[4];
     const int bh = blockIdx.y, blk = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -633,8 +633,8 @@ __global__ void __launch_bounds__(256) gate_grads_anchored_kernel(GateGradArgs a
     const int kc0 = blk * a.G, kc1 = min(kc0 + a.G, a.Nc);      // chunks [kc0, kc1)
     const long tb = (long)kc0 * a.L;                            // first step of the block
     const int len = (kc1 - kc0) * a.L;                          // steps in this block
-    const int SEG = SC > 0 ? SC : (a.G * a.L + 255) / 256;     // <= 8: G * L <= 2048
-    constexpr int NE = SC > 0 ? SC : 8;
+    const int SEG = SC > 0 ? SC : (a.G * a.L + 255) / 256;     // <= MOST: the launcher's rule
+    constexpr int NE = MOST;
     const int l0 = tid * SEG;                          // first of this thread's steps within the block
     float r[NE], c[NE], fpre[NE], ipre[NE];
     double tot = 0.0;
@@ -710,7 +710,7 @@ __global__ void __launch_bounds__(256) gate_grads_anchored_kernel(GateGradArgs a
 
 hipError_t launch_gate_grads(const GateGradArgs& a, int BH, hipStream_t s) {
     if (a.anchor) {
-        if (a.G < 1 || (long)a.G * a.L > 2048) return hipErrorInvalidValue;
+        if (a.G < 1 || (long)a.G * a.L > ANCHOR_STEPS) return hipErrorInvalidValue;
         const dim3 grid((a.Nc + a.G - 1) / a.G, BH);
         auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, a); };
         switch (a.G * a.L) {
@@ -718,7 +718,9 @@ hipError_t launch_gate_grads(const GateGradArgs& a, int BH, hipStream_t s) {
             case 512: launch(gate_grads_anchored_kernel<2>); break;
             case 1024: launch(gate_grads_anchored_kernel<4>); break;
             case 2048: launch(gate_grads_anchored_kernel<8>); break;
-            default: launch(gate_grads_anchored_kernel<0>);
+            default:
+                if (a.G * a.L < 2048) launch(gate_grads_anchored_kernel<0, 8>);
+                else launch(gate_grads_anchored_kernel<0, ANCHOR_STEPS / 256>);     // (heads wider than 512, chunks above 1024)
         }
         return hipGetLastError();
     }

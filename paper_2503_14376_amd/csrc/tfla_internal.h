@@ -58,7 +58,7 @@ struct GateGradArgs {
     int T, variant; long BHT;
     int Tvalid;                    // i_pre, f_pre, d_i, d_f are (BH, Tvalid)
     float softcap;                 // as in GateArgs: the gradients are taken through the cap
-    // optional anchors of the reverse cumulative sum, one per block of G chunks (G * L <= 2048): its exact value
+    // optional anchors of the reverse cumulative sum, one per block of G chunks (G * L <= ANCHOR_STEPS): its exact value
     // just after the last step of the block, <C, dC> at that boundary, as npart partial sums per boundary
     // (RecArgs::anc_part: (BH, nslot, npart)); NULL = one scan over the whole sequence
     const float* anchor; int L, Nc, G, npart;
@@ -71,9 +71,11 @@ hipError_t launch_copy(const float* from, float* to, int n, hipStream_t s);
 // as STATE_DOT_PARTS partial sums each
 constexpr int STATE_DOT_PARTS = 16;
 hipError_t launch_state_dot(const float* A, long perA, int lda, const float* Bm, int d1, int d2, double* out, int BH, hipStream_t s);
-// Chunks per block of the anchored forget-gate gradient scan: four (a block has at most 2048 steps); two for heads
-// wider than 512, where a row's dot products run over so many terms that the noise of a few chunks already shows
-// (behind a norm layer the forget-gate gradient is what survives of an almost complete cancellation).
+// Chunks per block of the anchored forget-gate gradient scan: four (a block then has at most 2048 steps, or one chunk); two for
+// heads wider than 512, whatever the chunk (at most 4096 steps), where a row's dot products run over so many terms that the
+// noise of a few chunks already shows (behind a norm layer the forget-gate gradient is what survives of an almost complete
+// cancellation).  The workspaces are laid out by it.
+constexpr int ANCHOR_STEPS = 4096;
 inline int anchor_chunks(int L, int dwide) {
     if (dwide > 512) return 2;
     return 4 * L <= 2048 ? 4 : (2048 / L > 0 ? 2048 / L : 1);

@@ -77,6 +77,19 @@ def test_wide_contractions(keep, variant, B, NH, T, dqk, dhv, chunk):
     _check_slices(w, dCn=True, keep=keep, scan=True)
 
 
+# heads wider than 512 with chunks above 1024: a block of the forget-gate gradient scan is two chunks, up to 4096 steps
+@pytest.mark.parametrize("variant,B,NH,T,dqk,dhv,chunk", [
+    (wl.EXP, 1, 2, 3 * 1088, 64, 1024, 1088),   # blocks of 2176 steps, the last one half full
+    (wl.SIG, 1, 1, 4000, 1000, 256, 1536),
+    (wl.EXP, 1, 1, 2 * 2048, 520, 64, 2048),    # one block of 4096
+    (wl.EXP, 1, 1, 2 * 2048 + 100, 128, 1024, 2048),
+    (wl.EXP, 1, 1, 2 * 1088, 1024, 1024, 1088),
+])
+def test_wide_heads_long_chunks(variant, B, NH, T, dqk, dhv, chunk):
+    w = wl.small(variant, wl.BF16, B=B, NH=NH, T=T, dqk=dqk, dhv=dhv, chunk=chunk, seed=2500 + T + dqk)
+    _check_slices(w, dCn=True, keep=T % 64 == 0, scan=True)
+
+
 # 128 x 256 state tiles of the recurrent kernel: from 129 of them on, but not from 257 to 320; one piece and several per chunk,
 # fewer pieces than ring stages, anchors, whole and ragged
 @pytest.mark.parametrize("variant,B,NH,T,dqk,dhv,chunk,state", [
