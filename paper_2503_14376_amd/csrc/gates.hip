@@ -139,8 +139,9 @@ template <int E, typename T> __device__ __forceinline__ void load_steps(T (&v)[E
 #pragma unroll
     for (int e = 0; e < E; ++e) v[e] = w[e];
 }
-template <int E, typename T> __device__ __forceinline__ void store_steps(T* p, const T (&v)[E]) {
-    typedef T vec __attribute__((ext_vector_type(E)));
+// ALIGN: what p is a multiple of, where that may be less than the vector's size (the caller's tensors)
+template <int E, int ALIGN = 0, typename T> __device__ __forceinline__ void store_steps(T* p, const T (&v)[E]) {
+    typedef T vec __attribute__((ext_vector_type(E), aligned(ALIGN > 0 ? ALIGN : E * sizeof(T))));
     vec w;
 #pragma unroll
     for (int e = 0; e < E; ++e) w[e] = v[e];
@@ -335,7 +336,7 @@ __global__ void __launch_bounds__(GATE_WAVES * 64) gates_step_kernel(GateArgs a)
         if (a.wrow_lo) store_steps<EC>(a.wrow_lo + row + t0, wl);
         store_steps<EC>(a.sH + row + t0, sh);
         store_steps<EC>(a.aK + row + t0, ak);
-        store_steps<EC>(a.mout + row + t0, mo);
+        store_steps<EC, 4>(a.mout + row + t0, mo);          // (may be the caller's tensor)
         if (a.mout_user) {
 #pragma unroll
             for (int e = 0; e < EC; ++e)

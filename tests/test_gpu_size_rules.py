@@ -134,6 +134,30 @@ def test_gates_of_many_chunks(dtype, variant, T, chunk):
     _check_slices(w, keep=T % 2 == 0, scan=True)
 
 
+# m_out and n_out are any float pointers: outputs that lie one float into a buffer are those of a call with aligned ones
+@pytest.mark.parametrize("dtype", [wl.BF16, wl.F32])
+@pytest.mark.parametrize("T,chunk", [(64 * 17, 64), (128 * 17, 128), (256 * 17, 256), (512 * 17, 512), (256 * 3, 256)])
+def test_unaligned_per_step_outputs(dtype, T, chunk):
+    import paper_2503_14376_amd as tfla
+    from tests import gpu_util as gu
+    w = wl.small(wl.EXP, dtype, B=1, NH=2, T=T, dqk=64, dhv=64, chunk=chunk, seed=2700 + T)
+    dev = gu.dev_inputs(w, wl.make_inputs(w))
+    args = [dev[x] for x in ("q", "k", "v", "i_pre", "f_pre", "C0", "n0", "m0")]
+    kw = dict(chunk=w.chunk, variant=w.variant, eps=1e-6)
+    ref = tfla.mlstm_fwd(*args, **kw)
+    out = {k: torch.empty_like(ref[k]) for k in ("H", "Cn", "nn", "mn")}
+    for k in ("n_out", "m_out"):
+        out[k] = torch.empty(ref[k].numel() + 1, device="cuda")[1:].view(ref[k].shape)
+        assert out[k].data_ptr() % 8 == 4
+    res = tfla.mlstm_fwd(*args, **kw, out=out)
+    a, b = (tfla.mlstm_bwd(*args[:5], dev["dH"], f["n_out"], f["m_out"], *args[5:], **kw, fwd_workspace=f["workspace"]) for f in (ref, res))
+    torch.cuda.synchronize()
+    for k in ("H", "Cn", "nn", "mn", "n_out", "m_out"):
+        assert torch.equal(ref[k], res[k]), k
+    for k in ("dq", "dk", "dv", "d_i_pre", "d_f_pre"):
+        assert torch.equal(a[k], b[k]), k
+
+
 # 256 rows per workgroup for contractions over 1024 columns: chunks of 256 and multiples, more than 128 workgroups, whole and ragged
 @pytest.mark.parametrize("variant,B,NH,T,dqk,dhv,chunk", [
     (wl.EXP, 3, 3, 1024, 1024, 1024, 256),      # 144 workgroups
