@@ -89,11 +89,14 @@ static hipError_t launch_tile_d1(const TileArgs& a, int BH, int bd2, hipStream_t
             if constexpr (D1 == 1024) {
                 // 256 rows per workgroup, eight wavefronts: a third less to bring into LDS per result, which is what these
                 // kernels wait for (7.5 TB/s with 128 rows).  16 heads of 1024, 4096 steps, chunk 256, H / dV / dQ / dK 268 / 239 /
-                // 274 / 286 -> 224 / 209 / 232 / 239 us.  A round of these workgroups lasts some 7/4 rounds of the others.  Forward +
-                // backward, 128 -> 256 rows, by the number of workgroups: 160 408 -> 342, 192 479 -> 425, 256 529 -> 496, 448 851 -> 798, 1024 1801 ->
-                // 1669; 320 646 -> 655 (H and dV alone) and 384 725 -> 708 stay with 128.
+                // 274 / 286 -> 224 / 209 / 232 / 239 us.  Forward + backward, 128 -> 256 rows, by the number of workgroups: 160 408 -> 342,
+                // 192 479 -> 425, 256 529 -> 496, 416 875 -> 800, 448 896 -> 817, 512 949 -> 883, 528 1067 -> 1053, 576 1095 -> 1073, 640 1159 ->
+                // 1115, 672 1285 -> 1189, 800 1516 -> 1460, 1024 1801 -> 1669; 1024 / 512 576 1340 -> 1335; 256 / 1024 640 1614 -> 1592; chunk 512 576
+                // 1067 -> 991.  With a second round that is less than half full the two are within 2 % and which is faster
+                // differs by shape: 288 636 -> 638 (1016 / 1000, 1000 steps 668 -> 679; chunk 768 615 -> 601), 320 649 -> 655 (689 -> 703; chunk 512
+                // 635 -> 623), 384 741 -> 727 (800 -> 798; 1024 / 512 885 -> 890).  Those keep 128.
                 const long wgs = (long)BH * a.T / 256 * (a.d2 / 256);
-                if (bd2 == 256 && a.L % 256 == 0 && 7 * ((wgs + 255) / 256) <= 4 * ((2 * wgs + 255) / 256))
+                if (bd2 == 256 && a.L % 256 == 0 && (wgs <= 256 || wgs > 384))
                     return launch_tile_t<DT, D1, 256, 8, MODE, SPLIT>(a, BH, s);
             }
             if (bd2 == 256) return launch_tile_t<DT, D1, 256, 4, MODE, SPLIT>(a, BH, s);

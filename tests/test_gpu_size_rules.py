@@ -165,6 +165,8 @@ def test_unaligned_per_step_outputs(dtype, T, chunk):
     (wl.EXP, 2, 5, 1536, 1024, 768, 768),       # (three row blocks per chunk)
     (wl.EXP, 1, 17, 1024, 1024, 512, 512),      # H and dV only, 136
     (wl.EXP, 1, 17, 1000, 512, 1024, 512),      # dQ and dK only
+    (wl.EXP, 1, 24, 1000, 1024, 1024, 256),     # 384 workgroups: the last with 128 rows
+    (wl.SIG, 1, 33, 1000, 1024, 1024, 256),     # 528
 ])
 def test_wide_contractions_256_rows(variant, B, NH, T, dqk, dhv, chunk):
     w = wl.small(variant, wl.BF16, B=B, NH=NH, T=T, dqk=dqk, dhv=dhv, chunk=chunk, seed=2300 + T + dqk)
