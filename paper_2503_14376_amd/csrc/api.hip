@@ -24,8 +24,9 @@ struct Dims {
     size_t esz;
 };
 
-// a contraction wider than the tiled kernels hold in registers runs as two launches that meet in fp32
-inline bool contraction_split(int d1, int dtype) { return dtype == TFLA_BF16 ? d1 > 512 : d1 > 256; }
+// a contraction wider than the tiled kernels hold in registers: it reads weights that a launch before it has left in memory
+// (bf16), or runs as two launches that meet in fp32 (fp32, and H of bf16 where the weights do not fit)
+inline bool contraction_wide(int d1, int dtype) { return dtype == TFLA_BF16 ? d1 > 512 : d1 > 256; }
 // the head dimension the kernels run a caller's head dimension at (the columns in between count as zeros)
 inline int kernel_dim(int d) { return d <= 64 ? 64 : (d <= 128 ? 128 : (d <= 256 ? 256 : (d <= 512 ? 512 : 1024))); }
 
@@ -101,9 +102,10 @@ FwdWs carve_fwd(const Dims& d, void* ws) {
     w.nst = c.take<float>(d.BH * d.Nc * d.dqk);
     w.Cfin = c.take<float>((size_t)d.BH * d.dqk * d.dhv);
     w.stT = c.take_bytes((size_t)d.BH * d.Nc * d.dqk * d.dhv * d.esz);
-    // d_qk above 512: the parallel kernel contracts over d_qk in two halves that meet in fp32
-    w.pacc = contraction_split(d.dqk, d.dtype) ? c.take<float>((size_t)d.BHT * d.dhv) : nullptr;
-    w.pnrm = contraction_split(d.dqk, d.dtype) ? c.take<float>(d.BHT) : nullptr;
+    // what a wide contraction over d_qk leaves for the next launch: fp32 partial results and normalisers, or, in the place of the
+    // former, the weighted matrix of H and the sums of its rows (weights_fit())
+    w.pacc = contraction_wide(d.dqk, d.dtype) ? c.take<float>((size_t)d.BHT * d.dhv) : nullptr;
+    w.pnrm = contraction_wide(d.dqk, d.dtype) ? c.take<float>(d.BHT) : nullptr;
     // bf16: fp32 copies of the state at the block boundaries of the forget-gate gradient scan (see bwd_core)
     w.anc = d.dtype == TFLA_BF16 ? c.take<float>(anchor_slots(d) * (size_t)d.BH * d.dqk * d.dhv) : nullptr;
     w.bytes = c.off;
@@ -114,7 +116,7 @@ struct BwdWs {
     float *wrow, *ucol, *sH, *aK, *gbar, *mout, *tmp, *csum, *wrowB, *sQ, *partQ, *partK, *Cfinal, *anchor, *pacc, *ancC;
     float *wrow_lo, *ucol_lo, *wrowB_lo;   // fp32 kernels: rounding remainders of the exponents (NULL for bf16)
     double *bsum, *cdot;
-    void *cN, *dcT, *E, *E2;
+    void *cN, *dcT, *E;
     int nbQ, nbK;
     size_t bytes;
 };
@@ -150,11 +152,12 @@ BwdWs carve_bwd(const Dims& d, void* ws) {
     w.cN = c.take_bytes(st); w.dcT = c.take_bytes(st);
     // bf16: the weighted intra-chunk matrix shared by dQ and dK, (BH, Nc, L, L)
     w.E = (d.dtype == TFLA_BF16 && tile_shares_E(d.dhv)) ? c.take_bytes((size_t)d.BHT * d.L * d.esz) : nullptr;
-    // head dimensions above 512: fp32 partial results of the gradient kernels' first half, and the second
-    // half's E when the products of dQ / dK run over the halves of d_hv
+    // wide contractions.  bf16: the weighted matrix of dV, (BH, Nc, L, L) (dQ and dK have E); fp32: partial results of the gradient
+    // kernels' first half
     const int dwide = d.dqk > d.dhv ? d.dqk : d.dhv;
-    w.pacc = contraction_split(dwide, d.dtype) ? c.take<float>((size_t)d.BHT * dwide) : nullptr;
-    w.E2 = (d.dtype == TFLA_BF16 && d.dhv > 512) ? c.take_bytes((size_t)d.BHT * d.L * d.esz) : nullptr;
+    w.pacc = nullptr;
+    if (d.dtype != TFLA_BF16) w.pacc = contraction_wide(dwide, d.dtype) ? c.take<float>((size_t)d.BHT * dwide) : nullptr;
+    else if (contraction_wide(d.dqk, d.dtype)) w.pacc = reinterpret_cast<float*>(c.take_bytes((size_t)d.BHT * d.L * d.esz));
     // bf16: fp32 boundary copies of C (used when the states are recomputed here), and the partial inner products
     // <C, dC> of every boundary
     w.ancC = d.dtype == TFLA_BF16 ? c.take<float>(anchor_slots(d) * (size_t)d.BH * d.dqk * d.dhv) : nullptr;
@@ -453,7 +456,7 @@ int bwd_impl(const void* q, const void* k, const void* v, const float* i_pre, co
     // 4. the three gradient kernels
     TileArgs t{};
     t.T = d.T; t.L = chunk; t.Nc = d.Nc; t.variant = variant; t.eps = eps;
-    t.nstate = nullptr; t.mout = nullptr; t.nout = nullptr; t.E = w.E; t.E2 = w.E2; t.part_acc = w.pacc;
+    t.nstate = nullptr; t.mout = nullptr; t.nout = nullptr; t.E = w.E; t.part_acc = w.pacc;
     // dV: rows = kv index j
     t.X = k; t.Y = q; t.Z = dH; t.Out = dv; t.out_T = T; t.out_ld = dhv; t.in_ld1 = t.in_cols1 = dqk; t.wrow_lo = ucol_lo; t.wcol_lo = wrowB_lo; t.wrowB_lo_out = nullptr; t.wrow = ucol; t.wcol = wrowB; t.srow = aK; t.St = w.dcT;
     t.d1 = d.dqk; t.d2 = d.dhv; t.dotwith = nullptr; t.dotpart = nullptr;

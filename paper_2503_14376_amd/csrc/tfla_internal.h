@@ -198,12 +198,13 @@ struct TileArgs {
     float* dotpart;                 // (d2/BD2, BH*T)
     // bf16 MODE_DQ writes, bf16 MODE_DK reads: the weighted matrix E of every chunk, (BH, Nc, L, L)
     void* E;
-    // Contraction widths above 512 (bf16): every term of the result is linear in the products over d1, so the
-    // launcher runs the kernel once per 512-wide half and the halves meet in fp32.  The caller provides the
-    // buffers; the remaining fields are filled in by the launcher.
-    float* part_acc;                // (BH, T, d2) unnormalised result of the first half
+    // Contractions wider than the kernels hold in registers.  bf16, above 512: a launch before the mode's own leaves the weighted
+    // matrix in memory (tile_weights.h), dQ's in E, the others' in part_acc, for H with the sums of its rows behind it.  fp32, above
+    // 256, and H of bf16 where that does not fit (weights_fit()): every term of the result is linear in the products over d1, so the
+    // launcher runs the kernel once per half and the halves meet in fp32.  The caller provides the buffers; the remaining fields
+    // are filled in by the launcher.
+    float* part_acc;                // (BH, T, d2) unnormalised result of the first half; or (BH, Nc, L, L) weights, bf16
     float* part_nrm;                // (BH, T) its share of the normaliser (MODE_H, mLSTMexp)
-    void* E2;                       // the second half's E (MODE_DQ writes, MODE_DK reads)
     const float* acc_in; const float* nrm_in;   // add these to the accumulators / normaliser before the epilogue
     float* acc_out; float* nrm_out;             // store the raw accumulators / normaliser instead of the output
     // The caller's tensors are read and written where they are also when the sequence ends inside its last chunk or a
@@ -234,10 +235,10 @@ struct LayerFuse {
 template <int MODE> hipError_t launch_tile_mode(const TileArgs& a, int BH, int dtype, hipStream_t s);
 // d2 block of a tiled kernel (mode MODE_*) with contraction width d1; rows = batch*head x steps.
 // 128 columns keep a bf16 wavefront within 256 registers, so that two workgroups share a CU when d1 <= 256.  From
-// d1 = 512 on (also as the halves of a contraction over 1024) a workgroup's own X rows fill half of the register file
-// and one workgroup takes the CU in any case: a 256-wide block then halves how often the X rows and the column tiles
-// are fetched and the score tile is computed (forward + backward, 4096 steps, 4 heads of 1024: 3.18 -> 2.78 ms; 8
-// heads of 512, batch 4: 1.418 -> 1.335 ms).  It pays only while its workgroups still cover the 256 CUs: at 64
+// d1 = 512 on a workgroup's own X rows fill half of the register file and one workgroup takes the CU in any case: a
+// 256-wide block then halves how often the X rows and the column tiles are fetched and the score tile is computed (forward
+// + backward, 8 heads of 512, batch 4, 4096 steps: 1.418 -> 1.335 ms); at d1 = 1024 it halves how often the X rows and the
+// weights in memory are fetched.  It pays only while its workgroups still cover the 256 CUs: at 64
 // workgroups (8 heads of 512, 512 steps, forward) it measured 40.5 us against 36.0 us for 128 columns, at 128
 // workgroups (1024 steps, forward + backward) 155 against 144 us.
 // (The 256-wide instantiations exist for the four-wavefront workgroups only, i.e. for chunk sizes that are
@@ -246,9 +247,9 @@ template <int MODE> hipError_t launch_tile_mode(const TileArgs& a, int BH, int d
 // described above; 64 / 128 force that width wherever it divides d2; 256 changes nothing (it is already taken
 // wherever it is built).  The workspace layout depends on the width, so it must not change between the
 // workspace query, the forward call and the backward call of one step.
-// A contraction over 1024 columns (bf16): whether the weighted matrix of H or dV, L values per row, and the sums of its rows (H),
-// one per 64 columns at most, fit where the fp32 partial results of a split contraction would lie: d_hv values per row, the wider
-// head dimension's in the backward workspace.  (dQ and dK have memory of their own for it.)
+// A contraction over 1024 columns (bf16): whether the weighted matrix of H, L values per row, and the sums of its rows, one per 64
+// columns at most, fit where the fp32 partial results of a split contraction would lie: d_hv values per row, a size that callers
+// have planned with.  (The other modes have memory that is sized for the matrix.)
 inline bool weights_fit(int L, int d2, int mode) { return mode != MODE_H || 2 * L + L / 16 <= 4 * d2; }
 extern int tile_width_override;
 inline int tile_bd2(int d1, int d2, int dtype, int L, long rows) {

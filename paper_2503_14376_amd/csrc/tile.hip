@@ -160,8 +160,7 @@ hipError_t launch_tile_mode(const TileArgs& a0, int BH, int dtype, hipStream_t s
     }
     if (a.d1 <= 512) return launch_tile_m<bf16_t, MODE>(a, BH, bd2, s);
     // d1 = 1024: the kernels hold a workgroup's X rows in registers where they form the weighted matrix, which ends at 512
-    // columns.  So a launch before them leaves the matrix in memory (dK reads what dQ's has left) and they read it.  It takes the
-    // memory of the fp32 partial results below, for dQ and dK that of E.
+    // columns.  So a launch before them leaves the matrix in memory (dK reads what dQ's has left) and they read it.
     // 16 heads of 1024, 4096 steps, chunk 256, us per mode H / dV / dQ / dK, split contraction -> this: 454 / 461 / 501 / 421 ->
     // 312 / 280 / 316 / 249 (65 of the first three the weights), forward + backward 2758 -> 2087; chunk 128, 3000 steps of 8 heads
     // 1310 -> 1040; chunk 64, 2048 steps of 4 heads 848 -> 706.
@@ -171,11 +170,10 @@ hipError_t launch_tile_mode(const TileArgs& a0, int BH, int dtype, hipStream_t s
         if (!STT) {
             if (!a.part_acc) return hipErrorInvalidValue;
             a.E = a.part_acc;
-            a.nrm_out = reinterpret_cast<float*>(reinterpret_cast<char*>(a.part_acc) + (size_t)BH * a.T * a.L * 2);
-            a.nrm_in = a.nrm_out;
+            if (MODE == MODE_H) a.nrm_in = a.nrm_out = reinterpret_cast<float*>(reinterpret_cast<char*>(a.part_acc) + (size_t)BH * a.T * a.L * 2);
         }
         if (!a.E) return hipErrorInvalidValue;
-        if (MODE != MODE_DK) {
+        if constexpr (MODE != MODE_DK) {
             hipError_t e = a.L % 128 == 0 ? launch_weights<4, MODE>(a, BH, s) : launch_weights<2, MODE>(a, BH, s);
             if (e != hipSuccess) return e;
         }

@@ -5,8 +5,8 @@
 // then read it (NOE == 2 in tile_fast.h) where they would form it.
 // A workgroup forms one block of 32 NW x 32 NW values; both operands arrive in slices of 64 contraction columns through a ring of
 // asynchronous loads, as in tile_fast.h.  Blocks beyond the diagonal are not launched.
-// Bound by how fast the slices arrive: 16 heads of 1024, 4096 steps, chunk 256 62 - 72 us per launch, 403 MB of slices (268 MB
-// of operands once) and 50 MB of E, 6.3 TB/s together.
+// Bound by how fast the slices arrive: 16 heads of 1024, 4096 steps, chunk 256 65 - 79 us per launch (H, whose row sums come on top,
+// the longest), 403 MB of slices (268 MB of operands once) and 25 MB of E, 5.4 - 6.6 TB/s together.
 #pragma once
 #include "lds_tiles.h"
 #include "tfla_internal.h"
