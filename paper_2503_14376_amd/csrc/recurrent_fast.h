@@ -40,7 +40,7 @@ static __device__ unsigned long long tfla_rec_timeline[8192];
 #ifndef TFLA_TL_BY
 #define TFLA_TL_BY 0
 #endif
-#define TFLA_RTL(slot) if ((tid & 255) == 0 && blockIdx.x == 0 && blockIdx.y == TFLA_TL_BY && blockIdx.z == 0 && (slot) >= 0 && (slot) < 128) tl_lds[tid >> 8][(slot)] = __builtin_amdgcn_s_memtime()
+#define TFLA_RTL(slot) if (lane == 0 && (wave == 0 || wave == WN) && blockIdx.x == 0 && blockIdx.y == TFLA_TL_BY && blockIdx.z == 0 && (slot) >= 0 && (slot) < 128) tl_lds[wave == WN][(slot)] = __builtin_amdgcn_s_memtime()
 #define TFLA_RTL_FLUSH __syncthreads(); if (blockIdx.x == 0 && blockIdx.y == TFLA_TL_BY && blockIdx.z == 0) for (int q_ = tid; q_ < 256; q_ += blockDim.x) tfla_rec_timeline[(q_ >> 7) * 4096 + (q_ & 127)] = tl_lds[q_ >> 7][q_ & 127];
 #else
 #define TFLA_RTL_DECL
