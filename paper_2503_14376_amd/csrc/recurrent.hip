@@ -346,6 +346,9 @@ static hipError_t launch_rec_bf16(const RecArgs& a, int BH, hipStream_t s) {
     // by the number of 128 x 256 tiles (heads of 512, 2048 steps, chunk 256): 128 346 -> 361, 160 485 -> 457, 192 503 -> 481, 224 639 -> 587,
     // 256 656 -> 597, 288 808 -> 816, 320 838 -> 842, 352 973 -> 937, 512 1278 -> 1173, 576 1449 -> 1406; 256 / 512, 256 tiles
     // 732 -> 670; heads of 256, 256 tiles 782 -> 746; 16 heads of 1024, 4096 steps 2040 -> 1797 (launches 471 -> 342).
+    // The chunk does not move the line, also where every piece opens one.  Chunk 64: 136 700 -> 664, 192 854 -> 823, 256 1157 -> 1040,
+    // 768 3524 -> 3129, 256 / 512, 160 757 -> 727, 128 / 256, 256 648 -> 630, heads of 1024, 512 2027 -> 1775; 128: 192 523 -> 514, 256 699 -> 641; 192:
+    // 192 747 -> 694, 256 992 -> 892; 512: 192 603 -> 548, 256 742 -> 686.
     const long tall_tiles = a.d1 % 128 == 0 && a.d2 % 256 == 0 ? (long)BH * (a.d1 / 128) * (a.d2 / 256) : 0;
     if (tall_tiles > 0 && 8 * ((tall_tiles + 255) / 256) <= 3 * ((4 * tall_tiles + 255) / 256)) {
         hipLaunchKernelGGL((recurrent_kernel_bf16<8, 64, PAD, 128, 4>), dim3(a.d2 / 256, a.d1 / 128, BH), dim3(768), 0, s, a);

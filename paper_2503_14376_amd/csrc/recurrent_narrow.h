@@ -29,6 +29,11 @@
 // consumers, those sums in registers and the anchors through LDS, forward + backward, us: 32 heads of 128, 2048 steps, chunk 128 104 ->
 // 96; 4 heads of 512, 4096 steps 202 -> 195; 16 heads 96 / 192, batch 2, 3000 steps 194 -> 184; 8 heads 256 / 512, 8192 steps,
 // chunk 64 652 -> 628, 256 416 -> 410; forward, 1000 steps, chunk 128 38.8 -> 35.7, 32768 steps, chunk 512 600 -> 587.
+// More tiles than CUs (d_hv up to 64 has no other kernel).  In pieces of 64 rows two workgroups of the two-consumer form shared a
+// CU, and two of this one do without the LDS for anchors (76 KB; loaded by the consumers then).  Forward + backward, us, two
+// consumers / four without / four with it, which is one workgroup per CU: heads of 64, 2048 steps, chunk 64 320 tiles 388 / 388 / 383, 384
+// 454 / 451 / 446, 512 601 / 590 / 588, 1024 1216 / 1207 / 1204, chunk 192 512 554 / 548 / 549; 1024 / 64, 1024 tiles 572 / 572 / 565; 256 / 64, 512 480 /
+// 472 / 469; heads of 32, 1024 tiles 516 / 494 / 494; forward 258 / 245 / 246.
 #pragma once
 #include <type_traits>
 

@@ -110,6 +110,40 @@ def test_large_state_tiles(variant, B, NH, T, dqk, dhv, chunk, state):
     _check_slices(w, dCn=state, keep=T % 128 == 0, scan=True)
 
 
+# every (batch, head) of a problem, not two of them: the slices hold two slices' inputs in turn, and each one's results are,
+# bit for bit, those of the first two, which the oracle has checked in the tests around
+@pytest.mark.parametrize("variant,B,NH,T,dqk,dhv,chunk", [
+    (wl.EXP, 3, 43, 320, 128, 256, 64),         # large state tiles
+    (wl.SIG, 19, 7, 100, 120, 248, 128),
+    (wl.EXP, 2, 3, 900, 1000, 1024, 128),
+    (wl.EXP, 3, 3, 1024, 1024, 1024, 256),      # 256 rows per workgroup
+    (wl.SIG, 2, 5, 1100, 1000, 1024, 512),
+    (wl.EXP, 1, 5, 900, 1024, 256, 448),        # 64 rows
+    (wl.EXP, 5, 13, 700, 64, 64, 64),           # few state tiles
+    (wl.EXP, 9, 37, 320, 64, 64, 64),           # ... and more than CUs
+    (wl.EXP, 3, 5, 256 * 17 - 3, 64, 128, 256), # gate kernels of more than sixteen chunks
+])
+def test_every_slice(variant, B, NH, T, dqk, dhv, chunk):
+    import paper_2503_14376_amd as tfla
+    from tests import gpu_util as gu
+    w = wl.small(variant, wl.BF16, B=B, NH=NH, T=T, dqk=dqk, dhv=dhv, chunk=chunk, seed=2900 + T + dqk)
+    dev = gu.dev_inputs(w, wl.make_inputs(wl.small(variant, wl.BF16, B=1, NH=2, T=T, dqk=dqk, dhv=dhv, chunk=chunk, seed=w.seed)))
+    which = torch.arange(B * NH, device="cuda") % 2
+    dev = {k: x.reshape((2,) + x.shape[2:])[which].reshape((B, NH) + x.shape[2:]).contiguous() for k, x in dev.items()}
+    args, kw = [dev[x] for x in ("q", "k", "v", "i_pre", "f_pre")], dict(chunk=chunk, variant=variant, eps=1e-6)
+    st = [dev.get(x) for x in ("C0", "n0", "m0")]
+    f = tfla.mlstm_fwd(*args, *st, **kw)
+    b = tfla.mlstm_bwd(*args, dev["dH"], f["n_out"], f["m_out"], *st, **kw, fwd_workspace=f["workspace"])
+    torch.cuda.synchronize()
+    for o in (f, b):
+        for k, x in o.items():
+            if k == "workspace":
+                continue
+            x = x.reshape((B * NH,) + x.shape[2:])
+            assert torch.isfinite(x.float()).all(), k
+            assert torch.equal(x, x[:2][which]), k
+
+
 # Few state tiles: the reversed launch's anchors arrive through a ring of LDS buffers.  The first one belongs to piece 1, 2, 3, 4, ...
 # (the chunks past the last whole block), the next to one four or (heads wider than 512) two chunks on, and there may be none
 @pytest.mark.parametrize("B,NH,T,dqk,dhv,chunk", [
